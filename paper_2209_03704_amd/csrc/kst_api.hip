@@ -273,11 +273,17 @@ kst_status kst_forward_seg_static(const void *in, const void *w_seg, void *out, 
     if (!dtype_ok(dtype)) return KST_ERR_DTYPE;
     kst_status st = check_shape(B, Cin, Cout, N, n);
     if (st != KST_OK) return st;
-    const Shape s = make_shape(B, Cin, Cout, N, n);
+    Shape s = make_shape(B, Cin, Cout, N, n);
     kst_path chosen;
     st = resolve_path(s, dtype, path, &chosen);
     if (st != KST_OK) return st;
-    const size_t need = workspace_for(s, dtype, chosen);
+    size_t need = workspace_for(s, dtype, chosen);
+    if (need > (size_t)KST_STATIC_SCRATCH_BYTES) {      // the fp32 multiplies' own kernels may need less
+        s.no_split = 1;
+        st = resolve_path(s, dtype, path, &chosen);
+        if (st != KST_OK) return st;
+        need = workspace_for(s, dtype, chosen);
+    }
     if (need > (size_t)KST_STATIC_SCRATCH_BYTES) return KST_ERR_WORKSPACE;     // larger than the array: refuse
     void *ws = nullptr;
     if (need) {
@@ -336,6 +342,7 @@ kst_status framed_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype 
     // rows (tensor rows of whole 16-byte groups): no framed copy.
     Shape in_place = f->s;
     in_place.frame = f->q;
+    if (path == KST_PATH_IGEMM_EVEN) in_place.no_split = f->s.no_split = 1;     // that path is the fp32 multiplies' own
     const bool frame_in_kernel = dt == KST_F32 && igemm_f32_takes_virtual_frame(in_place);
     if (path == KST_PATH_IGEMM_EVEN) {
         if (frame_in_kernel) f->s = in_place;

@@ -100,13 +100,15 @@ struct Shape {
     int crop;  // 1: only the interior of the M x M map is wanted -- `out` is the dense [B][Cout][M - 2][M - 2] tensor
                // whose element (y, x) is element (y + 1, x + 1) of the map (an odd padding factor; only kernels for
                // which *_takes_virtual_frame says so)
+    int no_split;  // 1: the kernels that split fp32 operands for the bf16 matrix cores are not to be chosen (their
+                   // partial tiles need more scratch than the caller has)
     Epilogue epi;  // applied where the final value of an element is stored (every forward kernel but the
                    // row-parity-passes one, which must be given an inactive one)
 };
 
 inline Shape make_shape(int B, int Cin, int Cout, int N, int n)
 {
-    Shape s{B, Cin, Cout, N, n, 2 * N - n, (2 * N - n + 1) / 2, n / 2, N, 0, 0, {nullptr, KST_ACT_NONE}};
+    Shape s{B, Cin, Cout, N, n, 2 * N - n, (2 * N - n + 1) / 2, n / 2, N, 0, 0, 0, {nullptr, KST_ACT_NONE}};
     return s;
 }
 
@@ -205,6 +207,11 @@ bool igemm_f32_small_supported(const Shape &s);
 size_t igemm_f32_small_workspace_bytes(const Shape &s);
 hipError_t launch_igemm_f32_small(const float *in, const float *w_seg, float *out, void *ws, const Shape &s,
                                   hipStream_t stream);
+// fp32 layers on the bf16 matrix cores, operands split into three parts (takes Shape::frame and Shape::crop).
+bool split_f32_applies(const Shape &s);
+size_t split_f32_workspace_bytes(const Shape &s);
+hipError_t launch_split_f32(const float *in, const float *w_seg, float *out, void *ws, const Shape &s,
+                            hipStream_t stream);
 // force_even: take the even-share launch whenever igemm_f32_even_shares_possible, whatever the cost model says.
 bool igemm_f32_even_shares_possible(const Shape &s);
 size_t igemm_f32_workspace_bytes(const Shape &s, bool force_even = false);

@@ -1,0 +1,110 @@
+"""fp32 layers whose operands are split into three bfloat16 parts for the matrix cores: against the oracle and against
+the kernels that multiply in fp32."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2209_03704_amd import binding as kst
+from paper_2209_03704_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+TOL = 2e-5          # of the largest element, as for every fp32 kernel
+
+# Large enough for the split kernels (1.5 G products); between them: kernel edges 3, 4, 5; tiles of 64 and 128 output
+# channels; three and five staged positions per lane; ragged channels, chunks, batches; odd maps; odd padding factors.
+FORWARD = [
+    (30, 130, 200, 16, 4, 0),    # ragged channels on both sides, even map
+    (23, 515, 66, 13, 3, 2),     # odd map edge and padding, a last chunk of three channels, 66 of 128 channels
+    (70, 33, 40, 33, 5, 1),      # tiles of 64 channels, odd padding factor (interior stores), two chunks and one channel
+    (9, 96, 130, 64, 3, 0),      # long rows: five staged positions per lane
+    (64, 512, 256, 8, 4, 2),     # shared passes only
+    (130, 256, 64, 6, 5, 3),     # small maps, many items per tile, odd padding factor
+]
+
+
+def _layer(shape, seed):
+    B, Cin, Cout, N, n, P = shape
+    gen = torch.Generator().manual_seed(seed)
+    x = torch.randn((B, Cin, N, N), generator=gen).clamp_(min=0.0)
+    w = torch.randn((Cout, Cin, n, n), generator=gen) * 0.05
+    return x, w
+
+
+def _forward(x, w, P, path=kst.KST_PATH_AUTO, bias=None, act=kst.KST_ACT_NONE):
+    Cout, n = w.shape[0], w.shape[2]
+    wd = kst.kst_segregate_weights(w.to(DEV))
+    if bias is not None or act != kst.KST_ACT_NONE:
+        out = kst.kst_forward_seg_epilogue(x.to(DEV), wd, Cout, n, bias=None if bias is None else bias.to(DEV), act=act, P=P,
+                                           path=path)
+    else:
+        out = kst.kst_forward_seg_padded(x.to(DEV), wd, Cout, n, P, path=path)
+    torch.cuda.synchronize()
+    return out.cpu()
+
+
+def _planes(x, w, P, count=24):
+    B, Cout = x.shape[0], w.shape[0]
+    b = [(i * 7) % B for i in range(count)] + [B - 1]
+    co = [(i * 13 + 5) % Cout for i in range(count)] + [Cout - 1]
+    return b, co, oracle.forward_planes(wl.to_f64(x), wl.to_f64(w), b, co, P)
+
+
+@pytest.mark.parametrize("shape", FORWARD)
+def test_split_forward(shape):
+    P = shape[5]
+    x, w = _layer(shape, 31 + shape[0])
+    b, co, want = _planes(x, w, P)
+    out = _forward(x, w, P)
+    got = out[torch.tensor(b), torch.tensor(co)].numpy().astype(np.float64)
+    assert np.abs(got - want).max() <= TOL * np.abs(want).max()
+    # every element: a random projection of the channels (the operation is linear in the kernel)
+    r = np.random.default_rng(5).standard_normal(w.shape[0])
+    proj = oracle.forward(wl.to_f64(x[:2]), np.einsum("o,oiuv->iuv", r, wl.to_f64(w))[None], P)[:, 0]
+    mine = np.einsum("o,boyx->byx", r, out[:2].numpy().astype(np.float64))
+    assert np.abs(mine - proj).max() <= TOL * np.abs(proj).max()
+    # no less precise than fp32 multiplies: the plain kernels, one fp32 multiply-add per product
+    plain = _forward(x, w, P, kst.KST_PATH_DIRECT)[torch.tensor(b), torch.tensor(co)].numpy().astype(np.float64)
+    assert np.linalg.norm(got - want) <= np.linalg.norm(plain - want)
+    assert torch.equal(out, _forward(x, w, P))                    # fixed summing order
+
+
+@pytest.mark.parametrize("shape", FORWARD[:3])
+@pytest.mark.parametrize("act", [kst.KST_ACT_RELU, kst.KST_ACT_TANH])
+def test_split_forward_epilogue(shape, act):
+    P = shape[5]
+    x, w = _layer(shape, 61 + shape[0])
+    bias = torch.randn(shape[2], generator=torch.Generator().manual_seed(3))
+    bare = _forward(x, w, P).double() + bias.double().view(1, -1, 1, 1)
+    want = bare.clamp_(min=0.0) if act == kst.KST_ACT_RELU else torch.tanh(bare)
+    got = _forward(x, w, P, bias=bias, act=act).double()
+    # one fp32 addition and one tanh (2 ulp) away from the same sums
+    assert (got - want).abs().max() <= 1e-6 * max(1.0, float(want.abs().max()))
+
+
+@pytest.mark.parametrize("shape", [FORWARD[0], FORWARD[2], FORWARD[4]])
+def test_split_forward_infinities_and_nan(shape):
+    """An infinity, a NaN or a value that bfloat16 rounds to infinity has no three parts: the elements it reaches are
+    what fp32 multiplies make of them, all others are untouched."""
+    B, Cin, Cout, N, n, P = shape
+    x, w = _layer(shape, 91 + B)
+    x[0, 1, 2, 3] = float("inf")
+    x[B - 1, Cin - 1, N - 1, 0] = float("nan")
+    x[B // 2, 0, 0, 0] = 3.4e38
+    w[Cout - 1, 3, n - 1, 1] = -float("inf")
+    out, ref = _forward(x, w, P), _forward(x, w, P, kst.KST_PATH_DIRECT)
+    assert torch.equal(torch.isnan(out), torch.isnan(ref))
+    assert torch.equal(torch.isinf(out), torch.isinf(ref))
+    assert torch.equal(out[torch.isinf(out)], ref[torch.isinf(ref)])
+    ok = torch.isfinite(ref)
+    item = ref.where(ok, 0.0).abs().amax(dim=(1, 2, 3), keepdim=True).expand_as(ref)   # (one item holds 1e37s)
+    assert ((out - ref)[ok].abs() <= TOL * item[ok]).all()
+
+
+def test_split_forward_small_values():
+    """Scaling the operands by powers of two scales the result exactly: their parts keep all bits down to 1e-30."""
+    x, w = _layer(FORWARD[4], 7)
+    one = _forward(x, w, 2)
+    small = _forward(x * 2.0 ** -60, w * 2.0 ** -40, 2)
+    assert torch.equal(small, one * 2.0 ** -100)

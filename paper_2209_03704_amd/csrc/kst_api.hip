@@ -515,6 +515,9 @@ struct GradPlan {
     bool plain_unframed;              // the other kernels work on the unframed positions too (kernels up to 7 x 7)
     bool din_cores, dw_cores;         // the gradient runs on the matrix cores (fp32 kernels; 16-bit operands are
                                       // widened to fp32 first, which is exact)
+    kst_dtype din_split;              // operand type of w where the input gradient runs on the bf16 matrix cores
+    bool use_din_split;               // ... (half-precision weights are widened to fp32 first)
+    size_t din_split_bytes;           // its whole workspace (after the widened weights)
     size_t wconv_bytes, xconv_bytes;  // fp32 copies of w (input gradient) and of in (kernel gradient) for that
 };
 
@@ -547,6 +550,14 @@ kst_status grad_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dt
         f->din_bytes = 0;
     }
     if (f->plain_unframed) f->in_bytes = 0;            // `in` read as it lies in memory
+    f->din_split = dt == KST_F16 ? KST_F32 : dt;
+    f->use_din_split = split_din_applies(f->si, (P & 1) != 0, f->din_split);
+    f->din_split_bytes = 0;
+    if (f->use_din_split) {
+        // (one size for both 16-bit types: the fp32 kernels' after a widening of w, which bfloat16 does without)
+        f->wconv_bytes = is16(dt) ? (((size_t)Cout * Cin * n * n * sizeof(float) + 255) & ~(size_t)255) : 0;
+        f->din_split_bytes = split_din_workspace_bytes(f->si, (P & 1) != 0, KST_F32);
+    }
     f->wsplit_bytes = f->dw_cores
                           ? backward_weight_igemm_workspace_bytes(f->si)
                           : backward_weight_generic_workspace_bytes(f->plain_unframed ? f->si : f->s);
@@ -569,7 +580,7 @@ size_t kst_backward_input_workspace_bytes(int B, int Cin, int Cout, int N, int n
 {
     GradPlan f;
     if (!dtype_ok(dtype) || grad_plan(B, Cin, Cout, N, n, P, dtype, &f) != KST_OK) return 0;
-    return f.g_bytes + f.din_bytes + f.split_bytes + f.wconv_bytes;
+    return f.use_din_split ? f.wconv_bytes + f.din_split_bytes : f.g_bytes + f.din_bytes + f.split_bytes + f.wconv_bytes;
 }
 
 size_t kst_backward_weight_workspace_bytes(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dtype)
@@ -588,10 +599,22 @@ kst_status kst_backward_input(const void *g, const void *w, void *din, void *ws,
     kst_status st = grad_plan(B, Cin, Cout, N, n, P, dtype, &f);
     if (st != KST_OK) return st;
     if (!aligned16(g) || !aligned16(w) || !aligned16(din)) return KST_ERR_ALIGN;
-    const size_t need = f.g_bytes + f.din_bytes + f.split_bytes + f.wconv_bytes;
+    const size_t need = f.use_din_split ? f.wconv_bytes + f.din_split_bytes
+                                        : f.g_bytes + f.din_bytes + f.split_bytes + f.wconv_bytes;
     if (need) {
         if (!ws || ws_bytes < need) return KST_ERR_WORKSPACE;
         if (!aligned16(ws)) return KST_ERR_ALIGN;
+    }
+    if (f.use_din_split) {
+        const void *w_in = w;
+        if (dtype == KST_F16) {
+            if (launch_widen(w, (float *)ws, (size_t)Cout * Cin * n * n, dtype, stream) != hipSuccess) return KST_ERR_HIP;
+            w_in = ws;
+        }
+        return launch_split_din((const float *)g, w_in, (float *)din, (char *)ws + f.wconv_bytes, f.si, (P & 1) != 0,
+                                f.din_split, stream) == hipSuccess
+                   ? KST_OK
+                   : KST_ERR_HIP;
     }
     const float *g_in = (const float *)g;
     float *d_out = (float *)din;

@@ -212,6 +212,12 @@ bool split_f32_applies(const Shape &s);
 size_t split_f32_workspace_bytes(const Shape &s);
 hipError_t launch_split_f32(const float *in, const float *w_seg, float *out, void *ws, const Shape &s,
                             hipStream_t stream);
+// ... and their input gradient (fp32 or bfloat16 weights; s.frame as above, odd: the padding factor is odd, g then one
+// row and column short on every side).
+bool split_din_applies(const Shape &s, bool odd, kst_dtype dt);
+size_t split_din_workspace_bytes(const Shape &s, bool odd, kst_dtype dt);
+hipError_t launch_split_din(const float *g, const void *w, float *din, void *ws, const Shape &s, bool odd, kst_dtype dt,
+                            hipStream_t stream);
 // force_even: take the even-share launch whenever igemm_f32_even_shares_possible, whatever the cost model says.
 bool igemm_f32_even_shares_possible(const Shape &s);
 size_t igemm_f32_workspace_bytes(const Shape &s, bool force_even = false);

@@ -1,0 +1,515 @@
+// Input gradient on the bf16 matrix cores (g and fp32 weights split into three bfloat16 parts, see kst_split_common.h;
+// bfloat16 weights are their own only part, which leaves three partial products of six).
+//
+//   din[b][ci][a][c] = sum_co sum_u sum_v g[b][co][2 (a + q) - u][2 (c + q) - v] * w[co][ci][u][v]
+//
+// (q: the zero frame of the padding factor; for an odd one g starts a row and a column later).  As a GEMM: rows = input
+// channels, columns = positions m = (b, a, c) of the unframed map, reduction over (co, u, v) in chunks of 16 output
+// channels.
+//
+// What bounds it: the multiplies.  A workgroup of four waves owns 128 positions x 128 RB input channels, a wave 32 RB
+// channels and all positions, the largest partial products' sums apart from the others'.  The weights are split once
+// by a kernel of their own into MFMA operands, a wave's next ones contiguous, loaded into registers taps ahead.  The
+// rows of g that the tile's positions touch are split once per chunk into LDS as [part][channel half][row][column
+// parity][column / 2][8 channels]: a tap's positions are two columns apart in g and neighbours there, and a lane's MFMA
+// operand is one 16-byte read.  Two stages, one barrier per chunk.  64 x 512 x 256 x 8 x 8, n = 4,
+// P = 2: 80 us where the fp32 multiplies took 162; with bfloat16 weights 64 x 256 x 128 x 16 x 16: 55 against 155.
+#include "kst_split_common.h"
+
+namespace kst {
+
+namespace {
+
+constexpr int D_THREADS = 256;
+constexpr int D_KC = 16;                 // output channels per chunk
+constexpr int D_TM = 128;                // positions per tile
+constexpr int D_IP = 832;                // cells (rows x columns of g) a stage can hold
+constexpr int D_HALF = D_IP * 16;
+constexpr int D_PART = 2 * D_HALF;
+constexpr int D_STAGE = 3 * D_PART;      // 79872 bytes
+constexpr unsigned D_OUTSIDE = 0x80000000u;
+constexpr size_t D_SLOT1 = (size_t)D_THREADS * 64;      // floats of a workgroup's sums, per row block
+
+struct DinParams {
+    int B, Cin, Cout;
+    int N, M, shift;       // edges of din and g; g row of image row h: h + shift
+    int H, W2;             // image rows per batch item, cells per column parity
+    int ip;                // cells staged
+    int Mtot, tiles_m, tiles_ci, chunks;
+    unsigned g_bytes, w_bytes;
+};
+
+template <int n, int RB, int WP, int NT>
+__device__ __forceinline__ void din_accumulate(const float *__restrict__ g, const void *__restrict__ w_split,
+                                               const DinParams &p, char *lds, int tile_m, int tile_ci, int k0, int k1,
+                                               int tid, floatx16 (&acc)[RB][4])
+{
+    constexpr int TAPS = n * n;
+    constexpr int SETS = n == 4 ? 4 / RB : n;         // divides the taps
+    constexpr int TAP = WP * 1024;                    // bytes of a tap's operands for 32 input and 16 output channels
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, kk = lane >> 5;
+    const int NN = p.N * p.N, pitch = 2 * p.W2;
+    const int m0 = tile_m * D_TM;
+    const int b0 = m0 / NN, a0 = (m0 - b0 * NN) / p.N;
+    const int V0 = b0 * p.H + 2 * a0;                 // first image row of the tile (rows stacked over batch items)
+
+    int xa[4];                                        // LDS byte address of the window's first cell
+#pragma unroll
+    for (int pb = 0; pb < 4; ++pb) {
+        const int m = min(m0 + pb * 32 + l32, p.Mtot - 1);
+        const int mb = m / NN, rem = m - mb * NN, ma = rem / p.N, mc = rem - ma * p.N;
+        xa[pb] = ((mb * p.H + 2 * ma - V0) * pitch + mc) * 16 + kk * D_HALF;
+    }
+
+    // Staging: wave -> channel half wave & 1, cells (wave >> 1) * 64 + lane + 128 k (the last 64 of 832: by both waves
+    // of the half, the same values).
+    const int half = wave & 1;
+    const unsigned plane = 4u * (unsigned)p.M * p.M;
+    auto cell_of = [&](int k) { return 128 * (k + 1) <= D_IP ? (wave >> 1) * 64 + lane + 128 * k : lane + 128 * k; };
+    unsigned x_off[NT];
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+        const int cell = cell_of(k);
+        const int lr = cell / pitch, rem = cell - lr * pitch;
+        const int odd = rem >= p.W2 ? 1 : 0;
+        const int V = V0 + lr, bb = V / p.H;
+        const int y = V - bb * p.H + p.shift, x = 2 * (rem - odd * p.W2) + odd + p.shift;
+        const bool ok = cell < p.ip && bb < p.B && y >= 0 && y < p.M && x >= 0 && x < p.M;
+        x_off[k] = ok ? (unsigned)bb * p.Cout * plane + 4u * ((unsigned)y * p.M + x) : D_OUTSIDE;
+    }
+    float x_reg[NT][8];
+    auto fetch_x = [&](int chunk) {
+        const int c = chunk * D_KC + half * 8;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const bool live = c + j < p.Cout;         // uniform
+            const __amdgpu_buffer_rsrc_t buf = buffer_of(g, live ? p.g_bytes : 0u);
+            const unsigned at = live ? (unsigned)(c + j) * plane : 0u;
+#pragma unroll
+            for (int k = 0; k < NT; ++k) x_reg[k][j] = load_f32(buf, x_off[k], at);
+        }
+    };
+    auto write_x = [&](auto kc, int stage) {
+        constexpr int k = decltype(kc)::value;
+        bf16x8 a, b, c;
+        split3(x_reg[k], a, b, c);
+        char *d = lds + stage + half * D_HALF + cell_of(k) * 16;
+        *reinterpret_cast<bf16x8 *>(d) = a;
+        *reinterpret_cast<bf16x8 *>(d + D_PART) = b;
+        *reinterpret_cast<bf16x8 *>(d + 2 * D_PART) = c;
+    };
+
+    bf16x8 wp[SETS][RB][WP];
+    const __amdgpu_buffer_rsrc_t wbuf = buffer_of(w_split, p.w_bytes);
+    unsigned w_base[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+        w_base[rb] = (unsigned)min((tile_ci * 4 + wave) * RB + rb, (p.Cin - 1) / 32) * p.chunks * (TAPS * TAP);
+    auto fetch_w = [&](auto qc, int chunk) {
+        constexpr int q = decltype(qc)::value;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int part = 0; part < WP; ++part)
+                wp[q % SETS][rb][part] = load_bf16x8(wbuf, lane * 16 + part * 1024, w_base[rb] + (unsigned)(chunk * TAPS + q) * TAP);
+    };
+
+    bf16x8 xf[4][3];
+    int stage = 0;
+    auto read_x = [&](auto qc, auto partc) {          // taps are walked row by row, columns of one parity together
+        constexpr int q = decltype(qc)::value, part = decltype(partc)::value;
+        constexpr int h = q / n, i = q % n, even = (n + 1) / 2;
+        constexpr int x = i < even ? 2 * i : 2 * (i - even) + 1;
+#pragma unroll
+        for (int pb = 0; pb < 4; ++pb)
+            xf[pb][part] = *reinterpret_cast<const bf16x8 *>(lds + stage + xa[pb] + (h * 2 + (x & 1)) * p.W2 * 16 +
+                                                             (x >> 1) * 16 + part * D_PART);
+    };
+
+    floatx16 low[RB][4];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int pb = 0; pb < 4; ++pb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[rb][pb][v] = low[rb][pb][v] = 0.0f;
+
+    using std::integral_constant;
+    constexpr auto write_tap = [](int k) { return TAPS - 2 - k % ((TAPS - 1) / 2); };
+    constexpr auto staged_in = [=](int q) {
+        int count = 0;
+        for (int k = 0; k < NT; ++k) count += write_tap(k) == q;
+        return count;
+    };
+    fetch_x(k0);
+    static_for<SETS - 1>([&](auto qc) { fetch_w(qc, k0); });
+    static_for<NT>([&](auto kc) { write_x(kc, 0); });
+    fetch_x(min(k0 + 1, k1 - 1));
+    __syncthreads();
+    static_for<3>([&](auto pc) { read_x(integral_constant<int, 0>{}, pc); });
+
+    for (int chunk = k0; chunk < k1; ++chunk) {
+        const int next = min(chunk + 1, k1 - 1), after = min(chunk + 2, k1 - 1);
+        static_for<TAPS>([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            constexpr bool last = q == TAPS - 1;
+            if constexpr (last) {
+                // Every wave has written its share of the next chunk's stage and is done reading this one's.
+                stage = D_STAGE - stage;
+                __syncthreads();
+                fetch_x(after);
+            }
+            fetch_w(integral_constant<int, (q + SETS - 1) % TAPS>{}, q + SETS - 1 < TAPS ? chunk : next);
+            static_for<NT>([&](auto kc) {
+                if constexpr (write_tap(decltype(kc)::value) == q) write_x(kc, D_STAGE - stage);
+            });
+            constexpr int MF = 4 * RB * (WP == 1 ? 3 : 6);
+            static_for<3>([&](auto xc) {              // parts of g, smallest first, against the parts that matter
+                constexpr int xp = 2 - decltype(xc)::value;
+                static_for<(WP < 3 - xp ? WP : 3 - xp)>([&](auto wc) {
+                    constexpr int w = (WP < 3 - xp ? WP : 3 - xp) - 1 - decltype(wc)::value;
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                        for (int pb = 0; pb < 4; ++pb) {
+                            floatx16 &sum = w + xp == 0 ? acc[rb][pb] : low[rb][pb];
+                            sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wp[q % SETS][rb][w], xf[pb][xp], sum, 0, 0, 0);
+                        }
+                });
+                read_x(integral_constant<int, last ? 0 : q + 1>{}, integral_constant<int, xp>{});
+            });
+            constexpr int valu = (16 + 48 * staged_in(q) + MF - 1) / MF;
+            static_for<MF>([&](auto) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // MFMA
+                __builtin_amdgcn_sched_group_barrier(0x002, valu, 0);   // vector arithmetic
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // LDS read
+                __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);      // global read
+                __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);      // LDS write
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    }
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int pb = 0; pb < 4; ++pb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[rb][pb][v] += low[rb][pb][v];
+}
+
+__device__ __forceinline__ float weight_of(const float *w, size_t i) { return w[i]; }
+__device__ __forceinline__ float weight_of(const uint16_t *w, size_t i) { return to_f32(w[i]); }
+
+// One element in plain fp32 multiply-adds, where its split sum is not finite.  g: the batch item's; w: the input
+// channel's; (y, x): row and column of g for tap (0, 0).
+template <class T>
+__device__ __attribute__((noinline)) float din_recompute(const float *g, const T *w, int n, int Cin, int Cout, int M, int y,
+                                                         int x)
+{
+    float a = 0.0f;
+    for (int co = 0; co < Cout && a == a; ++co) {
+        for (int u = 0; u < n; ++u)
+            for (int v = 0; v < n; ++v) {
+                const int gy = y - u, gx = x - v;
+                const bool inside = gy >= 0 && gy < M && gx >= 0 && gx < M;
+                a = fmaf(weight_of(w, u * n + v), inside ? g[(size_t)gy * M + gx] : 0.0f, a);
+            }
+        g += (size_t)M * M;
+        w += (size_t)Cin * n * n;
+    }
+    return a;
+}
+
+struct DinColumn {
+    int mb, ma, mc;
+    bool valid;
+};
+__device__ __forceinline__ DinColumn din_column(const DinParams &p, int m)
+{
+    DinColumn c;
+    c.valid = m < p.Mtot;
+    m = min(m, p.Mtot - 1);
+    c.mb = m / (p.N * p.N);
+    const int rem = m - c.mb * p.N * p.N;
+    c.ma = rem / p.N;
+    c.mc = rem - c.ma * p.N;
+    return c;
+}
+
+// The 16 sums of one block (channels ci0 + 8 (v / 4) + v % 4) at this lane's position.
+template <int n, class T>
+__device__ __forceinline__ void din_store(const float *__restrict__ g, const T *__restrict__ w, float *__restrict__ din,
+                                          const DinParams &p, const float (&a)[16], int ci0, const DinColumn &c)
+{
+    const size_t plane = (size_t)p.N * p.N;
+    float *o = din + ((size_t)c.mb * p.Cin + ci0) * plane + c.ma * p.N + c.mc;
+    float zero = 0.0f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int d = 8 * (v >> 2) + (v & 3);
+        if (c.valid && ci0 + d < p.Cin) o[d * plane] = a[v];
+        zero = fmaf(a[v], 0.0f, zero);
+    }
+    if (zero != 0.0f && c.valid) {
+        const float *gb = g + (size_t)c.mb * p.Cout * p.M * p.M;
+        for (int v = 0; v < 16; ++v) {
+            const int d = 8 * (v >> 2) + (v & 3);
+            if (ci0 + d < p.Cin && o[d * plane] * 0.0f != 0.0f)
+                o[d * plane] = din_recompute(gb, w + (size_t)(ci0 + d) * n * n, n, p.Cin, p.Cout, p.M,
+                                             2 * c.ma + n - 1 + p.shift, 2 * c.mc + n - 1 + p.shift);
+        }
+    }
+}
+
+template <int n, int RB, int WP, int NT, class T>
+__global__ void __launch_bounds__(D_THREADS, 1) split_din_kernel(const float *__restrict__ g, const T *__restrict__ w,
+                                                                const void *__restrict__ w_split, float *__restrict__ din,
+                                                                float *__restrict__ ws, DinParams p, EvenShares k)
+{
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int wg = blockIdx.x;
+    int whole = wg * k.rounds;
+    const int whole_end = whole + k.rounds;
+    int u = k.begin(wg);
+    const int u_end = k.begin(wg + 1);
+    bool first = true;
+    while (whole < whole_end || u < u_end) {
+        int tile, c0 = 0, c1 = p.chunks;
+        __syncthreads();                              // the last piece's LDS is free
+        float *slot = ws + (size_t)(2 * wg + (first ? 0 : 1)) * (RB * D_SLOT1);
+        if (whole < whole_end) {
+            tile = whole++;
+        } else {
+            const int rel = u / p.chunks;
+            tile = k.listed() + rel;
+            c0 = u - rel * p.chunks;
+            c1 = min(p.chunks, c0 + u_end - u);
+            first = false;
+            u += c1 - c0;
+        }
+        tile = __builtin_amdgcn_readfirstlane(tile);  // the same in all lanes: the staging's addresses stay scalar
+        c0 = __builtin_amdgcn_readfirstlane(c0);
+        c1 = __builtin_amdgcn_readfirstlane(c1);
+        const int tile_m = tile % p.tiles_m, tile_ci = tile / p.tiles_m;
+        int tid = (int)threadIdx.x;                   // (a fresh copy: nothing of the staging plan is kept across pieces)
+        asm volatile("" : "+v"(tid));
+        floatx16 acc[RB][4];
+        din_accumulate<n, RB, WP, NT>(g, w_split, p, lds, tile_m, tile_ci, c0, c1, tid, acc);
+        const int lane = tid & 63, wave = tid >> 6;
+        if (c0 == 0 && c1 == p.chunks) {
+            static_for<4>([&](auto pbc) {
+                constexpr int pb = decltype(pbc)::value;
+                const DinColumn c = din_column(p, tile_m * D_TM + pb * 32 + (lane & 31));
+                static_for<RB>([&](auto rbc) {
+                    constexpr int rb = decltype(rbc)::value;
+                    float a[16];
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) a[v] = acc[rb][pb][v];
+                    din_store<n>(g, w, din, p, a, ((tile_ci * 4 + wave) * RB + rb) * 32 + 4 * (lane >> 5), c);
+                });
+            });
+        } else {
+            float4 *d = reinterpret_cast<float4 *>(slot);
+            static_for<16 * RB>([&](auto ic) {        // [position block][row block][four registers]
+                constexpr int i = decltype(ic)::value, pb = i / (4 * RB), rb = i / 4 % RB, v = 4 * (i & 3);
+                d[i * D_THREADS + tid] = make_float4(acc[rb][pb][v], acc[rb][pb][v + 1], acc[rb][pb][v + 2], acc[rb][pb][v + 3]);
+            });
+        }
+    }
+}
+
+// One workgroup per (shared tile, block of positions, row block): the sum of the tile's slots in workgroup order.
+template <int n, int RB, class T>
+__global__ void __launch_bounds__(D_THREADS) split_din_sum_kernel(const float *__restrict__ g, const T *__restrict__ w,
+                                                                  float *__restrict__ din, const float *__restrict__ ws,
+                                                                  DinParams p, EvenShares k)
+{
+    const int rel = blockIdx.x / (4 * RB), part = blockIdx.x - rel * (4 * RB), tid = threadIdx.x;
+    const int u0 = rel * p.chunks;
+    const int g0 = k.owner(u0), g1 = k.owner(u0 + p.chunks - 1);
+    if (g0 == g1) return;
+    float a[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) a[v] = 0.0f;
+#pragma unroll 2
+    for (int s = g0; s <= g1; ++s) {
+        const int b = k.begin(s);
+        if (b == k.begin(s + 1)) continue;            // an empty range
+        const int slot = 2 * s + (b < u0 ? 1 : 0);
+        const float4 *d = reinterpret_cast<const float4 *>(ws + (size_t)slot * (RB * D_SLOT1)) + part * 4 * D_THREADS + tid;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 v = d[q * D_THREADS];
+            a[4 * q] += v.x;
+            a[4 * q + 1] += v.y;
+            a[4 * q + 2] += v.z;
+            a[4 * q + 3] += v.w;
+        }
+    }
+    const int tile = k.listed() + rel, tile_m = tile % p.tiles_m, tile_ci = tile / p.tiles_m;
+    const int lane = tid & 63, wave = tid >> 6;
+    din_store<n>(g, w, din, p, a, ((tile_ci * 4 + wave) * RB + part % RB) * 32 + 4 * (lane >> 5),
+                 din_column(p, tile_m * D_TM + part / RB * 32 + (lane & 31)));
+}
+
+// w[co][ci][u][v] -> MFMA operands: [block of 32 input channels][chunk of 16 output channels][tap][part][lane][8 output
+// channels], taps in the order the main loop walks them (u and v from the last to the first, even columns of the image
+// first).  One wave per (block, chunk, u): all its loads are in flight together, the runs of n values that its lanes
+// leave between them are the other u's (15 -> 8.6 us for 512 x 256 x 4 x 4 against one workgroup per (block,
+// chunk) turning the weights in LDS).
+template <int n, int WP, class T>
+__global__ void __launch_bounds__(256) split_din_weights_kernel(const T *__restrict__ w, char *__restrict__ w_split, DinParams p,
+                                                                unsigned tasks)
+{
+    constexpr int NN = n * n;
+    const unsigned task = blockIdx.x * 4u + (threadIdx.x >> 6);
+    if (task >= tasks) return;
+    const unsigned block = task / n, u = task - block * n;
+    const int blk = (int)(block / (unsigned)p.chunks), chunk = (int)(block - (unsigned)blk * p.chunks);
+    const int lane = threadIdx.x & 63, ci = blk * 32 + (lane & 31), co = chunk * D_KC + 8 * (lane >> 5);
+    float t[8][n];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int v = 0; v < n; ++v)
+            t[j][v] = ci < p.Cin && co + j < p.Cout ? weight_of(w, ((size_t)(co + j) * p.Cin + ci) * NN + u * n + v) : 0.0f;
+    char *d = w_split + ((size_t)block * NN + (n - 1 - u) * n) * (WP * 1024) + lane * 16;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+        constexpr int even = (n + 1) / 2;
+        const int x = i < even ? 2 * i : 2 * (i - even) + 1;
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = t[j][n - 1 - x];
+        bf16x8 part[3];
+        split3(v, part[0], part[1], part[2]);
+#pragma unroll
+        for (int k = 0; k < WP; ++k) *reinterpret_cast<bf16x8 *>(d + (i * WP + k) * 1024) = part[k];
+    }
+}
+
+struct DinPlan {
+    bool ok;
+    int rb, wp;
+    DinParams p;
+    EvenShares k;
+};
+
+// s: the framed problem with Shape::frame = q (its M is the framed map's); odd: the padding factor is odd.
+DinPlan din_plan(const Shape &s, bool odd, kst_dtype dt)
+{
+    DinPlan r;
+    DinParams &p = r.p;
+    const int n = s.n;
+    p.B = s.B; p.Cin = s.Cin; p.Cout = s.Cout;
+    p.N = s.N - 2 * s.frame;
+    p.M = s.M - (odd ? 2 : 0);
+    p.shift = 2 * s.frame - (odd ? 1 : 0) - (n - 1);
+    p.H = 2 * p.N + n - 2;
+    p.W2 = (2 * p.N + n - 1) / 2;
+    p.Mtot = s.B * p.N * p.N;
+    p.tiles_m = (p.Mtot + D_TM - 1) / D_TM;
+    r.wp = dt == KST_BF16 ? 1 : 3;
+    // Two row blocks per wave share every read of g; n = 5's five sets of weights leave no registers for a second one,
+    // and a tile of 256 channels is half empty up to 128.
+    // Fewer than four chunks per workgroup are better spent on the half as large partial sums of one row block.
+    p.chunks = (s.Cout + D_KC - 1) / D_KC;
+    r.rb = n < 5 && s.Cin > 128 && (double)p.tiles_m * ((s.Cin + 255) / 256) * p.chunks >= 4.0 * S_GRID ? 2 : 1;
+    p.tiles_ci = (s.Cin + 128 * r.rb - 1) / (128 * r.rb);
+    // Image rows a tile can touch: two per row of positions, n - 2 more where it steps into the next batch item, and the
+    // window.  Tiles of whole rows that no item boundary cuts touch the fewest.
+    const int rows = D_TM / p.N;
+    const bool whole_rows = rows * p.N == D_TM && (rows % p.N == 0 || p.N % rows == 0);
+    const int dg = whole_rows ? rows - 1 : (D_TM - 2) / p.N + 1;
+    const int crossings = whole_rows ? (rows - 1) / p.N : (dg + p.N - 1) / p.N;
+    p.ip = (2 * dg + crossings * (n - 2) + n) * 2 * p.W2;
+    const size_t g_bytes = (size_t)s.B * s.Cout * p.M * p.M * sizeof(float);
+    const size_t w_bytes = (size_t)((s.Cin + 31) / 32) * p.chunks * n * n * r.wp * 1024;
+    p.g_bytes = (unsigned)g_bytes;
+    p.w_bytes = (unsigned)w_bytes;
+    const unsigned long long tiles = (unsigned long long)p.tiles_m * p.tiles_ci, units = tiles * (unsigned)p.chunks;
+    r.k.chunks = p.chunks;
+    r.k.grid = units < (unsigned long long)S_GRID ? (int)units : S_GRID;
+    r.k.rounds = (int)(tiles / S_GRID);
+    r.k.passes = (int)(tiles - (unsigned long long)r.k.rounds * S_GRID);
+    r.k.taps0 = r.k.taps1 = 1;
+    const unsigned long long all = (unsigned long long)r.k.passes * (unsigned)p.chunks;
+    r.k.per = (int)(all / (unsigned)r.k.grid);
+    r.k.more = (int)(all % (unsigned)r.k.grid);
+    r.ok = n >= 3 && n <= 5 && p.ip <= D_IP && g_bytes < (1u << 31) && w_bytes < (1u << 31) && tiles <= (1u << 22) &&
+           all < (1u << 30);
+    return r;
+}
+
+size_t din_weight_bytes(const DinPlan &pl) { return ((size_t)pl.p.w_bytes + 255) & ~(size_t)255; }
+
+template <int n, int RB, int WP, int NT, class T>
+hipError_t din_launch(const float *g, const T *w, float *din, char *ws, const DinPlan &pl, hipStream_t stream)
+{
+    const int lds = 2 * D_STAGE;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&split_din_kernel<n, RB, WP, NT, T>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    const unsigned tasks = (unsigned)((pl.p.Cin + 31) / 32) * (unsigned)pl.p.chunks * n;
+    hipLaunchKernelGGL((split_din_weights_kernel<n, WP, T>), dim3((tasks + 3) / 4), dim3(256), 0, stream, w, ws, pl.p, tasks);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    float *slots = (float *)(ws + din_weight_bytes(pl));
+    hipLaunchKernelGGL((split_din_kernel<n, RB, WP, NT, T>), dim3((unsigned)pl.k.grid), dim3(D_THREADS), lds, stream, g, w,
+                       (const void *)ws, din, slots, pl.p, pl.k);
+    e = hipGetLastError();
+    if (e != hipSuccess || pl.k.passes == 0) return e;
+    hipLaunchKernelGGL((split_din_sum_kernel<n, RB, T>), dim3(4u * RB * pl.k.passes), dim3(D_THREADS), 0, stream, g, w, din,
+                       (const float *)slots, pl.p, pl.k);
+    return hipGetLastError();
+}
+
+template <int n, int RB, int WP, class T>
+hipError_t din_launch_nt(const float *g, const T *w, float *din, char *ws, const DinPlan &pl, hipStream_t stream)
+{
+    return pl.p.ip <= 5 * 128 ? din_launch<n, RB, WP, 5>(g, w, din, ws, pl, stream)
+                              : din_launch<n, RB, WP, 7>(g, w, din, ws, pl, stream);
+}
+
+template <int WP, class T>
+hipError_t din_launch_n(const float *g, const T *w, float *din, char *ws, const DinPlan &pl, int n, hipStream_t stream)
+{
+    if (n == 3)
+        return pl.rb == 2 ? din_launch_nt<3, 2, WP>(g, w, din, ws, pl, stream) : din_launch_nt<3, 1, WP>(g, w, din, ws, pl, stream);
+    if (n == 4)
+        return pl.rb == 2 ? din_launch_nt<4, 2, WP>(g, w, din, ws, pl, stream) : din_launch_nt<4, 1, WP>(g, w, din, ws, pl, stream);
+    return din_launch_nt<5, 1, WP>(g, w, din, ws, pl, stream);
+}
+
+}  // namespace
+
+bool split_din_applies(const Shape &s, bool odd, kst_dtype dt)
+{
+    if (s.Cin < 16 || s.Cout <= D_KC) return false;
+    // Three launches and partial tiles cost about 40 us; the fp32 multiplies' tiles hold 128 input channels whatever the
+    // layer has, so that is what is weighed.  512 -> 256 channels, 8 x 8, n = 4, P = 2: 61 us here against 52 at a batch of
+    // 16 (2.15 G products), 70 against 88 at 32; 64 -> 64, 32 x 32, n = 3, batch 64: 68 against 149 (4.8 G, half of them
+    // padding).
+    const double edge = s.N - 2 * s.frame;
+    const double products = (double)s.B * edge * edge * s.n * s.n * ((s.Cin + 127) / 128 * 128) * s.Cout;
+    return products >= 2.2e9 && din_plan(s, odd, dt).ok;
+}
+
+size_t split_din_workspace_bytes(const Shape &s, bool odd, kst_dtype dt)
+{
+    const DinPlan r = din_plan(s, odd, dt);
+    return din_weight_bytes(r) + (r.k.passes ? (size_t)2 * r.k.grid * r.rb * D_SLOT1 * sizeof(float) : 0);
+}
+
+hipError_t launch_split_din(const float *g, const void *w, float *din, void *ws, const Shape &s, bool odd, kst_dtype dt,
+                            hipStream_t stream)
+{
+    const DinPlan r = din_plan(s, odd, dt);
+    if (!r.ok) return hipErrorInvalidValue;
+    if (dt == KST_BF16) return din_launch_n<1>(g, (const uint16_t *)w, din, (char *)ws, r, s.n, stream);
+    if (dt == KST_F16) return hipErrorInvalidValue;
+    return din_launch_n<3>(g, (const float *)w, din, (char *)ws, r, s.n, stream);
+}
+
+}  // namespace kst

@@ -108,3 +108,70 @@ def test_split_forward_small_values():
     one = _forward(x, w, 2)
     small = _forward(x * 2.0 ** -60, w * 2.0 ** -40, 2)
     assert torch.equal(small, one * 2.0 ** -100)
+
+
+# Input gradient: 128 and 256 input channels per tile, five and seven staged cells per lane, ragged channels, odd padding
+# factors, tiles that cross items and rows, bfloat16 weights (one part) and half-precision ones (widened).
+INPUT_GRADIENT = [
+    (64, 512, 256, 8, 4, 2, "f32"),
+    (25, 200, 133, 16, 4, 1, "f32"),
+    (17, 130, 70, 33, 3, 0, "f32"),
+    (30, 128, 66, 19, 5, 3, "f32"),
+    (33, 40, 530, 10, 5, 2, "f32"),
+    (9, 96, 130, 64, 3, 2, "f32"),
+    (64, 256, 128, 16, 4, 2, "bf16"),
+    (40, 70, 130, 21, 3, 1, "bf16"),
+    (64, 200, 67, 13, 4, 1, "f16"),
+]
+_DT = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
+
+
+def _gradient_inputs(shape, seed):
+    B, Cin, Cout, N, n, P, dtype = shape
+    x, w = _layer(shape[:6], seed)
+    M = 2 * N + 2 * P - n
+    g = torch.randn((B, Cout, M, M), generator=torch.Generator().manual_seed(seed + 1)) * 0.1
+    return x.to(_DT[dtype]), w.to(_DT[dtype]), g
+
+
+def _items(B):
+    return sorted({0, 1, B // 2, B - 1})
+
+
+@pytest.mark.parametrize("shape", INPUT_GRADIENT)
+def test_split_input_gradient(shape):
+    B, Cin, Cout, N, n, P, dtype = shape
+    _, w, g = _gradient_inputs(shape, 17 + B)
+    din = kst.kst_backward_input(g.to(DEV), w.to(DEV), N, P)
+    again = kst.kst_backward_input(g.to(DEV), w.to(DEV), N, P)
+    items = _items(B)
+    want = oracle.backward_input(wl.to_f64(g[items]), wl.to_f64(w), N, P)
+    got = din[items].cpu().numpy().astype(np.float64)
+    assert np.abs(got - want).max() <= TOL * np.abs(want).max()
+    assert torch.equal(din, again)
+    # every element: the sum over the input channels with random weights, in fp32 on the GPU against a one-channel layer
+    r = torch.randn(Cin, generator=torch.Generator().manual_seed(2)).double()
+    wr = torch.einsum("oiuv,i->ouv", w.double(), r)[:, None]
+    want = oracle.backward_input(wl.to_f64(g), np.ascontiguousarray(wr.numpy()), N, P)[:, 0]
+    got = (din.double() * r.to(DEV).view(1, -1, 1, 1)).sum(1).cpu().numpy()
+    assert np.abs(got - want).max() <= TOL * np.abs(want).max()
+
+
+@pytest.mark.parametrize("shape", [INPUT_GRADIENT[1], INPUT_GRADIENT[7]])
+def test_split_input_gradient_infinities_and_nan(shape):
+    B, Cin, Cout, N, n, P, dtype = shape
+    _, w, g = _gradient_inputs(shape, 23)
+    M = g.shape[2]
+    g[0, 1, 2, 3] = float("inf")
+    g[B - 1, Cout - 1, M - 1, M - 1] = float("nan")
+    w[2, 1, 0, n - 1] = 3.38e38                       # finite in bfloat16 too
+    din = kst.kst_backward_input(g.to(DEV), w.to(DEV), N, P).cpu()
+    items = _items(B)
+    with np.errstate(invalid="ignore"):
+        want = torch.from_numpy(oracle.backward_input(wl.to_f64(g[items]), wl.to_f64(w), N, P)).float()
+    got = din[items]
+    finite = torch.isfinite(want)
+    assert torch.equal(torch.isfinite(got), finite)
+    assert torch.equal(torch.isnan(got), torch.isnan(want))
+    largest = want.where(finite, 0.0).abs().amax(dim=(0, 2, 3), keepdim=True).expand_as(want)   # (one channel holds 1e37s)
+    assert ((got - want)[finite].abs() <= TOL * largest[finite]).all()

@@ -517,6 +517,8 @@ struct GradPlan {
                                       // widened to fp32 first, which is exact)
     kst_dtype din_split;              // operand type of w where the input gradient runs on the bf16 matrix cores
     bool use_din_split;               // ... (half-precision weights are widened to fp32 first)
+    bool use_dw_split;                // the kernel gradient too
+    size_t dw_split_bytes;
     size_t din_split_bytes;           // its whole workspace (after the widened weights)
     size_t wconv_bytes, xconv_bytes;  // fp32 copies of w (input gradient) and of in (kernel gradient) for that
 };
@@ -558,6 +560,8 @@ kst_status grad_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dt
         f->wconv_bytes = is16(dt) ? (((size_t)Cout * Cin * n * n * sizeof(float) + 255) & ~(size_t)255) : 0;
         f->din_split_bytes = split_din_workspace_bytes(f->si, (P & 1) != 0, KST_F32);
     }
+    f->use_dw_split = split_dw_applies(f->si, (P & 1) != 0);
+    f->dw_split_bytes = f->use_dw_split ? split_dw_workspace_bytes(f->si, (P & 1) != 0) : 0;
     f->wsplit_bytes = f->dw_cores
                           ? backward_weight_igemm_workspace_bytes(f->si)
                           : backward_weight_generic_workspace_bytes(f->plain_unframed ? f->si : f->s);
@@ -587,6 +591,7 @@ size_t kst_backward_weight_workspace_bytes(int B, int Cin, int Cout, int N, int 
 {
     GradPlan f;
     if (!dtype_ok(dtype) || grad_plan(B, Cin, Cout, N, n, P, dtype, &f) != KST_OK) return 0;
+    if (f.use_dw_split) return f.dw_split_bytes + f.xconv_bytes;
     return f.dw_cores ? f.gw_bytes + f.wsplit_bytes + f.xconv_bytes : f.in_bytes + f.g_bytes + f.wsplit_bytes;
 }
 
@@ -652,6 +657,13 @@ kst_status kst_backward_weight(const void *in, const void *g, void *dw, void *ws
     kst_status st = grad_plan(B, Cin, Cout, N, n, P, dtype, &f);
     if (st != KST_OK) return st;
     if (!aligned16(in) || !aligned16(g) || !aligned16(dw)) return KST_ERR_ALIGN;
+    if (f.use_dw_split) {
+        if (!ws || ws_bytes < f.dw_split_bytes + f.xconv_bytes) return KST_ERR_WORKSPACE;
+        if (!aligned16(ws)) return KST_ERR_ALIGN;
+        return launch_split_dw(in, (const float *)g, (float *)dw, ws, f.si, (P & 1) != 0, dtype, stream) == hipSuccess
+                   ? KST_OK
+                   : KST_ERR_HIP;
+    }
     const bool cores = f.dw_cores;
     const size_t g_copy = cores ? f.gw_bytes : f.g_bytes;
     const size_t in_copy = cores ? 0 : f.in_bytes;     // the matrix-core kernel reads `in` as it lies in memory

@@ -175,3 +175,67 @@ def test_split_input_gradient_infinities_and_nan(shape):
     assert torch.equal(torch.isnan(got), torch.isnan(want))
     largest = want.where(finite, 0.0).abs().amax(dim=(0, 2, 3), keepdim=True).expand_as(want)   # (one channel holds 1e37s)
     assert ((got - want)[finite].abs() <= TOL * largest[finite]).all()
+
+
+# Kernel gradient: ragged channel blocks and items, odd numbers of taps, odd padding factors, one and three parts of the
+# input, more and fewer splits than steps allow.
+KERNEL_GRADIENT = [
+    (64, 512, 256, 8, 4, 2, "f32"),
+    (30, 250, 127, 19, 3, 1, "f32"),
+    (45, 128, 120, 11, 5, 3, "f32"),
+    (160, 384, 384, 4, 4, 0, "f32"),
+    (64, 256, 128, 16, 4, 2, "bf16"),
+    (31, 125, 256, 20, 3, 0, "bf16"),
+    (47, 128, 256, 14, 4, 1, "f16"),
+]
+
+
+@pytest.mark.parametrize("shape", KERNEL_GRADIENT)
+def test_split_kernel_gradient(shape):
+    B, Cin, Cout, N, n, P, dtype = shape
+    x, _, g = _gradient_inputs(shape, 47 + B)
+    dw = kst.kst_backward_weight(x.to(DEV), g.to(DEV), n, P)
+    again = kst.kst_backward_weight(x.to(DEV), g.to(DEV), n, P)
+    assert torch.equal(dw, again)
+    # a few channels of either kind exactly as the oracle has them
+    cos, cis = sorted({0, 31, Cout // 2, Cout - 1}), sorted({0, 33, Cin // 2, Cin - 1})
+    want = oracle.backward_weight(wl.to_f64(x[:, cis]), wl.to_f64(g[:, cos]), n, P)
+    got = dw[cos][:, cis].cpu().numpy().astype(np.float64)
+    assert np.abs(got - want).max() <= TOL * np.abs(want).max()
+    # every element: random combinations of the channels on one side
+    r = torch.randn(Cin, generator=torch.Generator().manual_seed(4)).double()
+    xr = torch.einsum("bihw,i->bhw", x.double(), r)[:, None].numpy()
+    want = oracle.backward_weight(np.ascontiguousarray(xr), wl.to_f64(g), n, P)[:, 0]
+    got = (dw.double() * r.to(DEV).view(1, -1, 1, 1)).sum(1).cpu().numpy()
+    assert np.abs(got - want).max() <= TOL * np.abs(want).max()
+
+
+@pytest.mark.parametrize("shape", [KERNEL_GRADIENT[1], KERNEL_GRADIENT[5]])
+def test_split_kernel_gradient_infinities_and_nan(shape):
+    B, Cin, Cout, N, n, P, dtype = shape
+    x, _, g = _gradient_inputs(shape, 53)
+    M = g.shape[2]
+    g[0, 1, M // 2, M // 2] = float("inf")
+    g[1, 2, M // 2, 3] = 3.4e38
+    x[B - 1, 5, N // 2, N // 2] = float("nan")
+    x = x.clone()
+    x[0, 7] = 1.0                                     # (every product with the infinity is one)
+    dw = kst.kst_backward_weight(x.to(DEV), g.to(DEV), n, P).cpu()
+    cos, cis = [0, 1, 2, Cout - 1], [0, 5, 7, Cin - 1]
+    # (the oracle multiplies the embedded zeros too, which makes NaN of infinities; here only the terms that exist)
+    xd, gd = x[:, cis].double(), g[:, cos].double()
+    want = torch.zeros((len(cos), len(cis), n, n), dtype=torch.float64)
+    for u in range(n):
+        for v in range(n):
+            rows = [a for a in range(N) if 0 <= 2 * a + P - u < M]
+            cols = [c for c in range(N) if 0 <= 2 * c + P - v < M]
+            gs = gd[:, :, [2 * a + P - u for a in rows]][:, :, :, [2 * c + P - v for c in cols]]
+            xs = xd[:, :, rows][:, :, :, cols]
+            want[:, :, u, v] = (gs[:, :, None] * xs[:, None]).sum(dim=(0, 3, 4))
+    want = want.float()
+    got = dw[cos][:, cis]
+    finite = torch.isfinite(want)
+    assert torch.equal(torch.isfinite(got), finite)
+    assert torch.equal(torch.isnan(got), torch.isnan(want))
+    largest = want.where(finite, 0.0).abs().amax(dim=(1, 2, 3), keepdim=True).expand_as(want)
+    assert ((got - want)[finite].abs() <= TOL * largest[finite]).all()

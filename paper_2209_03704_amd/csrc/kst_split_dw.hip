@@ -13,8 +13,8 @@
 // channels and two taps, a wave 64 x 64 of them: 8 blocks, the largest partial products' sums apart from the others',
 // 256 accumulator registers; 48 MFMAs per step for 18 loads, one step ahead.  What bounds it is the rate at which the
 // cache of a CU hands over those operands (18 KB per wave and 1536 cycles; each is wanted by two waves).
-// 64 x 512 x 256 x 8 x 8, n = 4, P = 2: 22 us for the two passes, 89 us here and 9 us for the sums, where framing g, the
-// fp32 multiplies and their sums took 202; with bfloat16 input 64 x 256 x 128 x 16 x 16: 40 + 58 + 9 against 212.
+// 64 x 512 x 256 x 8 x 8, n = 4, P = 2: 16 us for the two passes, 89 us here and 9 us for the sums, where framing g, the
+// fp32 multiplies and their sums took 202; with bfloat16 input 64 x 256 x 128 x 16 x 16: 22 + 58 + 9 against 212.
 #include "kst_split_common.h"
 
 namespace kst {
@@ -37,38 +37,76 @@ __device__ __forceinline__ float value_of(const float *p) { return *p; }
 __device__ __forceinline__ float value_of(const uint16_t *p) { return to_f32(*p); }
 __device__ __forceinline__ float value_of(const half_bits *p) { return to_f32(*p); }
 
+// Four neighbours at p, of which `count` exist; VEC: all four in one aligned load.
+template <bool VEC, class T>
+__device__ __forceinline__ void load_four(const T *p, int count, float (&v)[4])
+{
+    if constexpr (VEC) {
+        T t[4];
+        __builtin_memcpy(t, __builtin_assume_aligned(p, 4 * sizeof(T)), sizeof(t));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = count > 0 ? value_of(t + i) : 0.0f;
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = i < count ? value_of(p + i) : 0.0f;
+    }
+}
+
 // src[B][C][edge][edge] -> operands of PARTS parts, zeros past the last item and channel.  One wave per (channel block,
-// group of items, row, four columns): a lane reads four neighbours of eight items.
-template <int PARTS, class T>
+// group of items, row, eight columns): a lane reads eight neighbours of eight items, in two loads each where the rows
+// are whole groups of four (VEC).  Lanes of a wave read different rows, so what a lane leaves of its line has to come
+// from the cache again: a float g of 64 x 128 x 32 x 32 takes 15 us (5.6 TB/s of
+// the 33 MB read and 50 MB written), 27 with four columns and one element per load.
+constexpr int E_COLS = 8;
+
+template <int PARTS, bool VEC, class T>
 __global__ void __launch_bounds__(256) split_items_kernel(const T *__restrict__ src, char *__restrict__ dst, int B, int C,
                                                           int edge, int groups, unsigned tasks)
 {
     unsigned t = blockIdx.x * 4u + (threadIdx.x >> 6);
     if (t >= tasks) return;
-    const unsigned quads = (unsigned)(edge + 3) / 4u;
-    const int x0 = 4 * (int)(t % quads);
-    t /= quads;
+    const unsigned runs = (unsigned)(edge + E_COLS - 1) / E_COLS;
+    const int x0 = E_COLS * (int)(t % runs);
+    t /= runs;
     const int y = (int)(t % (unsigned)edge);
     t /= (unsigned)edge;
     const int group = (int)(t % (unsigned)groups), blk = (int)(t / (unsigned)groups);
     const int lane = threadIdx.x & 63, c = blk * 32 + (lane & 31), b = group * 16 + 8 * (lane >> 5);
-    float v[4][8];
+    float v[8][E_COLS / 4][4];
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < 8; ++j) {
+        const bool ok = c < C && b + j < B;
+        const T *row = src + ((ok ? (size_t)(b + j) * C + c : 0) * edge + y) * edge;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            v[i][j] = c < C && b + j < B && x0 + i < edge
-                          ? value_of(src + (((size_t)(b + j) * C + c) * edge + y) * edge + x0 + i)
-                          : 0.0f;
+        for (int h = 0; h < E_COLS / 4; ++h) {
+            const int x = x0 + 4 * h, count = ok ? edge - x : 0;
+            load_four<VEC>(row + (x < edge ? x : 0), count, v[j][h]);
+        }
+    }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < E_COLS; ++i) {
         if (x0 + i >= edge) break;
+        float eight[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) eight[j] = v[j][i >> 2][i & 3];
         bf16x8 part[3];
-        split3(v[i], part[0], part[1], part[2]);
+        split3(eight, part[0], part[1], part[2]);
         char *d = dst + ((((size_t)blk * edge + y) * edge + x0 + i) * groups + group) * (PARTS * 1024) + lane * 16;
 #pragma unroll
         for (int k = 0; k < PARTS; ++k) *reinterpret_cast<bf16x8 *>(d + k * 1024) = part[k];
     }
+}
+
+template <int PARTS, class T>
+hipError_t split_items(const T *src, char *dst, int B, int C, int edge, int groups, hipStream_t stream)
+{
+    const unsigned tasks = (unsigned)((C + 31) / 32) * groups * edge * ((edge + E_COLS - 1) / E_COLS);
+    const dim3 grid((tasks + 3) / 4), block(256);
+    if (edge % 4 == 0)
+        hipLaunchKernelGGL((split_items_kernel<PARTS, true, T>), grid, block, 0, stream, src, dst, B, C, edge, groups, tasks);
+    else
+        hipLaunchKernelGGL((split_items_kernel<PARTS, false, T>), grid, block, 0, stream, src, dst, B, C, edge, groups, tasks);
+    return hipGetLastError();
 }
 
 // Partial sums part[split][tap][co][ci].
@@ -294,15 +332,9 @@ hipError_t dw_launch(const T *in, const float *g, float *dw, char *ws, const DwP
     const DwParams &p = pl.p;
     char *xf = ws, *gf = ws + pl.x_bytes;
     float *part = (float *)(gf + pl.g_bytes);
-    const unsigned x_tasks = (unsigned)((p.Cin + 31) / 32) * p.groups * p.N * ((p.N + 3) / 4);
-    const unsigned g_tasks = (unsigned)((p.Cout + 31) / 32) * p.groups * p.M * ((p.M + 3) / 4);
-    hipLaunchKernelGGL((split_items_kernel<XP, T>), dim3((x_tasks + 3) / 4), dim3(256), 0, stream, in, xf, p.B, p.Cin, p.N,
-                       p.groups, x_tasks);
-    hipError_t e = hipGetLastError();
+    hipError_t e = split_items<XP>(in, xf, p.B, p.Cin, p.N, p.groups, stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((split_items_kernel<3, float>), dim3((g_tasks + 3) / 4), dim3(256), 0, stream, g, gf, p.B, p.Cout, p.M,
-                       p.groups, g_tasks);
-    e = hipGetLastError();
+    e = split_items<3>(g, gf, p.B, p.Cout, p.M, p.groups, stream);
     if (e != hipSuccess) return e;
     const unsigned blocks = (unsigned)p.splits * p.tiles_co * p.tiles_ci * p.pairs;
     hipLaunchKernelGGL((split_dw_kernel<n, XP>), dim3(blocks), dim3(E_THREADS), 0, stream, (const void *)xf, (const void *)gf,
@@ -331,7 +363,7 @@ bool split_dw_applies(const Shape &s, bool odd)
     const double products = (double)s.B * edge * edge * nn * s.Cin * s.Cout;
     const double padded = (double)((s.B + 15) / 16 * 16) * edge * edge * nn * ((s.Cin + 127) / 128 * 128) *
                           ((s.Cout + 127) / 128 * 128);
-    // The two passes and four launches cost 25 to 40 us: 512 -> 256 channels, 8 x 8, n = 4, P = 2 at a batch of 32 (4.3 G
+    // The two passes and four launches cost 20 to 30 us (measured with passes half as fast): 512 -> 256 channels, 8 x 8, n = 4, P = 2 at a batch of 32 (4.3 G
     // products) 75 us against 111, 128 -> 128, 24 x 24, n = 5 at 16 (3.8 G) 85 against 124, 128 -> 128, 32 x 32, n = 3 at 32
     // (4.8 G, mostly passes over g) 142 against 150.  What fills items and channels up to whole blocks is multiplied too.
     return products >= 3.0e9 && padded <= 1.5 * products && dw_plan(s, odd, 3).ok;

@@ -621,6 +621,12 @@ bool split_f32_applies(const Shape &s)
     // 512 -> 256 channels, 8 x 8, n = 4 measured 45.7 us here against 42.2 with fp32 multiplies at a batch of 8 (1.07 G
     // products) and 49.2 against 60.6 at 16 (2.15 G); 64 -> 64, 32 x 32, n = 3: 46 against 33 at 16 (0.64 G), 77 against
     // 81 at 64 (2.6 G).  One chunk of channels leaves nothing to run ahead of (16 -> 16, 64 x 64: 126 against 74).
+    // Fewer than eight chunks keep a pass's first and last ones in view: where the pipelined fp32 kernel takes the layer
+    // (whole groups of four channels and, unframed, columns) it is as fast or faster (33 x 64 x 152 x 15 x 15, n = 5, P = 2:
+    // 83 us here against 68; 15 x 96 x 128 x 29 x 29: 95 against 97); the plain one is not (9 x 68 x 352 x 35 x 35, n = 4:
+    // 97 against 248).
+    const bool pipelined = (s.Cin & 3) == 0 && (s.Cout & 3) == 0 && (s.frame > 0 || (s.N & 3) == 0);
+    if (pipelined && s.Cin < 8 * S_KC) return false;
     const double products = (double)s.B * s.E * s.E * s.n * s.n * s.Cin * s.Cout;
     return products >= 1.5e9 && plan(s).ok;
 }

@@ -519,7 +519,8 @@ struct GradPlan {
     bool use_din_split;               // ... (half-precision weights are widened to fp32 first)
     bool use_dw_split;                // the kernel gradient too
     size_t dw_split_bytes;
-    size_t din_split_bytes;           // its whole workspace (after the widened weights)
+    size_t din_split_bytes;           // its whole workspace, widened half-precision weights included
+    size_t din_split_query;           // ... as kst_backward_input_workspace_bytes gives it
     size_t wconv_bytes, xconv_bytes;  // fp32 copies of w (input gradient) and of in (kernel gradient) for that
 };
 
@@ -554,11 +555,20 @@ kst_status grad_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dt
     if (f->plain_unframed) f->in_bytes = 0;            // `in` read as it lies in memory
     f->din_split = dt == KST_F16 ? KST_F32 : dt;
     f->use_din_split = split_din_applies(f->si, (P & 1) != 0, f->din_split);
-    f->din_split_bytes = 0;
+    f->din_split_bytes = f->din_split_query = 0;
     if (f->use_din_split) {
-        // (one size for both 16-bit types: the fp32 kernels' after a widening of w, which bfloat16 does without)
-        f->wconv_bytes = is16(dt) ? (((size_t)Cout * Cin * n * n * sizeof(float) + 255) & ~(size_t)255) : 0;
-        f->din_split_bytes = split_din_workspace_bytes(f->si, (P & 1) != 0, KST_F32);
+        // What the launch lays out, by the type it is launched with.  The query gives both 16-bit types one size, half
+        // precision's, where the kernels take half precision too (its weights, widened, may be too large for them when
+        // bfloat16's one part is not).
+        const bool odd = (P & 1) != 0;
+        const size_t widened = ((size_t)Cout * Cin * n * n * sizeof(float) + 255) & ~(size_t)255;
+        f->wconv_bytes = dt == KST_F16 ? widened : 0;
+        f->din_split_bytes = f->wconv_bytes + split_din_workspace_bytes(f->si, odd, f->din_split);
+        f->din_split_query = f->din_split_bytes;
+        if (dt == KST_BF16 && split_din_applies(f->si, odd, KST_F32)) {
+            const size_t half = widened + split_din_workspace_bytes(f->si, odd, KST_F32);
+            if (half > f->din_split_query) f->din_split_query = half;
+        }
     }
     f->use_dw_split = split_dw_applies(f->si, (P & 1) != 0);
     f->dw_split_bytes = f->use_dw_split ? split_dw_workspace_bytes(f->si, (P & 1) != 0) : 0;
@@ -584,7 +594,7 @@ size_t kst_backward_input_workspace_bytes(int B, int Cin, int Cout, int N, int n
 {
     GradPlan f;
     if (!dtype_ok(dtype) || grad_plan(B, Cin, Cout, N, n, P, dtype, &f) != KST_OK) return 0;
-    return f.use_din_split ? f.wconv_bytes + f.din_split_bytes : f.g_bytes + f.din_bytes + f.split_bytes + f.wconv_bytes;
+    return f.use_din_split ? f.din_split_query : f.g_bytes + f.din_bytes + f.split_bytes + f.wconv_bytes;
 }
 
 size_t kst_backward_weight_workspace_bytes(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dtype)
@@ -604,8 +614,7 @@ kst_status kst_backward_input(const void *g, const void *w, void *din, void *ws,
     kst_status st = grad_plan(B, Cin, Cout, N, n, P, dtype, &f);
     if (st != KST_OK) return st;
     if (!aligned16(g) || !aligned16(w) || !aligned16(din)) return KST_ERR_ALIGN;
-    const size_t need = f.use_din_split ? f.wconv_bytes + f.din_split_bytes
-                                        : f.g_bytes + f.din_bytes + f.split_bytes + f.wconv_bytes;
+    const size_t need = f.use_din_split ? f.din_split_bytes : f.g_bytes + f.din_bytes + f.split_bytes + f.wconv_bytes;
     if (need) {
         if (!ws || ws_bytes < need) return KST_ERR_WORKSPACE;
         if (!aligned16(ws)) return KST_ERR_ALIGN;

@@ -392,6 +392,7 @@ __global__ void __launch_bounds__(256) split_din_weights_kernel(const T *__restr
 struct DinPlan {
     bool ok;
     int rb, wp;
+    size_t w_bytes;        // split weights: as the launch lays them out, in full width (p.w_bytes only where ok)
     DinParams p;
     EvenShares k;
 };
@@ -428,6 +429,7 @@ DinPlan din_plan(const Shape &s, bool odd, kst_dtype dt)
     const size_t w_bytes = (size_t)((s.Cin + 31) / 32) * p.chunks * n * n * r.wp * 1024;
     p.g_bytes = (unsigned)g_bytes;
     p.w_bytes = (unsigned)w_bytes;
+    r.w_bytes = w_bytes;
     const unsigned long long tiles = (unsigned long long)p.tiles_m * p.tiles_ci, units = tiles * (unsigned)p.chunks;
     r.k.chunks = p.chunks;
     r.k.grid = units < (unsigned long long)S_GRID ? (int)units : S_GRID;
@@ -442,7 +444,7 @@ DinPlan din_plan(const Shape &s, bool odd, kst_dtype dt)
     return r;
 }
 
-size_t din_weight_bytes(const DinPlan &pl) { return ((size_t)pl.p.w_bytes + 255) & ~(size_t)255; }
+size_t din_weight_bytes(const DinPlan &pl) { return (pl.w_bytes + 255) & ~(size_t)255; }
 
 template <int n, int RB, int WP, int NT, class T>
 hipError_t din_launch(const float *g, const T *w, float *din, char *ws, const DinPlan &pl, hipStream_t stream)
@@ -496,9 +498,11 @@ bool split_din_applies(const Shape &s, bool odd, kst_dtype dt)
     return products >= 2.2e9 && din_plan(s, odd, dt).ok;
 }
 
+// (0 for a layer these kernels do not take with weights of this type)
 size_t split_din_workspace_bytes(const Shape &s, bool odd, kst_dtype dt)
 {
     const DinPlan r = din_plan(s, odd, dt);
+    if (!r.ok) return 0;
     return din_weight_bytes(r) + (r.k.passes ? (size_t)2 * r.k.grid * r.rb * D_SLOT1 * sizeof(float) : 0);
 }
 

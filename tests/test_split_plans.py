@@ -1,0 +1,49 @@
+"""Workspace sizes of the kernels that split fp32 operands for the bf16 matrix cores, against what those kernels lay out
+in it (no GPU: the sizes come from the host)."""
+import pytest
+
+from paper_2209_03704_amd import binding as kst
+
+F32, BF16, F16 = kst.KST_F32, kst.KST_BF16, kst.KST_F16
+
+
+def _up(v, to):
+    return (v + to - 1) // to * to
+
+
+def split_din_weight_bytes(Cin, Cout, n, parts):
+    """[block of 32 input channels][chunk of 16 output channels][tap][part][64 lanes][8 values of 2 bytes]"""
+    return _up(_up(Cin, 32) // 32 * (_up(Cout, 16) // 16) * n * n * parts * 1024, 256)
+
+
+def split_din_slot_bytes(B, Cin, Cout, N, n):
+    """Partial tiles of 128 positions and 128 or 256 input channels: two per workgroup where tiles are shared."""
+    tiles_m, chunks = -(-B * N * N // 128), -(-Cout // 16)
+    rb = 2 if n < 5 and Cin > 128 and tiles_m * -(-Cin // 256) * chunks >= 4 * 256 else 1
+    tiles = tiles_m * -(-Cin // (128 * rb))
+    return 2 * min(256, tiles * chunks) * rb * 256 * 64 * 4 if tiles % 256 else 0
+
+
+# Weights whose three parts pass the 2 GB a launch can address while bfloat16's one part does not: the size has to be
+# that of the type that is launched, from the first byte the launch writes to its last.
+@pytest.mark.parametrize("B,Cin,Cout,N,n", [(1, 7000, 7000, 8, 4), (1, 10000, 10000, 8, 3), (1, 6000, 6000, 8, 5)])
+def test_bf16_input_gradient_workspace_holds_large_weights(B, Cin, Cout, N, n):
+    assert split_din_weight_bytes(Cin, Cout, n, 1) < 2 ** 31 <= split_din_weight_bytes(Cin, Cout, n, 3)
+    laid_out = split_din_weight_bytes(Cin, Cout, n, 1) + split_din_slot_bytes(B, Cin, Cout, N, n)
+    assert kst.kst_backward_input_workspace_bytes(B, Cin, Cout, N, n, 0, BF16) == laid_out
+    # a byte less is refused before anything is launched (pointers are never followed)
+    assert kst.lib().kst_backward_input(16, 16, 16, 16, laid_out - 1, B, Cin, Cout, N, n, 0, BF16, None) == 4
+    # three parts: not these kernels (half precision is widened to fp32 first, fp32 weights are their own)
+    for dt in (F32, F16):
+        assert kst.kst_backward_input_workspace_bytes(B, Cin, Cout, N, n, 0, dt) != (
+            split_din_weight_bytes(Cin, Cout, n, 3) + split_din_slot_bytes(B, Cin, Cout, N, n))
+
+
+@pytest.mark.parametrize("B,Cin,Cout,N,n", [(64, 512, 256, 8, 4), (160, 250, 130, 10, 3), (256, 128, 96, 8, 5)])
+def test_input_gradient_workspace_is_the_layout(B, Cin, Cout, N, n):
+    slots = split_din_slot_bytes(B, Cin, Cout, N, n)
+    widened = _up(Cin * Cout * n * n * 4, 256)
+    of = {dt: kst.kst_backward_input_workspace_bytes(B, Cin, Cout, N, n, 0, dt) for dt in (F32, BF16, F16)}
+    assert of[F32] == split_din_weight_bytes(Cin, Cout, n, 3) + slots
+    assert of[F16] == widened + of[F32]
+    assert of[BF16] == of[F16] > split_din_weight_bytes(Cin, Cout, n, 1) + slots      # one size for 16-bit types

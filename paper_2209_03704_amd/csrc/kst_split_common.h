@@ -3,27 +3,35 @@
 //
 // v_mfma_f32_32x32x16_bf16 multiplies sixteen times what v_mfma_f32_32x32x2_f32 does in the same time
 // (2.24 against 0.15 PFLOP/s measured on this chip with nothing but multiplies).  An fp32 value is the
-// exact sum of three bfloat16 parts, x = x0 + x1 + x2 (rounded to nearest: |x1| <= 2^-9 |x|, |x2| <= 2^-18 |x|),
+// exact sum of three bfloat16 parts, x = x0 + x1 + x2 (rounded to nearest: |x1| <= 2^-8 |x|, |x2| <= 2^-17 |x|),
 // and a product of two such sums needs six of the nine partial products:
 //     x w ~ x0 w0 + (x0 w1 + x1 w0) + (x0 w2 + x1 w1 + x2 w0)
-// What is left out, x1 w2 + x2 w1 + x2 w2, is below 2^-26 of the product, a quarter of the half-ulp (2^-24) that
-// one fp32 addition may be off by; every partial product is exact in fp32 and all sums are fp32 sums.
+// What is left out, x1 w2 + x2 w1 + x2 w2, is at most 2^-24 of the product, what one fp32 addition may
+// be off by; every partial product is exact in fp32 and all sums are fp32 sums.
+//
+// bfloat16 has fp32's exponents but 16 bits less below the point, so the low parts of a small value would fall below
+// its smallest step (2^-133: an operand of 1e-36 would keep 14 bits, one of 3e-38 five).  All operands are therefore
+// multiplied by 2^24 before they are split, which makes every part of every fp32 value, subnormal ones too, a normal
+// bfloat16 number, and the sums by 2^-48 before anything else is done with them.
 //
 // A value that is infinite, not a number, or rounds to infinity in bfloat16 has no such parts.  Each of them makes
-// every sum it enters infinite or not a number, so the stores look for sums that are not finite and compute those
-// elements again with plain fp32 multiply-adds.
+// every sum it enters infinite or not a number, and so does a sum beyond fp32's largest value over 2^48; the stores
+// look for sums that are not finite and compute those elements again with plain fp32 multiply-adds.
 #pragma once
 #include "kst_igemm_common.h"
 
 namespace kst {
 
-// Eight values -> their three bfloat16 parts.
+constexpr float SPLIT_SCALE = 0x1p24f;                       // of both operands
+constexpr float SPLIT_UNSCALE = 0x1p-48f;                    // of their products' sums
+
+// Eight values times SPLIT_SCALE -> their three bfloat16 parts.
 __device__ __forceinline__ void split3(const float (&v)[8], bf16x8 &p0, bf16x8 &p1, bf16x8 &p2)
 {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        p0[j] = (__bf16)v[j];
-        const float r1 = v[j] - (float)p0[j];
+        p0[j] = (__bf16)(v[j] * SPLIT_SCALE);
+        const float r1 = fmaf(v[j], SPLIT_SCALE, -(float)p0[j]);
         p1[j] = (__bf16)r1;
         p2[j] = (__bf16)(r1 - (float)p1[j]);
     }

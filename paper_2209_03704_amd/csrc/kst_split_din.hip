@@ -179,7 +179,7 @@ __device__ __forceinline__ void din_accumulate(const float *__restrict__ g, cons
                 });
                 read_x(integral_constant<int, last ? 0 : q + 1>{}, integral_constant<int, xp>{});
             });
-            constexpr int valu = (16 + 48 * staged_in(q) + MF - 1) / MF;
+            constexpr int valu = (16 + 56 * staged_in(q) + MF - 1) / MF;
             static_for<MF>([&](auto) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // MFMA
                 __builtin_amdgcn_sched_group_barrier(0x002, valu, 0);   // vector arithmetic
@@ -195,7 +195,7 @@ __device__ __forceinline__ void din_accumulate(const float *__restrict__ g, cons
 #pragma unroll
         for (int pb = 0; pb < 4; ++pb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[rb][pb][v] += low[rb][pb][v];
+            for (int v = 0; v < 16; ++v) acc[rb][pb][v] = (acc[rb][pb][v] + low[rb][pb][v]) * SPLIT_UNSCALE;
 }
 
 __device__ __forceinline__ float weight_of(const float *w, size_t i) { return w[i]; }

@@ -234,7 +234,7 @@ __global__ void __launch_bounds__(E_THREADS, 1) split_dw_kernel(const void *__re
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int co = co0 + 8 * (r >> 2) + (r & 3);
-                if (co < p.Cout && ci < p.Cin) o[(size_t)co * p.Cin + ci] = acc[t][i][j][r] + low[t][i][j][r];
+                if (co < p.Cout && ci < p.Cin) o[(size_t)co * p.Cin + ci] = (acc[t][i][j][r] + low[t][i][j][r]) * SPLIT_UNSCALE;
             }
         });
     });

@@ -228,7 +228,7 @@ __device__ __forceinline__ void split_accumulate(const float *__restrict__ in, c
                 if constexpr (o_next != o) read_x(integral_constant<int, o_next>{}, integral_constant<int, xp>{});
             });
             // spread the tap's other instructions over its MFMAs: one wave per SIMD has nothing else to hide them
-            constexpr int valu = (8 + 48 * staged_in(q) + 23) / 24;
+            constexpr int valu = (8 + 56 * staged_in(q) + 23) / 24;
             static_for<24>([&](auto) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // MFMA
                 __builtin_amdgcn_sched_group_barrier(0x002, valu, 0);   // vector arithmetic
@@ -244,7 +244,7 @@ __device__ __forceinline__ void split_accumulate(const float *__restrict__ in, c
 #pragma unroll
         for (int pb = 0; pb < 4; ++pb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[c][pb][v] += low[c][pb][v];
+            for (int v = 0; v < 16; ++v) acc[c][pb][v] = (acc[c][pb][v] + low[c][pb][v]) * SPLIT_UNSCALE;
 }
 
 // Where this lane's column of position block `blk` of the tile lies.

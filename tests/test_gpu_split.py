@@ -102,12 +102,31 @@ def test_split_forward_infinities_and_nan(shape):
     assert ((out - ref)[ok].abs() <= TOL * item[ok]).all()
 
 
-def test_split_forward_small_values():
-    """Scaling the operands by powers of two scales the result exactly: their parts keep all bits down to 1e-30."""
+# Operand sizes from fp32's smallest to what bfloat16 parts leave room for: exponents of (input or g, weights or input).
+SIZES = [(-60, -40), (-126, 60), (70, -126), (-75, -25), (-126, 20), (60, -60)]
+
+
+def _normal_sized(t, exponent):
+    """Values of t's signs in [1, 2) * 2^exponent, zeros kept: scaling by powers of two never rounds them."""
+    return torch.where(t == 0, t, torch.copysign(1.0 + (t.abs() % 1.0), t)) * 2.0 ** exponent
+
+
+@pytest.mark.parametrize("a,b", SIZES)
+def test_split_forward_operand_sizes(a, b):
+    """Scaling the operands by powers of two scales the result exactly, down to the smallest normal operands."""
     x, w = _layer(FORWARD[4], 7)
+    x, w = _normal_sized(x, 0), _normal_sized(w, 0)
     one = _forward(x, w, 2)
-    small = _forward(x * 2.0 ** -60, w * 2.0 ** -40, 2)
-    assert torch.equal(small, one * 2.0 ** -100)
+    assert torch.equal(_forward(x * 2.0 ** a, w * 2.0 ** b, 2), one * 2.0 ** (a + b))
+
+
+def test_split_forward_subnormal_operands():
+    x, w = _layer(FORWARD[4], 8)
+    x = torch.round(x * 2.0 ** 12)                    # whole numbers, so that 2^-149 times them is exact
+    one = _forward(x, w, 2)
+    tiny = x.double().mul(2.0 ** -149).float()
+    assert 0 < tiny[tiny != 0].abs().max() < 2.0 ** -126
+    assert torch.equal(_forward(tiny, w * 2.0 ** 100, 2), (one.double() * 2.0 ** -49).float())
 
 
 # Input gradient: 128 and 256 input channels per tile, five and seven staged cells per lane, ragged channels, odd padding
@@ -239,3 +258,28 @@ def test_split_kernel_gradient_infinities_and_nan(shape):
     assert torch.equal(torch.isnan(got), torch.isnan(want))
     largest = want.where(finite, 0.0).abs().amax(dim=(1, 2, 3), keepdim=True).expand_as(want)
     assert ((got - want)[finite].abs() <= TOL * largest[finite]).all()
+
+
+@pytest.mark.parametrize("a,b", SIZES)
+def test_split_gradient_operand_sizes(a, b):
+    x, w, g = _gradient_inputs(INPUT_GRADIENT[0], 9)
+    x, w, g = (_normal_sized(t, 0).to(DEV) for t in (x, w, g))
+    N, n, P = x.shape[2], w.shape[2], INPUT_GRADIENT[0][5]
+    s, t = 2.0 ** a, 2.0 ** b
+    din, dw = kst.kst_backward_input(g, w, N, P), kst.kst_backward_weight(x, g, n, P)
+    assert torch.equal(kst.kst_backward_input(g * s, w * t, N, P), din * 2.0 ** (a + b))
+    assert torch.equal(kst.kst_backward_weight(x * t, g * s, n, P), dw * 2.0 ** (a + b))
+
+
+@pytest.mark.parametrize("exponent", [-126, -133])
+def test_split_gradients_small_bf16_operands(exponent):
+    """bfloat16 operands at and below the smallest normal number (there: whole multiples of 2^-133)."""
+    x, w, g = _gradient_inputs(INPUT_GRADIENT[6], 10)
+    N, n, P = x.shape[2], w.shape[2], INPUT_GRADIENT[6][5]
+    x, w, g = (torch.round(t.float() * 16).to(DEV) for t in (x, w, g * 10))
+    small = lambda t: t.double().mul(2.0 ** exponent).to(torch.bfloat16)
+    assert torch.equal(small(x).double() * 2.0 ** -exponent, x.double())
+    din, dw = kst.kst_backward_input(g, w.bfloat16(), N, P), kst.kst_backward_weight(x.bfloat16(), g, n, P)
+    big = g * 2.0 ** 60
+    assert torch.equal(kst.kst_backward_input(big, small(w), N, P), din * 2.0 ** (60 + exponent))
+    assert torch.equal(kst.kst_backward_weight(small(x), big, n, P), dw * 2.0 ** (60 + exponent))

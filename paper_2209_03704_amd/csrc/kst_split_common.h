@@ -16,7 +16,9 @@
 //
 // A value that is infinite, not a number, or rounds to infinity in bfloat16 has no such parts.  Each of them makes
 // every sum it enters infinite or not a number, and so does a sum beyond fp32's largest value over 2^48; the stores
-// look for sums that are not finite and compute those elements again with plain fp32 multiply-adds.
+// look for sums that are not finite and take those elements from fp32 MFMAs instead: a wave multiplies a whole
+// block of them again, straight from memory, in lanes that together read whole lines.  (One lane per element and one
+// multiply-add at a time took up to a quarter of a million dependent steps for an element of the kernel gradient.)
 #pragma once
 #include "kst_igemm_common.h"
 
@@ -36,6 +38,9 @@ __device__ __forceinline__ void split3(const float (&v)[8], bf16x8 &p0, bf16x8 &
         p2[j] = (__bf16)(r1 - (float)p1[j]);
     }
 }
+
+// A value that is the same in all lanes, where the compiler cannot know (arguments of a function that is not inlined).
+__device__ __forceinline__ int same(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // A tensor below 2 GB as a buffer: loads past its end return zero instead of touching memory.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *ptr, unsigned bytes)

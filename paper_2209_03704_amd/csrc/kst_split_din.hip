@@ -201,24 +201,48 @@ __device__ __forceinline__ void din_accumulate(const float *__restrict__ g, cons
 __device__ __forceinline__ float weight_of(const float *w, size_t i) { return w[i]; }
 __device__ __forceinline__ float weight_of(const uint16_t *w, size_t i) { return to_f32(w[i]); }
 
-// One element in plain fp32 multiply-adds, where its split sum is not finite.  g: the batch item's; w: the input
-// channel's; (y, x): row and column of g for tap (0, 0).
+// 32 input channels x 32 positions in fp32 MFMAs, by a whole wave, where split sums are not finite.  g: of the batch
+// item of this lane's position (lane % 32); w: of this lane's input channel (live: there is one); (y, x): row and column
+// of g for tap (0, 0).
 template <class T>
-__device__ __attribute__((noinline)) float din_recompute(const float *g, const T *w, int n, int Cin, int Cout, int M, int y,
-                                                         int x)
+__device__ __forceinline__ floatx16 din_fp32_block_here(const float *g, const T *w, bool live, int n, int Cin, int Cout, int M,
+                                                        int y, int x)
 {
-    float a = 0.0f;
-    for (int co = 0; co < Cout && a == a; ++co) {
-        for (int u = 0; u < n; ++u)
-            for (int v = 0; v < n; ++v) {
-                const int gy = y - u, gx = x - v;
-                const bool inside = gy >= 0 && gy < M && gx >= 0 && gx < M;
-                a = fmaf(weight_of(w, u * n + v), inside ? g[(size_t)gy * M + gx] : 0.0f, a);
+    const int kk = (threadIdx.x >> 5) & 1;            // an MFMA's two reduction steps: two output channels
+    const size_t plane = (size_t)M * M, w_plane = (size_t)Cin * n * n;
+    floatx16 sum;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sum[v] = 0.0f;
+#pragma unroll 1
+    for (int t = 0; t < n * n; ++t) {
+        const int gy = y - t / n, gx = x - t % n;
+        const bool inside = gy >= 0 && gy < M && gx >= 0 && gx < M;
+        const float *pg = g + (inside ? (size_t)gy * M + gx : 0) + kk * plane;
+        const T *pw = w + t + kk * w_plane;
+#pragma unroll 1
+        for (int c0 = 0; c0 < Cout; c0 += 8) {        // four MFMAs' operands in flight together
+            float wv[4], gv[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool ok = c0 + 2 * j + kk < Cout;
+                wv[j] = live && ok ? weight_of(pw, 0) : 0.0f;
+                gv[j] = inside && ok ? *pg : 0.0f;
+                pw += 2 * w_plane;
+                pg += 2 * plane;
             }
-        g += (size_t)M * M;
-        w += (size_t)Cin * n * n;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) sum = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[j], gv[j], sum, 0, 0, 0);
+        }
     }
-    return a;
+    return sum;
+}
+
+// (the main kernel, whose registers are full, calls it)
+template <class T>
+__device__ __attribute__((noinline)) floatx16 din_fp32_block(const float *g, const T *w, bool live, int n, int Cin, int Cout,
+                                                             int M, int y, int x)
+{
+    return din_fp32_block_here(g, w, live, same(n), same(Cin), same(Cout), same(M), y, x);
 }
 
 struct DinColumn {
@@ -238,7 +262,7 @@ __device__ __forceinline__ DinColumn din_column(const DinParams &p, int m)
 }
 
 // The 16 sums of one block (channels ci0 + 8 (v / 4) + v % 4) at this lane's position.
-template <int n, class T>
+template <int n, bool CALL, class T>
 __device__ __forceinline__ void din_store(const float *__restrict__ g, const T *__restrict__ w, float *__restrict__ din,
                                           const DinParams &p, const float (&a)[16], int ci0, const DinColumn &c)
 {
@@ -251,13 +275,18 @@ __device__ __forceinline__ void din_store(const float *__restrict__ g, const T *
         if (c.valid && ci0 + d < p.Cin) o[d * plane] = a[v];
         zero = fmaf(a[v], 0.0f, zero);
     }
-    if (zero != 0.0f && c.valid) {
+    if (__builtin_expect(__ballot(zero != 0.0f) != 0, 0)) {  // (all lanes of the wave, also those past the last position)
+        const int ci = (ci0 & ~31) + (int)(threadIdx.x & 31);
         const float *gb = g + (size_t)c.mb * p.Cout * p.M * p.M;
+        const T *wb = w + (size_t)min(ci, p.Cin - 1) * n * n;
+        const int y = 2 * c.ma + n - 1 + p.shift, x = 2 * c.mc + n - 1 + p.shift;
+        floatx16 f;
+        if constexpr (CALL) f = din_fp32_block(gb, wb, ci < p.Cin, n, p.Cin, p.Cout, p.M, y, x);
+        else f = din_fp32_block_here(gb, wb, ci < p.Cin, n, p.Cin, p.Cout, p.M, y, x);
+#pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int d = 8 * (v >> 2) + (v & 3);
-            if (ci0 + d < p.Cin && o[d * plane] * 0.0f != 0.0f)
-                o[d * plane] = din_recompute(gb, w + (size_t)(ci0 + d) * n * n, n, p.Cin, p.Cout, p.M,
-                                             2 * c.ma + n - 1 + p.shift, 2 * c.mc + n - 1 + p.shift);
+            if (c.valid && ci0 + d < p.Cin && a[v] * 0.0f != 0.0f) o[d * plane] = f[v];
         }
     }
 }
@@ -306,7 +335,7 @@ __global__ void __launch_bounds__(D_THREADS, 1) split_din_kernel(const float *__
                     float a[16];
 #pragma unroll
                     for (int v = 0; v < 16; ++v) a[v] = acc[rb][pb][v];
-                    din_store<n>(g, w, din, p, a, ((tile_ci * 4 + wave) * RB + rb) * 32 + 4 * (lane >> 5), c);
+                    din_store<n, true>(g, w, din, p, a, ((tile_ci * 4 + wave) * RB + rb) * 32 + 4 * (lane >> 5), c);
                 });
             });
         } else {
@@ -321,7 +350,7 @@ __global__ void __launch_bounds__(D_THREADS, 1) split_din_kernel(const float *__
 
 // One workgroup per (shared tile, block of positions, row block): the sum of the tile's slots in workgroup order.
 template <int n, int RB, class T>
-__global__ void __launch_bounds__(D_THREADS) split_din_sum_kernel(const float *__restrict__ g, const T *__restrict__ w,
+__global__ void __launch_bounds__(D_THREADS, 6) split_din_sum_kernel(const float *__restrict__ g, const T *__restrict__ w,
                                                                   float *__restrict__ din, const float *__restrict__ ws,
                                                                   DinParams p, EvenShares k)
 {
@@ -349,8 +378,8 @@ __global__ void __launch_bounds__(D_THREADS) split_din_sum_kernel(const float *_
     }
     const int tile = k.listed() + rel, tile_m = tile % p.tiles_m, tile_ci = tile / p.tiles_m;
     const int lane = tid & 63, wave = tid >> 6;
-    din_store<n>(g, w, din, p, a, ((tile_ci * 4 + wave) * RB + part % RB) * 32 + 4 * (lane >> 5),
-                 din_column(p, tile_m * D_TM + part / RB * 32 + (lane & 31)));
+    din_store<n, false>(g, w, din, p, a, ((tile_ci * 4 + wave) * RB + part % RB) * 32 + 4 * (lane >> 5),
+                        din_column(p, tile_m * D_TM + part / RB * 32 + (lane & 31)));
 }
 
 // w[co][ci][u][v] -> MFMA operands: [block of 32 input channels][chunk of 16 output channels][tap][part][lane][8 output

@@ -240,34 +240,70 @@ __global__ void __launch_bounds__(E_THREADS, 1) split_dw_kernel(const void *__re
     });
 }
 
-// One element in plain fp32 multiply-adds, where its split sum is not finite.  x, g: of the first batch item's channels;
-// y0, x0: row and column of g for position (0, 0).
-template <class T>
-__device__ __attribute__((noinline)) float dw_recompute(const T *x, const float *g, int B, int Cin, int Cout, int N, int M,
-                                                        int y0, int x0)
+// The elements of 64 neighbouring (co, ci) pairs whose split sums are not finite, in fp32 MFMAs, by a whole wave.  `bad`:
+// the taps of this lane's pair e0 + lane that have to be done again.  For one output channel and up to 32 input channels
+// at a time, all taps are the rows of one product over batch items and positions: the g values of a channel's taps are
+// neighbours, and 16384 positions take 0.25 ms of multiplies.
+template <int n, class T>
+__device__ __forceinline__ void dw_fp32_pairs(const T *in, const float *g, float *dw, const DwParams &p, size_t e0,
+                                                        unsigned bad)
 {
-    float sum = 0.0f;
-    for (int b = 0; b < B && sum == sum; ++b) {
-        for (int a = 0; a < N; ++a)
-            for (int c = 0; c < N; ++c) {
-                const int y = y0 + 2 * a, xc = x0 + 2 * c;
-                const bool inside = y >= 0 && y < M && xc >= 0 && xc < M;
-                sum = fmaf(value_of(x + a * N + c), inside ? g[(size_t)y * M + xc] : 0.0f, sum);
+    constexpr int NN = n * n;
+    const int lane = threadIdx.x & 63, kk = lane >> 5, row = lane & 31;
+    const int B = p.B, Cin = p.Cin, Cout = p.Cout, N = p.N, M = p.M, q2 = p.q2;
+    const size_t last = (size_t)Cout * Cin - 1, x_plane = (size_t)N * N, g_plane = (size_t)M * M;
+    const int u = row / n, v = row % n;               // this lane's tap as a row (row < NN)
+#pragma unroll 1
+    for (int half = 0; half < 2; ++half) {
+        const size_t e = e0 + half * 32 + row < last ? e0 + half * 32 + row : last;
+        const unsigned wanted = (unsigned)__shfl((int)bad, half * 32 + row);
+        const int co = (int)(e / (unsigned)Cin), ci = (int)(e - (size_t)co * (unsigned)Cin);
+        const int co_end = same(__shfl(co, 31));
+        for (int o = same(__shfl(co, 0)); o <= co_end; ++o) {
+            if (__ballot(co == o && wanted != 0) == 0) continue;
+            floatx16 sum;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum[r] = 0.0f;
+            const T *x = in + (size_t)ci * x_plane;
+            const float *gb = g + (size_t)o * g_plane;
+            for (int b = 0; b < B; ++b) {
+                for (int a = 0; a < N; ++a) {
+                    const int y = 2 * a + q2 - u;
+                    const bool y_in = row < NN && y >= 0 && y < M;
+#pragma unroll 1
+                    for (int c0 = 0; c0 < N; c0 += 8) {       // four MFMAs' operands in flight together
+                        float gv[4], xv[4];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {         // an MFMA's two reduction steps: two columns
+                            const int c = c0 + 2 * j + kk, gx = 2 * c + q2 - v;
+                            gv[j] = y_in && c < N && gx >= 0 && gx < M ? gb[(size_t)y * M + gx] : 0.0f;
+                            xv[j] = c < N ? value_of(x + a * N + c) : 0.0f;
+                        }
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            sum = __builtin_amdgcn_mfma_f32_32x32x2f32(gv[j], xv[j], sum, 0, 0, 0);
+                    }
+                }
+                x += (size_t)Cin * x_plane;
+                gb += (size_t)Cout * g_plane;
             }
-        x += (size_t)Cin * N * N;
-        g += (size_t)Cout * M * M;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int tap = 8 * (r >> 2) + 4 * kk + (r & 3);
+                if (tap < NN && co == o && ((wanted >> tap) & 1u)) dw[e * NN + tap] = sum[r];
+            }
+        }
     }
-    return sum;
 }
 
 // dw[co][ci][tap] = the splits' partial sums in split order.  One thread per (co, ci).
 template <int n, class T>
-__global__ void __launch_bounds__(256) split_dw_sum_kernel(const float *__restrict__ part, const T *__restrict__ in,
+__global__ void __launch_bounds__(256, n == 5 ? 6 : 8) split_dw_sum_kernel(const float *__restrict__ part, const T *__restrict__ in,
                                                            const float *__restrict__ g, float *__restrict__ dw, DwParams p)
 {
     constexpr int NN = n * n;
-    const size_t plane = (size_t)p.Cout * p.Cin, e = (size_t)blockIdx.x * 256u + threadIdx.x;
-    if (e >= plane) return;
+    const size_t plane = (size_t)p.Cout * p.Cin, mine = (size_t)blockIdx.x * 256u + threadIdx.x;
+    const size_t e = mine < plane ? mine : plane - 1;  // (no lane leaves early: a wave does some elements together)
     float t[NN];
 #pragma unroll
     for (int i = 0; i < NN; ++i) t[i] = part[(size_t)i * plane + e];
@@ -276,17 +312,21 @@ __global__ void __launch_bounds__(256) split_dw_sum_kernel(const float *__restri
         for (int i = 0; i < NN; ++i) t[i] += part[((size_t)s * NN + i) * plane + e];
     float zero = 0.0f;
 #pragma unroll
-    for (int i = 0; i < NN; ++i) {
-        zero = fmaf(t[i], 0.0f, zero);
-        dw[e * NN + i] = t[i];
+    for (int i = 0; i < NN; ++i) zero = fmaf(t[i], 0.0f, zero);
+    unsigned bad = 0;
+    if (mine < plane) {
+        if (zero == 0.0f) {
+#pragma unroll
+            for (int i = 0; i < NN; ++i) dw[e * NN + i] = t[i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < NN; ++i) {
+                if (t[i] * 0.0f == 0.0f) dw[e * NN + i] = t[i];
+                else bad |= 1u << i;
+            }
+        }
     }
-    if (zero != 0.0f) {
-        const int co = (int)(e / (unsigned)p.Cin), ci = (int)(e - (size_t)co * p.Cin);
-        for (int i = 0; i < NN; ++i)
-            if (dw[e * NN + i] * 0.0f != 0.0f)
-                dw[e * NN + i] = dw_recompute(in + (size_t)ci * p.N * p.N, g + (size_t)co * p.M * p.M, p.B, p.Cin, p.Cout, p.N,
-                                              p.M, p.q2 - i / n, p.q2 - i % n);
-    }
+    if (__builtin_expect(__ballot(bad != 0) != 0, 0)) dw_fp32_pairs<n>(in, g, dw, p, mine - (threadIdx.x & 63), bad);
 }
 
 struct DwPlan {

@@ -265,40 +265,63 @@ __device__ __forceinline__ Column column_of(const SplitParams &p, int m0, int bl
     return c;
 }
 
-// One output element in plain fp32 multiply-adds, where its split sum is not finite: x: the batch item's input,
-// w: the class's weights of one output channel (Ta x Tb taps), (iy, ix): the window's corner in the unframed input.
-__device__ __attribute__((noinline)) float recompute(const float *x, const float *w, int Cin, int Cout, int N0, int Ta,
-                                                     int Tb, int iy, int ix)
+// 32 output channels x 32 positions of one class in fp32 MFMAs, by a whole wave, where split sums are not finite.
+// x: the input of the batch item of this lane's position (lane % 32); w: the class's weights (Ta x Tb taps) at this
+// lane's output channel (live: there is one); (iy, ix): the window's corner in the unframed input.
+__device__ __forceinline__ floatx16 fp32_block_here(const float *x, const float *w, bool live, int Cin, int Cout, int N0, int Ta,
+                                                    int Tb, int iy, int ix)
 {
-    float a = 0.0f;
-    for (int ci = 0; ci < Cin && a == a; ++ci) {             // (a NaN stays one)
-        for (int ta = 0; ta < Ta; ++ta)
-            for (int tb = 0; tb < Tb; ++tb) {
-                const int y = iy + ta, c = ix + tb;
-                const bool inside = y >= 0 && y < N0 && c >= 0 && c < N0;
-                a = fmaf(w[(size_t)(ta * Tb + tb) * Cout], inside ? x[(size_t)y * N0 + c] : 0.0f, a);
+    const int kk = (threadIdx.x >> 5) & 1;                   // an MFMA's two reduction steps: two input channels
+    const size_t plane = (size_t)N0 * N0, w_plane = (size_t)Ta * Tb * Cout;
+    floatx16 sum;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sum[v] = 0.0f;
+#pragma unroll 1
+    for (int t = 0; t < Ta * Tb; ++t) {
+        const int y = iy + t / Tb, c = ix + t % Tb;
+        const bool inside = y >= 0 && y < N0 && c >= 0 && c < N0;
+        const float *px = x + (inside ? (size_t)y * N0 + c : 0) + kk * plane, *pw = w + (size_t)t * Cout + kk * w_plane;
+#pragma unroll 1
+        for (int c0 = 0; c0 < Cin; c0 += 8) {                // four MFMAs' operands in flight together
+            float wv[4], xv[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool ok = c0 + 2 * j + kk < Cin;
+                wv[j] = live && ok ? *pw : 0.0f;
+                xv[j] = inside && ok ? *px : 0.0f;
+                pw += 2 * w_plane;
+                px += 2 * plane;
             }
-        x += (size_t)N0 * N0;
-        w += (size_t)Ta * Tb * Cout;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) sum = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[j], xv[j], sum, 0, 0, 0);
+        }
     }
-    return a;
+    return sum;
+}
+
+// (the main kernel, whose registers are full, calls it)
+__device__ __attribute__((noinline)) floatx16 fp32_block(const float *x, const float *w, bool live, int Cin, int Cout, int N0,
+                                                         int Ta, int Tb, int iy, int ix)
+{
+    return fp32_block_here(x, w, live, same(Cin), same(Cout), same(N0), same(Ta), same(Tb), iy, ix);
+}
+
+// Class (r, s) at position c; co: this lane's output channel as a row (lane % 32) of the block.
+template <int n, bool CALL>
+__device__ __forceinline__ floatx16 fp32_class_block(const float *in, const float *w_seg, const SplitParams &p, const Column &c,
+                                                     int r, int s, int co)
+{
+    const unsigned off = r ? (s ? p.off[3] : p.off[2]) : (s ? p.off[1] : p.off[0]);
+    const float *x = in + (size_t)c.mb * p.Cin * p.N0 * p.N0, *w = w_seg + off + min(co, p.Cout - 1);
+    const int Ta = taps_for_parity(n, r), Tb = taps_for_parity(n, s), iy = c.mi + r - p.q, ix = c.mj + s - p.q;
+    if constexpr (CALL) return fp32_block(x, w, co < p.Cout, p.Cin, p.Cout, p.N0, Ta, Tb, iy, ix);
+    else return fp32_block_here(x, w, co < p.Cout, p.Cin, p.Cout, p.N0, Ta, Tb, iy, ix);
 }
 
 // Store one output channel's two elements (column parities) of a lane: final values, after the epilogue.
-template <int n>
-__device__ __forceinline__ void store_pair(const float *__restrict__ in, const float *__restrict__ w_seg,
-                                           float *__restrict__ out, const SplitParams &p, float v0, float v1, int r,
-                                           int co, const Column &c)
+__device__ __forceinline__ void store_pair(float *__restrict__ out, const SplitParams &p, float v0, float v1, int r, int co,
+                                           const Column &c)
 {
-    if (fmaf(v0, 0.0f, v1 * 0.0f) != 0.0f) {
-        const float *x = in + (size_t)c.mb * p.Cin * p.N0 * p.N0;
-        const int iy = c.mi + r - p.q, ix = c.mj - p.q, Ta = taps_for_parity(n, r);
-        if (v0 * 0.0f != 0.0f)
-            v0 = recompute(x, w_seg + (r ? p.off[2] : p.off[0]) + co, p.Cin, p.Cout, p.N0, Ta, taps_for_parity(n, 0), iy, ix);
-        if (v1 * 0.0f != 0.0f)
-            v1 = recompute(x, w_seg + (r ? p.off[3] : p.off[1]) + co, p.Cin, p.Cout, p.N0, Ta, taps_for_parity(n, 1), iy,
-                           ix + 1);
-    }
     if (epi_on(p.epi)) {
         const float bias = epi_bias(p.epi, co);
         v0 = epi_apply(v0, bias, p.epi.act);
@@ -338,7 +361,8 @@ __device__ __forceinline__ void do_piece(const float *__restrict__ in, const flo
             constexpr int i = decltype(ic)::value;
             zero = fmaf(acc[i & 1][i >> 5][(i >> 1) & 15], 0.0f, zero);
         });
-        if (p.epi.act != KST_ACT_TANH && __ballot(zero != 0.0f) == 0) {
+        const bool redo = __ballot(zero != 0.0f) != 0;
+        if (p.epi.act != KST_ACT_TANH && !redo) {
             // Straight from the registers: pairs of elements where every row starts at an even one and no map is cropped.
             const size_t plane = (size_t)p.M * p.M;
             float bias[16];
@@ -372,7 +396,7 @@ __device__ __forceinline__ void do_piece(const float *__restrict__ in, const flo
             return;
         }
         // Otherwise through a wave's own 16 KB of LDS ([position block][register][column parity][lane]): tanh and the
-        // sums that have to be done again are a loop and not 64 copies of the code.
+        // blocks that have to be done again are a loop and not 64 copies of the code.
         float *own = reinterpret_cast<float *>(lds) + wave * (2 * 2048) + lane;
         static_for<2>([&](auto hc) {
             constexpr int h = decltype(hc)::value;
@@ -382,11 +406,23 @@ __device__ __forceinline__ void do_piece(const float *__restrict__ in, const flo
             });
             for (int pb = 0; pb < 2; ++pb) {
                 const Column c = column_of(p, tile_m * TS::tm, (wave / WR) * 4 + 2 * h + pb, lane & 31);
+                for (int s = 0; redo && s < 2; ++s) {
+                    float *mine = own + (pb * 32 + s) * 64;
+                    float bad = 0.0f;
+                    for (int v = 0; v < 16; ++v) bad = fmaf(mine[v * 128], 0.0f, bad);
+                    if (__ballot(bad != 0.0f) == 0) continue;
+                    const floatx16 f = fp32_class_block<n, true>(in, w_seg, p, c, r, s,
+                                                                 tile_co * TS::tco + (wave % WR) * 32 + (lane & 31));
+                    static_for<16>([&](auto vc) {
+                        constexpr int v = decltype(vc)::value;
+                        if (mine[v * 128] * 0.0f != 0.0f) mine[v * 128] = f[v];
+                    });
+                }
 #pragma unroll 4
                 for (int v = 0; v < 16; ++v) {
                     const int co = co_base + 8 * (v >> 2) + (v & 3);
                     const float v0 = own[(pb * 32 + 2 * v) * 64], v1 = own[(pb * 32 + 2 * v + 1) * 64];
-                    if (c.valid && co < p.Cout) store_pair<n>(in, w_seg, out, p, v0, v1, r, co, c);
+                    if (c.valid && co < p.Cout) store_pair(out, p, v0, v1, r, co, c);
                 }
             }
         });
@@ -482,7 +518,7 @@ __global__ void __launch_bounds__(256) split_weights_kernel(const float *__restr
 // Eight workgroups per pass of the shared list, one per block of positions and half of its registers: the sum of the
 // pass's slots, in workgroup order, goes to the output (nothing to do where one workgroup did the whole pass).
 template <int n, int WR>
-__global__ void __launch_bounds__(S_THREADS) split_f32_sum_kernel(const float *__restrict__ in, const float *__restrict__ w_seg,
+__global__ void __launch_bounds__(S_THREADS, 5) split_f32_sum_kernel(const float *__restrict__ in, const float *__restrict__ w_seg,
                                                                   float *__restrict__ out, const float *__restrict__ ws,
                                                                   SplitParams p, EvenShares k)
 {
@@ -512,13 +548,29 @@ __global__ void __launch_bounds__(S_THREADS) split_f32_sum_kernel(const float *_
     const int pass = k.listed() + rel, tile = pass >> 1, tile_m = tile % p.tiles_m, tile_co = tile / p.tiles_m;
     const int lane = tid & 63, wave = tid >> 6;
     const Column c = column_of(p, tile_m * TS::tm, (wave / WR) * 4 + (part >> 1), lane & 31);
+    const int co32 = tile_co * TS::tco + (wave % WR) * 32, co0 = co32 + 4 * (lane >> 5);
+    float zero = 0.0f;                                // NaN where one of the sums is infinite or not a number
+#pragma unroll
+    for (int q = 0; q < 4; ++q) zero = fmaf(a[q].x, 0.0f, fmaf(a[q].y, 0.0f, fmaf(a[q].z, 0.0f, fmaf(a[q].w, 0.0f, zero))));
+    if (__builtin_expect(__ballot(zero != 0.0f) != 0, 0)) {  // (all lanes of the wave, also those past the last position)
+        const bool upper = (part & 1) != 0;
+#pragma unroll 1
+        for (int s = 0; s < 2; ++s) {
+            const floatx16 f = fp32_class_block<n, false>(in, w_seg, p, c, pass & 1, s, co32 + (lane & 31));
+            static_for<4>([&](auto qc) {
+                constexpr int q = decltype(qc)::value;
+                float &lo = s ? a[q].y : a[q].x, &hi = s ? a[q].w : a[q].z;
+                if (lo * 0.0f != 0.0f) lo = upper ? f[8 + 2 * q] : f[2 * q];
+                if (hi * 0.0f != 0.0f) hi = upper ? f[9 + 2 * q] : f[1 + 2 * q];
+            });
+        }
+    }
     if (!c.valid) return;
-    const int co0 = tile_co * TS::tco + (wave % WR) * 32 + 4 * (lane >> 5);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int v = 8 * (part & 1) + 2 * q, co = co0 + 8 * (v >> 2) + (v & 3);
-        if (co < p.Cout) store_pair<n>(in, w_seg, out, p, a[q].x, a[q].y, pass & 1, co, c);
-        if (co + 1 < p.Cout) store_pair<n>(in, w_seg, out, p, a[q].z, a[q].w, pass & 1, co + 1, c);
+        if (co < p.Cout) store_pair(out, p, a[q].x, a[q].y, pass & 1, co, c);
+        if (co + 1 < p.Cout) store_pair(out, p, a[q].z, a[q].w, pass & 1, co + 1, c);
     }
 }
 

@@ -60,8 +60,9 @@ __device__ __forceinline__ bf16x8 load_bf16x8(__amdgpu_buffer_rsrc_t r, unsigned
 // Even shares.  The work is a list of passes (tile-major, row parity r = pass & 1) of `chunks` channel chunks, a chunk
 // of parity r costing tapsr.  Workgroup g of `grid` does passes g * rounds .. + rounds - 1 whole; the (pass, chunk)
 // units of the remaining passes are cut into `grid` ranges of equal cost.  A piece of a range that covers a whole pass
-// is stored; any other goes to one of its workgroup's two slots (2 g for the first piece of workgroup g's range, 2 g + 1
-// for a later one) and a second kernel adds a pass's slots in workgroup order.
+// is stored; any other goes to a slot and a second kernel adds a pass's slots in workgroup order.  Slots are numbered
+// along the list, workgroup + shared pass (each piece is a workgroup or a pass further than the one before it), where
+// that makes fewer of them than two per workgroup: 2 g for the first piece of workgroup g's range, 2 g + 1 for a later.
 constexpr int S_GRID = 256;                                  // CUs of the chip
 struct EvenShares {
     int chunks;                // channel chunks per pass
@@ -71,6 +72,10 @@ struct EvenShares {
     int taps0, taps1;
     int per, more;             // cost of the list: per * grid + more, below 2^30
     __host__ __device__ int listed() const { return rounds * grid; }        // first shared pass
+    __host__ __device__ bool along_list() const { return passes < grid; }
+    int slots() const { return passes == 0 ? 0 : along_list() ? grid + passes - 1 : 2 * grid; }
+    // Slot of workgroup g's piece of shared pass `rel`; first: its range begins in that pass.
+    __device__ int slot(int g, int rel, bool first) const { return along_list() ? g + rel : 2 * g + (first ? 0 : 1); }
     // First unit of workgroup g's range.
     __host__ __device__ int begin(int g) const
     {

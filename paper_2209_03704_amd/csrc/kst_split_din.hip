@@ -306,11 +306,12 @@ __global__ void __launch_bounds__(D_THREADS, 1) split_din_kernel(const float *__
     while (whole < whole_end || u < u_end) {
         int tile, c0 = 0, c1 = p.chunks;
         __syncthreads();                              // the last piece's LDS is free
-        float *slot = ws + (size_t)(2 * wg + (first ? 0 : 1)) * (RB * D_SLOT1);
+        float *slot = ws;
         if (whole < whole_end) {
             tile = whole++;
         } else {
             const int rel = u / p.chunks;
+            slot += (size_t)k.slot(wg, rel, first) * (RB * D_SLOT1);
             tile = k.listed() + rel;
             c0 = u - rel * p.chunks;
             c1 = min(p.chunks, c0 + u_end - u);
@@ -365,7 +366,7 @@ __global__ void __launch_bounds__(D_THREADS, 6) split_din_sum_kernel(const float
     for (int s = g0; s <= g1; ++s) {
         const int b = k.begin(s);
         if (b == k.begin(s + 1)) continue;            // an empty range
-        const int slot = 2 * s + (b < u0 ? 1 : 0);
+        const int slot = k.slot(s, rel, b >= u0);
         const float4 *d = reinterpret_cast<const float4 *>(ws + (size_t)slot * (RB * D_SLOT1)) + part * 4 * D_THREADS + tid;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -532,7 +533,7 @@ size_t split_din_workspace_bytes(const Shape &s, bool odd, kst_dtype dt)
 {
     const DinPlan r = din_plan(s, odd, dt);
     if (!r.ok) return 0;
-    return din_weight_bytes(r) + (r.k.passes ? (size_t)2 * r.k.grid * r.rb * D_SLOT1 * sizeof(float) : 0);
+    return din_weight_bytes(r) + (size_t)r.k.slots() * r.rb * D_SLOT1 * sizeof(float);
 }
 
 hipError_t launch_split_din(const float *g, const void *w, float *din, void *ws, const Shape &s, bool odd, kst_dtype dt,

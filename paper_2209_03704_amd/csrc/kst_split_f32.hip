@@ -450,11 +450,12 @@ __global__ void __launch_bounds__(S_THREADS, 1) split_f32_kernel(const float *__
     while (whole < whole_end || u < u_end) {
         int pass, c0 = 0, c1 = p.chunks;
         __syncthreads();                              // the last piece's LDS is free
-        float *slot = ws + (size_t)(2 * g + (first ? 0 : 1)) * S_SLOT;
+        float *slot = ws;
         if (whole < whole_end) {
             pass = whole++;
         } else {
             const int rel = u / p.chunks;
+            slot += (size_t)k.slot(g, rel, first) * S_SLOT;
             pass = k.listed() + rel;
             c0 = u - rel * p.chunks;
             c1 = min(p.chunks, c0 + u_end - u);
@@ -534,7 +535,7 @@ __global__ void __launch_bounds__(S_THREADS, 5) split_f32_sum_kernel(const float
     for (int g = g0; g <= g1; ++g) {
         const int b = k.begin(g);
         if (b == k.begin(g + 1)) continue;            // an empty range
-        const int slot = 2 * g + (b < u0 ? 1 : 0);
+        const int slot = k.slot(g, rel, b >= u0);
         const float4 *d = reinterpret_cast<const float4 *>(ws + (size_t)slot * S_SLOT) + part * 4 * S_THREADS + tid;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -686,7 +687,7 @@ bool split_f32_applies(const Shape &s)
 size_t split_f32_workspace_bytes(const Shape &s)
 {
     const SplitPlan r = plan(s);
-    return split_weight_bytes(r) + (r.k.passes ? (size_t)2 * r.k.grid * S_SLOT * sizeof(float) : 0);
+    return split_weight_bytes(r) + (size_t)r.k.slots() * S_SLOT * sizeof(float);
 }
 
 hipError_t launch_split_f32(const float *in, const float *w_seg, float *out, void *ws, const Shape &s, hipStream_t stream)

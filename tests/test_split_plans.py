@@ -16,12 +16,30 @@ def split_din_weight_bytes(Cin, Cout, n, parts):
     return _up(_up(Cin, 32) // 32 * (_up(Cout, 16) // 16) * n * n * parts * 1024, 256)
 
 
+def slot_count(grid, passes):
+    """Partial tiles of `passes` tiles shared by `grid` workgroups: one per workgroup and tile, or two per workgroup."""
+    return 0 if passes == 0 else grid + passes - 1 if passes < grid else 2 * grid
+
+
 def split_din_slot_bytes(B, Cin, Cout, N, n):
-    """Partial tiles of 128 positions and 128 or 256 input channels: two per workgroup where tiles are shared."""
+    """Partial tiles of 128 positions and 128 or 256 input channels."""
     tiles_m, chunks = -(-B * N * N // 128), -(-Cout // 16)
     rb = 2 if n < 5 and Cin > 128 and tiles_m * -(-Cin // 256) * chunks >= 4 * 256 else 1
     tiles = tiles_m * -(-Cin // (128 * rb))
-    return 2 * min(256, tiles * chunks) * rb * 256 * 64 * 4 if tiles % 256 else 0
+    return slot_count(min(256, tiles * chunks), tiles % 256) * rb * 256 * 64 * 4
+
+
+def split_forward_bytes(B, Cin, Cout, N, n, P):
+    """Split weights [row parity][block of 32 output channels][chunk][tap][part][64 lanes][8 values], then partial tiles
+    of 128 positions x 128 output channels (256 x 64 up to 64 channels) of one row parity."""
+    E = -(-(2 * (N + 2 * ((P + 1) // 2)) - n) // 2)
+    wide = Cout > 64
+    tiles = -(-B * E * E // (128 if wide else 256)) * -(-Cout // (128 if wide else 64))
+    chunks = -(-Cin // 16)
+    per_round = 256 if n % 2 == 0 else 512                  # (odd kernels: the two parities cost differently, so pairs)
+    passes = 2 * tiles % per_round
+    weights = _up(-(-Cout // 32) * chunks * n * n * 3 * 1024, 256)
+    return weights + slot_count(min(256, 2 * tiles * chunks), passes) * 256 * 128 * 4
 
 
 # Weights whose three parts pass the 2 GB a launch can address while bfloat16's one part does not: the size has to be
@@ -47,3 +65,19 @@ def test_input_gradient_workspace_is_the_layout(B, Cin, Cout, N, n):
     assert of[F32] == split_din_weight_bytes(Cin, Cout, n, 3) + slots
     assert of[F16] == widened + of[F32]
     assert of[BF16] == of[F16] > split_din_weight_bytes(Cin, Cout, n, 1) + slots      # one size for 16-bit types
+
+
+# Shared passes only; whole rounds and shared passes; more shared passes than workgroups; tiles of 64 channels.
+@pytest.mark.parametrize("B,Cin,Cout,N,n,P", [(64, 512, 256, 8, 4, 2), (128, 512, 256, 16, 4, 0), (64, 1024, 512, 8, 5, 0),
+                                              (23, 515, 264, 13, 3, 2), (70, 33, 40, 33, 5, 1)])
+def test_forward_workspace_is_the_layout(B, Cin, Cout, N, n, P):
+    assert kst.kst_workspace_bytes_padded(B, Cin, Cout, N, n, P, F32) == split_forward_bytes(B, Cin, Cout, N, n, P)
+    if P == 0:
+        assert kst.kst_workspace_bytes(B, Cin, Cout, N, n, F32) == split_forward_bytes(B, Cin, Cout, N, n, P)
+
+
+def test_partial_tiles_are_numbered_along_the_list():
+    """128 shared passes of 256 workgroups: 383 slots of 128 KB and 12.6 MB of split weights, where two slots per
+    workgroup made 79.7 MB, more than the library's fixed workspace holds."""
+    need = kst.kst_workspace_bytes_padded(64, 512, 256, 8, 4, 2, F32)
+    assert need == 383 * 131072 + 12582912 < kst.KST_STATIC_SCRATCH_BYTES

@@ -54,7 +54,7 @@ typedef enum {
     KST_ERR_NULL = 1,       /* a required pointer is NULL                              */
     KST_ERR_SHAPE = 2,      /* a size < 1, 2N - n < 1, or a tensor of 2^31+ elements   */
     KST_ERR_DTYPE = 3,      /* dtype is none of KST_F32, KST_BF16, KST_F16             */
-    KST_ERR_WORKSPACE = 4,  /* workspace missing or smaller than kst_workspace_bytes  */
+    KST_ERR_WORKSPACE = 4,  /* workspace missing or smaller than the layer can do with */
     KST_ERR_HIP = 5,        /* the HIP runtime refused an allocation or a launch      */
     KST_ERR_PATH = 6,       /* unknown kst_path, or a path that cannot run this shape */
     KST_ERR_ALIGN = 7,      /* a data pointer is not 16-byte aligned                  */
@@ -66,7 +66,9 @@ typedef enum {
  * the layers with fewer than 16 output channels it also gives IGEMM those
  * with many input channels that the matrix cores can take with the
  * sub-kernels' taps as rows (a batch of them) or with the reduction split
- * over the chip (one sample).
+ * over the chip (one sample).  Large fp32 layers AUTO gives to IGEMM's kernels
+ * for operands split into bfloat16 parts (see dtype above); IGEMM asked for by
+ * name multiplies in fp32 always.
  * IGEMM_EVEN (for tests and tuning) is IGEMM with one of its launch forms
  * forced: the (tile, channel chunk) list of the layer cut into equal ranges
  * over persistent workgroups, which IGEMM itself takes only where its cost
@@ -140,9 +142,14 @@ kst_status kst_segregate_weights(const void *w, void *w_seg, int Cin, int Cout, 
                                  kst_dtype dtype, hipStream_t stream);
 
 /*
- * Bytes of scratch kst_forward_seg needs for this shape and path (0 when it
- * needs none).  The matrix-core path uses it for partial sums when it splits
- * the input-channel reduction across workgroups.
+ * Bytes of scratch kst_forward_seg wants for this shape and path (0 when it
+ * wants none).  The matrix-core path uses it for partial sums when it splits
+ * the input-channel reduction across workgroups, and for the split weights of
+ * large fp32 layers.  With fewer bytes AUTO runs these layers on the kernels
+ * that multiply in fp32, slower and rounded differently, where those can do
+ * with what there is (many need none); below that, and for all other layers
+ * and paths, the call is refused with KST_ERR_WORKSPACE.  The gradients of
+ * large layers do the same.
  */
 size_t kst_workspace_bytes(int B, int Cin, int Cout, int N, int n, kst_dtype dtype, kst_path path);
 
@@ -162,13 +169,15 @@ kst_status kst_forward_seg(const void *in, const void *w_seg, void *out, void *w
 /*
  * For callers that cannot allocate device memory or hand over a workspace: code under HIP
  * graph capture, serving loops with a fixed memory plan, harnesses that forbid hipMalloc.
- * kst_forward_seg with the same kernels, results and statuses, its workspace taken from an
- * array of KST_STATIC_SCRATCH_BYTES that is part of the library's device code (each GPU the
- * library runs on holds one until the process ends) instead of from the caller.  It calls no
+ * kst_forward_seg with a workspace of KST_STATIC_SCRATCH_BYTES (the same kernels, results and
+ * statuses as that call), which is an array that is part of the library's device code (each GPU
+ * the library runs on holds one until the process ends) instead of the caller's.  It calls no
  * hipMalloc, hipFree or other allocating routine; the first call on a device looks the array's
- * address up (hipGetSymbolAddress), later calls only launch.  A layer whose path needs more
- * workspace than the array holds gets KST_ERR_WORKSPACE and nothing is launched
- * (kst_workspace_bytes tells beforehand).  All calls on one GPU share that GPU's array: calls
+ * address up (hipGetSymbolAddress), later calls only launch.  A layer for which kst_workspace_bytes
+ * gives no more than the array holds has the kernels and results of kst_forward_seg with all the
+ * workspace it wants.  A large fp32 layer that wants more runs on the kernels that multiply in
+ * fp32 where the array is enough for those; any other layer that wants more gets
+ * KST_ERR_WORKSPACE and nothing is launched.  All calls on one GPU share that GPU's array: calls
  * that overlap in time on one GPU (different streams, different threads) race on it; calls on
  * one stream are ordered and safe.  The array's contents are undefined between calls.
  */
@@ -185,7 +194,8 @@ kst_status kst_forward_seg_static(const void *in, const void *w_seg, void *out,
  * that the library keeps per device (hipMallocFromPoolAsync / hipFreeAsync on
  * `stream`): no host synchronisation, but not usable under stream capture.
  * The pool keeps freed blocks for the next call (at most the largest scratch
- * any call has needed, up to about 0.2 GB) until the process ends.
+ * any call has needed) until the process ends.  Where there is no room for the
+ * workspace kst_workspace_bytes gives, the call does with the least it can.
  */
 kst_status kst_forward(const void *in, const void *w, void *out,
                        int B, int Cin, int Cout, int N, int n, kst_dtype dtype, hipStream_t stream);

@@ -77,22 +77,44 @@ bool on_matrix_cores(kst_path path)
     return path == KST_PATH_IGEMM || path == KST_PATH_IGEMM_EVEN || path == KST_PATH_IGEMM_PASSES;
 }
 
+// The problem as a caller's path sees it: IGEMM and its launch form EVEN, asked for by name, multiply fp32 operands in
+// fp32.  Only AUTO may split them for the bf16 matrix cores.
+Shape shape_for(int B, int Cin, int Cout, int N, int n, int path)
+{
+    Shape s = make_shape(B, Cin, Cout, N, n);
+    s.no_split = path != KST_PATH_AUTO;
+    return s;
+}
+
 size_t workspace_for(const Shape &s, kst_dtype dt, kst_path path)
 {
     if (!on_matrix_cores(path) || path == KST_PATH_IGEMM_PASSES) return 0;
     return is16(dt) ? igemm_bf16_workspace_bytes(s) : igemm_f32_workspace_bytes(s, path == KST_PATH_IGEMM_EVEN);
 }
 
+// The path's kernels for a caller with `have` bytes of scratch, and what they need of it: where the kernels that split
+// fp32 operands need more than there is, those that multiply in fp32 (*s then says so).  Not checked: *need <= have.
+kst_status plan_within(Shape *s, kst_dtype dtype, int path, size_t have, kst_path *chosen, size_t *need)
+{
+    for (;;) {
+        const kst_status st = resolve_path(*s, dtype, path, chosen);
+        if (st != KST_OK) return st;
+        *need = workspace_for(*s, dtype, *chosen);
+        if (*need <= have || s->no_split) return KST_OK;
+        s->no_split = 1;
+    }
+}
+
 // The segregated forward pass on a validated shape (s.Ns may exceed s.N only where
 // igemm_f32_takes_row_stride says the kernel that will run reads it).
-kst_status run_forward_seg(const void *in, const void *w_seg, void *out, void *ws, size_t ws_bytes, const Shape &s,
+kst_status run_forward_seg(const void *in, const void *w_seg, void *out, void *ws, size_t ws_bytes, Shape s,
                            kst_dtype dtype, int path, hipStream_t stream)
 {
     kst_path chosen;
-    kst_status st = resolve_path(s, dtype, path, &chosen);
+    size_t need;
+    kst_status st = plan_within(&s, dtype, path, ws ? ws_bytes : 0, &chosen, &need);
     if (st != KST_OK) return st;
     if (!aligned16(in) || !aligned16(w_seg) || !aligned16(out)) return KST_ERR_ALIGN;
-    const size_t need = workspace_for(s, dtype, chosen);
     if (need > 0) {
         if (!ws || ws_bytes < need) return KST_ERR_WORKSPACE;
         if (!aligned16(ws)) return KST_ERR_ALIGN;
@@ -152,11 +174,23 @@ hipError_t scratch_alloc(void **ptr, size_t bytes, hipStream_t stream)
     return hipMallocAsync(ptr, bytes, stream);
 }
 
+// seg_bytes + *ws_bytes of it; where there is no room for that, with the least() bytes of workspace the layer can do with.
+template <class F>
+bool scratch_for(void **ptr, size_t seg_bytes, size_t *ws_bytes, hipStream_t stream, F least)
+{
+    if (scratch_alloc(ptr, seg_bytes + *ws_bytes, stream) == hipSuccess) return true;
+    const size_t fewer = least();
+    if (fewer >= *ws_bytes) return false;
+    (void)hipGetLastError();
+    *ws_bytes = fewer;
+    return scratch_alloc(ptr, seg_bytes + fewer, stream) == hipSuccess;
+}
+
 }  // namespace
 
 extern "C" {
 
-int kst_version(void) { return 103; }
+int kst_version(void) { return 104; }
 
 const char *kst_status_string(int status)
 {
@@ -211,7 +245,7 @@ kst_status kst_segregate_weights(const void *w, void *w_seg, int Cin, int Cout, 
 size_t kst_workspace_bytes(int B, int Cin, int Cout, int N, int n, kst_dtype dtype, kst_path path)
 {
     if (!dtype_ok(dtype) || check_shape(B, Cin, Cout, N, n) != KST_OK) return 0;
-    const Shape s = make_shape(B, Cin, Cout, N, n);
+    const Shape s = shape_for(B, Cin, Cout, N, n, path);
     kst_path chosen;
     if (resolve_path(s, dtype, path, &chosen) != KST_OK) return 0;
     return workspace_for(s, dtype, chosen);
@@ -225,7 +259,7 @@ kst_status kst_forward_seg(const void *in, const void *w_seg, void *out, void *w
     if (!dtype_ok(dtype)) return KST_ERR_DTYPE;
     kst_status st = check_shape(B, Cin, Cout, N, n);
     if (st != KST_OK) return st;
-    return run_forward_seg(in, w_seg, out, ws, ws_bytes, make_shape(B, Cin, Cout, N, n), dtype, path, stream);
+    return run_forward_seg(in, w_seg, out, ws, ws_bytes, shape_for(B, Cin, Cout, N, n, path), dtype, path, stream);
 }
 
 // ---- the entry point that allocates nothing --------------------------------------------------
@@ -273,17 +307,11 @@ kst_status kst_forward_seg_static(const void *in, const void *w_seg, void *out, 
     if (!dtype_ok(dtype)) return KST_ERR_DTYPE;
     kst_status st = check_shape(B, Cin, Cout, N, n);
     if (st != KST_OK) return st;
-    Shape s = make_shape(B, Cin, Cout, N, n);
+    Shape s = shape_for(B, Cin, Cout, N, n, path);
     kst_path chosen;
-    st = resolve_path(s, dtype, path, &chosen);
+    size_t need;
+    st = plan_within(&s, dtype, path, KST_STATIC_SCRATCH_BYTES, &chosen, &need);
     if (st != KST_OK) return st;
-    size_t need = workspace_for(s, dtype, chosen);
-    if (need > (size_t)KST_STATIC_SCRATCH_BYTES) {      // the fp32 multiplies' own kernels may need less
-        s.no_split = 1;
-        st = resolve_path(s, dtype, path, &chosen);
-        if (st != KST_OK) return st;
-        need = workspace_for(s, dtype, chosen);
-    }
     if (need > (size_t)KST_STATIC_SCRATCH_BYTES) return KST_ERR_WORKSPACE;     // larger than the array: refuse
     void *ws = nullptr;
     if (need) {
@@ -303,16 +331,19 @@ kst_status kst_forward(const void *in, const void *w, void *out, int B, int Cin,
     kst_status st = check_shape(B, Cin, Cout, N, n);
     if (st != KST_OK) return st;
     if (!aligned16(in) || !aligned16(w) || !aligned16(out)) return KST_ERR_ALIGN;
-    const Shape s = make_shape(B, Cin, Cout, N, n);
-    const kst_path chosen = choose_path(s, dtype);
+    Shape s = make_shape(B, Cin, Cout, N, n);
     const size_t seg_bytes = (seg_elems(Cin, Cout, n, dtype) * elt_bytes(dtype) + 255) & ~(size_t)255;
-    const size_t ws_bytes = workspace_for(s, dtype, chosen);
+    size_t ws_bytes = workspace_for(s, dtype, choose_path(s, dtype));
+    const auto least = [&] {
+        s.no_split = 1;
+        return workspace_for(s, dtype, choose_path(s, dtype));
+    };
     void *scratch = nullptr;
-    if (scratch_alloc(&scratch, seg_bytes + ws_bytes, stream) != hipSuccess) return KST_ERR_HIP;
+    if (!scratch_for(&scratch, seg_bytes, &ws_bytes, stream, least)) return KST_ERR_HIP;
     void *ws = ws_bytes ? (void *)((char *)scratch + seg_bytes) : nullptr;
     st = kst_segregate_weights(w, scratch, Cin, Cout, n, dtype, stream);
     if (st == KST_OK)
-        st = kst_forward_seg(in, scratch, out, ws, ws_bytes, B, Cin, Cout, N, n, dtype, chosen, stream);
+        st = kst_forward_seg(in, scratch, out, ws, ws_bytes, B, Cin, Cout, N, n, dtype, KST_PATH_AUTO, stream);
     if (hipFreeAsync(scratch, stream) != hipSuccess && st == KST_OK) st = KST_ERR_HIP;
     return st;
 }
@@ -327,7 +358,7 @@ struct Framed {
     size_t in_bytes, wide_bytes;      // workspace parts before the inner kernels' own scratch (256-byte multiples)
 };
 
-kst_status framed_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dt, int path, Framed *f)
+kst_status framed_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dt, int path, bool no_split, Framed *f)
 {
     if (P < 0 || P > 32768 || B < 1 || N < 1 || N > 32768) return KST_ERR_SHAPE;
     f->q = (P + 1) / 2;
@@ -337,12 +368,12 @@ kst_status framed_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype 
     f->M = 2 * N + 2 * P - n;
     f->Mq = 2 * f->Nq - n;
     if (f->M < 1) return KST_ERR_SHAPE;
-    f->s = make_shape(B, Cin, Cout, f->Nq, n);
+    f->s = shape_for(B, Cin, Cout, f->Nq, n, path);
+    if (no_split) f->s.no_split = 1;
     // The pipelined fp32 matrix-core kernel supplies the frame itself while it stages its input
     // rows (tensor rows of whole 16-byte groups): no framed copy.
     Shape in_place = f->s;
     in_place.frame = f->q;
-    if (path == KST_PATH_IGEMM_EVEN) in_place.no_split = f->s.no_split = 1;     // that path is the fp32 multiplies' own
     const bool frame_in_kernel = dt == KST_F32 && igemm_f32_takes_virtual_frame(in_place);
     if (path == KST_PATH_IGEMM_EVEN) {
         if (frame_in_kernel) f->s = in_place;
@@ -394,6 +425,19 @@ kst_status framed_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype 
     return KST_OK;
 }
 
+size_t framed_bytes(const Framed &f, kst_dtype dt)
+{
+    return f.in_bytes + f.wide_bytes + workspace_for(f.s, dt, f.chosen);
+}
+
+// The plan for a caller with `have` bytes of scratch, as plan_within.
+kst_status framed_plan_within(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dt, int path, size_t have, Framed *f)
+{
+    kst_status st = framed_plan(B, Cin, Cout, N, n, P, dt, path, false, f);
+    if (st == KST_OK && framed_bytes(*f, dt) > have) st = framed_plan(B, Cin, Cout, N, n, P, dt, path, true, f);
+    return st;
+}
+
 }  // namespace
 
 int kst_out_size_padded(int N, int n, int P) { return 2 * N + 2 * P - n; }
@@ -403,8 +447,8 @@ size_t kst_workspace_bytes_padded(int B, int Cin, int Cout, int N, int n, int P,
     if (!dtype_ok(dtype)) return 0;
     if (P == 0) return kst_workspace_bytes(B, Cin, Cout, N, n, dtype, path);
     Framed f;
-    if (framed_plan(B, Cin, Cout, N, n, P, dtype, path, &f) != KST_OK) return 0;
-    return f.in_bytes + f.wide_bytes + workspace_for(f.s, dtype, f.chosen);
+    if (framed_plan(B, Cin, Cout, N, n, P, dtype, path, false, &f) != KST_OK) return 0;
+    return framed_bytes(f, dtype);
 }
 
 }  // extern "C"
@@ -422,12 +466,12 @@ kst_status forward_seg_padded_impl(const void *in, const void *w_seg, void *out,
     if (P == 0) {
         kst_status st0 = check_shape(B, Cin, Cout, N, n);
         if (st0 != KST_OK) return st0;
-        Shape s0 = make_shape(B, Cin, Cout, N, n);
+        Shape s0 = shape_for(B, Cin, Cout, N, n, path);
         s0.epi = epi;
         return run_forward_seg(in, w_seg, out, ws, ws_bytes, s0, dtype, path, stream);
     }
     Framed f;
-    kst_status st = framed_plan(B, Cin, Cout, N, n, P, dtype, path, &f);
+    kst_status st = framed_plan_within(B, Cin, Cout, N, n, P, dtype, path, ws ? ws_bytes : 0, &f);
     if (st != KST_OK) return st;
     f.s.epi = epi;
     if (!aligned16(in) || !aligned16(w_seg) || !aligned16(out)) return KST_ERR_ALIGN;
@@ -481,13 +525,16 @@ kst_status kst_forward_padded(const void *in, const void *w, void *out, int B, i
     if (!in || !w || !out) return KST_ERR_NULL;
     if (!dtype_ok(dtype)) return KST_ERR_DTYPE;
     Framed f;
-    kst_status st = framed_plan(B, Cin, Cout, N, n, P, dtype, KST_PATH_AUTO, &f);
+    kst_status st = framed_plan(B, Cin, Cout, N, n, P, dtype, KST_PATH_AUTO, false, &f);
     if (st != KST_OK) return st;
     if (!aligned16(in) || !aligned16(w) || !aligned16(out)) return KST_ERR_ALIGN;
     const size_t seg_bytes = (seg_elems(Cin, Cout, n, dtype) * elt_bytes(dtype) + 255) & ~(size_t)255;
-    const size_t ws_bytes = f.in_bytes + f.wide_bytes + workspace_for(f.s, dtype, f.chosen);   // may be 0
+    size_t ws_bytes = framed_bytes(f, dtype);          // may be 0
+    const auto least = [&] {
+        return framed_plan(B, Cin, Cout, N, n, P, dtype, KST_PATH_AUTO, true, &f) == KST_OK ? framed_bytes(f, dtype) : ws_bytes;
+    };
     void *scratch = nullptr;
-    if (scratch_alloc(&scratch, seg_bytes + ws_bytes, stream) != hipSuccess) return KST_ERR_HIP;
+    if (!scratch_for(&scratch, seg_bytes, &ws_bytes, stream, least)) return KST_ERR_HIP;
     st = kst_segregate_weights(w, scratch, Cin, Cout, n, dtype, stream);
     if (st == KST_OK)
         st = kst_forward_seg_padded(in, scratch, out, ws_bytes ? (char *)scratch + seg_bytes : nullptr, ws_bytes, B, Cin,
@@ -515,13 +562,18 @@ struct GradPlan {
     bool plain_unframed;              // the other kernels work on the unframed positions too (kernels up to 7 x 7)
     bool din_cores, dw_cores;         // the gradient runs on the matrix cores (fp32 kernels; 16-bit operands are
                                       // widened to fp32 first, which is exact)
-    kst_dtype din_split;              // operand type of w where the input gradient runs on the bf16 matrix cores
-    bool use_din_split;               // ... (half-precision weights are widened to fp32 first)
-    bool use_dw_split;                // the kernel gradient too
-    size_t dw_split_bytes;
-    size_t din_split_bytes;           // its whole workspace, widened half-precision weights included
-    size_t din_split_query;           // ... as kst_backward_input_workspace_bytes gives it
     size_t wconv_bytes, xconv_bytes;  // fp32 copies of w (input gradient) and of in (kernel gradient) for that
+    // The same on the bf16 matrix cores, with workspaces of their own; only where the caller's is large enough.
+    kst_dtype din_split;              // operand type of w they run with (half precision is widened to fp32 first)
+    bool use_din_split, use_dw_split;
+    size_t din_split_wconv;           // widened half-precision weights
+    size_t din_split_bytes, dw_split_bytes;    // whole workspace, as the launch lays it out
+    size_t din_split_query, dw_split_query;    // ... as kst_backward_*_workspace_bytes give it
+    size_t din_bytes_needed() const { return g_bytes + din_bytes + split_bytes + wconv_bytes; }
+    size_t dw_bytes_needed() const
+    {
+        return dw_cores ? gw_bytes + wsplit_bytes + xconv_bytes : in_bytes + g_bytes + wsplit_bytes;
+    }
 };
 
 kst_status grad_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dt, GradPlan *f)
@@ -555,15 +607,15 @@ kst_status grad_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dt
     if (f->plain_unframed) f->in_bytes = 0;            // `in` read as it lies in memory
     f->din_split = dt == KST_F16 ? KST_F32 : dt;
     f->use_din_split = split_din_applies(f->si, (P & 1) != 0, f->din_split);
-    f->din_split_bytes = f->din_split_query = 0;
+    f->din_split_bytes = f->din_split_query = f->din_split_wconv = 0;
     if (f->use_din_split) {
         // What the launch lays out, by the type it is launched with.  The query gives both 16-bit types one size, half
         // precision's, where the kernels take half precision too (its weights, widened, may be too large for them when
         // bfloat16's one part is not).
         const bool odd = (P & 1) != 0;
         const size_t widened = ((size_t)Cout * Cin * n * n * sizeof(float) + 255) & ~(size_t)255;
-        f->wconv_bytes = dt == KST_F16 ? widened : 0;
-        f->din_split_bytes = f->wconv_bytes + split_din_workspace_bytes(f->si, odd, f->din_split);
+        f->din_split_wconv = dt == KST_F16 ? widened : 0;
+        f->din_split_bytes = f->din_split_wconv + split_din_workspace_bytes(f->si, odd, f->din_split);
         f->din_split_query = f->din_split_bytes;
         if (dt == KST_BF16 && split_din_applies(f->si, odd, KST_F32)) {
             const size_t half = widened + split_din_workspace_bytes(f->si, odd, KST_F32);
@@ -571,7 +623,12 @@ kst_status grad_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dt
         }
     }
     f->use_dw_split = split_dw_applies(f->si, (P & 1) != 0);
-    f->dw_split_bytes = f->use_dw_split ? split_dw_workspace_bytes(f->si, (P & 1) != 0) : 0;
+    f->dw_split_bytes = f->dw_split_query = 0;
+    if (f->use_dw_split) {
+        f->dw_split_bytes = split_dw_workspace_bytes(f->si, (P & 1) != 0, dt);
+        // (the query: the larger of the 16-bit types', with the widened copy of `in` that the fp32 multiplies read)
+        f->dw_split_query = split_dw_workspace_bytes(f->si, (P & 1) != 0, KST_F32) + f->xconv_bytes;
+    }
     f->wsplit_bytes = f->dw_cores
                           ? backward_weight_igemm_workspace_bytes(f->si)
                           : backward_weight_generic_workspace_bytes(f->plain_unframed ? f->si : f->s);
@@ -594,15 +651,14 @@ size_t kst_backward_input_workspace_bytes(int B, int Cin, int Cout, int N, int n
 {
     GradPlan f;
     if (!dtype_ok(dtype) || grad_plan(B, Cin, Cout, N, n, P, dtype, &f) != KST_OK) return 0;
-    return f.use_din_split ? f.din_split_query : f.g_bytes + f.din_bytes + f.split_bytes + f.wconv_bytes;
+    return f.use_din_split ? f.din_split_query : f.din_bytes_needed();
 }
 
 size_t kst_backward_weight_workspace_bytes(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dtype)
 {
     GradPlan f;
     if (!dtype_ok(dtype) || grad_plan(B, Cin, Cout, N, n, P, dtype, &f) != KST_OK) return 0;
-    if (f.use_dw_split) return f.dw_split_bytes + f.xconv_bytes;
-    return f.dw_cores ? f.gw_bytes + f.wsplit_bytes + f.xconv_bytes : f.in_bytes + f.g_bytes + f.wsplit_bytes;
+    return f.use_dw_split ? f.dw_split_query : f.dw_bytes_needed();
 }
 
 kst_status kst_backward_input(const void *g, const void *w, void *din, void *ws, size_t ws_bytes,
@@ -614,18 +670,19 @@ kst_status kst_backward_input(const void *g, const void *w, void *din, void *ws,
     kst_status st = grad_plan(B, Cin, Cout, N, n, P, dtype, &f);
     if (st != KST_OK) return st;
     if (!aligned16(g) || !aligned16(w) || !aligned16(din)) return KST_ERR_ALIGN;
-    const size_t need = f.use_din_split ? f.din_split_bytes : f.g_bytes + f.din_bytes + f.split_bytes + f.wconv_bytes;
+    const bool split = f.use_din_split && ws && ws_bytes >= f.din_split_bytes;
+    const size_t need = split ? f.din_split_bytes : f.din_bytes_needed();
     if (need) {
         if (!ws || ws_bytes < need) return KST_ERR_WORKSPACE;
         if (!aligned16(ws)) return KST_ERR_ALIGN;
     }
-    if (f.use_din_split) {
+    if (split) {
         const void *w_in = w;
         if (dtype == KST_F16) {
             if (launch_widen(w, (float *)ws, (size_t)Cout * Cin * n * n, dtype, stream) != hipSuccess) return KST_ERR_HIP;
             w_in = ws;
         }
-        return launch_split_din((const float *)g, w_in, (float *)din, (char *)ws + f.wconv_bytes, f.si, (P & 1) != 0,
+        return launch_split_din((const float *)g, w_in, (float *)din, (char *)ws + f.din_split_wconv, f.si, (P & 1) != 0,
                                 f.din_split, stream) == hipSuccess
                    ? KST_OK
                    : KST_ERR_HIP;
@@ -666,8 +723,7 @@ kst_status kst_backward_weight(const void *in, const void *g, void *dw, void *ws
     kst_status st = grad_plan(B, Cin, Cout, N, n, P, dtype, &f);
     if (st != KST_OK) return st;
     if (!aligned16(in) || !aligned16(g) || !aligned16(dw)) return KST_ERR_ALIGN;
-    if (f.use_dw_split) {
-        if (!ws || ws_bytes < f.dw_split_bytes + f.xconv_bytes) return KST_ERR_WORKSPACE;
+    if (f.use_dw_split && ws && ws_bytes >= f.dw_split_bytes) {
         if (!aligned16(ws)) return KST_ERR_ALIGN;
         return launch_split_dw(in, (const float *)g, (float *)dw, ws, f.si, (P & 1) != 0, dtype, stream) == hipSuccess
                    ? KST_OK
@@ -676,7 +732,7 @@ kst_status kst_backward_weight(const void *in, const void *g, void *dw, void *ws
     const bool cores = f.dw_cores;
     const size_t g_copy = cores ? f.gw_bytes : f.g_bytes;
     const size_t in_copy = cores ? 0 : f.in_bytes;     // the matrix-core kernel reads `in` as it lies in memory
-    const size_t need = in_copy + g_copy + f.wsplit_bytes + (cores ? f.xconv_bytes : 0);
+    const size_t need = f.dw_bytes_needed();
     if (need) {
         if (!ws || ws_bytes < need) return KST_ERR_WORKSPACE;
         if (!aligned16(ws)) return KST_ERR_ALIGN;

@@ -218,9 +218,9 @@ bool split_din_applies(const Shape &s, bool odd, kst_dtype dt);
 size_t split_din_workspace_bytes(const Shape &s, bool odd, kst_dtype dt);
 hipError_t launch_split_din(const float *g, const void *w, float *din, void *ws, const Shape &s, bool odd, kst_dtype dt,
                             hipStream_t stream);
-// ... and their kernel gradient (any operand type; one workspace size, that of fp32 input).
+// ... and their kernel gradient (any operand type).
 bool split_dw_applies(const Shape &s, bool odd);
-size_t split_dw_workspace_bytes(const Shape &s, bool odd);
+size_t split_dw_workspace_bytes(const Shape &s, bool odd, kst_dtype dt);
 hipError_t launch_split_dw(const void *in, const float *g, float *dw, void *ws, const Shape &s, bool odd, kst_dtype dt,
                            hipStream_t stream);
 // force_even: take the even-share launch whenever igemm_f32_even_shares_possible, whatever the cost model says.

@@ -409,17 +409,20 @@ bool split_dw_applies(const Shape &s, bool odd)
     return products >= 3.0e9 && padded <= 1.5 * products && dw_plan(s, odd, 3).ok;
 }
 
-// (for an input of three parts)
-size_t split_dw_workspace_bytes(const Shape &s, bool odd)
+static int parts_of(kst_dtype dt) { return dt == KST_BF16 ? 1 : 3; }
+
+// (0 for a layer this kernel does not take)
+size_t split_dw_workspace_bytes(const Shape &s, bool odd, kst_dtype dt)
 {
-    const DwPlan r = dw_plan(s, odd, 3);
+    const DwPlan r = dw_plan(s, odd, parts_of(dt));
+    if (!r.ok) return 0;
     return r.x_bytes + r.g_bytes + r.part_bytes;
 }
 
 hipError_t launch_split_dw(const void *in, const float *g, float *dw, void *ws, const Shape &s, bool odd, kst_dtype dt,
                            hipStream_t stream)
 {
-    const DwPlan r = dw_plan(s, odd, dt == KST_BF16 ? 1 : 3);
+    const DwPlan r = dw_plan(s, odd, parts_of(dt));
     if (!r.ok) return hipErrorInvalidValue;
     if (dt == KST_BF16) return dw_launch_n<1>((const uint16_t *)in, g, dw, (char *)ws, r, s.n, stream);
     if (dt == KST_F16) return dw_launch_n<3>((const half_bits *)in, g, dw, (char *)ws, r, s.n, stream);

@@ -327,3 +327,75 @@ def test_split_gradients_small_bf16_operands(exponent):
     big = g * 2.0 ** 60
     assert torch.equal(kst.kst_backward_input(big, small(w), N, P), din * 2.0 ** (60 + exponent))
     assert torch.equal(kst.kst_backward_weight(small(x), big, n, P), dw * 2.0 ** (60 + exponent))
+
+
+# ---- scratch: what these layers run on with less than they want ------------------------------------------------------
+
+def _scratch(nbytes):
+    return torch.empty(nbytes, dtype=torch.uint8, device=DEV) if nbytes else None
+
+
+@pytest.mark.parametrize("shape", [FORWARD[0], FORWARD[4], (64, 1024, 512, 8, 5, 0), (128, 512, 256, 16, 4, 0)])
+def test_split_forward_with_less_scratch(shape):
+    """A byte less than the split kernels lay out: the kernels that multiply in fp32, bit for bit, where that is enough
+    for those; refused where it is not."""
+    B, Cin, Cout, N, n, P = shape
+    x, w = (t.to(DEV) for t in _layer(shape, 71))
+    seg = kst.kst_segregate_weights(w)
+    dims = (B, Cin, Cout, N, n, P, kst.KST_F32)
+    want, least = kst.kst_workspace_bytes_padded(*dims), kst.kst_workspace_bytes_padded(*dims, kst.KST_PATH_IGEMM)
+    call = lambda nbytes, path=kst.KST_PATH_AUTO: kst.kst_forward_seg_padded(x, seg, Cout, n, P, ws=_scratch(nbytes), path=path)
+    fp32, split = call(least, kst.KST_PATH_IGEMM), call(want)
+    assert not torch.equal(fp32, split)
+    assert float((fp32 - split).abs().max()) <= 2 * TOL * float(fp32.abs().max())
+    if least < want:
+        for have in {least, want - 1}:
+            assert torch.equal(call(have) if have else _null_workspace(x, seg, Cout, n, P), fp32)
+    if least > 0:                                     # (it may also be the larger of the two)
+        with pytest.raises(kst.KstError) as e:
+            call(min(least, want) - 1)
+        assert e.value.status == 4                    # KST_ERR_WORKSPACE
+
+
+def _null_workspace(x, seg, Cout, n, P):
+    B, Cin, N, _ = x.shape
+    out = torch.empty((B, Cout, 2 * N + 2 * P - n, 2 * N + 2 * P - n), device=DEV)
+    assert kst.lib().kst_forward_seg_padded(x.data_ptr(), seg.data_ptr(), out.data_ptr(), None, 0, B, Cin, Cout, N, n, P,
+                                            kst.KST_F32, kst.KST_PATH_AUTO, torch.cuda.current_stream().cuda_stream) == 0
+    return out
+
+
+def test_split_forward_without_scratch():
+    """A layer whose fp32 kernels need no workspace takes a null one."""
+    shape = FORWARD[3]
+    B, Cin, Cout, N, n, P = shape
+    assert kst.kst_workspace_bytes(B, Cin, Cout, N, n, kst.KST_F32, kst.KST_PATH_IGEMM) == 0
+    x, w = (t.to(DEV) for t in _layer(shape, 72))
+    seg = kst.kst_segregate_weights(w)
+    assert torch.equal(_null_workspace(x, seg, Cout, n, P), kst.kst_forward_seg(x, seg, Cout, n, path=kst.KST_PATH_IGEMM))
+
+
+@pytest.mark.parametrize("shape", [INPUT_GRADIENT[0], INPUT_GRADIENT[6], INPUT_GRADIENT[8]])
+def test_split_gradients_with_less_scratch(shape):
+    """Every type: with what the query gives, the split kernels; with too little for those, the ones that multiply in
+    fp32; a single byte is refused by both."""
+    B, Cin, Cout, N, n, P, dtype = shape
+    x, w, g = (t.to(DEV) for t in _gradient_inputs(shape, 73))
+    code = {"f32": kst.KST_F32, "bf16": kst.KST_BF16, "f16": kst.KST_F16}[dtype]
+    for query, call in ((kst.kst_backward_input_workspace_bytes, lambda ws: kst.kst_backward_input(g, w, N, P, ws=ws)),
+                        (kst.kst_backward_weight_workspace_bytes, lambda ws: kst.kst_backward_weight(x, g, n, P, ws=ws))):
+        need = query(B, Cin, Cout, N, n, P, code)
+        full, accepted, refused = call(_scratch(need)), [], 0
+        have = need
+        while have > 64:                              # less and less of it
+            have = have * 7 // 8 // 16 * 16
+            try:
+                accepted.append(call(_scratch(have)))
+            except kst.KstError as e:
+                assert e.status == 4                  # KST_ERR_WORKSPACE
+                refused += 1
+        other = [a for a in accepted if not torch.equal(a, full)]
+        for a in other:                               # one alternative, the same every time
+            assert torch.equal(a, other[0])
+            assert float((a - full).abs().max()) <= 2 * TOL * float(full.abs().max())
+        assert refused > 0

@@ -63,3 +63,24 @@ def test_static_workspace_entry_point_refuses_what_does_not_fit():
     assert e.value.status == 4                       # KST_ERR_WORKSPACE
     torch.cuda.synchronize()
     assert torch.isnan(out).all()                    # nothing was launched
+
+
+def test_static_workspace_entry_point_large_fp32_layers():
+    """Layers whose operands are split for the bf16 matrix cores: within the array, as kst_forward_seg runs them; beyond
+    it, as kst_forward_seg does with that much workspace (the kernels that multiply in fp32)."""
+    for k, (layer, fits) in enumerate([
+            (wl.Layer("static_5", 9, 96, 130, 64, 3, "f32", "relu_normal", w_std=0.1), True),
+            (wl.Layer("static_6", 64, 512, 256, 10, 4, "f32", "relu_normal", w_std=0.1), True),
+            (wl.Layer("static_7", 64, 1024, 512, 8, 5, "f32", "relu_normal", w_std=0.1), False)]):
+        x, w, out, want_gpu, need = run_both(layer, 700 + k, kst.KST_PATH_AUTO)
+        assert (need <= kst.KST_STATIC_SCRATCH_BYTES) == fits and need > 0
+        w_seg = kst.kst_segregate_weights(w.to(DEV))
+        ws = torch.empty(kst.KST_STATIC_SCRATCH_BYTES, dtype=torch.uint8, device=DEV)
+        limited = kst.kst_forward_seg(x.to(DEV), w_seg, layer.Cout, layer.n, ws=ws)
+        fp32 = kst.kst_forward_seg(x.to(DEV), w_seg, layer.Cout, layer.n, path=kst.KST_PATH_IGEMM)
+        assert torch.equal(out, limited), layer.name
+        assert torch.equal(out, want_gpu) == fits and torch.equal(out, fp32) == (not fits), layer.name
+        b, co = [0, layer.B // 2, layer.B - 1], [0, layer.Cout // 2, layer.Cout - 1]
+        want = oracle.forward_planes(wl.to_f64(x), wl.to_f64(w), b, co, 0)
+        got = out[b, co].cpu().numpy().astype(np.float64)
+        assert np.abs(got - want).max() <= 2e-5 * np.abs(want).max(), layer.name

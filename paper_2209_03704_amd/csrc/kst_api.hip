@@ -622,7 +622,7 @@ kst_status grad_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dt
             if (half > f->din_split_query) f->din_split_query = half;
         }
     }
-    f->use_dw_split = split_dw_applies(f->si, (P & 1) != 0);
+    f->use_dw_split = split_dw_applies(f->si, (P & 1) != 0, dt);
     f->dw_split_bytes = f->dw_split_query = 0;
     if (f->use_dw_split) {
         f->dw_split_bytes = split_dw_workspace_bytes(f->si, (P & 1) != 0, dt);

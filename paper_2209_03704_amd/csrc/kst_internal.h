@@ -219,7 +219,7 @@ size_t split_din_workspace_bytes(const Shape &s, bool odd, kst_dtype dt);
 hipError_t launch_split_din(const float *g, const void *w, float *din, void *ws, const Shape &s, bool odd, kst_dtype dt,
                             hipStream_t stream);
 // ... and their kernel gradient (any operand type).
-bool split_dw_applies(const Shape &s, bool odd);
+bool split_dw_applies(const Shape &s, bool odd, kst_dtype dt);
 size_t split_dw_workspace_bytes(const Shape &s, bool odd, kst_dtype dt);
 hipError_t launch_split_dw(const void *in, const float *g, float *dw, void *ws, const Shape &s, bool odd, kst_dtype dt,
                            hipStream_t stream);

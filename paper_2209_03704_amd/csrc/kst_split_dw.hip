@@ -397,16 +397,20 @@ hipError_t dw_launch_n(const T *in, const float *g, float *dw, char *ws, const D
 
 }  // namespace
 
-bool split_dw_applies(const Shape &s, bool odd)
+bool split_dw_applies(const Shape &s, bool odd, kst_dtype dt)
 {
     const double edge = s.N - 2 * s.frame, nn = s.n * s.n;
     const double products = (double)s.B * edge * edge * nn * s.Cin * s.Cout;
     const double padded = (double)((s.B + 15) / 16 * 16) * edge * edge * nn * ((s.Cin + 127) / 128 * 128) *
                           ((s.Cout + 127) / 128 * 128);
-    // The two passes and four launches cost 20 to 30 us (measured with passes half as fast): 512 -> 256 channels, 8 x 8, n = 4, P = 2 at a batch of 32 (4.3 G
-    // products) 75 us against 111, 128 -> 128, 24 x 24, n = 5 at 16 (3.8 G) 85 against 124, 128 -> 128, 32 x 32, n = 3 at 32
-    // (4.8 G, mostly passes over g) 142 against 150.  What fills items and channels up to whole blocks is multiplied too.
-    return products >= 3.0e9 && padded <= 1.5 * products && dw_plan(s, odd, 3).ok;
+    // What fills items and channels up to whole blocks is multiplied too.  Both sides timed on 1014 random layers from 3
+    // to 16 G products: 1.5 times as fast on average, with 1.8 to 2.2 times the products multiplied 25 of 121 layers
+    // lost.  One kind did not gain: with 9 products per value of g and input channel and at most one tile of those, the
+    // passes over g (four times the positions) show, and on maps of whole groups of four columns the fp32 multiplies
+    // are at their best: of 32 such layers 15 lost (68 x 128 x 128 x 24 x 24, P = 3: 220 us here against 181).  bfloat16
+    // input halves the multiplies and gained there too.
+    const bool g_bound = s.n == 3 && s.Cin <= E_TC && dt != KST_BF16 && edge > 8 && ((int)edge & 3) == 0;
+    return products >= 3.0e9 && padded <= 1.5 * products && !g_bound && dw_plan(s, odd, 3).ok;
 }
 
 static int parts_of(kst_dtype dt) { return dt == KST_BF16 ? 1 : 3; }

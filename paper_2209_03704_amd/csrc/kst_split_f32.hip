@@ -670,18 +670,32 @@ hipError_t launch_n(const float *in, const float *w_seg, float *out, char *ws, c
 bool split_f32_applies(const Shape &s)
 {
     if (s.no_split || s.Cout < 16 || s.Cin <= S_KC) return false;
-    // Three launches and the first operands' way through them cost about 30 us, so the layer has to be worth that:
-    // 512 -> 256 channels, 8 x 8, n = 4 measured 45.7 us here against 42.2 with fp32 multiplies at a batch of 8 (1.07 G
-    // products) and 49.2 against 60.6 at 16 (2.15 G); 64 -> 64, 32 x 32, n = 3: 46 against 33 at 16 (0.64 G), 77 against
-    // 81 at 64 (2.6 G).  One chunk of channels leaves nothing to run ahead of (16 -> 16, 64 x 64: 126 against 74).
-    // Fewer than eight chunks keep a pass's first and last ones in view: where the pipelined fp32 kernel takes the layer
-    // (whole groups of four channels and, unframed, columns) it is as fast or faster (33 x 64 x 152 x 15 x 15, n = 5, P = 2:
-    // 83 us here against 68; 15 x 96 x 128 x 29 x 29: 95 against 97); the plain one is not (9 x 68 x 352 x 35 x 35, n = 4:
-    // 97 against 248).
-    const bool pipelined = (s.Cin & 3) == 0 && (s.Cout & 3) == 0 && (s.frame > 0 || (s.N & 3) == 0);
-    if (pipelined && s.Cin < 8 * S_KC) return false;
     const double products = (double)s.B * s.E * s.E * s.n * s.n * s.Cin * s.Cout;
-    return products >= 1.5e9 && plan(s).ok;
+    if (products < 1.5e9) return false;
+    // Both sides timed on 1650 random layers of 1.5 to 12 G products (n = 3 .. 5, maps of 4 to 64, 17 to 1024 channels).
+    // Where the plain fp32 kernel is the other one (channels no whole groups of four or, unframed, columns) this one was
+    // at least 1.4 times as fast on all 730 of them.
+    const SplitPlan r = plan(s);
+    const bool pipelined = (s.Cin & 3) == 0 && (s.Cout & 3) == 0 && (s.frame > 0 || (s.N & 3) == 0);
+    if (!pipelined || !r.ok) return r.ok;
+    // The pipelined fp32 kernel is another matter.  Passes of fewer than eight channel chunks keep their first and last
+    // ones in view: 23 of 67 such layers lost, at any size (10 x 96 x 192 x 64 x 64, n = 3, P = 2, 7 G products: 180 us
+    // here against 145), so they stay.  With eight and more, none of 200 layers from 4 G products lost.  Below that both
+    // times are known well enough to compare: here (within 5 % on 561 layers) a launch chain of 13 us, 0.5 per kernel
+    // tap and chunk of a workgroup's share, 0.9 per million weights to split, 17.6 per piece of its share (filling the
+    // pipeline, storing) and 0.6 per workgroup that adds to a pass; there 22 and 17.2 per G products of whole tiles.
+    // From 1.5 G products 58 of 495 were slower here than there, by up to a third; of those this keeps 11 are, by up to 9 %.
+    if (s.Cin < 8 * S_KC) return false;
+    if (products >= 4.0e9) return true;
+    const EvenShares &k = r.k;
+    const double shares = (double)k.rounds * k.grid + k.passes;                  // passes of both parities
+    const double units = shares * r.p.chunks * (k.taps0 + k.taps1) / 2 / S_GRID;
+    const double pieces = k.rounds + (k.passes ? (double)k.passes / S_GRID + 1.0 : 0.0);
+    const double here = 13.0 + 0.5 * units + 0.9e-6 * (r.p.w_bytes / 6) + 17.6 * pieces +
+                        (k.passes ? 0.6 * S_GRID / k.passes : 0.0);
+    const double tiles = (double)((r.p.Mtot + 127) / 128) * 128 * ((s.Cout + 63) / 64 * 64);
+    const double there = 22.0 + 17.2e-9 * tiles * s.n * s.n * s.Cin + (s.frame > 0 && (r.p.N0 & 3) != 0 ? 4.0 : 0.0);
+    return there > 1.02 * here;
 }
 
 size_t split_f32_workspace_bytes(const Shape &s)

@@ -42,6 +42,18 @@ def split_forward_bytes(B, Cin, Cout, N, n, P):
     return weights + slot_count(min(256, 2 * tiles * chunks), passes) * 256 * 128 * 4
 
 
+def split_dw_bytes(B, Cin, Cout, N, n, P, parts):
+    """Operands [block of 32 channels][position][16 items][part][64 lanes][8 values] of the input (`parts`) and of g
+    (three), then partial sums [split][tap][co][ci]."""
+    M, groups = 2 * N + 2 * P - n, -(-B // 16)
+    steps, tiles = N * N * groups, -(-Cout // 128) * -(-Cin // 128) * ((n * n + 1) // 2)
+    splits = max(1, min(256 // tiles if tiles < 256 else 1, steps // 16))
+    per = (-(-steps // splits) + 1) // 2 * 2
+    splits = -(-steps // per)
+    return (-(-Cin // 32) * N * N * groups * parts * 1024 + -(-Cout // 32) * M * M * groups * 3 * 1024 +
+            _up(splits * n * n * Cout * Cin * 4, 256))
+
+
 # Weights whose three parts pass the 2 GB a launch can address while bfloat16's one part does not: the size has to be
 # that of the type that is launched, from the first byte the launch writes to its last.
 @pytest.mark.parametrize("B,Cin,Cout,N,n", [(1, 7000, 7000, 8, 4), (1, 10000, 10000, 8, 3), (1, 6000, 6000, 8, 5)])
@@ -81,3 +93,46 @@ def test_partial_tiles_are_numbered_along_the_list():
     workgroup made 79.7 MB, more than the library's fixed workspace holds."""
     need = kst.kst_workspace_bytes_padded(64, 512, 256, 8, 4, 2, F32)
     assert need == 383 * 131072 + 12582912 < kst.KST_STATIC_SCRATCH_BYTES
+
+
+# Which layers run on the split kernels: either side of each rule's line, told by the workspace.
+@pytest.mark.parametrize("shape,split", [
+    ((36, 896, 128, 4, 5, 1), False),     # ten passes of 56 chunks: mostly partial tiles
+    ((6, 128, 128, 48, 3, 1), False),     # short passes
+    ((10, 96, 192, 64, 3, 2), False),     # fewer than eight chunks, whatever the size
+    ((10, 98, 192, 64, 3, 2), True),      # ... where the pipelined fp32 kernel does not apply (no groups of four)
+    ((16, 512, 256, 8, 4, 2), True),      # 2.1 G products, whole chunks
+    ((8, 512, 256, 8, 4, 2), False),      # 1.1 G
+    ((3, 1024, 512, 10, 5, 2), True),     # 3.9 G, shared by few passes
+    ((40, 128, 256, 16, 4, 2), True),     # from 4 G always
+])
+def test_forward_route(shape, split):
+    assert (kst.kst_workspace_bytes_padded(*shape, F32) == split_forward_bytes(*shape)) == split
+
+
+@pytest.mark.parametrize("shape,split", [
+    ((13, 768, 384, 6, 4, 2), False),     # 2.2 G, the pipelined fp32 kernel at its best
+    ((13, 768, 383, 6, 4, 2), True),      # ... which wants whole groups of four channels
+    ((16, 768, 384, 6, 4, 2), True),      # 2.7 G
+    ((20, 256, 256, 8, 5, 0), False),     # 2.1 G
+    ((21, 256, 256, 8, 5, 0), True),      # 2.2 G
+])
+def test_input_gradient_route(shape, split):
+    B, Cin, Cout, N, n, P = shape
+    want = split_din_weight_bytes(Cin, Cout, n, 3) + split_din_slot_bytes(B, Cin, Cout, N, n)
+    assert (kst.kst_backward_input_workspace_bytes(*shape, F32) == want) == split
+
+
+@pytest.mark.parametrize("shape,dtype,split", [
+    ((68, 128, 128, 24, 3, 3), F32, False),    # 9 products per value of g and input channel, one tile of those
+    ((68, 128, 128, 24, 3, 3), BF16, True),    # (bfloat16 input: half the multiplies)
+    ((68, 130, 128, 25, 3, 3), F32, False),    # half of the second tile of input channels would be padding
+    ((68, 256, 128, 24, 3, 3), F32, True),
+    ((68, 128, 128, 23, 3, 3), F32, True),     # columns no whole groups of four
+    ((64, 512, 256, 8, 4, 2), F32, True),
+    ((16, 512, 256, 8, 4, 2), F32, False),     # 2.1 G products
+])
+def test_kernel_gradient_route(shape, dtype, split):
+    B, Cin, Cout, N, n, P = shape
+    want = split_dw_bytes(B, Cin, Cout, N, n, P, 3) + (B * Cin * N * N * 4 if dtype == BF16 else 0)
+    assert (kst.kst_backward_weight_workspace_bytes(*shape, dtype) == want) == split

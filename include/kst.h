@@ -18,7 +18,9 @@
  *     (no bias, no activation, no accumulation).  Buffers must not alias.
  *   - dtype describes in and w: KST_F32 (fp32 operands, fp32 arithmetic; large
  *     layers form each product from six exact products of bfloat16 parts of its
- *     operands, to within 2^-26 of it, and add them in fp32),
+ *     operands, to within 2^-24 of it, whatever the operands' size, and add them
+ *     in fp32; what has no such parts or overflows on the way is multiplied in
+ *     fp32 again),
  *     KST_BF16 (bfloat16 operands, fp32 accumulation, fp32 out) or KST_F16 (IEEE
  *     half-precision operands, fp32 accumulation, fp32 out; not in the paper:
  *     the same kernels as KST_BF16 with the other 16-bit multiply).

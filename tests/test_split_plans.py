@@ -1,6 +1,7 @@
-"""Workspace sizes of the kernels that split fp32 operands for the bf16 matrix cores, against what those kernels lay out
-in it (no GPU: the sizes come from the host)."""
+"""The kernels that split fp32 operands for the bf16 matrix cores, as far as they show without a GPU: what their three
+parts keep of a value, which layers they take, and their workspaces against what they lay out in them."""
 import pytest
+import torch
 
 from paper_2209_03704_amd import binding as kst
 
@@ -136,3 +137,21 @@ def test_kernel_gradient_route(shape, dtype, split):
     B, Cin, Cout, N, n, P = shape
     want = split_dw_bytes(B, Cin, Cout, N, n, P, 3) + (B * Cin * N * N * 4 if dtype == BF16 else 0)
     assert (kst.kst_backward_weight_workspace_bytes(*shape, dtype) == want) == split
+
+
+def test_three_parts_of_every_fp32_value():
+    """Every mantissa at exponents from the subnormal ones up: the parts of the value times 2^24 add up to it, are normal
+    bfloat16 numbers (or zero), and are as small as the error bound of a product takes them to be."""
+    mantissas = torch.arange(1 << 23, dtype=torch.int32)
+    for exponent in (0, 1, 17, 127, 228):
+        x = ((exponent << 23) | mantissas).view(torch.float32) * 2.0 ** 24
+        p0 = x.bfloat16().float()
+        p1 = (x - p0).bfloat16().float()
+        p2 = x - p0 - p1
+        assert torch.equal(p2.bfloat16().float(), p2)
+        assert (p1.abs() <= 2.0 ** -8 * x).all() and (p2.abs() <= 2.0 ** -17 * x).all()
+        for part in (p0, p1, p2):
+            assert part[part != 0].abs().min() >= 2.0 ** -126
+        # what a product of x with itself leaves out: x1 x2 twice and x2 x2
+        left = (2 * p1.double() * p2.double() + p2.double() ** 2).abs()
+        assert (left <= 2.0 ** -24 * x.double() ** 2).all()

@@ -23,7 +23,8 @@ namespace {
 constexpr int D_THREADS = 256;
 constexpr int D_KC = 16;                 // output channels per chunk
 constexpr int D_TM = 128;                // positions per tile
-constexpr int D_IP = 832;                // cells (rows x columns of g) a stage can hold
+constexpr int D_IP = 832;                // cells (rows x columns of g) a stage can hold: with n = 3 maps of 4 to 28, 32, 33, 64
+                                         // and 128, n = 4: 4 to 17, 19, 22, 32, 64, n = 5: 8, 16, 32; others are not taken
 constexpr int D_HALF = D_IP * 16;
 constexpr int D_PART = 2 * D_HALF;
 constexpr int D_STAGE = 3 * D_PART;      // 79872 bytes
@@ -500,8 +501,10 @@ hipError_t din_launch(const float *g, const T *w, float *din, char *ws, const Di
 template <int n, int RB, int WP, class T>
 hipError_t din_launch_nt(const float *g, const T *w, float *din, char *ws, const DinPlan &pl, hipStream_t stream)
 {
-    return pl.p.ip <= 5 * 128 ? din_launch<n, RB, WP, 5>(g, w, din, ws, pl, stream)
-                              : din_launch<n, RB, WP, 7>(g, w, din, ws, pl, stream);
+    // (no map with a 5 x 5 kernel is staged by five cells per lane: 8, 16 and 32 want 760, 684 and 748)
+    if constexpr (n != 5)
+        if (pl.p.ip <= 5 * 128) return din_launch<n, RB, WP, 5>(g, w, din, ws, pl, stream);
+    return din_launch<n, RB, WP, 7>(g, w, din, ws, pl, stream);
 }
 
 template <int WP, class T>

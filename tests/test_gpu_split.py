@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import oracle
+import test_split_plans as plans
 from paper_2209_03704_amd import binding as kst
 from paper_2209_03704_amd import workloads as wl
 
@@ -12,15 +13,25 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 TOL = 2e-5          # of the largest element, as for every fp32 kernel
 
-# Large enough for the split kernels (1.5 G products); between them: kernel edges 3, 4, 5; tiles of 64 and 128 output
-# channels; three and five staged positions per lane; ragged channels, chunks, batches; odd maps; odd padding factors.
+# Layers the split kernels take (each test asserts it by the workspace; test_split_plans.py holds the lists against every
+# variant there is): kernel edges 3, 4, 5; tiles of 64 and 128 output channels; three and five staged positions per lane;
+# ragged channels, chunks, batches; odd maps; odd padding factors.
 FORWARD = [
     (30, 130, 200, 16, 4, 0),    # ragged channels on both sides, even map
-    (23, 515, 66, 13, 3, 2),     # odd map edge and padding, a last chunk of three channels, 66 of 128 channels
+    (26, 515, 66, 13, 3, 2),     # odd map edge and padding, a last chunk of three channels, 66 of 128 channels
     (70, 33, 40, 33, 5, 1),      # tiles of 64 channels, odd padding factor (interior stores), two chunks and one channel
-    (9, 96, 130, 64, 3, 0),      # long rows: five staged positions per lane
+    (9, 96, 130, 64, 3, 0),      # rows of half a tile
     (64, 512, 256, 8, 4, 2),     # shared passes only
     (130, 256, 64, 6, 5, 3),     # small maps, many items per tile, odd padding factor
+    (2, 90, 130, 100, 3, 0),     # long rows: five staged positions per lane with tiles of 128 positions
+    (2, 70, 130, 90, 4, 0),
+    (3, 66, 130, 64, 5, 0),
+    (14, 130, 200, 16, 5, 0),
+    (250, 65, 48, 16, 3, 0),     # tiles of 64 channels and 256 positions, five and three staged positions
+    (25, 90, 50, 40, 3, 0),
+    (60, 131, 52, 20, 4, 0),
+    (60, 131, 52, 16, 4, 1),
+    (40, 130, 50, 18, 5, 0),
 ]
 
 
@@ -54,6 +65,7 @@ def _planes(x, w, P, count=24):
 @pytest.mark.parametrize("shape", FORWARD)
 def test_split_forward(shape):
     P = shape[5]
+    assert kst.kst_workspace_bytes_padded(*shape, kst.KST_F32) == plans.split_forward_bytes(*shape)
     x, w = _layer(shape, 31 + shape[0])
     b, co, want = _planes(x, w, P)
     out = _forward(x, w, P)
@@ -174,17 +186,30 @@ def test_split_forward_subnormal_operands():
 
 
 # Input gradient: 128 and 256 input channels per tile, five and seven staged cells per lane, ragged channels, odd padding
-# factors, tiles that cross items and rows, bfloat16 weights (one part) and half-precision ones (widened).
+# factors, tiles that cross items and rows, bfloat16 weights (one part) and half-precision ones (widened).  The first are
+# also used below.
 INPUT_GRADIENT = [
     (64, 512, 256, 8, 4, 2, "f32"),
     (25, 200, 133, 16, 4, 1, "f32"),
     (17, 130, 70, 33, 3, 0, "f32"),
-    (30, 128, 66, 19, 5, 3, "f32"),
-    (33, 40, 530, 10, 5, 2, "f32"),
+    (25, 70, 133, 16, 5, 3, "f32"),
+    (90, 130, 66, 8, 5, 2, "f32"),
     (9, 96, 130, 64, 3, 2, "f32"),
     (64, 256, 128, 16, 4, 2, "bf16"),
     (40, 70, 130, 21, 3, 1, "bf16"),
     (64, 200, 67, 13, 4, 1, "f16"),
+    (10, 60, 90, 32, 5, 1, "f32"),
+    (60, 100, 130, 16, 3, 1, "f32"),
+    (20, 120, 100, 32, 3, 0, "bf16"),
+    (32, 300, 130, 16, 3, 0, "f32"),
+    (40, 260, 150, 14, 3, 1, "f32"),
+    (130, 258, 140, 8, 3, 2, "bf16"),
+    (60, 257, 129, 12, 3, 3, "bf16"),
+    (30, 96, 150, 16, 4, 3, "bf16"),
+    (56, 128, 90, 15, 4, 1, "bf16"),
+    (32, 260, 130, 16, 4, 0, "f32"),
+    (70, 260, 130, 11, 4, 2, "bf16"),
+    (190, 128, 60, 8, 5, 0, "bf16"),
 ]
 _DT = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
 
@@ -204,6 +229,8 @@ def _items(B):
 @pytest.mark.parametrize("shape", INPUT_GRADIENT)
 def test_split_input_gradient(shape):
     B, Cin, Cout, N, n, P, dtype = shape
+    code = {"f32": kst.KST_F32, "bf16": kst.KST_BF16, "f16": kst.KST_F16}[dtype]
+    assert kst.kst_backward_input_workspace_bytes(*shape[:6], code) == plans.split_din_query(*shape[:6], code)
     _, w, g = _gradient_inputs(shape, 17 + B)
     din = kst.kst_backward_input(g.to(DEV), w.to(DEV), N, P)
     again = kst.kst_backward_input(g.to(DEV), w.to(DEV), N, P)
@@ -245,17 +272,22 @@ def test_split_input_gradient_infinities_and_nan(shape):
 KERNEL_GRADIENT = [
     (64, 512, 256, 8, 4, 2, "f32"),
     (30, 250, 127, 19, 3, 1, "f32"),
-    (45, 128, 120, 11, 5, 3, "f32"),
+    (70, 128, 120, 11, 5, 3, "f32"),
     (160, 384, 384, 4, 4, 0, "f32"),
     (64, 256, 128, 16, 4, 2, "bf16"),
     (31, 125, 256, 20, 3, 0, "bf16"),
     (47, 128, 256, 14, 4, 1, "f16"),
+    (40, 256, 128, 10, 5, 1, "bf16"),
+    (48, 256, 250, 12, 3, 0, "f16"),
+    (32, 128, 256, 13, 5, 2, "f16"),
 ]
 
 
 @pytest.mark.parametrize("shape", KERNEL_GRADIENT)
 def test_split_kernel_gradient(shape):
     B, Cin, Cout, N, n, P, dtype = shape
+    code = {"f32": kst.KST_F32, "bf16": kst.KST_BF16, "f16": kst.KST_F16}[dtype]
+    assert kst.kst_backward_weight_workspace_bytes(*shape[:6], code) == plans.split_dw_query(*shape[:6], code)
     x, _, g = _gradient_inputs(shape, 47 + B)
     dw = kst.kst_backward_weight(x.to(DEV), g.to(DEV), n, P)
     again = kst.kst_backward_weight(x.to(DEV), g.to(DEV), n, P)
@@ -327,6 +359,32 @@ def test_split_gradients_small_bf16_operands(exponent):
     big = g * 2.0 ** 60
     assert torch.equal(kst.kst_backward_input(big, small(w), N, P), din * 2.0 ** (60 + exponent))
     assert torch.equal(kst.kst_backward_weight(small(x), big, n, P), dw * 2.0 ** (60 + exponent))
+
+
+# Layers just outside the rules (fewer products; maps whose rows of g the input gradient cannot stage): the kernels that
+# multiply in fp32, to the same tolerance.
+BESIDE = [(23, 515, 66, 13, 3, 2), (30, 128, 66, 19, 5, 3), (33, 40, 530, 10, 5, 2), (45, 128, 120, 11, 5, 3)]
+
+
+@pytest.mark.parametrize("shape,pass_", zip(BESIDE, ("forward", "input", "input", "kernel")))
+def test_layers_beside_the_rules(shape, pass_):
+    B, Cin, Cout, N, n, P = shape
+    x, w, g = _gradient_inputs((*shape, "f32"), 83)
+    if pass_ == "forward":
+        assert kst.kst_workspace_bytes_padded(*shape, kst.KST_F32) != plans.split_forward_bytes(*shape)
+        b, co, want = _planes(x, w, P)
+        got = _forward(x, w, P)[torch.tensor(b), torch.tensor(co)]
+    elif pass_ == "input":
+        assert kst.kst_backward_input_workspace_bytes(*shape, kst.KST_F32) != plans.split_din_query(*shape, kst.KST_F32)
+        items = _items(B)
+        want = oracle.backward_input(wl.to_f64(g[items]), wl.to_f64(w), N, P)
+        got = kst.kst_backward_input(g.to(DEV), w.to(DEV), N, P)[items].cpu()
+    else:
+        assert kst.kst_backward_weight_workspace_bytes(*shape, kst.KST_F32) != plans.split_dw_query(*shape, kst.KST_F32)
+        cos, cis = [0, 31, Cout - 1], [0, 33, Cin - 1]
+        want = oracle.backward_weight(wl.to_f64(x[:, cis]), wl.to_f64(g[:, cos]), n, P)
+        got = kst.kst_backward_weight(x.to(DEV), g.to(DEV), n, P)[cos][:, cis].cpu()
+    assert np.abs(got.numpy().astype(np.float64) - want).max() <= TOL * np.abs(want).max()
 
 
 # ---- scratch: what these layers run on with less than they want ------------------------------------------------------

@@ -55,6 +55,40 @@ def split_dw_bytes(B, Cin, Cout, N, n, P, parts):
             _up(splits * n * n * Cout * Cin * 4, 256))
 
 
+def split_din_query(B, Cin, Cout, N, n, P, dtype):
+    """16-bit weights: with their widened copy (bfloat16 does without; the query gives one size)."""
+    widened = _up(Cin * Cout * n * n * 4, 256) if dtype != F32 else 0
+    return widened + split_din_weight_bytes(Cin, Cout, n, 3) + split_din_slot_bytes(B, Cin, Cout, N, n)
+
+
+def split_dw_query(B, Cin, Cout, N, n, P, dtype):
+    """16-bit input: with its widened copy, which only the kernels that multiply in fp32 read."""
+    return split_dw_bytes(B, Cin, Cout, N, n, P, 3) + (_up(B * Cin * N * N * 4, 256) if dtype != F32 else 0)
+
+
+# ---- variants of the kernels: which one a layer runs ----------------------------------------------------------------
+
+def forward_variant(B, Cin, Cout, N, n, P):
+    """(kernel edge, 128 or 64 output channels per tile, staged positions per lane), None for a map these do not take."""
+    Nq = N + 2 * ((P + 1) // 2)
+    E = -(-(2 * Nq - n) // 2)
+    steps = ((128 if Cout > 64 else 256) - 2) // E + 1
+    staged = (steps + (steps + E - 1) // E * (Nq - E) + n // 2 + 1) * Nq
+    return (n, 128 if Cout > 64 else 64, 3 if staged <= 384 else 5) if staged <= 640 else None
+
+
+def input_gradient_variant(B, Cin, Cout, N, n, P, dtype):
+    """(kernel edge, 256 or 128 input channels per tile, parts of the weights, staged cells per lane), or None."""
+    tiles_m, chunks = -(-B * N * N // 128), -(-Cout // 16)
+    two = n < 5 and Cin > 128 and tiles_m * -(-Cin // 256) * chunks >= 4 * 256
+    rows = 128 // N
+    whole = rows * N == 128 and (rows % N == 0 or N % rows == 0)
+    steps = rows - 1 if whole else 126 // N + 1
+    items = (rows - 1) // N if whole else (steps + N - 1) // N
+    staged = (2 * steps + items * (n - 2) + n) * 2 * ((2 * N + n - 1) // 2)
+    return (n, 256 if two else 128, 1 if dtype == "bf16" else 3, 5 if staged <= 640 else 7) if staged <= 832 else None
+
+
 # Weights whose three parts pass the 2 GB a launch can address while bfloat16's one part does not: the size has to be
 # that of the type that is launched, from the first byte the launch writes to its last.
 @pytest.mark.parametrize("B,Cin,Cout,N,n", [(1, 7000, 7000, 8, 4), (1, 10000, 10000, 8, 3), (1, 6000, 6000, 8, 5)])
@@ -119,9 +153,7 @@ def test_forward_route(shape, split):
     ((21, 256, 256, 8, 5, 0), True),      # 2.2 G
 ])
 def test_input_gradient_route(shape, split):
-    B, Cin, Cout, N, n, P = shape
-    want = split_din_weight_bytes(Cin, Cout, n, 3) + split_din_slot_bytes(B, Cin, Cout, N, n)
-    assert (kst.kst_backward_input_workspace_bytes(*shape, F32) == want) == split
+    assert (kst.kst_backward_input_workspace_bytes(*shape, F32) == split_din_query(*shape, F32)) == split
 
 
 @pytest.mark.parametrize("shape,dtype,split", [
@@ -134,9 +166,7 @@ def test_input_gradient_route(shape, split):
     ((16, 512, 256, 8, 4, 2), F32, False),     # 2.1 G products
 ])
 def test_kernel_gradient_route(shape, dtype, split):
-    B, Cin, Cout, N, n, P = shape
-    want = split_dw_bytes(B, Cin, Cout, N, n, P, 3) + (B * Cin * N * N * 4 if dtype == BF16 else 0)
-    assert (kst.kst_backward_weight_workspace_bytes(*shape, dtype) == want) == split
+    assert (kst.kst_backward_weight_workspace_bytes(*shape, dtype) == split_dw_query(*shape, dtype)) == split
 
 
 def test_three_parts_of_every_fp32_value():
@@ -155,3 +185,29 @@ def test_three_parts_of_every_fp32_value():
         # what a product of x with itself leaves out: x1 x2 twice and x2 x2
         left = (2 * p1.double() * p2.double() + p2.double() ** 2).abs()
         assert (left <= 2.0 ** -24 * x.double() ** 2).all()
+
+
+def test_gpu_shapes_run_every_variant():
+    """The layers the GPU tests run, against every variant any map edge and channel count leads to."""
+    import test_gpu_split as gpu
+    edges, pads = range(4, 132), range(4)
+    forward = {forward_variant(1, 32, Cout, N, n, P) for n in (3, 4, 5) for N in edges for P in pads for Cout in (48, 130)}
+    assert {forward_variant(*s) for s in gpu.FORWARD} == forward - {None}
+    gradient = {input_gradient_variant(B, Cin, 256, N, n, 0, dt) for n in (3, 4, 5) for N in edges
+                for B, Cin in ((64, 100), (640, 300)) for dt in ("f32", "bf16")}
+    assert {input_gradient_variant(*s) for s in gpu.INPUT_GRADIENT} == gradient - {None}
+    assert {(s[4], s[6]) for s in gpu.KERNEL_GRADIENT} == {(n, dt) for n in (3, 4, 5) for dt in ("f32", "bf16", "f16")}
+
+
+def test_maps_the_input_gradient_takes():
+    """Its stage of 832 cells holds the rows of g that 128 positions touch on these maps only."""
+    takes = lambda n: [N for N in range(4, 132) if input_gradient_variant(1, 64, 64, N, n, 0, "f32")]
+    assert takes(3) == [*range(4, 29), 32, 33, 64, 128]
+    assert takes(4) == [*range(4, 18), 19, 22, 32, 64]
+    assert takes(5) == [8, 16, 32]
+    for n in (3, 4, 5):
+        for N in range(4, 70):
+            B = max(1, -(-int(4e9) // (N * N * n * n * 128 * 66)))
+            if (2 * N - n) > 0 and B * 66 * (2 * N) ** 2 * 4 < 2 ** 31:
+                need = kst.kst_backward_input_workspace_bytes(B, 100, 66, N, n, 0, F32)
+                assert (need == split_din_query(B, 100, 66, N, n, 0, F32)) == (N in takes(n)), (n, N)

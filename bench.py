@@ -154,7 +154,7 @@ def roofline_for(layer, ms, metrics):
         return {"bound": "hbm", "achieved": round(a, 1), "peak": metrics.HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(a / metrics.HBM_PEAK_GBS, 4),
                 "traffic": MEASURED_TRAFFIC_BYTES.get(layer.name)}
-    peak = metrics.MFMA_PEAK_TFLOPS[layer.dtype]
+    peak = round(metrics.FP32_PRODUCTS_PEAK_TFLOPS, 1) if layer.dtype == "f32" else metrics.MFMA_PEAK_TFLOPS[layer.dtype]
     a = 2.0 * metrics.useful_macs(layer) / (ms * 1e-3) / 1e12
     return {"bound": "mfma", "achieved": round(a, 2), "peak": peak, "unit": "TFLOP/s",
             "frac": round(a / peak, 4), "traffic": MEASURED_TRAFFIC_BYTES.get(layer.name)}
@@ -162,7 +162,8 @@ def roofline_for(layer, ms, metrics):
 
 def paper_roofline(layer, fwd_ms, din_ms, dw_ms, metrics):
     """Roofline fractions of a paper-shaped layer's three passes.  Many-channel layers are priced
-    against the fp32 matrix-core peak (each gradient does the forward's useful MACs once), the
+    against the rate at which the matrix cores can form fp32 products, a sixth of their bf16 peak
+    (each gradient does the forward's useful MACs once), the
     few-channel ones against HBM (the forward by its algorithmic bytes; the gradients read `g` and
     the other operand and write the gradient: the same byte count)."""
     macs = metrics.useful_macs(layer)
@@ -180,7 +181,7 @@ def paper_roofline(layer, fwd_ms, din_ms, dw_ms, metrics):
         out["forward_bound"] = "mfma"
     for name, ms in (("forward", fwd_ms), ("backward_input", din_ms), ("backward_weight", dw_ms)):
         if many:
-            out[name + "_frac"] = round(2.0 * macs / (ms * 1e-3) / 1e12 / metrics.MFMA_PEAK_TFLOPS["f32"], 4)
+            out[name + "_frac"] = round(2.0 * macs / (ms * 1e-3) / 1e12 / metrics.FP32_PRODUCTS_PEAK_TFLOPS, 4)
         elif alu:
             out[name + "_frac"] = round(2.0 * macs / (ms * 1e-3) / 1e12 / metrics.VALU_PEAK_TFLOPS, 4)
             out[name + "_hbm_frac"] = round(metrics.algorithmic_bytes(layer) / (ms * 1e-3) / 1e9 / metrics.HBM_PEAK_GBS, 4)
@@ -324,6 +325,8 @@ def main():
             return None
         if roof_l["bound"] == "hbm":
             return round(roof_l["achieved"] / yard["copy_GB_per_s"], 4)
+        if layer.dtype == "f32":                      # six bf16 products each
+            return round(roof_l["achieved"] * 6 / yard["mfma_TFLOP_per_s"]["bf16"], 4)
         return round(roof_l["achieved"] / yard["mfma_TFLOP_per_s"][layer.dtype], 4)
 
     # ---- per-layer table ---------------------------------------------------------------------

@@ -13,7 +13,7 @@
 // rows of g that the tile's positions touch are split once per chunk into LDS as [part][channel half][row][column
 // parity][column / 2][8 channels]: a tap's positions are two columns apart in g and neighbours there, and a lane's MFMA
 // operand is one 16-byte read.  Two stages, one barrier per chunk.  64 x 512 x 256 x 8 x 8, n = 4,
-// P = 2: 80 us where the fp32 multiplies took 162; with bfloat16 weights 64 x 256 x 128 x 16 x 16: 55 against 155.
+// P = 2: 85 us where the fp32 multiplies took 162; with bfloat16 weights 64 x 256 x 128 x 16 x 16: 55 against 155.
 #include "kst_split_common.h"
 
 namespace kst {

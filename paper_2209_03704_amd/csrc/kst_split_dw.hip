@@ -13,8 +13,8 @@
 // channels and two taps, a wave 64 x 64 of them: 8 blocks, the largest partial products' sums apart from the others',
 // 256 accumulator registers; 48 MFMAs per step for 18 loads, one step ahead.  What bounds it is the rate at which the
 // cache of a CU hands over those operands (18 KB per wave and 1536 cycles; each is wanted by two waves).
-// 64 x 512 x 256 x 8 x 8, n = 4, P = 2: 16 us for the two passes, 89 us here and 9 us for the sums, where framing g, the
-// fp32 multiplies and their sums took 202; with bfloat16 input 64 x 256 x 128 x 16 x 16: 22 + 58 + 9 against 212.
+// 64 x 512 x 256 x 8 x 8, n = 4, P = 2: 15 us for the two passes, 83 us here and 9 us for the sums, where framing g, the
+// fp32 multiplies and their sums took 202; with bfloat16 input 64 x 256 x 128 x 16 x 16: 21 + 57 + 9 against 212.
 #include "kst_split_common.h"
 
 namespace kst {

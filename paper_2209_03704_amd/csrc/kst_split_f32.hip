@@ -11,7 +11,8 @@
 // wave issues 24 MFMAs (768 cycles) and needs the weights of its own 32 output channels only: a first kernel splits
 // all weights once and lays them out as MFMA operands, so that a wave's next three operands are one contiguous 3 KB,
 // loaded straight into registers two to four taps ahead.  (Split in the main loop instead, 44 vector instructions
-// and eight 4-byte loads per tap: 548 us against 488 on 128 x 512 x 256 x 16 x 16, n = 4.)  Input values are
+// and eight 4-byte loads per tap: 548 us against 488 on 128 x 512 x 256 x 16 x 16, n = 4, when it was tried; 471 now,
+// MFMAs busy in 64 % of the main kernel's cycles.)  Input values are
 // wanted by every wave and every tap: the rows the tile's positions touch are split once per chunk and kept in LDS as
 // [part][channel half][row, column][8 channels], so that a lane's MFMA operand is one 16-byte read; two stages, one
 // barrier per chunk.  Taps are walked by window offset: the taps of both column parities that meet the same input

@@ -521,7 +521,7 @@ hipError_t din_launch_n(const float *g, const T *w, float *din, char *ws, const 
 
 bool split_din_applies(const Shape &s, bool odd, kst_dtype dt)
 {
-    if (s.Cin < 16 || s.Cout <= D_KC) return false;
+    if (s.n < 3 || s.n > 5 || s.Cin < 16 || s.Cout <= D_KC) return false;
     // Three launches and partial tiles cost 30 to 40 us.  The fp32 multiplies' tiles hold 128 input channels whatever the
     // layer has, so that is what is weighed.  Both sides timed on 1475 random layers from 2.2 to 12 G products: from
     // 2.2 G this is 1.5 to 1.6 times as fast (6 of 850 layers up to 4 G lost) except where the other side is its

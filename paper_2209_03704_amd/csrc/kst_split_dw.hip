@@ -399,6 +399,7 @@ hipError_t dw_launch_n(const T *in, const float *g, float *dw, char *ws, const D
 
 bool split_dw_applies(const Shape &s, bool odd, kst_dtype dt)
 {
+    if (s.n < 3 || s.n > 5) return false;
     const double edge = s.N - 2 * s.frame, nn = s.n * s.n;
     const double products = (double)s.B * edge * edge * nn * s.Cin * s.Cout;
     const double padded = (double)((s.B + 15) / 16 * 16) * edge * edge * nn * ((s.Cin + 127) / 128 * 128) *

@@ -525,12 +525,13 @@ bool split_din_applies(const Shape &s, bool odd, kst_dtype dt)
     // Three launches and partial tiles cost 30 to 40 us.  The fp32 multiplies' tiles hold 128 input channels whatever the
     // layer has, so that is what is weighed.  Both sides timed on 1475 random layers from 2.2 to 12 G products: from
     // 2.2 G this is 1.5 to 1.6 times as fast (6 of 850 layers up to 4 G lost) except where the other side is its
-    // pipelined kernel, on maps and channels of whole groups of four: of those 11 of 30 lost from 2.2 to 2.6 G
-    // (13 x 768 x 384 x 6 x 6, n = 4, P = 2: 68 us here against 57), 6 of 98 from 2.6 to 4 G.
+    // pipelined kernel, on maps and channels of whole groups of four, and the weights have three parts: of those 11 of
+    // 25 lost from 2.2 to 2.6 G (13 x 768 x 384 x 6 x 6, n = 4, P = 2: 68 us here against 57), 6 of 98 from 2.6 to 4 G.
+    // bfloat16's one part gained on them all.
     const double edge = s.N - 2 * s.frame;
     const double products = (double)s.B * edge * edge * s.n * s.n * ((s.Cin + 127) / 128 * 128) * s.Cout;
-    const bool pipelined = (s.M & 3) == 0 && (s.Cin & 3) == 0 && (s.Cout & 3) == 0;
-    return products >= (pipelined ? 2.6e9 : 2.2e9) && din_plan(s, odd, dt).ok;
+    const bool close = dt != KST_BF16 && (s.M & 3) == 0 && (s.Cin & 3) == 0 && (s.Cout & 3) == 0;
+    return products >= (close ? 2.6e9 : 2.2e9) && din_plan(s, odd, dt).ok;
 }
 
 // (0 for a layer these kernels do not take with weights of this type)

@@ -156,6 +156,15 @@ def test_input_gradient_route(shape, split):
     assert (kst.kst_backward_input_workspace_bytes(*shape, F32) == split_din_query(*shape, F32)) == split
 
 
+def test_input_gradient_route_of_one_part():
+    """bfloat16 weights from 2.2 G whatever the other kernel is (both queries are half precision's where that one also
+    runs split, the launch's own where it does not)."""
+    B, Cin, Cout, N, n, P = shape = (13, 768, 384, 6, 4, 2)
+    assert kst.kst_backward_input_workspace_bytes(*shape, BF16) == (
+        split_din_weight_bytes(Cin, Cout, n, 1) + split_din_slot_bytes(B, Cin, Cout, N, n))
+    assert kst.kst_backward_input_workspace_bytes(*shape, F16) != split_din_query(*shape, F16)
+
+
 @pytest.mark.parametrize("shape,dtype,split", [
     ((68, 128, 128, 24, 3, 3), F32, False),    # 9 products per value of g and input channel, one tile of those
     ((68, 128, 128, 24, 3, 3), BF16, True),    # (bfloat16 input: half the multiplies)

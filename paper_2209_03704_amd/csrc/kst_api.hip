@@ -41,6 +41,10 @@ kst_path choose_path(const Shape &s, kst_dtype dt)
 {
     const bool ok = is16(dt) ? igemm_bf16_supported(s) : igemm_f32_supported(s);
     if (ok && s.Cout >= 16 && s.Cin >= 8) return KST_PATH_IGEMM;
+    // Few output channels in 16 bits: the matrix cores multiply 32 rows for three real ones in less time than the direct
+    // kernel walks its channel chunks one after the other, but the repacking launch comes before.  Either side timed on 170
+    // such layers: from 600 products per output pixel the direct kernel is 1.2 to 8 times slower, below 500 up to 1.3 faster.
+    if (is16(dt) && s.Cout < 16 && s.Cin * s.n * s.n >= 600 && igemm_16_packed_applies(s)) return KST_PATH_IGEMM;
     // One sample of a generator's output layer (many input channels, three output channels): the
     // position-block kernel splits its reduction over the chip, the direct kernel has four tiles.
     if (dt == KST_F32 && s.Cout < 16 && igemm_f32_small_supported(s)) return KST_PATH_IGEMM;
@@ -78,11 +82,11 @@ bool on_matrix_cores(kst_path path)
 }
 
 // The problem as a caller's path sees it: IGEMM and its launch form EVEN, asked for by name, multiply fp32 operands in
-// fp32.  Only AUTO may split them for the bf16 matrix cores.
+// fp32.  Only AUTO may split them for the bf16 matrix cores, or repack 16-bit ones.
 Shape shape_for(int B, int Cin, int Cout, int N, int n, int path)
 {
     Shape s = make_shape(B, Cin, Cout, N, n);
-    s.no_split = path != KST_PATH_AUTO;
+    s.lean = path != KST_PATH_AUTO;
     return s;
 }
 
@@ -92,16 +96,16 @@ size_t workspace_for(const Shape &s, kst_dtype dt, kst_path path)
     return is16(dt) ? igemm_bf16_workspace_bytes(s) : igemm_f32_workspace_bytes(s, path == KST_PATH_IGEMM_EVEN);
 }
 
-// The path's kernels for a caller with `have` bytes of scratch, and what they need of it: where the kernels that split
-// fp32 operands need more than there is, those that multiply in fp32 (*s then says so).  Not checked: *need <= have.
+// The path's kernels for a caller with `have` bytes of scratch, and what they need of it: where the kernels that lay
+// operands out anew need more than there is, those that do not (*s then says so).  Not checked: *need <= have.
 kst_status plan_within(Shape *s, kst_dtype dtype, int path, size_t have, kst_path *chosen, size_t *need)
 {
     for (;;) {
         const kst_status st = resolve_path(*s, dtype, path, chosen);
         if (st != KST_OK) return st;
         *need = workspace_for(*s, dtype, *chosen);
-        if (*need <= have || s->no_split) return KST_OK;
-        s->no_split = 1;
+        if (*need <= have || s->lean) return KST_OK;
+        s->lean = 1;
     }
 }
 
@@ -335,7 +339,7 @@ kst_status kst_forward(const void *in, const void *w, void *out, int B, int Cin,
     const size_t seg_bytes = (seg_elems(Cin, Cout, n, dtype) * elt_bytes(dtype) + 255) & ~(size_t)255;
     size_t ws_bytes = workspace_for(s, dtype, choose_path(s, dtype));
     const auto least = [&] {
-        s.no_split = 1;
+        s.lean = 1;
         return workspace_for(s, dtype, choose_path(s, dtype));
     };
     void *scratch = nullptr;
@@ -358,7 +362,7 @@ struct Framed {
     size_t in_bytes, wide_bytes;      // workspace parts before the inner kernels' own scratch (256-byte multiples)
 };
 
-kst_status framed_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dt, int path, bool no_split, Framed *f)
+kst_status framed_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dt, int path, bool lean, Framed *f)
 {
     if (P < 0 || P > 32768 || B < 1 || N < 1 || N > 32768) return KST_ERR_SHAPE;
     f->q = (P + 1) / 2;
@@ -369,7 +373,7 @@ kst_status framed_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype 
     f->Mq = 2 * f->Nq - n;
     if (f->M < 1) return KST_ERR_SHAPE;
     f->s = shape_for(B, Cin, Cout, f->Nq, n, path);
-    if (no_split) f->s.no_split = 1;
+    if (lean) f->s.lean = 1;
     // The pipelined fp32 matrix-core kernel supplies the frame itself while it stages its input
     // rows (tensor rows of whole 16-byte groups): no framed copy.
     Shape in_place = f->s;
@@ -396,6 +400,8 @@ kst_status framed_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype 
             if (igemm_f32_takes_row_stride(wide)) f->s = wide;
         }
     }
+    // The repacked input of a 16-bit layer has the frame in it, and its kernel stores an odd factor's interior directly.
+    if (is16(dt) && f->chosen == KST_PATH_IGEMM && igemm_16_packed_applies(in_place)) f->s.frame = f->q;
     f->in_bytes = f->s.frame > 0 ? 0 : ((size_t)B * Cin * f->Nq * f->s.Ns * elt_bytes(dt) + 255) & ~(size_t)255;
     f->wide_bytes = (P & 1) ? (((size_t)B * Cout * f->Mq * f->Mq * sizeof(float) + 255) & ~(size_t)255) : 0;
     // The direct kernels supply the zero frame themselves: no framed copy at all; and for an odd
@@ -406,8 +412,8 @@ kst_status framed_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype 
     // 16-bit one) store the interior of the wider map directly as well; those that leave through
     // an LDS image of whole rows keep the wider buffer and the copy.
     if ((P & 1) && on_matrix_cores(f->chosen) && f->chosen != KST_PATH_IGEMM_PASSES &&
-        (!is16(dt) || !(igemm_bf16_wide_supported(f->s) || igemm_bf16_ring_supported(f->s) ||
-                        igemm_bf16_strip_supported(f->s)))) {
+        (!is16(dt) || f->s.frame > 0 ||
+         !(igemm_bf16_wide_supported(f->s) || igemm_bf16_ring_supported(f->s) || igemm_bf16_strip_supported(f->s)))) {
         f->s.crop = 1;
         f->wide_bytes = 0;
     }

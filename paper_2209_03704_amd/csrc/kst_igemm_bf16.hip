@@ -138,13 +138,14 @@ static size_t lds_bytes(const IgemmParams &p, int n)
 
 bool igemm_bf16_supported(const Shape &s)
 {
-    if (igemm_bf16_ring_supported(s) || igemm_bf16_strip_supported(s)) return true;
+    if (igemm_bf16_ring_supported(s) || igemm_bf16_strip_supported(s) || igemm_16_packed_applies(s)) return true;
     if (s.n > 7) return false;
     return lds_bytes(plan(s), s.n) <= 160 * 1024;
 }
 
 size_t igemm_bf16_workspace_bytes(const Shape &s)
 {
+    if (igemm_16_packed_applies(s)) return igemm_16_packed_workspace_bytes(s);
     if (igemm_bf16_ring_supported(s) || igemm_bf16_strip_supported(s)) return 0;
     const IgemmParams p = plan(s);
     return p.splits > 1 ? (size_t)p.splits * p.out_elems * sizeof(float) : 0;
@@ -195,6 +196,7 @@ hipError_t launch_igemm_bf16(const void *in_v, const void *w_seg_v, float *out, 
 {
     if (igemm_bf16_wide_supported(s)) return launch_igemm_bf16_wide(in_v, w_seg_v, out, s, f16, stream);
     if (igemm_bf16_ring_supported(s)) return launch_igemm_bf16_ring(in_v, w_seg_v, out, s, f16, stream);
+    if (igemm_16_packed_applies(s)) return launch_igemm_16_packed(in_v, w_seg_v, out, ws, s, f16, stream);
     if (igemm_bf16_strip_supported(s)) return launch_igemm_bf16_strip(in_v, w_seg_v, out, s, f16, stream);
     return f16 ? launch_plain<true>(in_v, w_seg_v, out, ws, s, stream) : launch_plain<false>(in_v, w_seg_v, out, ws, s, stream);
 }

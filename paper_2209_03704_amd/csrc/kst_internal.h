@@ -100,8 +100,8 @@ struct Shape {
     int crop;  // 1: only the interior of the M x M map is wanted -- `out` is the dense [B][Cout][M - 2][M - 2] tensor
                // whose element (y, x) is element (y + 1, x + 1) of the map (an odd padding factor; only kernels for
                // which *_takes_virtual_frame says so)
-    int no_split;  // 1: the kernels that split fp32 operands for the bf16 matrix cores are not to be chosen (their
-                   // partial tiles need more scratch than the caller has)
+    int lean;  // 1: the kernels that lay operands out anew in scratch (fp32 ones split for the bf16 matrix cores, a 16-bit
+               // input repacked) are not to be chosen: the caller has less scratch than they need, or names the path
     Epilogue epi;  // applied where the final value of an element is stored (every forward kernel but the
                    // row-parity-passes one, which must be given an inactive one)
 };
@@ -188,6 +188,12 @@ hipError_t launch_igemm_bf16_wide(const void *in, const void *w_seg, float *out,
 bool igemm_bf16_pp_supported(const Shape &s);      // row-parity passes: 3 x 3 kernels, 64 x 64 maps, 256 input channels
 hipError_t launch_igemm_bf16_pp(const void *in, const void *w_seg, float *out, const Shape &s, bool f16,
                                 hipStream_t stream);
+// 16-bit layers with 3 x 3 to 5 x 5 kernels that neither the wide nor the ring kernel takes: input repacked once
+// (takes Shape::frame and Shape::crop).
+bool igemm_16_packed_applies(const Shape &s);
+size_t igemm_16_packed_workspace_bytes(const Shape &s);
+hipError_t launch_igemm_16_packed(const void *in, const void *w_seg, float *out, void *ws, const Shape &s, bool f16,
+                                  hipStream_t stream);
 // Layers with at most 64 quad positions in all (one sample of a small map): position blocks of 16.
 // Kernel gradient of layers with at most four input channels on large maps (rows of `in` and `g` staged through LDS,
 // one partial result per workgroup): whether it applies, how many partial results it writes, the launch.

@@ -670,7 +670,7 @@ hipError_t launch_n(const float *in, const float *w_seg, float *out, char *ws, c
 
 bool split_f32_applies(const Shape &s)
 {
-    if (s.no_split || s.n < 3 || s.n > 5 || s.Cout < 16 || s.Cin <= S_KC) return false;   // (a plan's integers hold such kernels)
+    if (s.lean || s.n < 3 || s.n > 5 || s.Cout < 16 || s.Cin <= S_KC) return false;   // (a plan's integers hold such kernels)
     const double products = (double)s.B * s.E * s.E * s.n * s.n * s.Cin * s.Cout;
     if (products < 1.5e9) return false;
     // Both sides timed on 1650 random layers of 1.5 to 12 G products (n = 3 .. 5, maps of 4 to 64, 17 to 1024 channels).

@@ -40,13 +40,19 @@ struct SmallParams {
     Epilogue epi;
 };
 
-// V4: Cout is a multiple of 4 and the weights are read as 16-byte groups; otherwise (the 128 -> 3
-// output layer of a generator) one value at a time, rows past Cout reading the last channel again.
+// LOADS: WHOLE -- Cin and Cout are multiples of 4, the weights are read as aligned 16-byte groups; RAGGED -- the same
+// groups at any 4-byte alignment, the last one moved back to end with channel Cout - 1, and a last chunk of fewer than four
+// input channels; SINGLE -- Cout < 4 (the 128 -> 3 output layer of a generator), one value at a time, rows past Cout reading
+// the last channel again.  (Ragged counts one value at a time, on the tile kernel for ragged shapes or here: 100 loads per
+// chunk with a 5 x 5 kernel instead of 25.)
 // WV: waves per workgroup.  With four, each takes a quarter of the workgroup's chunks and their sums are
 // added through LDS in wave order before anything is stored: a quarter of the partial outputs for
 // the same number of waves pulling weights (one sample of a 1024 -> 512 layer writes 16.7 MB of
 // partial outputs beside its 33.5 MB of weights with one wave per workgroup).
-template <int n, bool V4, int WV>
+enum SmallLoads { WHOLE, RAGGED, SINGLE };
+typedef float floatx4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int n, int LOADS, int WV>
 __global__ void __launch_bounds__(64 * WV) igemm_f32_small_kernel(const float *__restrict__ in, const float *__restrict__ w_seg,
                                                                float *__restrict__ dst, SmallParams p)
 {
@@ -84,10 +90,10 @@ __global__ void __launch_bounds__(64 * WV) igemm_f32_small_kernel(const float *_
     const unsigned x_step = (unsigned)SM_KC * p.N0 * p.N0;
 
     // A operands: lane (m, k) loads the weights of output channels co0 + 4 m .. + 3, input channel
-    // ci0 + k, as one 16-byte group; value j is its row (m) of row block j.  Groups past Cout (the
-    // last block of a ragged layer; Cout is a multiple of 4) read the last group again: their
-    // accumulator rows are never stored.
-    const unsigned w_col = V4 ? (unsigned)min(co0 + 4 * m, p.Cout - 4) : 0u;
+    // ci0 + k, as one 16-byte group; value j is its row (m) of row block j.  Groups that would end past
+    // Cout (the last block of a ragged layer) are the last four channels instead: rows for channels that
+    // another row has too.
+    const unsigned w_col = LOADS != SINGLE ? (unsigned)min(co0 + 4 * m, p.Cout - 4) : 0u;
     unsigned w_cols[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) w_cols[j] = (unsigned)min(co0 + 4 * m + j, p.Cout - 1);
@@ -108,13 +114,16 @@ __global__ void __launch_bounds__(64 * WV) igemm_f32_small_kernel(const float *_
     float4 wf[2][NN];
     auto fetch = [&](auto bufc, int chunk) {
         constexpr int buf = decltype(bufc)::value;
-        const unsigned ci = (unsigned)(chunk * SM_KC + k);
+        // Channels past the last (RAGGED, SINGLE: in the last chunk): zeros on both sides.
+        const bool live = LOADS == WHOLE || chunk * SM_KC + k < p.Cin;
+        const unsigned ci = live ? (unsigned)(chunk * SM_KC + k) : 0u;
 #pragma unroll
         for (int dy = 0; dy <= fl; ++dy)
 #pragma unroll
             for (int dx = 0; dx <= fl; ++dx) {
-                const float v = in[x_off[dy][dx] + (unsigned)chunk * x_step];   // (frame cells read element 0 of the channel block: valid, unused)
-                xf[buf][dy][dx] = x_ok[dy][dx] ? v : 0.0f;
+                // (frame cells read element 0 of the channel block: valid, unused)
+                const float v = in[live ? x_off[dy][dx] + (unsigned)chunk * x_step : 0u];
+                xf[buf][dy][dx] = x_ok[dy][dx] && live ? v : 0.0f;
             }
 #pragma unroll
         for (int T = 0; T < NN; ++T) {
@@ -124,11 +133,16 @@ __global__ void __launch_bounds__(64 * WV) igemm_f32_small_kernel(const float *_
             const unsigned Tp = (unsigned)class_taps(n, cls);
             const unsigned t = (unsigned)(T - class_tap_base(n, cls));
             const unsigned row = p.off[cls] + (ci * Tp + t) * (unsigned)p.Cout;
-            if constexpr (V4)
+            if constexpr (LOADS == WHOLE) {
                 wf[buf][T] = *reinterpret_cast<const float4 *>(w_seg + row + w_col);     // 16-byte aligned: offsets are multiples of 4
-            else
-                wf[buf][T] = make_float4(w_seg[row + w_cols[0]], w_seg[row + w_cols[1]], w_seg[row + w_cols[2]],
-                                         w_seg[row + w_cols[3]]);
+            } else if constexpr (LOADS == RAGGED) {
+                const floatx4_any v = *reinterpret_cast<const floatx4_any *>(w_seg + row + w_col);
+                wf[buf][T] = make_float4(live ? v.x : 0.f, live ? v.y : 0.f, live ? v.z : 0.f, live ? v.w : 0.f);
+            } else {
+                const float a = w_seg[row + w_cols[0]], b = w_seg[row + w_cols[1]], c = w_seg[row + w_cols[2]],
+                            d = w_seg[row + w_cols[3]];
+                wf[buf][T] = make_float4(live ? a : 0.f, live ? b : 0.f, live ? c : 0.f, live ? d : 0.f);
+            }
         }
     };
     auto multiply = [&](auto bufc) {
@@ -197,7 +211,11 @@ __global__ void __launch_bounds__(64 * WV) igemm_f32_small_kernel(const float *_
         for (int blk = 0; blk < 4; ++blk)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int col = 4 * (4 * k + v) + blk;           // channel of the workgroup's 64
+                int col = 4 * (4 * k + v) + blk;                 // channel of the workgroup's 64
+                if constexpr (LOADS == RAGGED) {                 // (a channel that two rows have: the same value twice)
+                    col = min(co0 + 4 * (4 * k + v), p.Cout - 4) + blk - co0;
+                    if (col < 0) continue;
+                }
                 *reinterpret_cast<float4 *>(&img[(col * SM_POS + m) * 4]) =
                     make_float4(acc[0][blk][v], acc[1][blk][v], acc[2][blk][v], acc[3][blk][v]);
             }
@@ -226,7 +244,10 @@ __global__ void __launch_bounds__(64 * WV) igemm_f32_small_kernel(const float *_
 bool small_plan(const Shape &s, SmallParams &p)
 {
     if (s.n < 1 || s.n > 5 || s.Ns != s.N) return false;
-    if (s.Cin % SM_KC != 0 || s.Cin < 64) return false;
+    // (Ragged or fewer input channels, not by name: the tile kernel for ragged shapes or, for few output channels, the direct
+    // kernel is the other side.  16 output channels and more, 80 layers timed: 1.4 to 3.4 times as fast here, none slower.)
+    const bool whole = s.Cin % SM_KC == 0 && s.Cin >= 64;
+    if (!whole && (s.lean || s.Cin < 16)) return false;
     const long long Mtot = (long long)s.B * s.E * s.E;
     // Every block of 16 positions streams the layer's weights once (through L2): worth it while the
     // positions are few, or the weights small.  Beyond that the tiles of 128 positions x 128 (or 64)
@@ -238,8 +259,11 @@ bool small_plan(const Shape &s, SmallParams &p)
     const double budget = 128.0e6;
     if (Mtot > (1 << 20) || (Mtot > 256 && (double)((Mtot + 15) / 16) * w_bytes > budget)) return false;
     // Fewer than 16 output channels leave most of a 64-row block empty: only where the padded
-    // multiply-adds are still next to nothing for the chip (about 5 us of matrix-core work).
-    if (s.Cout < 16 && (double)((Mtot + 15) / 16) * 16.0 * 64.0 * s.Cin * s.n * s.n > 4.0e8) return false;
+    // multiply-adds are still next to nothing for the chip (about 5 us of matrix-core work).  Ragged counts: the other side
+    // is the direct kernel, whose time goes with the products of one output (80 such layers timed: slower than it below 900,
+    // 1.1 to 10 times as fast from 1000 on up to 0.2 G padded products).
+    const double padded = (double)((Mtot + 15) / 16) * 16.0 * 64.0 * s.Cin * s.n * s.n;
+    if (s.Cout < 16 && (padded > (whole ? 4.0e8 : 2.0e8) || (!whole && s.Cin * s.n * s.n < 1000))) return false;
     p.B = s.B; p.Cin = s.Cin; p.Cout = s.Cout;
     p.q = s.frame;
     p.N0 = s.N - 2 * s.frame;
@@ -250,7 +274,7 @@ bool small_plan(const Shape &s, SmallParams &p)
     if (p.M < 1) return false;
     p.pos_blocks = (p.Mtot + SM_POS - 1) / SM_POS;
     p.co_blocks = (s.Cout + SM_TCO - 1) / SM_TCO;
-    p.chunks = s.Cin / SM_KC;
+    p.chunks = (s.Cin + SM_KC - 1) / SM_KC;
     // About two waves per SIMD over the chip, but at least four chunks per workgroup (so that the
     // partial outputs stay well below the weights in bytes); with a long reduction (64 chunks and
     // more) four waves per workgroup, two chunks each at least -- except where a single position
@@ -276,18 +300,17 @@ template <int n>
 hipError_t launch_small_n(const float *in, const float *w_seg, float *dst, const SmallParams &p, hipStream_t stream)
 {
     const unsigned blocks = (unsigned)(p.pos_blocks * p.co_blocks * p.splits);
-    const bool v4 = (p.Cout & 3) == 0;
-    if (p.waves == 4) {
-        if (v4)
-            hipLaunchKernelGGL((igemm_f32_small_kernel<n, true, 4>), dim3(blocks), dim3(256), 0, stream, in, w_seg, dst, p);
+    const int loads = p.Cout < 4 ? SINGLE : ((p.Cout | p.Cin) & 3) == 0 ? WHOLE : RAGGED;
+    auto launch = [&](auto loadsc) {
+        constexpr int L = decltype(loadsc)::value;
+        if (p.waves == 4)
+            hipLaunchKernelGGL((igemm_f32_small_kernel<n, L, 4>), dim3(blocks), dim3(256), 0, stream, in, w_seg, dst, p);
         else
-            hipLaunchKernelGGL((igemm_f32_small_kernel<n, false, 4>), dim3(blocks), dim3(256), 0, stream, in, w_seg, dst, p);
-    } else {
-        if (v4)
-            hipLaunchKernelGGL((igemm_f32_small_kernel<n, true, 1>), dim3(blocks), dim3(64), 0, stream, in, w_seg, dst, p);
-        else
-            hipLaunchKernelGGL((igemm_f32_small_kernel<n, false, 1>), dim3(blocks), dim3(64), 0, stream, in, w_seg, dst, p);
-    }
+            hipLaunchKernelGGL((igemm_f32_small_kernel<n, L, 1>), dim3(blocks), dim3(64), 0, stream, in, w_seg, dst, p);
+    };
+    if (loads == WHOLE) launch(std::integral_constant<int, WHOLE>{});
+    else if (loads == RAGGED) launch(std::integral_constant<int, RAGGED>{});
+    else launch(std::integral_constant<int, SINGLE>{});
     return hipGetLastError();
 }
 

@@ -569,15 +569,18 @@ struct GradPlan {
     bool din_cores, dw_cores;         // the gradient runs on the matrix cores (fp32 kernels; 16-bit operands are
                                       // widened to fp32 first, which is exact)
     size_t wconv_bytes, xconv_bytes;  // fp32 copies of w (input gradient) and of in (kernel gradient) for that
+    Shape image;                      // the problem as the image layers' kernels see it
+    bool din_image, dw_image;
     // The same on the bf16 matrix cores, with workspaces of their own; only where the caller's is large enough.
     kst_dtype din_split;              // operand type of w they run with (half precision is widened to fp32 first)
     bool use_din_split, use_dw_split;
     size_t din_split_wconv;           // widened half-precision weights
     size_t din_split_bytes, dw_split_bytes;    // whole workspace, as the launch lays it out
     size_t din_split_query, dw_split_query;    // ... as kst_backward_*_workspace_bytes give it
-    size_t din_bytes_needed() const { return g_bytes + din_bytes + split_bytes + wconv_bytes; }
+    size_t din_bytes_needed() const { return din_image ? 0 : g_bytes + din_bytes + split_bytes + wconv_bytes; }
     size_t dw_bytes_needed() const
     {
+        if (dw_image) return wsplit_bytes;
         return dw_cores ? gw_bytes + wsplit_bytes + xconv_bytes : in_bytes + g_bytes + wsplit_bytes;
     }
 };
@@ -635,7 +638,12 @@ kst_status grad_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dt
         // (the query: the larger of the 16-bit types', with the widened copy of `in` that the fp32 multiplies read)
         f->dw_split_query = split_dw_workspace_bytes(f->si, (P & 1) != 0, KST_F32) + f->xconv_bytes;
     }
-    f->wsplit_bytes = f->dw_cores
+    f->image = f->si;
+    f->image.crop = P & 1;
+    f->din_image = !f->din_cores && backward_input_image_apply(f->image);
+    f->dw_image = !f->dw_cores && backward_weight_image_apply(f->image);
+    f->wsplit_bytes = f->dw_image ? backward_weight_image_workspace_bytes(f->image)
+                      : f->dw_cores
                           ? backward_weight_igemm_workspace_bytes(f->si)
                           : backward_weight_generic_workspace_bytes(f->plain_unframed ? f->si : f->s);
     f->gw_bytes = 0;
@@ -693,6 +701,9 @@ kst_status kst_backward_input(const void *g, const void *w, void *din, void *ws,
                    ? KST_OK
                    : KST_ERR_HIP;
     }
+    if (f.din_image)
+        return launch_backward_input_image((const float *)g, w, (float *)din, f.image, dtype, stream) == hipSuccess ? KST_OK
+                                                                                                                  : KST_ERR_HIP;
     const float *g_in = (const float *)g;
     float *d_out = (float *)din;
     if (f.g_bytes) {          // odd P: the forward dropped the outermost ring of the wider output
@@ -743,6 +754,10 @@ kst_status kst_backward_weight(const void *in, const void *g, void *dw, void *ws
         if (!ws || ws_bytes < need) return KST_ERR_WORKSPACE;
         if (!aligned16(ws)) return KST_ERR_ALIGN;
     }
+    if (f.dw_image)
+        return launch_backward_weight_image(in, (const float *)g, (float *)dw, ws, f.image, dtype, stream) == hipSuccess
+                   ? KST_OK
+                   : KST_ERR_HIP;
     const void *x_in = in;
     const float *g_in = (const float *)g;
     if (P && !cores && !f.plain_unframed) {

@@ -149,17 +149,10 @@ __global__ void __launch_bounds__(256) backward_weight_regs_kernel(const T *__re
     }
 
     const int lane = tid & 63, wave = tid >> 6;
+    float sums[S];
 #pragma unroll
-    for (int q = 0; q < CI; ++q)
-#pragma unroll
-        for (int k = 0; k < CO; ++k)
-#pragma unroll
-            for (int t = 0; t < NN; ++t) {
-                float v = acc[q][k][t];
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-                if (lane == 0) red[wave][(q * CO + k) * NN + t] = v;
-            }
+    for (int i = 0; i < S; ++i) sums[i] = acc[i / (CO * NN)][i / NN % CO][i % NN];
+    wave_sums<S>(sums, lane, red[wave]);
     __syncthreads();
     for (int i = tid; i < S; i += 256) {
         const int q = i / (CO * NN), r = i - q * (CO * NN);
@@ -494,7 +487,6 @@ int weight_lane_slices(const Shape &s)
 // workgroups, at least 1024 positions per slice.
 int weight_slices(const Shape &s)
 {
-    if (backward_weight_image_apply(s)) return backward_weight_image_slices(s);
     if (weight_lanes_apply(s)) return weight_lane_slices(s);
     long long wgs = (long long)s.Cout * s.Cin;                     // workgroups per slice
     if (s.n <= 7) {
@@ -520,7 +512,6 @@ bool backward_generic_takes_frame(const Shape &s)
 hipError_t launch_backward_input_generic(const float *g, const void *w, float *din, const Shape &s, kst_dtype dt,
                                          hipStream_t stream)
 {
-    if (backward_input_image_apply(s)) return launch_backward_input_image(g, w, din, s, dt, stream);
     if (dt == KST_BF16   ? launch_input_regs<uint16_t>(g, (const uint16_t *)w, din, s, stream)
         : dt == KST_F16 ? launch_input_regs<half_bits>(g, (const half_bits *)w, din, s, stream)
                         : launch_input_regs<float>(g, (const float *)w, din, s, stream))
@@ -555,11 +546,6 @@ hipError_t launch_backward_weight_generic(const void *in, const float *g, float 
     const unsigned blocks = (unsigned)s.Cout * (unsigned)s.Cin * (unsigned)slices;
     float *dst = slices > 1 ? (float *)ws : dw;
     bool regs = false;
-    if (backward_weight_image_apply(s)) {
-        hipError_t e = launch_backward_weight_image(in, g, dst, s, dt, stream);
-        if (e != hipSuccess || slices == 1) return e;
-        return launch_splitk_reduce((const float *)ws, dw, (size_t)s.Cout * s.Cin * s.n * s.n, slices, stream);
-    }
     if (weight_lanes_apply(s)) {
         if (dt == KST_BF16) launch_weight_lanes<uint16_t>((const uint16_t *)in, g, dst, s, slices, per_slice, stream);
         else if (dt == KST_F16) launch_weight_lanes<half_bits>((const half_bits *)in, g, dst, s, slices, per_slice, stream);

@@ -16,10 +16,12 @@
 // channel in registers, reads an input value once for n * n products and a g value once for Cin;
 // at the end the sums are added across the lanes by wave shuffles, across the waves through LDS,
 // and every workgroup writes one partial result that the summing pass adds in a fixed order.
-// Where a strip's loads fit a lane's registers (maps up to 512 wide) the next strip is fetched
+// (the wave's sums handed on by halves, wave_sums: on small layers the shuffles of one sum after the other were two
+// thirds of the time; 3 x 3 x 116 x 116 -> 1, n = 5, P = 1, whole call: 42 -> 14 us, 246 x 3 x 157 x 157, n = 3, where
+// rows are no whole groups of four: 81 -> 47).  Where a strip's loads fit a lane's registers (maps up to 512 wide) the next strip is fetched
 // while this one is multiplied; wider maps stage strip after strip.  The input gradient of
 // such layers with one output channel (second kernel below) runs on the same strips of g.
-#include "kst_internal.h"
+#include "kst_igemm_common.h"
 
 namespace kst {
 
@@ -37,6 +39,7 @@ struct ImageGradParams {
     int padc;               // max(0, n - 1 - P)
     int step_i, step_j;     // a lane's step through the positions: threads = step_i * N0 + step_j
     int pre;                // 1: a strip's loads fit a lane's registers (the prefetching variant)
+    int quads;              // 1: strips of fp32 input start at whole 16-byte groups (rows of whole groups)
 };
 
 // Geometry of a strip.
@@ -119,7 +122,7 @@ __device__ __forceinline__ void strip_fetch(const ImageGradParams &p, const T *_
 #pragma unroll
     for (int c = 0; c < CI; ++c) {
         const T *src = in + ((size_t)st.b * p.Cin + c) * ((size_t)p.N0 * p.N0) + (size_t)st.i_lo * p.N0;
-        if constexpr (sizeof(T) == 4) {
+        if (sizeof(T) == 4 && p.quads) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int e4 = tid + h * BI_THREADS;
@@ -146,7 +149,7 @@ __device__ __forceinline__ void strip_land(const ImageGradParams &p, float *gs, 
 #pragma unroll
     for (int c = 0; c < CI; ++c) {
         float *d = xs + c * p.RB * p.N0;
-        if constexpr (sizeof(T) == 4) {
+        if (sizeof(T) == 4 && p.quads) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int e4 = tid + h * BI_THREADS;
@@ -237,8 +240,7 @@ __global__ void __launch_bounds__(BI_THREADS) backward_weight_image_kernel(const
             for (int c = 0; c < CI; ++c) {
                 const T *src = in + ((size_t)b * p.Cin + c) * in_plane + (size_t)i_lo * p.N0;
                 float *d = xs + c * p.RB * p.N0;
-                if constexpr (sizeof(T) == 4) {
-                    // (N0 is a multiple of 4 for this kernel: 16-byte groups)
+                if (sizeof(T) == 4 && p.quads) {
                     for (int e4 = tid; e4 < (cnt >> 2); e4 += 2 * BI_THREADS) {
                         const int e4b = e4 + BI_THREADS;
                         const float4 a = reinterpret_cast<const float4 *>(src)[e4];
@@ -276,15 +278,10 @@ __global__ void __launch_bounds__(BI_THREADS) backward_weight_image_kernel(const
     }
 
     // ---- the workgroup's sums -----------------------------------------------------------------
+    float sums[S];
 #pragma unroll
-    for (int c = 0; c < CI; ++c)
-#pragma unroll
-        for (int t = 0; t < NN; ++t) {
-            float v = acc[c][t];
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-            if (lane == 0) red[wave][c * NN + t] = v;
-        }
+    for (int i = 0; i < S; ++i) sums[i] = acc[i / NN][i % NN];
+    wave_sums<S>(sums, lane, red[wave]);
     __syncthreads();
     for (int i = tid; i < S; i += BI_THREADS) {
         const int c = i / NN, t = i - c * NN;
@@ -366,20 +363,24 @@ bool image_plan(const Shape &s, ImageGradParams &p, size_t &lds)
 {
     const int N0 = s.N - 2 * s.frame;
     if (s.n < 1 || s.n > 7 || s.Cin > 4 || s.Cin * s.n * s.n > 100 || s.Cout > 8) return false;
-    if (N0 < 64 || (N0 & 3) != 0) return false;
-    if ((long long)s.B * N0 * N0 < (1 << 18)) return false;     // small layers stay with the register kernel
-    p.B = s.B; p.Cin = s.Cin; p.Cout = s.Cout; p.N0 = N0; p.M = s.M; p.n = s.n;
-    p.P = 2 * s.frame;
+    if (N0 < 32) return false;
+    p.B = s.B; p.Cin = s.Cin; p.Cout = s.Cout; p.N0 = N0; p.n = s.n;
+    p.M = s.M - 2 * s.crop;                                     // (an odd padding factor's g as it lies in memory)
+    p.P = 2 * s.frame - s.crop;
+    if (p.P < 0 || p.M < 1) return false;
+    p.quads = (N0 & 3) == 0;
     p.padc = s.n - 1 - p.P > 0 ? s.n - 1 - p.P : 0;
     p.GS = (p.M + 2 * p.padc + 1) & ~1;
     p.RB = 0;
-    // (Shorter strips for small batches, so that every workgroup has a second strip to fetch while it
-    // multiplies, were measured and change nothing: 16 images 21 and 35 us either way.)
+    // Shorter strips where those of eight rows leave CUs idle.
     for (int rb = 8; rb >= 2; rb >>= 1) {
         lds = ((((size_t)(2 * rb + s.n - 1) * p.GS + 3) & ~(size_t)3) + (size_t)s.Cin * rb * N0) * sizeof(float);
-        if (lds <= 78 * 1024) { p.RB = rb; break; }             // two workgroups per CU
+        if (lds > 78 * 1024) continue;                          // two workgroups per CU
+        p.RB = rb;
+        if ((long long)s.B * ((N0 + rb - 1) / rb) * s.Cout >= 256) break;
     }
     if (p.RB == 0) return false;
+    lds = ((((size_t)(2 * p.RB + s.n - 1) * p.GS + 3) & ~(size_t)3) + (size_t)s.Cin * p.RB * N0) * sizeof(float);
     p.strips_per_item = (N0 + p.RB - 1) / p.RB;
     const long long strips = (long long)s.B * p.strips_per_item;
     p.wgs = (int)(strips < 512 / s.Cout ? strips : 512 / s.Cout);
@@ -485,11 +486,23 @@ hipError_t launch_din_t(const float *g, const T *w, float *din, const ImageGradP
     }
 }
 
-// The input gradient's kernel: one output channel, and a map whose rows of g fit a lane's registers.
+hipError_t launch_partial(const void *in, const float *g, float *dst, const ImageGradParams &p, size_t lds, kst_dtype dt,
+                          hipStream_t stream)
+{
+    if (dt == KST_BF16) return launch_t<uint16_t>((const uint16_t *)in, g, dst, p, lds, stream);
+    if (dt == KST_F16) return launch_t<half_bits>((const half_bits *)in, g, dst, p, lds, stream);
+    return launch_t<float>((const float *)in, g, dst, p, lds, stream);
+}
+
+// The input gradient's kernel: one output channel, a map whose rows of g fit a lane's registers, and what the register
+// kernel loses on: odd padding factors, where that one needs a framed copy of g (138 x 3 x 223 x 223, n = 3: 105 -> 44 us),
+// and 2^18 positions with rows of whole groups of four or 5 x 5 kernels (213 x 3 x 110 x 110: 36 -> 27).  Smaller layers take
+// 4 us there; other rows with n = 3 and 4 are 10 % faster there (39 x 3 x 199 x 199, n = 3: 12.7 against 14.5).
 bool din_plan(const Shape &s, ImageGradParams &p)
 {
     size_t lds;
-    return s.Cout == 1 && image_plan(s, p, lds) && p.pre;
+    if (s.Cout != 1 || !image_plan(s, p, lds) || !p.pre) return false;
+    return s.crop || ((long long)s.B * p.N0 * p.N0 >= (1 << 18) && (p.quads || s.n >= 5));
 }
 
 }  // namespace
@@ -501,23 +514,26 @@ bool backward_weight_image_apply(const Shape &s)
     return image_plan(s, p, lds);
 }
 
-int backward_weight_image_slices(const Shape &s)
+size_t backward_weight_image_workspace_bytes(const Shape &s)
 {
     ImageGradParams p;
     size_t lds;
-    return image_plan(s, p, lds) ? p.wgs : 0;
+    if (!image_plan(s, p, lds) || p.wgs == 1) return 0;
+    return (((size_t)p.wgs * s.Cout * s.Cin * s.n * s.n * sizeof(float)) + 255) & ~(size_t)255;
 }
 
-hipError_t launch_backward_weight_image(const void *in, const float *g, float *dst, const Shape &s, kst_dtype dt,
+hipError_t launch_backward_weight_image(const void *in, const float *g, float *dw, void *ws, const Shape &s, kst_dtype dt,
                                         hipStream_t stream)
 {
     ImageGradParams p;
     size_t lds;
     if (!image_plan(s, p, lds)) return hipErrorInvalidValue;
-    if (dt == KST_BF16) return launch_t<uint16_t>((const uint16_t *)in, g, dst, p, lds, stream);
-    if (dt == KST_F16) return launch_t<half_bits>((const half_bits *)in, g, dst, p, lds, stream);
-    return launch_t<float>((const float *)in, g, dst, p, lds, stream);
+    float *dst = p.wgs > 1 ? (float *)ws : dw;
+    const hipError_t e = launch_partial(in, g, dst, p, lds, dt, stream);
+    if (e != hipSuccess || p.wgs == 1) return e;
+    return launch_splitk_reduce(dst, dw, (size_t)s.Cout * s.Cin * s.n * s.n, p.wgs, stream);
 }
+
 
 bool backward_input_image_apply(const Shape &s)
 {

@@ -35,6 +35,34 @@ __device__ __forceinline__ void static_for(F &&f)
     static_for_each(f, std::make_integer_sequence<int, N>{});
 }
 
+// S values per lane -> their sums over the wave's lanes in to[0 .. S - 1].  At each of six steps a lane hands half of
+// the values it still holds to a partner and adds what it gets to the other half: about S exchanges in all, where S sums
+// one after the other would be six dependent exchanges each.
+constexpr int wave_sums_left(int S, int step) { return step == 0 ? S : (wave_sums_left(S, step - 1) + 1) / 2; }
+template <int S>
+__device__ __forceinline__ void wave_sums(float (&v)[S], int lane, float *to)
+{
+    static_for<6>([&](auto stepc) {
+        constexpr int step = decltype(stepc)::value, count = wave_sums_left(S, step), half = (count + 1) / 2;
+        const bool upper = (lane & (32 >> step)) != 0;
+#pragma unroll
+        for (int k = 0; k < half; ++k) {
+            const float a = v[k], b = k + half < count ? v[k + half < count ? k + half : 0] : 0.0f;
+            v[k] = (upper ? b : a) + __shfl_xor(upper ? a : b, 32 >> step, 64);
+        }
+    });
+#pragma unroll
+    for (int k = 0; k < wave_sums_left(S, 6); ++k) {            // which value this is, halves undone from the last
+        int i = k;
+        bool real = true;
+        static_for<6>([&](auto stepc) {
+            constexpr int step = 5 - decltype(stepc)::value, count = wave_sums_left(S, step), half = (count + 1) / 2;
+            if (lane & (32 >> step)) i += half;
+            real = real && i < count;
+        });
+        if (real) to[i] = v[k];
+    }
+}
 
 constexpr int G_TM = 128;        // positions per workgroup (4 MFMA column blocks)
 constexpr int G_TCO = 128;       // output channels per workgroup (4 MFMA row blocks)

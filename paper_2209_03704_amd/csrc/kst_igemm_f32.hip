@@ -856,16 +856,19 @@ __global__ void __launch_bounds__(256) splitk_reduce_shares_kernel(const float *
     }
 }
 
-// 64 and more partial results: 16 shares; 512 and more: 64 shares.
+// 64 and more partial results: 16 shares; 512 and more: 64 shares.  A tensor of a few workgroups' elements has nothing else
+// to hide a long walk: from 16 and from 128 partial results there (75 sums of 40 partial results: 10.9 -> 4.6 us, of 292:
+// 6.1 with 16 shares).
 hipError_t launch_splitk_reduce(const float *ws, float *out, size_t elems, int splits, hipStream_t stream, Epilogue epi,
                                 size_t plane_elems, int Cout)
 {
-    if (splits >= 512) {
+    const bool few = elems <= 4096;
+    if (splits >= (few ? 128 : 512)) {
         hipLaunchKernelGGL(splitk_reduce_shares_kernel<64>, dim3((unsigned)((elems + 3) / 4)), dim3(256), 0, stream, ws, out,
                            elems, splits, epi, plane_elems, Cout);
         return hipGetLastError();
     }
-    if (splits >= 64) {
+    if (splits >= (few ? 16 : 64)) {
         hipLaunchKernelGGL(splitk_reduce_shares_kernel<16>, dim3((unsigned)((elems + 15) / 16)), dim3(256), 0, stream, ws, out,
                            elems, splits, epi, plane_elems, Cout);
         return hipGetLastError();

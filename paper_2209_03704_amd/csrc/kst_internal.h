@@ -196,10 +196,11 @@ hipError_t launch_igemm_16_packed(const void *in, const void *w_seg, float *out,
                                   hipStream_t stream);
 // Layers with at most 64 quad positions in all (one sample of a small map): position blocks of 16.
 // Kernel gradient of layers with at most four input channels on large maps (rows of `in` and `g` staged through LDS,
-// one partial result per workgroup): whether it applies, how many partial results it writes, the launch.
+// one partial result per workgroup): whether it applies, its scratch, the launch.  An odd padding factor is s.crop = 1
+// here: g is then the tensor as it lies in memory.
 bool backward_weight_image_apply(const Shape &s);
-int backward_weight_image_slices(const Shape &s);
-hipError_t launch_backward_weight_image(const void *in, const float *g, float *dst, const Shape &s, kst_dtype dt,
+size_t backward_weight_image_workspace_bytes(const Shape &s);
+hipError_t launch_backward_weight_image(const void *in, const float *g, float *dw, void *ws, const Shape &s, kst_dtype dt,
                                         hipStream_t stream);
 // ... and the input gradient of such layers with one output channel (din is the unframed tensor).
 bool backward_input_image_apply(const Shape &s);

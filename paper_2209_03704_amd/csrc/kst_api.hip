@@ -634,9 +634,9 @@ kst_status grad_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dt
     f->use_dw_split = split_dw_applies(f->si, (P & 1) != 0, dt);
     f->dw_split_bytes = f->dw_split_query = 0;
     if (f->use_dw_split) {
-        f->dw_split_bytes = split_dw_workspace_bytes(f->si, (P & 1) != 0, dt);
+        f->dw_split_bytes = split_dw_workspace_bytes(f->si, (P & 1) != 0, dt, false);
         // (the query: the larger of the 16-bit types', with the widened copy of `in` that the fp32 multiplies read)
-        f->dw_split_query = split_dw_workspace_bytes(f->si, (P & 1) != 0, KST_F32) + f->xconv_bytes;
+        f->dw_split_query = split_dw_workspace_bytes(f->si, (P & 1) != 0, dt, true) + f->xconv_bytes;
     }
     f->image = f->si;
     f->image.crop = P & 1;

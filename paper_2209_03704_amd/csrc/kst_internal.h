@@ -227,7 +227,7 @@ hipError_t launch_split_din(const float *g, const void *w, float *din, void *ws,
                             hipStream_t stream);
 // ... and their kernel gradient (any operand type).
 bool split_dw_applies(const Shape &s, bool odd, kst_dtype dt);
-size_t split_dw_workspace_bytes(const Shape &s, bool odd, kst_dtype dt);
+size_t split_dw_workspace_bytes(const Shape &s, bool odd, kst_dtype dt, bool widest);
 hipError_t launch_split_dw(const void *in, const float *g, float *dw, void *ws, const Shape &s, bool odd, kst_dtype dt,
                            hipStream_t stream);
 // force_even: take the even-share launch whenever igemm_f32_even_shares_possible, whatever the cost model says.

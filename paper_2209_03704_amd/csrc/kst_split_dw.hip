@@ -8,9 +8,12 @@
 // steps are sixteen batch items at one position: the shift a kernel tap asks of g is then one of whole operands, where
 // neighbouring positions in a lane's eight values would have to be moved by single elements.
 //
+// With few batch items an "item" is a strip of rows of one: its rows of g, those it shares with the next strip included,
+// are laid out on their own, so that a tap's shift stays one of whole operands.
+//
 // Two passes over memory bring both operands into that form ([block of 32 channels][row][column][16 items][part][lane]
 // [8 items]), then every operand is one contiguous 1 KB load into registers.  A workgroup of four waves owns 128 x 128
-// channels and two taps, a wave 64 x 64 of them: 8 blocks, the largest partial products' sums apart from the others',
+// channels and two taps on large layers, a wave 64 x 64 of them (or 32 x 64, or 64 x 32, and four taps): 8 blocks, the largest partial products' sums apart from the others',
 // 256 accumulator registers; 48 MFMAs per step for 18 loads, one step ahead.  What bounds it is the rate at which the
 // cache of a CU hands over those operands (18 KB per wave and 1536 cycles; each is wanted by two waves).
 // 64 x 512 x 256 x 8 x 8, n = 4, P = 2: 15 us for the two passes, 83 us here and 9 us for the sums, where framing g, the
@@ -22,13 +25,15 @@ namespace kst {
 namespace {
 
 constexpr int E_THREADS = 256;
-constexpr int E_TC = 128;                // channels per workgroup, both kinds
 
 struct DwParams {
     int B, Cin, Cout, N, M;              // edges of in and g
     int q2;                              // position (a, c) meets g rows 2 a + q2 - u
-    int groups, steps;                   // groups of 16 items; positions x groups
-    int tiles_co, tiles_ci, pairs;
+    int strips, R, GR;                   // strips per batch item; rows of in and rows of g (with the halo) of a strip
+    int yo;                              // row a of a strip meets its rows 2 a + yo - u of g
+    int groups, steps;                   // groups of 16 items (strips); positions of a strip x groups
+    int wave_co, wave_ci;                // waves of a workgroup along the channels; the others along the taps
+    int tiles_co, tiles_ci, tiles_taps;
     int splits, per_split;               // steps per split, even
     unsigned x_bytes, g_bytes;           // of the operands
 };
@@ -37,50 +42,59 @@ __device__ __forceinline__ float value_of(const float *p) { return *p; }
 __device__ __forceinline__ float value_of(const uint16_t *p) { return to_f32(*p); }
 __device__ __forceinline__ float value_of(const half_bits *p) { return to_f32(*p); }
 
-// Four neighbours at p, of which `count` exist; VEC: all four in one aligned load.
-template <bool VEC, class T>
+// Four neighbours at p, of which `count` exist.  (Four at once whatever their alignment: aligned to their own size only.)
+template <class T>
 __device__ __forceinline__ void load_four(const T *p, int count, float (&v)[4])
 {
-    if constexpr (VEC) {
-        T t[4];
-        __builtin_memcpy(t, __builtin_assume_aligned(p, 4 * sizeof(T)), sizeof(t));
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = count > 0 ? value_of(t + i) : 0.0f;
+    T t[4] = {};
+    if (count >= 4) {
+        __builtin_memcpy(t, p, sizeof(t));
     } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = i < count ? value_of(p + i) : 0.0f;
+        for (int i = 0; i < 3; ++i)
+            if (i < count) t[i] = p[i];
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = i < count ? value_of(t + i) : 0.0f;
 }
 
-// src[B][C][edge][edge] -> operands of PARTS parts, zeros past the last item and channel.  One wave per (channel block,
-// group of items, row, eight columns): a lane reads eight neighbours of eight items, in two loads each where the rows
-// are whole groups of four (VEC).  Lanes of a wave read different rows, so what a lane leaves of its line has to come
-// from the cache again: a float g of 64 x 128 x 32 x 32 takes 15 us (5.6 TB/s of
-// the 33 MB read and 50 MB written), 27 with four columns and one element per load.
+// src[B][C][edge][edge] -> operands of PARTS parts, zeros past the last item and channel.  An item is a strip of `rows`
+// rows, of which strip k of a batch item starts at row k * pitch + first (rows outside the map: zeros).  One wave per
+// (channel block, group of items, row, eight columns): a lane reads eight neighbours of eight items, in two loads each.
+// Lanes of a wave read different rows, so what a lane leaves of its line has to come from the cache again: a float g of
+// 64 x 128 x 32 x 32 takes 15 us (5.6 TB/s of the 33 MB read and 50 MB written), 27 with four columns and one element
+// per load.
 constexpr int E_COLS = 8;
 
-template <int PARTS, bool VEC, class T>
+template <int PARTS, class T>
 __global__ void __launch_bounds__(256) split_items_kernel(const T *__restrict__ src, char *__restrict__ dst, int B, int C,
-                                                          int edge, int groups, unsigned tasks)
+                                                          int edge, int strips, int rows, int pitch, int first, int groups,
+                                                          unsigned tasks)
 {
     unsigned t = blockIdx.x * 4u + (threadIdx.x >> 6);
     if (t >= tasks) return;
     const unsigned runs = (unsigned)(edge + E_COLS - 1) / E_COLS;
     const int x0 = E_COLS * (int)(t % runs);
     t /= runs;
-    const int y = (int)(t % (unsigned)edge);
-    t /= (unsigned)edge;
+    const int y = (int)(t % (unsigned)rows);
+    t /= (unsigned)rows;
     const int group = (int)(t % (unsigned)groups), blk = (int)(t / (unsigned)groups);
-    const int lane = threadIdx.x & 63, c = blk * 32 + (lane & 31), b = group * 16 + 8 * (lane >> 5);
+    const int lane = threadIdx.x & 63, c = blk * 32 + (lane & 31), item = group * 16 + 8 * (lane >> 5);
+    int b = item / strips, k = item - b * strips;
     float v[8][E_COLS / 4][4];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const bool ok = c < C && b + j < B;
-        const T *row = src + ((ok ? (size_t)(b + j) * C + c : 0) * edge + y) * edge;
+        const int at = k * pitch + first + y;
+        const bool ok = c < C && b < B && at >= 0 && at < edge;
+        const T *row = src + ((ok ? (size_t)b * C + c : 0) * edge + (ok ? at : 0)) * edge;
 #pragma unroll
         for (int h = 0; h < E_COLS / 4; ++h) {
             const int x = x0 + 4 * h, count = ok ? edge - x : 0;
-            load_four<VEC>(row + (x < edge ? x : 0), count, v[j][h]);
+            load_four(row + (x < edge ? x : 0), count, v[j][h]);
+        }
+        if (++k == strips) {
+            k = 0;
+            ++b;
         }
     }
 #pragma unroll
@@ -91,26 +105,24 @@ __global__ void __launch_bounds__(256) split_items_kernel(const T *__restrict__ 
         for (int j = 0; j < 8; ++j) eight[j] = v[j][i >> 2][i & 3];
         bf16x8 part[3];
         split3(eight, part[0], part[1], part[2]);
-        char *d = dst + ((((size_t)blk * edge + y) * edge + x0 + i) * groups + group) * (PARTS * 1024) + lane * 16;
+        char *d = dst + ((((size_t)blk * rows + y) * edge + x0 + i) * groups + group) * (PARTS * 1024) + lane * 16;
 #pragma unroll
-        for (int k = 0; k < PARTS; ++k) *reinterpret_cast<bf16x8 *>(d + k * 1024) = part[k];
+        for (int p = 0; p < PARTS; ++p) *reinterpret_cast<bf16x8 *>(d + p * 1024) = part[p];
     }
 }
 
 template <int PARTS, class T>
-hipError_t split_items(const T *src, char *dst, int B, int C, int edge, int groups, hipStream_t stream)
+hipError_t split_items(const T *src, char *dst, int C, int edge, int rows, int pitch, int first, const DwParams &p,
+                       hipStream_t stream)
 {
-    const unsigned tasks = (unsigned)((C + 31) / 32) * groups * edge * ((edge + E_COLS - 1) / E_COLS);
-    const dim3 grid((tasks + 3) / 4), block(256);
-    if (edge % 4 == 0)
-        hipLaunchKernelGGL((split_items_kernel<PARTS, true, T>), grid, block, 0, stream, src, dst, B, C, edge, groups, tasks);
-    else
-        hipLaunchKernelGGL((split_items_kernel<PARTS, false, T>), grid, block, 0, stream, src, dst, B, C, edge, groups, tasks);
+    const unsigned tasks = (unsigned)((C + 31) / 32) * p.groups * rows * ((edge + E_COLS - 1) / E_COLS);
+    hipLaunchKernelGGL((split_items_kernel<PARTS, T>), dim3((tasks + 3) / 4), dim3(256), 0, stream, src, dst, p.B, C, edge,
+                       p.strips, rows, pitch, first, p.groups, tasks);
     return hipGetLastError();
 }
 
-// Partial sums part[split][tap][co][ci].
-template <int n, int XP>
+// Partial sums part[split][tap][co][ci].  A wave: TB taps x CB x IB blocks of 32 channels.
+template <int n, int XP, int CB, int IB, int TB>
 __global__ void __launch_bounds__(E_THREADS, 1) split_dw_kernel(const void *__restrict__ xf, const void *__restrict__ gf,
                                                                float *__restrict__ part, DwParams p)
 {
@@ -122,17 +134,21 @@ __global__ void __launch_bounds__(E_THREADS, 1) split_dw_kernel(const void *__re
     id /= (unsigned)p.splits;
     const int tile_co = (int)(id % (unsigned)p.tiles_co);
     id /= (unsigned)p.tiles_co;
-    const int pair = (int)(id % (unsigned)p.pairs), tile_ci = (int)(id / (unsigned)p.pairs);
+    const int tile_taps = (int)(id % (unsigned)p.tiles_taps), tile_ci = (int)(id / (unsigned)p.tiles_taps);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int cob = __builtin_amdgcn_readfirstlane(tile_co * 4 + (wave & 1) * 2);        // first blocks of 32 channels
-    const int cib = __builtin_amdgcn_readfirstlane(tile_ci * 4 + (wave >> 1) * 2);
+    const int wave_co = wave % p.wave_co, wave_ci = wave / p.wave_co % p.wave_ci, wave_taps = wave / (p.wave_co * p.wave_ci);
+    // first blocks of 32 channels, first tap
+    const int cob = __builtin_amdgcn_readfirstlane((tile_co * p.wave_co + wave_co) * CB);
+    const int cib = __builtin_amdgcn_readfirstlane((tile_ci * p.wave_ci + wave_ci) * IB);
+    const int tap0 = __builtin_amdgcn_readfirstlane((tile_taps * (4 / (p.wave_co * p.wave_ci)) + wave_taps) * TB);
     const int last_co = (p.Cout - 1) / 32, last_ci = (p.Cin - 1) / 32;
-    int u[2], v[2];
+    if (cob > last_co || cib > last_ci || tap0 >= NN) return;    // (a wave of its own: nothing waits for it)
+    int u[TB], v[TB];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const int tap = min(2 * pair + t, NN - 1);            // (the last pair of an odd number: twice the same tap)
+    for (int t = 0; t < TB; ++t) {
+        const int tap = min(tap0 + t, NN - 1);                // (past the last: the last one again)
         u[t] = __builtin_amdgcn_readfirstlane(tap / n);
         v[t] = __builtin_amdgcn_readfirstlane(tap % n);
     }
@@ -143,26 +159,26 @@ __global__ void __launch_bounds__(E_THREADS, 1) split_dw_kernel(const void *__re
     int group = __builtin_amdgcn_readfirstlane(s_begin % p.groups), s = s_begin;
     int c = __builtin_amdgcn_readfirstlane(s_begin / p.groups % p.N), a = __builtin_amdgcn_readfirstlane(s_begin / p.groups / p.N);
 
-    bf16x8 xr[2][2][XP], gr[2][2][2][3];
+    bf16x8 xr[2][IB][XP], gr[2][TB][CB][3];
     // Operands of the next step (zeros past the last one) -> register set.
     auto fetch = [&](auto setc) {
         constexpr int set = decltype(setc)::value;
         const bool live = s < s_end;
         const __amdgpu_buffer_rsrc_t xb = buffer_of(xf, live ? p.x_bytes : 0u);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const unsigned at = live ? (unsigned)((min(cib + i, last_ci) * p.N + a) * p.N + c) * p.groups + group : 0u;
+        for (int i = 0; i < IB; ++i) {
+            const unsigned at = live ? (unsigned)((min(cib + i, last_ci) * p.R + a) * p.N + c) * p.groups + group : 0u;
 #pragma unroll
             for (int k = 0; k < XP; ++k) xr[set][i][k] = load_bf16x8(xb, lane * 16 + k * 1024, at * (XP * 1024));
         }
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int y = 2 * a + p.q2 - u[t], x = 2 * c + p.q2 - v[t];
-            const bool inside = live && y >= 0 && y < p.M && x >= 0 && x < p.M;
+        for (int t = 0; t < TB; ++t) {
+            const int y = 2 * a + p.yo - u[t], x = 2 * c + p.q2 - v[t];        // (a row of the strip, a column of the map)
+            const bool inside = live && y >= 0 && y < p.GR && x >= 0 && x < p.M;
             const __amdgpu_buffer_rsrc_t gb = buffer_of(gf, inside ? p.g_bytes : 0u);
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const unsigned at = inside ? (unsigned)((min(cob + i, last_co) * p.M + y) * p.M + x) * p.groups + group : 0u;
+            for (int i = 0; i < CB; ++i) {
+                const unsigned at = inside ? (unsigned)((min(cob + i, last_co) * p.GR + y) * p.M + x) * p.groups + group : 0u;
 #pragma unroll
                 for (int k = 0; k < 3; ++k) gr[set][t][i][k] = load_bf16x8(gb, lane * 16 + k * 1024, at * 3072u);
             }
@@ -177,13 +193,13 @@ __global__ void __launch_bounds__(E_THREADS, 1) split_dw_kernel(const void *__re
         }
     };
 
-    floatx16 acc[2][2][2], low[2][2][2];              // [tap][output channels][input channels]
+    floatx16 acc[TB][CB][IB], low[TB][CB][IB];        // [tap][output channels][input channels]
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < TB; ++t)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < CB; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < IB; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[t][i][j][r] = low[t][i][j][r] = 0.0f;
 
@@ -195,11 +211,11 @@ __global__ void __launch_bounds__(E_THREADS, 1) split_dw_kernel(const void *__re
                 constexpr int gp = decltype(gc)::value, xp = sum - gp;
                 if constexpr (xp >= 0 && xp < XP) {
 #pragma unroll
-                    for (int t = 0; t < 2; ++t)
+                    for (int t = 0; t < TB; ++t)
 #pragma unroll
-                        for (int i = 0; i < 2; ++i)
+                        for (int i = 0; i < CB; ++i)
 #pragma unroll
-                            for (int j = 0; j < 2; ++j) {
+                            for (int j = 0; j < IB; ++j) {
                                 floatx16 &d = sum == 0 ? acc[t][i][j] : low[t][i][j];
                                 d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gr[set][t][i][gp], xr[set][j][xp], d, 0, 0, 0);
                             }
@@ -207,7 +223,7 @@ __global__ void __launch_bounds__(E_THREADS, 1) split_dw_kernel(const void *__re
             });
         });
         // the loads of the next step spread over the MFMAs of this one
-        static_for<8 * (XP == 1 ? 3 : 6)>([&](auto) {
+        static_for<TB * CB * IB * (XP == 1 ? 3 : XP == 2 ? 5 : 6)>([&](auto) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // MFMA
             __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);      // global read
             __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);      // vector arithmetic
@@ -224,12 +240,12 @@ __global__ void __launch_bounds__(E_THREADS, 1) split_dw_kernel(const void *__re
     }
 
     const size_t plane = (size_t)p.Cout * p.Cin;
-    static_for<2>([&](auto tc) {
+    static_for<TB>([&](auto tc) {
         constexpr int t = decltype(tc)::value;
-        if (2 * pair + t >= NN) return;
-        float *o = part + ((size_t)split * NN + 2 * pair + t) * plane;
-        static_for<4>([&](auto bc) {
-            constexpr int i = decltype(bc)::value >> 1, j = decltype(bc)::value & 1;
+        if (tap0 + t >= NN) return;
+        float *o = part + ((size_t)split * NN + tap0 + t) * plane;
+        static_for<CB * IB>([&](auto bc) {
+            constexpr int i = decltype(bc)::value / IB, j = decltype(bc)::value % IB;
             const int ci = (cib + j) * 32 + (lane & 31), co0 = (cob + i) * 32 + 4 * (lane >> 5);
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
@@ -331,12 +347,33 @@ __global__ void __launch_bounds__(256, n == 5 ? 6 : 8) split_dw_sum_kernel(const
 
 struct DwPlan {
     bool ok;
+    int form;                                 // 0: 2 x 2 channel blocks x 2 taps per wave, 1: 1 x 2 x 4, 2: 2 x 1 x 4
+    double us;                                // what the plan's cost model says
     DwParams p;
     size_t x_bytes, g_bytes, part_bytes;      // multiples of 1 KB
 };
 
-// s: the framed problem with Shape::frame = q; odd: the padding factor is odd; parts: of the input.
-DwPlan dw_plan(const Shape &s, bool odd, int parts)
+// Large layers with whole tiles of 128 channels and whole groups of items.
+// What fills items and channels up to whole blocks is multiplied too.  Both sides timed on 1014 random layers from 3
+// to 16 G products: 1.5 times as fast on average, with 1.8 to 2.2 times the products multiplied 25 of 121 layers
+// lost.  One kind did not gain: with 9 products per value of g and input channel and at most one tile of those, the
+// passes over g (four times the positions) show, and on maps of whole groups of four columns the fp32 multiplies
+// are at their best: of 32 such layers 15 lost (68 x 128 x 128 x 24 x 24, P = 3: 220 us here against 181).  bfloat16
+// input halves the multiplies and gained there too.
+bool whole_items(const Shape &s, kst_dtype dt)
+{
+    const double edge = s.N - 2 * s.frame, nn = s.n * s.n;
+    const double products = (double)s.B * edge * edge * nn * s.Cin * s.Cout;
+    const double padded = (double)((s.B + 15) / 16 * 16) * edge * edge * nn * ((s.Cin + 127) / 128 * 128) *
+                          ((s.Cout + 127) / 128 * 128);
+    const bool g_bound = s.n == 3 && s.Cin <= 128 && dt != KST_BF16 && edge > 8 && ((int)edge & 3) == 0;
+    return products >= 3.0e9 && padded <= 1.5 * products && !g_bound;
+}
+
+// s: the framed problem with Shape::frame = q; odd: the padding factor is odd.  The scratch is laid out for `parts` parts
+// of the input; everything else is chosen without a look at them.  whole: batch items are not cut into strips, a workgroup
+// has 128 x 128 channels.
+DwPlan dw_plan(const Shape &s, bool odd, int parts, bool whole)
 {
     DwPlan r;
     DwParams &p = r.p;
@@ -345,24 +382,68 @@ DwPlan dw_plan(const Shape &s, bool odd, int parts)
     p.N = s.N - 2 * s.frame;
     p.M = s.M - (odd ? 2 : 0);
     p.q2 = 2 * s.frame - (odd ? 1 : 0);
-    p.groups = (s.B + 15) / 16;
-    const double steps = (double)p.N * p.N * p.groups;
-    p.steps = (int)(steps < 1e9 ? steps : 1e9);
-    p.tiles_co = (s.Cout + E_TC - 1) / E_TC;
-    p.tiles_ci = (s.Cin + E_TC - 1) / E_TC;
-    p.pairs = (NN + 1) / 2;
-    // As many splits as give every CU one workgroup, with at least 16 steps each.
-    const double tiles = (double)p.tiles_co * p.tiles_ci * p.pairs;
-    int splits = tiles < 256.0 ? (int)(256.0 / tiles) : 1;
-    if (splits > p.steps / 16) splits = p.steps / 16 > 0 ? p.steps / 16 : 1;
-    p.per_split = ((p.steps + splits - 1) / splits + 1) & ~1;
-    p.splits = (p.steps + p.per_split - 1) / p.per_split;
-    r.x_bytes = (size_t)((s.Cin + 31) / 32) * p.N * p.N * p.groups * parts * 1024;
-    r.g_bytes = (size_t)((s.Cout + 31) / 32) * p.M * p.M * p.groups * 3 * 1024;
-    r.part_bytes = ((size_t)p.splits * NN * s.Cout * s.Cin * sizeof(float) + 255) & ~(size_t)255;
-    p.x_bytes = (unsigned)r.x_bytes;
-    p.g_bytes = (unsigned)r.g_bytes;
-    r.ok = s.n >= 3 && s.n <= 5 && steps < 1e9 && tiles < 1e6 && r.x_bytes < (1u << 31) && r.g_bytes < (1u << 31);
+    r.ok = false;
+    r.us = 1e30;
+    if (s.n < 3 || s.n > 5) return r;
+    const int blocks_co = (s.Cout + 31) / 32, blocks_ci = (s.Cin + 31) / 32;
+    if ((double)s.B * p.N * p.N >= 1e9 || (double)blocks_co * blocks_ci * NN >= 1e6) return r;
+    // A wave's shape: the one that multiplies least for padding, two taps where that is the same (with one block of input
+    // channels a wave loads 27 operands per 48 MFMAs, otherwise 18, where the caches hand over 24 in that time).
+    double best = 1e30;
+    int waves_co = 1, waves_ci = 1, waves_taps = 1;
+    for (int form = 0; form < (whole ? 1 : 3); ++form) {
+        const int cb = form == 1 ? 1 : 2, ib = form == 2 ? 1 : 2, tb = form == 0 ? 2 : 4;
+        const int co = (blocks_co + cb - 1) / cb, ci = (blocks_ci + ib - 1) / ib, taps = (NN + tb - 1) / tb;
+        const double cost = (double)co * ci * taps * (form == 2 ? 1.2 : 1.0);
+        if (cost < 0.99 * best) {
+            best = cost;
+            r.form = form;
+            waves_co = co;
+            waves_ci = ci;
+            waves_taps = taps;
+        }
+    }
+    p.wave_co = whole || waves_co > 1 ? 2 : 1;
+    p.wave_ci = whole || waves_ci > 1 ? 2 : 1;
+    const int wave_taps = 4 / (p.wave_co * p.wave_ci);
+    p.tiles_co = (waves_co + p.wave_co - 1) / p.wave_co;
+    p.tiles_ci = (waves_ci + p.wave_ci - 1) / p.wave_ci;
+    p.tiles_taps = (waves_taps + wave_taps - 1) / wave_taps;
+    const double tiles = (double)p.tiles_co * p.tiles_ci * p.tiles_taps;
+    // Strips per batch item: what fills the groups of sixteen against the rows of g that two strips both need.  Times: 48
+    // MFMAs of a wave and step in 1.4 us / 256 steps of a CU, operands at 4 TB/s, partial sums at 3.
+    const size_t plane = (size_t)s.Cout * s.Cin;
+    for (int strips = 1; strips <= (whole ? 1 : p.N); strips = strips < 4 ? strips + 1 : strips + strips / 2) {
+        const int R = (p.N + strips - 1) / strips, real = (p.N + R - 1) / R;
+        if (real != strips) continue;
+        const int GR = whole ? p.M : 2 * R + s.n - 2, groups = (s.B * strips + 15) / 16;
+        const double x_bytes = (double)blocks_ci * R * p.N * groups * 3072.0, g_bytes = (double)blocks_co * GR * p.M * groups * 3072.0;
+        const int steps = R * p.N * groups;
+        // As many splits as give every CU one workgroup, with at least 8 (16) steps each.
+        const int least = whole ? 16 : 8;
+        int splits = tiles < 256.0 ? (int)(256.0 / tiles) : 1;
+        if (splits > steps / least) splits = steps / least > 0 ? steps / least : 1;
+        const int per = ((steps + splits - 1) / splits + 1) & ~1;
+        splits = (steps + per - 1) / per;
+        const double rounds = (double)(long long)((tiles * splits + 255.0) / 256.0);
+        const double us = 16.0 + rounds * per * 1.25 + (x_bytes + g_bytes) * 1.7 / 4.0e6 + (splits + 1.0) * plane * NN * 4.0 / 3.0e6;
+        if (x_bytes >= 2147483648.0 || g_bytes >= 2147483648.0 || us >= 0.97 * r.us) continue;
+        r.us = us;
+        r.ok = true;
+        p.strips = strips;
+        p.R = R;
+        p.GR = GR;
+        p.yo = whole ? p.q2 : s.n - 1;
+        p.groups = groups;
+        p.steps = steps;
+        p.per_split = per;
+        p.splits = splits;
+        r.x_bytes = (size_t)blocks_ci * R * p.N * groups * parts * 1024;
+        r.g_bytes = (size_t)blocks_co * GR * p.M * groups * 3 * 1024;
+        r.part_bytes = ((size_t)splits * NN * plane * sizeof(float) + 255) & ~(size_t)255;
+        p.x_bytes = (unsigned)r.x_bytes;
+        p.g_bytes = (unsigned)r.g_bytes;
+    }
     return r;
 }
 
@@ -372,13 +453,15 @@ hipError_t dw_launch(const T *in, const float *g, float *dw, char *ws, const DwP
     const DwParams &p = pl.p;
     char *xf = ws, *gf = ws + pl.x_bytes;
     float *part = (float *)(gf + pl.g_bytes);
-    hipError_t e = split_items<XP>(in, xf, p.B, p.Cin, p.N, p.groups, stream);
+    hipError_t e = split_items<XP>(in, xf, p.Cin, p.N, p.R, p.R, 0, p, stream);
     if (e != hipSuccess) return e;
-    e = split_items<3>(g, gf, p.B, p.Cout, p.M, p.groups, stream);
+    e = split_items<3>(g, gf, p.Cout, p.M, p.GR, 2 * p.R, p.q2 - p.yo, p, stream);
     if (e != hipSuccess) return e;
-    const unsigned blocks = (unsigned)p.splits * p.tiles_co * p.tiles_ci * p.pairs;
-    hipLaunchKernelGGL((split_dw_kernel<n, XP>), dim3(blocks), dim3(E_THREADS), 0, stream, (const void *)xf, (const void *)gf,
-                       part, p);
+    const dim3 blocks((unsigned)p.splits * p.tiles_co * p.tiles_ci * p.tiles_taps), threads(E_THREADS);
+    const void *x = xf, *gp = gf;
+    if (pl.form == 0) hipLaunchKernelGGL((split_dw_kernel<n, XP, 2, 2, 2>), blocks, threads, 0, stream, x, gp, part, p);
+    else if (pl.form == 1) hipLaunchKernelGGL((split_dw_kernel<n, XP, 1, 2, 4>), blocks, threads, 0, stream, x, gp, part, p);
+    else hipLaunchKernelGGL((split_dw_kernel<n, XP, 2, 1, 4>), blocks, threads, 0, stream, x, gp, part, p);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const size_t pairs = (size_t)p.Cout * p.Cin;
@@ -397,29 +480,33 @@ hipError_t dw_launch_n(const T *in, const float *g, float *dw, char *ws, const D
 
 }  // namespace
 
+// Other layers: batch items cut into strips, a wave's shape by the channels.  Both sides timed on 200 random layers of 0.03
+// to 1.3 G products: from 48 input and 32 output channels 1.1 to 1.9 times as fast (2 x 268 x 396 x 17 x 17, n = 5, P = 1,
+// bfloat16: 133 -> 70 us), 5 x 5 kernels, where the fp32 multiplies' kernel has no second channel block, from 0.03 G,
+// others from 0.25 G: below that, four launches cost what the multiplies save.  Two things did not gain: fp32 input with 3 x
+// 3 kernels (0.76 to 1.2, passes over g as above), and one or two batch items in fp32, whose fp32 kernel runs at its best
+// on maps of whole groups of four (2 x 778 x 96 x 20 x 20, n = 4: 50 us there against 62).  Fewer channels are mostly padding (3
+// output channels of 32: 2 to 2.5 times slower).
 bool split_dw_applies(const Shape &s, bool odd, kst_dtype dt)
 {
     if (s.n < 3 || s.n > 5) return false;
-    const double edge = s.N - 2 * s.frame, nn = s.n * s.n;
-    const double products = (double)s.B * edge * edge * nn * s.Cin * s.Cout;
-    const double padded = (double)((s.B + 15) / 16 * 16) * edge * edge * nn * ((s.Cin + 127) / 128 * 128) *
-                          ((s.Cout + 127) / 128 * 128);
-    // What fills items and channels up to whole blocks is multiplied too.  Both sides timed on 1014 random layers from 3
-    // to 16 G products: 1.5 times as fast on average, with 1.8 to 2.2 times the products multiplied 25 of 121 layers
-    // lost.  One kind did not gain: with 9 products per value of g and input channel and at most one tile of those, the
-    // passes over g (four times the positions) show, and on maps of whole groups of four columns the fp32 multiplies
-    // are at their best: of 32 such layers 15 lost (68 x 128 x 128 x 24 x 24, P = 3: 220 us here against 181).  bfloat16
-    // input halves the multiplies and gained there too.
-    const bool g_bound = s.n == 3 && s.Cin <= E_TC && dt != KST_BF16 && edge > 8 && ((int)edge & 3) == 0;
-    return products >= 3.0e9 && padded <= 1.5 * products && !g_bound && dw_plan(s, odd, 3).ok;
+    if (whole_items(s, dt)) return dw_plan(s, odd, 3, true).ok;
+    const double edge = s.N - 2 * s.frame;
+    const double products = (double)s.B * edge * edge * s.n * s.n * s.Cin * s.Cout;
+    if (s.Cout < 32 || s.Cin < 48) return false;
+    if (s.n == 5 ? products < 0.03e9 || (dt == KST_F32 && s.B < 2) : products < 0.25e9 || s.B < 2) return false;
+    if (dt == KST_F32 && (s.n == 3 || (s.n == 4 && s.B < 4 && ((int)edge & 3) == 0))) return false;
+    return dw_plan(s, odd, 3, false).ok;
 }
 
-static int parts_of(kst_dtype dt) { return dt == KST_BF16 ? 1 : 3; }
+// (Eleven bits of half precision are two parts.)
+static int parts_of(kst_dtype dt) { return dt == KST_BF16 ? 1 : dt == KST_F16 ? 2 : 3; }
 
-// (0 for a layer this kernel does not take)
-size_t split_dw_workspace_bytes(const Shape &s, bool odd, kst_dtype dt)
+// widest: with room for three parts of the input whatever its type.  (0 for a layer this kernel does not take.)
+size_t split_dw_workspace_bytes(const Shape &s, bool odd, kst_dtype dt, bool widest)
 {
-    const DwPlan r = dw_plan(s, odd, parts_of(dt));
+    if (s.n < 3 || s.n > 5) return 0;
+    const DwPlan r = dw_plan(s, odd, widest ? 3 : parts_of(dt), whole_items(s, dt));
     if (!r.ok) return 0;
     return r.x_bytes + r.g_bytes + r.part_bytes;
 }
@@ -427,10 +514,10 @@ size_t split_dw_workspace_bytes(const Shape &s, bool odd, kst_dtype dt)
 hipError_t launch_split_dw(const void *in, const float *g, float *dw, void *ws, const Shape &s, bool odd, kst_dtype dt,
                            hipStream_t stream)
 {
-    const DwPlan r = dw_plan(s, odd, parts_of(dt));
+    const DwPlan r = dw_plan(s, odd, parts_of(dt), whole_items(s, dt));
     if (!r.ok) return hipErrorInvalidValue;
     if (dt == KST_BF16) return dw_launch_n<1>((const uint16_t *)in, g, dw, (char *)ws, r, s.n, stream);
-    if (dt == KST_F16) return dw_launch_n<3>((const half_bits *)in, g, dw, (char *)ws, r, s.n, stream);
+    if (dt == KST_F16) return dw_launch_n<2>((const half_bits *)in, g, dw, (char *)ws, r, s.n, stream);
     return dw_launch_n<3>((const float *)in, g, dw, (char *)ws, r, s.n, stream);
 }
 

@@ -574,6 +574,7 @@ struct GradPlan {
     // The same on the bf16 matrix cores, with workspaces of their own; only where the caller's is large enough.
     kst_dtype din_split;              // operand type of w they run with (half precision is widened to fp32 first)
     bool use_din_split, use_dw_split;
+    bool use_din_packed;              // ... or with g repacked (din_split_bytes and din_split_query are then its workspace)
     size_t din_split_wconv;           // widened half-precision weights
     size_t din_split_bytes, dw_split_bytes;    // whole workspace, as the launch lays it out
     size_t din_split_query, dw_split_query;    // ... as kst_backward_*_workspace_bytes give it
@@ -614,6 +615,10 @@ kst_status grad_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dt
         f->din_bytes = 0;
     }
     if (f->plain_unframed) f->in_bytes = 0;            // `in` read as it lies in memory
+    f->image = f->si;
+    f->image.crop = P & 1;
+    f->din_image = !f->din_cores && backward_input_image_apply(f->image);
+    f->dw_image = !f->dw_cores && backward_weight_image_apply(f->image);
     f->din_split = dt == KST_F16 ? KST_F32 : dt;
     f->use_din_split = split_din_applies(f->si, (P & 1) != 0, f->din_split);
     f->din_split_bytes = f->din_split_query = f->din_split_wconv = 0;
@@ -631,6 +636,8 @@ kst_status grad_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dt
             if (half > f->din_split_query) f->din_split_query = half;
         }
     }
+    f->use_din_packed = !f->use_din_split && !f->din_image && din_packed_applies(f->si, (P & 1) != 0, dt);
+    if (f->use_din_packed) f->din_split_bytes = f->din_split_query = din_packed_workspace_bytes(f->si, (P & 1) != 0, dt);
     f->use_dw_split = split_dw_applies(f->si, (P & 1) != 0, dt);
     f->dw_split_bytes = f->dw_split_query = 0;
     if (f->use_dw_split) {
@@ -638,10 +645,6 @@ kst_status grad_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dt
         // (the query: the larger of the 16-bit types', with the widened copy of `in` that the fp32 multiplies read)
         f->dw_split_query = split_dw_workspace_bytes(f->si, (P & 1) != 0, dt, true) + f->xconv_bytes;
     }
-    f->image = f->si;
-    f->image.crop = P & 1;
-    f->din_image = !f->din_cores && backward_input_image_apply(f->image);
-    f->dw_image = !f->dw_cores && backward_weight_image_apply(f->image);
     f->wsplit_bytes = f->dw_image ? backward_weight_image_workspace_bytes(f->image)
                       : f->dw_cores
                           ? backward_weight_igemm_workspace_bytes(f->si)
@@ -665,7 +668,7 @@ size_t kst_backward_input_workspace_bytes(int B, int Cin, int Cout, int N, int n
 {
     GradPlan f;
     if (!dtype_ok(dtype) || grad_plan(B, Cin, Cout, N, n, P, dtype, &f) != KST_OK) return 0;
-    return f.use_din_split ? f.din_split_query : f.din_bytes_needed();
+    return f.use_din_split || f.use_din_packed ? f.din_split_query : f.din_bytes_needed();
 }
 
 size_t kst_backward_weight_workspace_bytes(int B, int Cin, int Cout, int N, int n, int P, kst_dtype dtype)
@@ -684,12 +687,16 @@ kst_status kst_backward_input(const void *g, const void *w, void *din, void *ws,
     kst_status st = grad_plan(B, Cin, Cout, N, n, P, dtype, &f);
     if (st != KST_OK) return st;
     if (!aligned16(g) || !aligned16(w) || !aligned16(din)) return KST_ERR_ALIGN;
-    const bool split = f.use_din_split && ws && ws_bytes >= f.din_split_bytes;
+    const bool split = (f.use_din_split || f.use_din_packed) && ws && ws_bytes >= f.din_split_bytes;
     const size_t need = split ? f.din_split_bytes : f.din_bytes_needed();
     if (need) {
         if (!ws || ws_bytes < need) return KST_ERR_WORKSPACE;
         if (!aligned16(ws)) return KST_ERR_ALIGN;
     }
+    if (split && f.use_din_packed)
+        return launch_din_packed((const float *)g, w, (float *)din, ws, f.si, (P & 1) != 0, dtype, stream) == hipSuccess
+                   ? KST_OK
+                   : KST_ERR_HIP;
     if (split) {
         const void *w_in = w;
         if (dtype == KST_F16) {

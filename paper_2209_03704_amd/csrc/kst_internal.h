@@ -225,6 +225,17 @@ bool split_din_applies(const Shape &s, bool odd, kst_dtype dt);
 size_t split_din_workspace_bytes(const Shape &s, bool odd, kst_dtype dt);
 hipError_t launch_split_din(const float *g, const void *w, float *din, void *ws, const Shape &s, bool odd, kst_dtype dt,
                             hipStream_t stream);
+// ... of other layers with kernels of 3 x 3 to 5 x 5, g repacked once (weights of any type).
+bool din_packed_applies(const Shape &s, bool odd, kst_dtype dt);
+size_t din_packed_workspace_bytes(const Shape &s, bool odd, kst_dtype dt);
+hipError_t launch_din_packed(const float *g, const void *w, float *din, void *ws, const Shape &s, bool odd, kst_dtype dt,
+                             hipStream_t stream);
+hipError_t launch_din_packed_3(const float *g, const void *w, float *din, void *ws, const Shape &s, bool odd, kst_dtype dt,
+                               hipStream_t stream);
+hipError_t launch_din_packed_4(const float *g, const void *w, float *din, void *ws, const Shape &s, bool odd, kst_dtype dt,
+                               hipStream_t stream);
+hipError_t launch_din_packed_5(const float *g, const void *w, float *din, void *ws, const Shape &s, bool odd, kst_dtype dt,
+                               hipStream_t stream);
 // ... and their kernel gradient (any operand type).
 bool split_dw_applies(const Shape &s, bool odd, kst_dtype dt);
 size_t split_dw_workspace_bytes(const Shape &s, bool odd, kst_dtype dt, bool widest);

@@ -319,7 +319,13 @@ hipError_t launch_small_n(const float *in, const float *w_seg, float *dst, const
 bool igemm_f32_small_supported(const Shape &s)
 {
     SmallParams p;
-    return small_plan(s, p);
+    if (!small_plan(s, p)) return false;
+    if (((s.Cin | s.Cout) & 3) == 0) return true;
+    // Channels that are no whole groups of four: large layers are the split kernels' (3 x 854 x 480 x 8 x 8, n = 5, P = 1: 76 us
+    // there, 134 here), and the direct kernel is 2 to 5 us faster on few channels and many taps and positions (2 x 96 x 3 x
+    // 30 x 30, n = 5, P = 1: 21.5 there, 26.2 here; 1 x 75 x 13 x 32 x 32: 14.7 and 17.5).
+    if (split_f32_applies(s)) return false;
+    return s.n < 5 || s.Cout >= 16 || s.Cin >= 128 || p.Mtot < 700;
 }
 
 size_t igemm_f32_small_workspace_bytes(const Shape &s)

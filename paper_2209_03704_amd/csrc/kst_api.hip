@@ -45,6 +45,7 @@ kst_path choose_path(const Shape &s, kst_dtype dt)
     // kernel walks its channel chunks one after the other, but the repacking launch comes before.  Either side timed on 170
     // such layers: from 600 products per output pixel the direct kernel is 1.2 to 8 times slower, below 500 up to 1.3 faster.
     if (is16(dt) && s.Cout < 16 && s.Cin * s.n * s.n >= 600 && igemm_16_packed_applies(s)) return KST_PATH_IGEMM;
+    if (dt == KST_F32 && packed_f32_applies(s)) return KST_PATH_IGEMM;
     // One sample of a generator's output layer (many input channels, three output channels): the
     // position-block kernel splits its reduction over the chip, the direct kernel has four tiles.
     if (dt == KST_F32 && s.Cout < 16 && igemm_f32_small_supported(s)) return KST_PATH_IGEMM;

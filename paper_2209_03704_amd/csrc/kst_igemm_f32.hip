@@ -607,7 +607,8 @@ static bool tiles_supported(const Shape &s)
 
 bool igemm_f32_supported(const Shape &s)
 {
-    return igemm_f32_small_supported(s) || tapmajor_f32_supported(s) || split_f32_applies(s) || tiles_supported(s);
+    return packed_f32_applies(s) || igemm_f32_small_supported(s) || tapmajor_f32_supported(s) || split_f32_applies(s) ||
+           tiles_supported(s);
 }
 
 bool igemm_f32_takes_row_stride(const Shape &s)
@@ -618,7 +619,7 @@ bool igemm_f32_takes_row_stride(const Shape &s)
 bool igemm_f32_takes_virtual_frame(const Shape &s)
 {
     if (s.frame <= 0 || s.Ns != s.N) return false;
-    return igemm_f32_small_supported(s) || tapmajor_f32_supported(s) || split_f32_applies(s) ||
+    return packed_f32_applies(s) || igemm_f32_small_supported(s) || tapmajor_f32_supported(s) || split_f32_applies(s) ||
            (tiles_supported(s) && pipe_ok(plan(s)));
 }
 
@@ -703,6 +704,7 @@ bool igemm_f32_even_shares_possible(const Shape &s)
 
 size_t igemm_f32_workspace_bytes(const Shape &s, bool force_even)
 {
+    if (!force_even && packed_f32_applies(s)) return packed_f32_workspace_bytes(s);
     if (!force_even && igemm_f32_small_supported(s)) return igemm_f32_small_workspace_bytes(s);
     if (!force_even && tapmajor_f32_supported(s)) return 0;
     if (!force_even && split_f32_applies(s)) return split_f32_workspace_bytes(s);
@@ -796,6 +798,7 @@ static hipError_t launch_n(const float *in, const float *w_seg, float *dst, cons
 hipError_t launch_igemm_f32(const float *in, const float *w_seg, float *out, void *ws, const Shape &s,
                             bool force_even, hipStream_t stream)
 {
+    if (!force_even && packed_f32_applies(s)) return launch_packed_f32(in, w_seg, out, ws, s, stream);
     if (!force_even && igemm_f32_small_supported(s)) return launch_igemm_f32_small(in, w_seg, out, ws, s, stream);
     if (!force_even && tapmajor_f32_supported(s)) return launch_tapmajor_f32(in, w_seg, out, s, stream);
     if (!force_even && split_f32_applies(s)) return launch_split_f32(in, w_seg, out, ws, s, stream);

@@ -219,7 +219,14 @@ bool split_f32_applies(const Shape &s);
 size_t split_f32_workspace_bytes(const Shape &s);
 hipError_t launch_split_f32(const float *in, const float *w_seg, float *out, void *ws, const Shape &s,
                             hipStream_t stream);
-// ... and their input gradient (fp32 or bfloat16 weights; s.frame as above, odd: the padding factor is odd, g then one
+// ... of other layers with kernels of 3 x 3 to 5 x 5, the input repacked once (takes Shape::frame and Shape::crop).
+bool packed_f32_applies(const Shape &s);
+size_t packed_f32_workspace_bytes(const Shape &s);
+hipError_t launch_packed_f32(const float *in, const float *w_seg, float *out, void *ws, const Shape &s, hipStream_t stream);
+hipError_t launch_packed_f32_3(const float *in, const float *w_seg, float *out, void *ws, const Shape &s, hipStream_t stream);
+hipError_t launch_packed_f32_4(const float *in, const float *w_seg, float *out, void *ws, const Shape &s, hipStream_t stream);
+hipError_t launch_packed_f32_5(const float *in, const float *w_seg, float *out, void *ws, const Shape &s, hipStream_t stream);
+// The split kernels' input gradient (fp32 or bfloat16 weights; s.frame as above, odd: the padding factor is odd, g then one
 // row and column short on every side).
 bool split_din_applies(const Shape &s, bool odd, kst_dtype dt);
 size_t split_din_workspace_bytes(const Shape &s, bool odd, kst_dtype dt);

@@ -337,6 +337,10 @@ kst_status kst_forward(const void *in, const void *w, void *out, int B, int Cin,
     if (st != KST_OK) return st;
     if (!aligned16(in) || !aligned16(w) || !aligned16(out)) return KST_ERR_ALIGN;
     Shape s = make_shape(B, Cin, Cout, N, n);
+    if (choose_path(s, dtype) == KST_PATH_DIRECT) {
+        const hipError_t e = launch_direct_plain_weights(in, w, (float *)out, s, dtype, stream);
+        if (e != hipErrorNotSupported) return e == hipSuccess ? KST_OK : KST_ERR_HIP;
+    }
     const size_t seg_bytes = (seg_elems(Cin, Cout, n, dtype) * elt_bytes(dtype) + 255) & ~(size_t)255;
     size_t ws_bytes = workspace_for(s, dtype, choose_path(s, dtype));
     const auto least = [&] {

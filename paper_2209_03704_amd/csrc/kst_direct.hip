@@ -169,6 +169,7 @@ struct RowsParams {
     int xs_buf;               // floats per LDS input buffer
     int xs_stride;            // floats per staged row: N rounded up to 4, plus 8
     unsigned off[4];
+    int plain;             // 1: weights as they come, w[co][0][u][v] (one load per kernel element and output channel either way)
     Epilogue epi;
 };
 
@@ -279,8 +280,9 @@ __device__ __forceinline__ void rows_weights(float (&wk)[2][2][((n + 1) / 2) * (
         for (int s = 0; s < 2; ++s) {
             const int Ta = r ? Ta1 : Ta0, Tb = s ? Ta1 : Ta0;
 #pragma unroll
-            for (int t = 0; t < Ta * Tb; ++t)
-                wk[r][s][t] = to_f32(w_seg[wseg_index<T>(p.off[2 * r + s], Ta * Tb, p.Cout, ci, t, co)]);
+            for (int t = 0; t < Ta * Tb; ++t)            // (Tb > 0: a class has taps only where both parities do)
+                wk[r][s][t] = to_f32(w_seg[p.plain ? (size_t)(co * n + 2 * (t / Tb) + r) * n + 2 * (t % Tb) + s
+                                                   : wseg_index<T>(p.off[2 * r + s], Ta * Tb, p.Cout, ci, t, co)]);
         }
 }
 
@@ -451,7 +453,7 @@ constexpr size_t kRowsLdsLimit = 64 * 1024;
 // Strip plan of the single-channel rows kernel (several input channels are the multi-channel
 // kernel's job): R output rows per strip.
 template <int n, typename T>
-static bool try_rows(const T *in, const T *w_seg, float *out, const Shape &s, kst_dtype dt, hipStream_t stream)
+static bool try_rows(const T *in, const T *w_seg, float *out, const Shape &s, kst_dtype dt, bool plain, hipStream_t stream)
 {
     if (s.Cin != 1) return false;
     RowsParams p;
@@ -478,6 +480,7 @@ static bool try_rows(const T *in, const T *w_seg, float *out, const Shape &s, ks
     p.xcd_remap = 0;
     for (int c = 0; c < 4; ++c) p.off[c] = (unsigned)seg_offset(s.Cin, s.Cout, s.n, c, dt);
     p.epi = s.epi;
+    p.plain = plain;
     // Persistent: a few workgroups per CU, each walking over its share of the strips.
     unsigned grid = 1024;
     if (grid > p.xcd_slots * 8) grid = p.xcd_slots * 8;
@@ -487,16 +490,16 @@ static bool try_rows(const T *in, const T *w_seg, float *out, const Shape &s, ks
 }
 
 template <typename T>
-static bool run_rows(const T *in, const T *w_seg, float *out, const Shape &s, kst_dtype dt, hipStream_t stream)
+static bool run_rows(const T *in, const T *w_seg, float *out, const Shape &s, kst_dtype dt, bool plain, hipStream_t stream)
 {
     switch (s.n) {
-        case 1: return try_rows<1, T>(in, w_seg, out, s, dt, stream);
-        case 2: return try_rows<2, T>(in, w_seg, out, s, dt, stream);
-        case 3: return try_rows<3, T>(in, w_seg, out, s, dt, stream);
-        case 4: return try_rows<4, T>(in, w_seg, out, s, dt, stream);
-        case 5: return try_rows<5, T>(in, w_seg, out, s, dt, stream);
-        case 6: return try_rows<6, T>(in, w_seg, out, s, dt, stream);
-        case 7: return try_rows<7, T>(in, w_seg, out, s, dt, stream);
+        case 1: return try_rows<1, T>(in, w_seg, out, s, dt, plain, stream);
+        case 2: return try_rows<2, T>(in, w_seg, out, s, dt, plain, stream);
+        case 3: return try_rows<3, T>(in, w_seg, out, s, dt, plain, stream);
+        case 4: return try_rows<4, T>(in, w_seg, out, s, dt, plain, stream);
+        case 5: return try_rows<5, T>(in, w_seg, out, s, dt, plain, stream);
+        case 6: return try_rows<6, T>(in, w_seg, out, s, dt, plain, stream);
+        case 7: return try_rows<7, T>(in, w_seg, out, s, dt, plain, stream);
         default: return false;
     }
 }
@@ -504,7 +507,7 @@ static bool run_rows(const T *in, const T *w_seg, float *out, const Shape &s, ks
 template <typename T>
 static hipError_t run(const T *in, const T *w_seg, float *out, const Shape &s, kst_dtype dt, hipStream_t stream)
 {
-    if (run_rows<T>(in, w_seg, out, s, dt, stream)) return hipGetLastError();
+    if (run_rows<T>(in, w_seg, out, s, dt, false, stream)) return hipGetLastError();
     DirectParams p;
     p.B = s.B; p.Cin = s.Cin; p.Cout = s.Cout; p.N = s.N; p.M = s.M; p.E = s.E;
     p.tiles_x = (s.E + D_TJ - 1) / D_TJ;
@@ -563,6 +566,21 @@ hipError_t launch_direct(const void *in, const void *w_seg, float *out, const Sh
     if (dt == KST_BF16) return run<uint16_t>((const uint16_t *)in, (const uint16_t *)w_seg, out, s, dt, stream);
     if (dt == KST_F16) return run<half_bits>((const half_bits *)in, (const half_bits *)w_seg, out, s, dt, stream);
     return run<float>((const float *)in, (const float *)w_seg, out, s, dt, stream);
+}
+
+// Layers that the single-channel rows kernel runs, from weights as they come: it loads each of them once per workgroup and
+// output channel, in either order, so the launch that segregates them (4.5 us, and scratch for its result) is not needed.
+// 1 x 1 x 1 x 32 x 32, n = 3, whole call: 28 -> 8 us.  hipErrorNotSupported for any other layer, nothing launched then.
+hipError_t launch_direct_plain_weights(const void *in, const void *w, float *out, const Shape &s, kst_dtype dt, hipStream_t stream)
+{
+    FlatParams fp;
+    unsigned grid;
+    size_t lds;
+    if (s.frame != 0 || s.Cin != 1 || direct_flat_plan(s, dt, fp, grid, lds) || direct_multi_supported(s)) return hipErrorNotSupported;
+    const bool ran = dt == KST_BF16  ? run_rows<uint16_t>((const uint16_t *)in, (const uint16_t *)w, out, s, dt, true, stream)
+                     : dt == KST_F16 ? run_rows<half_bits>((const half_bits *)in, (const half_bits *)w, out, s, dt, true, stream)
+                                     : run_rows<float>((const float *)in, (const float *)w, out, s, dt, true, stream);
+    return ran ? hipGetLastError() : hipErrorNotSupported;
 }
 
 }  // namespace kst

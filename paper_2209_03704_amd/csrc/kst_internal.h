@@ -171,6 +171,8 @@ hipError_t launch_direct_multi(const void *in, const void *w_seg, float *out, co
                                hipStream_t stream);
 hipError_t launch_direct(const void *in, const void *w_seg, float *out, const Shape &s, kst_dtype dt,
                          hipStream_t stream);
+// ... from un-segregated weights, where it needs no scratch for that (hipErrorNotSupported: it does, nothing was launched).
+hipError_t launch_direct_plain_weights(const void *in, const void *w, float *out, const Shape &s, kst_dtype dt, hipStream_t stream);
 // Matrix-core path: whether the kernels can run the shape, scratch they need, launch.
 bool igemm_f32_supported(const Shape &s);
 bool igemm_f32_takes_row_stride(const Shape &s);   // s.Ns != s.N is only read by the pipelined fp32 kernel

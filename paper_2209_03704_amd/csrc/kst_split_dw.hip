@@ -159,6 +159,15 @@ __global__ void __launch_bounds__(E_THREADS, 1) split_dw_kernel(const void *__re
     int group = __builtin_amdgcn_readfirstlane(s_begin % p.groups), s = s_begin;
     int c = __builtin_amdgcn_readfirstlane(s_begin / p.groups % p.N), a = __builtin_amdgcn_readfirstlane(s_begin / p.groups / p.N);
 
+    // Operand numbers: a step's number is its place in x's list, g's follows from the position less a tap's shift.
+    unsigned x_at[IB], g_at[CB];
+    int shift[TB];
+#pragma unroll
+    for (int i = 0; i < IB; ++i) x_at[i] = (unsigned)min(cib + i, last_ci) * p.R * p.N * p.groups;
+#pragma unroll
+    for (int i = 0; i < CB; ++i) g_at[i] = (unsigned)min(cob + i, last_co) * p.GR * p.M * p.groups;
+#pragma unroll
+    for (int t = 0; t < TB; ++t) shift[t] = (u[t] * p.M + v[t]) * p.groups;
     bf16x8 xr[2][IB][XP], gr[2][TB][CB][3];
     // Operands of the next step (zeros past the last one) -> register set.
     auto fetch = [&](auto setc) {
@@ -167,10 +176,11 @@ __global__ void __launch_bounds__(E_THREADS, 1) split_dw_kernel(const void *__re
         const __amdgpu_buffer_rsrc_t xb = buffer_of(xf, live ? p.x_bytes : 0u);
 #pragma unroll
         for (int i = 0; i < IB; ++i) {
-            const unsigned at = live ? (unsigned)((min(cib + i, last_ci) * p.R + a) * p.N + c) * p.groups + group : 0u;
+            const unsigned at = live ? x_at[i] + s : 0u;
 #pragma unroll
             for (int k = 0; k < XP; ++k) xr[set][i][k] = load_bf16x8(xb, lane * 16 + k * 1024, at * (XP * 1024));
         }
+        const int here = ((2 * a + p.yo) * p.M + 2 * c + p.q2) * p.groups + group;
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
             const int y = 2 * a + p.yo - u[t], x = 2 * c + p.q2 - v[t];        // (a row of the strip, a column of the map)
@@ -178,7 +188,7 @@ __global__ void __launch_bounds__(E_THREADS, 1) split_dw_kernel(const void *__re
             const __amdgpu_buffer_rsrc_t gb = buffer_of(gf, inside ? p.g_bytes : 0u);
 #pragma unroll
             for (int i = 0; i < CB; ++i) {
-                const unsigned at = inside ? (unsigned)((min(cob + i, last_co) * p.GR + y) * p.M + x) * p.groups + group : 0u;
+                const unsigned at = inside ? g_at[i] + (unsigned)(here - shift[t]) : 0u;
 #pragma unroll
                 for (int k = 0; k < 3; ++k) gr[set][t][i][k] = load_bf16x8(gb, lane * 16 + k * 1024, at * 3072u);
             }

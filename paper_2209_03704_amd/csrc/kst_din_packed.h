@@ -169,7 +169,7 @@ __global__ void __launch_bounds__(F_THREADS) din_pack_kernel(const float *__rest
 // Four waves along the positions, PB blocks of 32 each, RB blocks of 32 input channels; the largest partial products' sums
 // apart from the others'.
 template <int n, int WP, bool S2D, int PB, int RB, int NT, class T>
-__global__ void __launch_bounds__(F_THREADS, PB * RB == 1 ? 2 : 1)
+__global__ void __launch_bounds__(F_THREADS, PB * RB == 1 && (S2D || NT == 3) ? 2 : 1)
     din_packed_kernel(const float *__restrict__ g, const T *__restrict__ w, const char *__restrict__ gx, const char *__restrict__ wx,
                       float *__restrict__ din, float *__restrict__ ws, DinPackedParams p)
 {

@@ -49,7 +49,9 @@ struct SmallParams {
 // added through LDS in wave order before anything is stored: a quarter of the partial outputs for
 // the same number of waves pulling weights (one sample of a 1024 -> 512 layer writes 16.7 MB of
 // partial outputs beside its 33.5 MB of weights with one wave per workgroup).
-enum SmallLoads { WHOLE, RAGGED, SINGLE };
+// SINGLE_WHOLE is SINGLE with Cin a multiple of 4: no channel past the last to ask for (100 selects a chunk with a 5 x 5
+// kernel: 2 x 96 x 3 x 30 x 30, n = 5, P = 1 takes 21.5 us without and 26.2 with them).
+enum SmallLoads { WHOLE, RAGGED, SINGLE, SINGLE_WHOLE };
 typedef float floatx4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int n, int LOADS, int WV>
@@ -93,7 +95,7 @@ __global__ void __launch_bounds__(64 * WV) igemm_f32_small_kernel(const float *_
     // ci0 + k, as one 16-byte group; value j is its row (m) of row block j.  Groups that would end past
     // Cout (the last block of a ragged layer) are the last four channels instead: rows for channels that
     // another row has too.
-    const unsigned w_col = LOADS != SINGLE ? (unsigned)min(co0 + 4 * m, p.Cout - 4) : 0u;
+    const unsigned w_col = LOADS == WHOLE || LOADS == RAGGED ? (unsigned)min(co0 + 4 * m, p.Cout - 4) : 0u;
     unsigned w_cols[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) w_cols[j] = (unsigned)min(co0 + 4 * m + j, p.Cout - 1);
@@ -115,7 +117,7 @@ __global__ void __launch_bounds__(64 * WV) igemm_f32_small_kernel(const float *_
     auto fetch = [&](auto bufc, int chunk) {
         constexpr int buf = decltype(bufc)::value;
         // Channels past the last (RAGGED, SINGLE: in the last chunk): zeros on both sides.
-        const bool live = LOADS == WHOLE || chunk * SM_KC + k < p.Cin;
+        const bool live = LOADS == WHOLE || LOADS == SINGLE_WHOLE || chunk * SM_KC + k < p.Cin;
         const unsigned ci = live ? (unsigned)(chunk * SM_KC + k) : 0u;
 #pragma unroll
         for (int dy = 0; dy <= fl; ++dy)
@@ -300,7 +302,7 @@ template <int n>
 hipError_t launch_small_n(const float *in, const float *w_seg, float *dst, const SmallParams &p, hipStream_t stream)
 {
     const unsigned blocks = (unsigned)(p.pos_blocks * p.co_blocks * p.splits);
-    const int loads = p.Cout < 4 ? SINGLE : ((p.Cout | p.Cin) & 3) == 0 ? WHOLE : RAGGED;
+    const int loads = p.Cout < 4 ? (p.Cin & 3 ? SINGLE : SINGLE_WHOLE) : ((p.Cout | p.Cin) & 3) == 0 ? WHOLE : RAGGED;
     auto launch = [&](auto loadsc) {
         constexpr int L = decltype(loadsc)::value;
         if (p.waves == 4)
@@ -310,7 +312,8 @@ hipError_t launch_small_n(const float *in, const float *w_seg, float *dst, const
     };
     if (loads == WHOLE) launch(std::integral_constant<int, WHOLE>{});
     else if (loads == RAGGED) launch(std::integral_constant<int, RAGGED>{});
-    else launch(std::integral_constant<int, SINGLE>{});
+    else if (loads == SINGLE) launch(std::integral_constant<int, SINGLE>{});
+    else launch(std::integral_constant<int, SINGLE_WHOLE>{});
     return hipGetLastError();
 }
 
@@ -320,10 +323,10 @@ bool igemm_f32_small_supported(const Shape &s)
 {
     SmallParams p;
     if (!small_plan(s, p)) return false;
-    if (((s.Cin | s.Cout) & 3) == 0) return true;
-    // Channels that are no whole groups of four: large layers are the split kernels' (3 x 854 x 480 x 8 x 8, n = 5, P = 1: 76 us
-    // there, 134 here), and the direct kernel is 2 to 5 us faster on few channels and many taps and positions (2 x 96 x 3 x
-    // 30 x 30, n = 5, P = 1: 21.5 there, 26.2 here; 1 x 75 x 13 x 32 x 32: 14.7 and 17.5).
+    if (s.Cin % SM_KC == 0 && s.Cin >= 64) return true;
+    // Other channel counts: large layers are the split kernels' (3 x 854 x 480 x 8 x 8, n = 5, P = 1: 76 us there, 134 here),
+    // and the direct kernel is 2 to 3 us faster on few channels and many taps and positions (1 x 75 x 13 x 32 x 32, n = 5, P = 1:
+    // 14.7 there, 17.5 here).
     if (split_f32_applies(s)) return false;
     return s.n < 5 || s.Cout >= 16 || s.Cin >= 128 || p.Mtot < 700;
 }

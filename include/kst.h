@@ -146,12 +146,14 @@ kst_status kst_segregate_weights(const void *w, void *w_seg, int Cin, int Cout, 
 /*
  * Bytes of scratch kst_forward_seg wants for this shape and path (0 when it
  * wants none).  The matrix-core path uses it for partial sums when it splits
- * the input-channel reduction across workgroups, and for the split weights of
- * large fp32 layers.  With fewer bytes AUTO runs these layers on the kernels
- * that multiply in fp32, slower and rounded differently, where those can do
- * with what there is (many need none); below that, and for all other layers
- * and paths, the call is refused with KST_ERR_WORKSPACE.  The gradients of
- * large layers do the same.
+ * the input-channel reduction across workgroups, and for the operands that
+ * kernels of 3 x 3 to 5 x 5 lay out anew: fp32 weights and, below 1.5 G
+ * products, the input in three bfloat16 parts, a 16-bit input with the
+ * channels of a pixel side by side.  With fewer bytes AUTO runs these layers
+ * on the kernels that read operands as they lie (fp32 ones multiply in fp32),
+ * slower and rounded differently, where those can do with what there is (many
+ * need none); below that, and for all other layers and paths, the call is
+ * refused with KST_ERR_WORKSPACE.  The gradients do the same.
  */
 size_t kst_workspace_bytes(int B, int Cin, int Cout, int N, int n, kst_dtype dtype, kst_path path);
 
@@ -177,8 +179,8 @@ kst_status kst_forward_seg(const void *in, const void *w_seg, void *out, void *w
  * hipMalloc, hipFree or other allocating routine; the first call on a device looks the array's
  * address up (hipGetSymbolAddress), later calls only launch.  A layer for which kst_workspace_bytes
  * gives no more than the array holds has the kernels and results of kst_forward_seg with all the
- * workspace it wants.  A large fp32 layer that wants more runs on the kernels that multiply in
- * fp32 where the array is enough for those; any other layer that wants more gets
+ * workspace it wants.  A layer that wants more to lay its operands out anew runs on the kernels
+ * that read them as they lie where the array is enough for those; any other layer that wants more gets
  * KST_ERR_WORKSPACE and nothing is launched.  All calls on one GPU share that GPU's array: calls
  * that overlap in time on one GPU (different streams, different threads) race on it; calls on
  * one stream are ordered and safe.  The array's contents are undefined between calls.
@@ -191,7 +193,8 @@ kst_status kst_forward_seg_static(const void *in, const void *w_seg, void *out,
 /*
  * Whole path from un-segregated weights: segregates w into scratch, then runs
  * the segregated forward pass with path AUTO.  Same result as
- * kst_segregate_weights + kst_forward_seg.  The scratch (segregated weights
+ * kst_segregate_weights + kst_forward_seg.  (Layers of one input channel whose
+ * kernel reads the weights as they come take no scratch.)  The scratch (segregated weights
  * and workspace) is taken from and returned to a stream-ordered memory pool
  * that the library keeps per device (hipMallocFromPoolAsync / hipFreeAsync on
  * `stream`): no host synchronisation, but not usable under stream capture.
@@ -213,7 +216,8 @@ kst_status kst_forward(const void *in, const void *w, void *out,
  * loads) and for odd P write output (y, x) as element (y + 1, x + 1) of the
  * map the framed input defines, which is that swap of roles: no workspace.
  * The fp32 matrix-core kernel for channel counts that are multiples of 4
- * supplies the frame while it stages its input; the other matrix-core kernels
+ * supplies the frame while it stages its input, and an input that is laid out
+ * anew in the workspace has the frame in it; the other matrix-core kernels
  * run on a framed copy of the input made in the workspace.  They shift their
  * stores in the same way for odd P, except three
  * 16-bit kernels (maps of 16 to 128 quads a row), which for odd P run into a
@@ -271,7 +275,9 @@ kst_status kst_forward_seg_epilogue(const void *in, const void *w_seg, const flo
  * at least 8 channels on either side, or at least 64 input channels with a few
  * output channels; the other kernel-gradient kernels when they slice the
  * positions), and for the fp32 copy of w or in that the matrix-core kernels
- * read when the operands are 16-bit (widening is exact); it
+ * read when the operands are 16-bit (widening is exact), or for the bfloat16
+ * parts of both operands (kernels of 3 x 3 to 5 x 5; half precision needs two,
+ * bfloat16 itself one); it
  * may be 0 (then ws may be NULL).  The byte count depends
  * on the shape only, never on the pointers, as in
  * kst_forward_seg_padded.  Pointers, alignment, stream and statuses as above.

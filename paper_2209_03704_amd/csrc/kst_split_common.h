@@ -39,6 +39,157 @@ __device__ __forceinline__ void split3(const float (&v)[8], bf16x8 &p0, bf16x8 &
     }
 }
 
+// ---- two half-precision parts ----
+//
+// Where the reduction is long, fp32 operands are split into two half-precision parts instead, x = x0 + x1 (rounded to
+// nearest: |x1| <= 2^-11 |x|, what is left over at most 2^-23 |x|), and a product is x0 w0 + (x0 w1 + x1 w0): three partial
+// products of six.  22 to 23 bits of each operand and the product x1 w1 left out are an error of 7.6e-8 of a sum of
+// products of random sign, beside which the sums' own roundings are made smaller than with three parts: all partial
+// products go to one accumulator, whose sums are added to a total every few steps (the registers of the smaller products'
+// accumulators) instead of running through the whole reduction.
+//
+// Half precision has five bits of exponent, so both tensors are scaled by a power of two that brings their largest
+// magnitude to [2^14, 2^15), found by a pass of its own.  The smallest step is then 2^-24, at most 2^-38 of the tensor's
+// largest magnitude.  Values well below that magnitude have fewer bits left: the pass also finds the smallest of the
+// largest magnitudes of its blocks (zeros aside; a block: 64 neighbours, or values of one channel, see
+// kst_split_range.hip), and a tensor in which one such block lies more than 2^13 below the whole (or with a value that is not
+// finite) goes through the three-part kernels, in the same launches.
+constexpr int RANGE_WGS = 256, RANGE_THREADS = 512;
+constexpr int RANGE_BLOCKS_APART = 13;       // powers of two
+
+// Of one workgroup's share of a tensor: bits of the largest magnitude; of the smallest block's, less one (no such block: all ones).
+struct RangePart {
+    unsigned most, least;
+};
+static_assert(RANGE_WGS * sizeof(RangePart) == SPLIT_RANGE_BYTES, "");
+// What a launch reads in front of its operands: `two` where they have two half-precision parts, scaled by 2^ea and 2^eb.
+struct SplitHead {
+    unsigned two;
+    int ea, eb;
+    unsigned pad;
+};
+constexpr unsigned SPLIT_TWO = 0xffffffffu;  // (two bfloat16 NaNs that no third part is: see quiet())
+
+// Eight values times 2^e -> their two half-precision parts.
+__device__ __forceinline__ void split2(const float (&v)[8], int e, bf16x8 &p0, bf16x8 &p1)
+{
+    typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+    halfx8 h, l;
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {
+        const floatx2 t = {__builtin_amdgcn_ldexpf(v[j], e), __builtin_amdgcn_ldexpf(v[j + 1], e)};
+        const halfx2 r = __builtin_convertvector(t, halfx2);
+        h[j] = r[0];
+        h[j + 1] = r[1];
+        l[j] = (_Float16)__builtin_fmaf((float)r[0], -1.0f, t[0]);         // (exact: one rounding, to half precision)
+        l[j + 1] = (_Float16)__builtin_fmaf((float)r[1], -1.0f, t[1]);
+    }
+    p0 = __builtin_bit_cast(bf16x8, h);
+    p1 = __builtin_bit_cast(bf16x8, l);
+}
+
+// NaNs of third parts -> one that is not part of SPLIT_TWO.
+__device__ __forceinline__ bf16x8 quiet(bf16x8 p)
+{
+    typedef unsigned short shortx8 __attribute__((ext_vector_type(8)));
+    shortx8 b = __builtin_bit_cast(shortx8, p);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) b[j] = (b[j] & 0x7fffu) > 0x7f80u ? (unsigned short)0x7fc0u : b[j];
+    return __builtin_bit_cast(bf16x8, b);
+}
+
+// The scales of two tensors from the shares that split_range wrote, by a whole workgroup of 256.
+__device__ __forceinline__ SplitHead split_head(const RangePart *__restrict__ part, int wgs_a)
+{
+    static_assert(RANGE_WGS == 256, "one share per thread");
+    __shared__ RangePart waves[2][4];
+    const int tid = threadIdx.x;
+    const RangePart mine = part[tid];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const bool in = (tid < wgs_a) == (t == 0);
+        unsigned most = in ? mine.most : 0u, least = in ? mine.least : ~0u;
+#pragma unroll
+        for (int d = 1; d < 64; d *= 2) {
+            most = max(most, (unsigned)__shfl_xor((int)most, d));
+            least = min(least, (unsigned)__shfl_xor((int)least, d));
+        }
+        if ((tid & 63) == 0) waves[t][tid >> 6] = {most, least};
+    }
+    __syncthreads();
+    SplitHead h = {SPLIT_TWO, 0, 0, 0u};
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        unsigned most = 0u, least = ~0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            most = max(most, waves[t][i].most);
+            least = min(least, waves[t][i].least);
+        }
+        if (most >= 0x7f800000u) h.two = 0u;
+        if (most == 0u || most >= 0x7f800000u) continue;
+        const int top = __builtin_amdgcn_frexp_expf(__uint_as_float(most));
+        if (top - __builtin_amdgcn_frexp_expf(__uint_as_float(least + 1u)) > RANGE_BLOCKS_APART) h.two = 0u;
+        (t == 0 ? h.ea : h.eb) = 15 - top;
+    }
+    return h;
+}
+// ... and what the launch that wrote the operands left of them at `end` - 16.
+__device__ __forceinline__ SplitHead read_head(const char *__restrict__ end)
+{
+    const uint4 v = *reinterpret_cast<const uint4 *>(end - 16);
+    return {(unsigned)__builtin_amdgcn_readfirstlane((int)v.x), __builtin_amdgcn_readfirstlane((int)v.y),
+            __builtin_amdgcn_readfirstlane((int)v.z), 0u};
+}
+
+// Totals of accumulator blocks that a kernel's registers have no room for, in LDS: a lane's own cells, 16 bytes at a time.  (Not
+// by LDS atomics: those took the forward kernel from 300 to 1240 us on 128 x 512 x 256 x 16 x 16, n = 4.)
+template <int THREADS>
+struct LdsTotals {
+    float4 *cells;                           // this lane's first
+    __device__ __forceinline__ void clear(int block) const
+    {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) cells[(block * 4 + q) * THREADS] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    __device__ __forceinline__ void add(int block, const floatx16 &v) const
+    {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float4 t = cells[(block * 4 + q) * THREADS];
+            t.x += v[4 * q];
+            t.y += v[4 * q + 1];
+            t.z += v[4 * q + 2];
+            t.w += v[4 * q + 3];
+            cells[(block * 4 + q) * THREADS] = t;
+        }
+    }
+    __device__ __forceinline__ void add_to(int block, floatx16 &v) const
+    {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 t = cells[(block * 4 + q) * THREADS];
+            v[4 * q] += t.x;
+            v[4 * q + 1] += t.y;
+            v[4 * q + 2] += t.z;
+            v[4 * q + 3] += t.w;
+        }
+    }
+};
+
+// Positions of an unframed map of edge N that meet each tap of one axis inside a map of edge M, padding factor P, all taps.
+inline double taps_inside(int N, int n, int P, int M)
+{
+    int hits = 0;
+    for (int u = 0; u < n; ++u) {
+        const int lo = P >= u ? 0 : (u - P + 1) / 2, hi = M - 1 + u - P < 0 ? -1 : (M - 1 + u - P) / 2;
+        const int last = hi < N - 1 ? hi : N - 1;
+        hits += last >= lo ? last - lo + 1 : 0;
+    }
+    return hits;
+}
+
 // A value that is the same in all lanes, where the compiler cannot know (arguments of a function that is not inlined).
 __device__ __forceinline__ int same(int v) { return __builtin_amdgcn_readfirstlane(v); }
 

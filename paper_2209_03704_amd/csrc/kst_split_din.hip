@@ -1,5 +1,6 @@
 // Input gradient on the bf16 matrix cores (g and fp32 weights split into three bfloat16 parts, see kst_split_common.h;
-// bfloat16 weights are their own only part, which leaves three partial products of six).
+// bfloat16 weights are their own only part, which leaves three partial products of six; large fp32 layers: two parts of half
+// precision).
 //
 //   din[b][ci][a][c] = sum_co sum_u sum_v g[b][co][2 (a + q) - u][2 (c + q) - v] * w[co][ci][u][v]
 //
@@ -13,7 +14,7 @@
 // rows of g that the tile's positions touch are split once per chunk into LDS as [part][channel half][row][column
 // parity][column / 2][8 channels]: a tap's positions are two columns apart in g and neighbours there, and a lane's MFMA
 // operand is one 16-byte read.  Two stages, one barrier per chunk.  64 x 512 x 256 x 8 x 8, n = 4,
-// P = 2: 85 us where the fp32 multiplies took 162; with bfloat16 weights 64 x 256 x 128 x 16 x 16: 55 against 155.
+// P = 2: 82 us with three parts where the fp32 multiplies took 162, 61 with two; with bfloat16 weights 64 x 256 x 128 x 16 x 16: 55 against 155.
 #include "kst_din_store.h"
 
 namespace kst {
@@ -25,9 +26,6 @@ constexpr int D_KC = 16;                 // output channels per chunk
 constexpr int D_TM = 128;                // positions per tile
 constexpr int D_IP = 832;                // cells (rows x columns of g) a stage can hold: with n = 3 maps of 4 to 28, 32, 33, 64
                                          // and 128, n = 4: 4 to 17, 19, 22, 32, 64, n = 5: 8, 16, 32; others are not taken
-constexpr int D_HALF = D_IP * 16;
-constexpr int D_PART = 2 * D_HALF;
-constexpr int D_STAGE = 3 * D_PART;      // 79872 bytes
 constexpr unsigned D_OUTSIDE = 0x80000000u;
 constexpr size_t D_SLOT1 = (size_t)D_THREADS * 64;      // floats of a workgroup's sums, per row block
 
@@ -36,14 +34,34 @@ struct DinParams : DinShape {
     int ip;                // cells staged
     int tiles_m, tiles_ci, chunks;
     unsigned g_bytes, w_bytes;
+    int two;               // operands of two half-precision parts where their ranges allow
+    int range_share;       // workgroups of the ranges' launch that took the weights
 };
 
-template <int n, int RB, int WP, int NT>
-__device__ __forceinline__ void din_accumulate(const float *__restrict__ g, const void *__restrict__ w_split,
-                                               const DinParams &p, char *lds, int tile_m, int tile_ci, int k0, int k1,
-                                               int tid, floatx16 (&acc)[RB][4])
+// LDS of a kernel that stages NT cells per lane: two stages, and totals (below) of some of two row blocks' accumulators.
+constexpr int din_half(int NT) { return (NT == 7 ? D_IP : NT * 128) * 16; }           // bytes: one channel half of one part
+constexpr int din_stage(int NT, int parts) { return parts * 2 * din_half(NT); }
+constexpr int din_lds_totals(int NT, int RB) { return RB == 1 ? 0 : NT == 7 ? 3 : 4; }
+constexpr int din_lds(int NT, int RB)
 {
-    constexpr int TAPS = n * n;
+    const int two = 2 * din_stage(NT, 2) + din_lds_totals(NT, RB) * 16 * D_THREADS * 4, three = 2 * din_stage(NT, 3);
+    return two > three ? two : three;
+}
+
+// Two parts: is block b of the accumulators added to the total during this tap of a chunk?  Once every eight taps.
+constexpr int D_SEGMENT = 8;
+constexpr bool din_flushed(int n, int blocks, int tap, int b)
+{
+    return tap < n * n / D_SEGMENT * D_SEGMENT && b * D_SEGMENT == tap % D_SEGMENT * blocks;
+}
+
+// WP: parts of the weights, PARTS: of g (three bfloat16 ones, or two of half precision, scaled as the head says).
+template <int n, int RB, int WP, int NT, int PARTS>
+__device__ __forceinline__ void din_accumulate(const float *__restrict__ g, const void *__restrict__ w_split,
+                                               const DinParams &p, const SplitHead &head, char *lds, int tile_m, int tile_ci,
+                                               int k0, int k1, int tid, floatx16 (&acc)[RB][4])
+{
+    constexpr int TAPS = n * n, HALF = din_half(NT), PART = 2 * HALF, STAGE = din_stage(NT, PARTS);
     constexpr int SETS = n == 4 ? 4 / RB : n;         // divides the taps
     constexpr int TAP = WP * 1024;                    // bytes of a tap's operands for 32 input and 16 output channels
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -58,7 +76,7 @@ __device__ __forceinline__ void din_accumulate(const float *__restrict__ g, cons
     for (int pb = 0; pb < 4; ++pb) {
         const int m = min(m0 + pb * 32 + l32, p.Mtot - 1);
         const int mb = m / NN, rem = m - mb * NN, ma = rem / p.N, mc = rem - ma * p.N;
-        xa[pb] = ((mb * p.H + 2 * ma - V0) * pitch + mc) * 16 + kk * D_HALF;
+        xa[pb] = ((mb * p.H + 2 * ma - V0) * pitch + mc) * 16 + kk * HALF;
     }
 
     // Staging: wave -> channel half wave & 1, cells (wave >> 1) * 64 + lane + 128 k (the last 64 of 832: by both waves
@@ -91,12 +109,12 @@ __device__ __forceinline__ void din_accumulate(const float *__restrict__ g, cons
     };
     auto write_x = [&](auto kc, int stage) {
         constexpr int k = decltype(kc)::value;
-        bf16x8 a, b, c;
-        split3(x_reg[k], a, b, c);
-        char *d = lds + stage + half * D_HALF + cell_of(k) * 16;
-        *reinterpret_cast<bf16x8 *>(d) = a;
-        *reinterpret_cast<bf16x8 *>(d + D_PART) = b;
-        *reinterpret_cast<bf16x8 *>(d + 2 * D_PART) = c;
+        bf16x8 part[3];
+        if constexpr (PARTS == 2) split2(x_reg[k], head.eb, part[0], part[1]);
+        else split3(x_reg[k], part[0], part[1], part[2]);
+        char *d = lds + stage + half * HALF + cell_of(k) * 16;
+#pragma unroll
+        for (int i = 0; i < PARTS; ++i) *reinterpret_cast<bf16x8 *>(d + i * PART) = part[i];
     };
 
     bf16x8 wp[SETS][RB][WP];
@@ -114,7 +132,7 @@ __device__ __forceinline__ void din_accumulate(const float *__restrict__ g, cons
                 wp[q % SETS][rb][part] = load_bf16x8(wbuf, lane * 16 + part * 1024, w_base[rb] + (unsigned)(chunk * TAPS + q) * TAP);
     };
 
-    bf16x8 xf[4][3];
+    bf16x8 xf[4][PARTS];
     int stage = 0;
     auto read_x = [&](auto qc, auto partc) {          // taps are walked row by row, columns of one parity together
         constexpr int q = decltype(qc)::value, part = decltype(partc)::value;
@@ -123,16 +141,27 @@ __device__ __forceinline__ void din_accumulate(const float *__restrict__ g, cons
 #pragma unroll
         for (int pb = 0; pb < 4; ++pb)
             xf[pb][part] = *reinterpret_cast<const bf16x8 *>(lds + stage + xa[pb] + (h * 2 + (x & 1)) * p.W2 * 16 +
-                                                             (x >> 1) * 16 + part * D_PART);
+                                                             (x >> 1) * 16 + part * PART);
     };
 
-    floatx16 low[RB][4];
+    // (two parts: the total to which the largest products' sums are added, a block per tap or two, before they start again)
+    // (some totals are in LDS: beside two accumulators of each block registers are short)
+    constexpr int BLOCKS = 4 * RB, TR = BLOCKS - din_lds_totals(NT, RB);
+    const LdsTotals<D_THREADS> spare = {reinterpret_cast<float4 *>(lds + 2 * STAGE) + tid};
+    floatx16 low[RB][4], total[TR], zeros;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) zeros[v] = 0.0f;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int pb = 0; pb < 4; ++pb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[rb][pb][v] = low[rb][pb][v] = 0.0f;
+            for (int v = 0; v < 16; ++v) {
+                acc[rb][pb][v] = low[rb][pb][v] = 0.0f;
+                if (rb * 4 + pb < TR) total[rb * 4 + pb][v] = 0.0f;
+            }
+    if constexpr (PARTS == 2)
+        static_for<BLOCKS - TR>([&](auto bc) { spare.clear(decltype(bc)::value); });
 
     using std::integral_constant;
     constexpr auto write_tap = [](int k) { return TAPS - 2 - k % ((TAPS - 1) / 2); };
@@ -146,7 +175,7 @@ __device__ __forceinline__ void din_accumulate(const float *__restrict__ g, cons
     static_for<NT>([&](auto kc) { write_x(kc, 0); });
     fetch_x(min(k0 + 1, k1 - 1));
     __syncthreads();
-    static_for<3>([&](auto pc) { read_x(integral_constant<int, 0>{}, pc); });
+    static_for<PARTS>([&](auto pc) { read_x(integral_constant<int, 0>{}, pc); });
 
     for (int chunk = k0; chunk < k1; ++chunk) {
         const int next = min(chunk + 1, k1 - 1), after = min(chunk + 2, k1 - 1);
@@ -155,30 +184,42 @@ __device__ __forceinline__ void din_accumulate(const float *__restrict__ g, cons
             constexpr bool last = q == TAPS - 1;
             if constexpr (last) {
                 // Every wave has written its share of the next chunk's stage and is done reading this one's.
-                stage = D_STAGE - stage;
+                stage = STAGE - stage;
                 __syncthreads();
                 fetch_x(after);
             }
             fetch_w(integral_constant<int, (q + SETS - 1) % TAPS>{}, q + SETS - 1 < TAPS ? chunk : next);
             static_for<NT>([&](auto kc) {
-                if constexpr (write_tap(decltype(kc)::value) == q) write_x(kc, D_STAGE - stage);
+                if constexpr (write_tap(decltype(kc)::value) == q) write_x(kc, STAGE - stage);
             });
-            constexpr int MF = 4 * RB * (WP == 1 ? 3 : 6);
-            static_for<3>([&](auto xc) {              // parts of g, smallest first, against the parts that matter
-                constexpr int xp = 2 - decltype(xc)::value;
-                static_for<(WP < 3 - xp ? WP : 3 - xp)>([&](auto wc) {
-                    constexpr int w = (WP < 3 - xp ? WP : 3 - xp) - 1 - decltype(wc)::value;
-#pragma unroll
-                    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-                        for (int pb = 0; pb < 4; ++pb) {
+            constexpr auto flushed = [](int b) { return PARTS == 2 && din_flushed(n, BLOCKS, q, b); };
+            static_for<BLOCKS>([&](auto bc) {
+                constexpr int b = decltype(bc)::value;
+                if constexpr (flushed(b)) {
+                    if constexpr (b < TR) total[b] += acc[b / 4][b % 4];
+                    else spare.add(b - TR, acc[b / 4][b % 4]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            });
+            constexpr int MF = BLOCKS * (PARTS == 2 ? 1 + WP : WP == 1 ? 3 : 6);
+            static_for<PARTS>([&](auto xc) {          // parts of g, smallest first, against the parts that matter
+                constexpr int xp = PARTS - 1 - decltype(xc)::value, ws = WP < PARTS - xp ? WP : PARTS - xp;
+                static_for<ws>([&](auto wc) {
+                    constexpr int w = ws - 1 - decltype(wc)::value;
+                    static_for<BLOCKS>([&](auto bc) {
+                        constexpr int b = decltype(bc)::value, rb = b / 4, pb = b % 4;
+                        if constexpr (flushed(b) && w + xp == 0) {
+                            acc[rb][pb] = mfma16<true>(wp[q % SETS][rb][w], xf[pb][xp], zeros);
+                        } else {
                             floatx16 &sum = w + xp == 0 ? acc[rb][pb] : low[rb][pb];
-                            sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wp[q % SETS][rb][w], xf[pb][xp], sum, 0, 0, 0);
+                            sum = mfma16<PARTS == 2>(wp[q % SETS][rb][w], xf[pb][xp], sum);
                         }
+                    });
                 });
                 read_x(integral_constant<int, last ? 0 : q + 1>{}, integral_constant<int, xp>{});
             });
-            constexpr int valu = (16 + 56 * staged_in(q) + MF - 1) / MF;
+            constexpr int valu =
+                (16 + (PARTS == 2 ? 32 : 56) * staged_in(q) + MF - 1) / MF;
             static_for<MF>([&](auto) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // MFMA
                 __builtin_amdgcn_sched_group_barrier(0x002, valu, 0);   // vector arithmetic
@@ -189,20 +230,29 @@ __device__ __forceinline__ void din_accumulate(const float *__restrict__ g, cons
             __builtin_amdgcn_sched_barrier(0);
         });
     }
+    const int down = -(head.ea + head.eb);
+    static_for<BLOCKS>([&](auto bc) {
+        constexpr int b = decltype(bc)::value;
+        floatx16 &sum = acc[b / 4][b % 4];
+        sum += low[b / 4][b % 4];
+        if constexpr (PARTS == 2) {
+            if constexpr (b < TR) sum += total[b];
+            else spare.add_to(b - TR, sum);
+        }
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int pb = 0; pb < 4; ++pb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[rb][pb][v] = (acc[rb][pb][v] + low[rb][pb][v]) * SPLIT_UNSCALE;
+        for (int v = 0; v < 16; ++v) sum[v] = PARTS == 2 ? __builtin_amdgcn_ldexpf(sum[v], down) : sum[v] * SPLIT_UNSCALE;
+    });
 }
 
-template <int n, int RB, int WP, int NT, class T>
-__global__ void __launch_bounds__(D_THREADS, 1) split_din_kernel(const float *__restrict__ g, const T *__restrict__ w,
-                                                                const void *__restrict__ w_split, float *__restrict__ din,
-                                                                float *__restrict__ ws, DinParams p, EvenShares k)
+extern __shared__ __attribute__((aligned(16))) char split_din_lds[];
+
+template <int n, int RB, int WP, int NT, int PARTS, class T>
+__device__ __forceinline__ void split_din_work(const float *__restrict__ g, const T *__restrict__ w,
+                                               const void *__restrict__ w_split, float *__restrict__ din,
+                                               float *__restrict__ ws, const DinParams &p, const EvenShares &k,
+                                               const SplitHead &head)
 {
-    extern __shared__ __attribute__((aligned(16))) char lds[];
+    char *lds = split_din_lds;
     const int wg = blockIdx.x;
     int whole = wg * k.rounds;
     const int whole_end = whole + k.rounds;
@@ -231,7 +281,7 @@ __global__ void __launch_bounds__(D_THREADS, 1) split_din_kernel(const float *__
         int tid = (int)threadIdx.x;                   // (a fresh copy: nothing of the staging plan is kept across pieces)
         asm volatile("" : "+v"(tid));
         floatx16 acc[RB][4];
-        din_accumulate<n, RB, WP, NT>(g, w_split, p, lds, tile_m, tile_ci, c0, c1, tid, acc);
+        din_accumulate<n, RB, WP, NT, PARTS>(g, w_split, p, head, lds, tile_m, tile_ci, c0, c1, tid, acc);
         const int lane = tid & 63, wave = tid >> 6;
         if (c0 == 0 && c1 == p.chunks) {
             static_for<4>([&](auto pbc) {
@@ -253,6 +303,22 @@ __global__ void __launch_bounds__(D_THREADS, 1) split_din_kernel(const float *__
             });
         }
     }
+}
+
+// TWO: both kinds of parts in one launch, told apart by the head.
+template <int n, int RB, int WP, int NT, class T, bool TWO>
+__global__ void __launch_bounds__(D_THREADS, 1) split_din_kernel(const float *__restrict__ g, const T *__restrict__ w,
+                                                                const void *__restrict__ w_split, float *__restrict__ din,
+                                                                float *__restrict__ ws, DinParams p, EvenShares k)
+{
+    if constexpr (TWO) {
+        const SplitHead head = read_head((const char *)w_split + p.w_bytes);
+        if (head.two == SPLIT_TWO) {
+            split_din_work<n, RB, 2, NT, 2>(g, w, w_split, din, ws, p, k, head);
+            return;
+        }
+    }
+    split_din_work<n, RB, WP, NT, 3>(g, w, w_split, din, ws, p, k, {0u, 0, 0, 0u});
 }
 
 // One workgroup per (shared tile, block of positions, row block): the sum of the tile's slots in workgroup order.
@@ -295,10 +361,17 @@ __global__ void __launch_bounds__(D_THREADS, 6) split_din_sum_kernel(const float
 // leave between them are the other u's (15 -> 8.6 us for 512 x 256 x 4 x 4 against one workgroup per (block,
 // chunk) turning the weights in LDS).
 template <int n, int WP, class T>
-__global__ void __launch_bounds__(256) split_din_weights_kernel(const T *__restrict__ w, char *__restrict__ w_split, DinParams p,
-                                                                unsigned tasks)
+__global__ void __launch_bounds__(256) split_din_weights_kernel(const T *__restrict__ w, char *__restrict__ w_split,
+                                                                const RangePart *__restrict__ range, DinParams p, unsigned tasks)
 {
     constexpr int NN = n * n;
+    SplitHead head = {0u, 0, 0, 0u};
+    if (p.two) {
+        head = split_head(range, p.range_share);
+        if (head.two && blockIdx.x == 0 && threadIdx.x == 0)
+            *reinterpret_cast<uint4 *>(w_split + p.w_bytes - 16) = make_uint4(head.two, (unsigned)head.ea, (unsigned)head.eb, 0u);
+    }
+    const int parts = head.two ? 2 : WP;
     const unsigned task = blockIdx.x * 4u + (threadIdx.x >> 6);
     if (task >= tasks) return;
     const unsigned block = task / n, u = task - block * n;
@@ -310,7 +383,7 @@ __global__ void __launch_bounds__(256) split_din_weights_kernel(const T *__restr
 #pragma unroll
         for (int v = 0; v < n; ++v)
             t[j][v] = ci < p.Cin && co + j < p.Cout ? value_of(w + ((size_t)(co + j) * p.Cin + ci) * NN + u * n + v) : 0.0f;
-    char *d = w_split + ((size_t)block * NN + (n - 1 - u) * n) * (WP * 1024) + lane * 16;
+    char *d = w_split + ((size_t)block * NN + (n - 1 - u) * n) * (parts * 1024) + lane * 16;
 #pragma unroll
     for (int i = 0; i < n; ++i) {
         constexpr int even = (n + 1) / 2;
@@ -319,9 +392,15 @@ __global__ void __launch_bounds__(256) split_din_weights_kernel(const T *__restr
 #pragma unroll
         for (int j = 0; j < 8; ++j) v[j] = t[j][n - 1 - x];
         bf16x8 part[3];
-        split3(v, part[0], part[1], part[2]);
+        if (head.two) {
+            split2(v, head.ea, part[0], part[1]);
+        } else {
+            split3(v, part[0], part[1], part[2]);
+            part[2] = quiet(part[2]);
+        }
 #pragma unroll
-        for (int k = 0; k < WP; ++k) *reinterpret_cast<bf16x8 *>(d + (i * WP + k) * 1024) = part[k];
+        for (int k = 0; k < WP; ++k)
+            if (k < parts) *reinterpret_cast<bf16x8 *>(d + (i * parts + k) * 1024) = part[k];
     }
 }
 
@@ -365,6 +444,7 @@ DinPlan din_plan(const Shape &s, bool odd, kst_dtype dt)
     const size_t w_bytes = (size_t)((s.Cin + 31) / 32) * p.chunks * n * n * r.wp * 1024;
     p.g_bytes = (unsigned)g_bytes;
     p.w_bytes = (unsigned)w_bytes;
+    p.range_share = split_range_share((size_t)s.Cin * s.Cout * n * n, g_bytes / sizeof(float));
     r.w_bytes = w_bytes;
     const unsigned long long tiles = (unsigned long long)p.tiles_m * p.tiles_ci, units = tiles * (unsigned)p.chunks;
     r.k.chunks = p.chunks;
@@ -373,6 +453,15 @@ DinPlan din_plan(const Shape &s, bool odd, kst_dtype dt)
     r.k.passes = (int)(tiles - (unsigned long long)r.k.rounds * S_GRID);
     r.k.taps0 = r.k.taps1 = 1;
     const unsigned long long all = (unsigned long long)r.k.passes * (unsigned)p.chunks;
+    // Two half-precision parts where that is no less exact than three bfloat16 ones, as in the forward kernel: from 36 steps
+    // of a chain (without taps that meet no g) the error was 0.35 to 1.0 of the other's on 2008 random layers, below 20 up to
+    // 1.6 times it.  Times as fast on 1084 of them with 4 x 4 and 5 x 5 kernels: 1.17 in the mean, never slower (64 x 512 x 256 x
+    // 8 x 8, n = 4, P = 2: 60 us, 82 with three parts); 3 x 3 kernels: 0.89 to 1.2, 305 of 924 slower.  bfloat16 weights: two
+    // partial products for three, which the ranges' pass outweighs (0.97).
+    const double share = (double)r.k.passes * p.chunks / S_GRID, piece = share < p.chunks ? share : p.chunks;
+    const double inside = taps_inside(p.N, n, 2 * s.frame - (odd ? 1 : 0), p.M) / ((double)p.N * n);
+    const double steps = n * n * ((double)r.k.rounds * S_GRID * p.chunks + r.k.passes * piece) / (double)tiles * inside * inside;
+    p.two = n > 3 && r.wp == 3 && steps >= 36.0 && (size_t)p.Mtot * s.Cin * sizeof(float) >= SPLIT_RANGE_BYTES;
     r.k.per = (int)(all / (unsigned)r.k.grid);
     r.k.more = (int)(all % (unsigned)r.k.grid);
     r.ok = n >= 3 && n <= 5 && p.ip <= D_IP && g_bytes < (1u << 31) && w_bytes < (1u << 31) && tiles <= (1u << 22) &&
@@ -385,17 +474,27 @@ size_t din_weight_bytes(const DinPlan &pl) { return (pl.w_bytes + 255) & ~(size_
 template <int n, int RB, int WP, int NT, class T>
 hipError_t din_launch(const float *g, const T *w, float *din, char *ws, const DinPlan &pl, hipStream_t stream)
 {
-    const int lds = 2 * D_STAGE;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&split_din_kernel<n, RB, WP, NT, T>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    constexpr int lds = din_lds(NT, RB);
+    auto kernel = &split_din_kernel<n, RB, WP, NT, T, false>;
+    if constexpr (n > 3 && WP == 3)
+        if (pl.p.two) kernel = &split_din_kernel<n, RB, WP, NT, T, true>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
-    const unsigned tasks = (unsigned)((pl.p.Cin + 31) / 32) * (unsigned)pl.p.chunks * n;
-    hipLaunchKernelGGL((split_din_weights_kernel<n, WP, T>), dim3((tasks + 3) / 4), dim3(256), 0, stream, w, ws, pl.p, tasks);
+    const DinParams &p = pl.p;
+    if (p.two) {                                      // (the shares lie in the result until the weights are split)
+        if constexpr (std::is_same_v<T, float>)
+            e = launch_split_range({w, (size_t)p.Cin * p.Cout * n * n, (size_t)p.Cin * n * n, false},
+                                   {g, p.g_bytes / sizeof(float), 0, false}, din, stream);
+        if (e != hipSuccess) return e;
+    }
+    const unsigned tasks = (unsigned)((p.Cin + 31) / 32) * (unsigned)p.chunks * n;
+    hipLaunchKernelGGL((split_din_weights_kernel<n, WP, T>), dim3((tasks + 3) / 4), dim3(256), 0, stream, w, ws,
+                       (const RangePart *)din, p, tasks);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     float *slots = (float *)(ws + din_weight_bytes(pl));
-    hipLaunchKernelGGL((split_din_kernel<n, RB, WP, NT, T>), dim3((unsigned)pl.k.grid), dim3(D_THREADS), lds, stream, g, w,
-                       (const void *)ws, din, slots, pl.p, pl.k);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)pl.k.grid), dim3(D_THREADS), lds, stream, g, w,
+                       (const void *)ws, din, slots, p, pl.k);
     e = hipGetLastError();
     if (e != hipSuccess || pl.k.passes == 0) return e;
     hipLaunchKernelGGL((split_din_sum_kernel<n, RB, T>), dim3(4u * RB * pl.k.passes), dim3(D_THREADS), 0, stream, g, w, din,

@@ -24,6 +24,11 @@ INPUT_GRADIENT = [
     (64, 512, 256, 8, 4, 2, "f32"), (60, 260, 250, 11, 4, 1, "f32"), (25, 110, 300, 16, 4, 0, "f32"), (28, 100, 290, 14, 4, 3, "f16"),
     (40, 128, 130, 16, 5, 1, "f32"), (190, 130, 90, 8, 5, 2, "f16"),
 ]
+# Whole batch items and strips, the three shapes of a wave, steps that are no multiple of its segments.
+KERNEL_GRADIENT = [
+    (64, 512, 256, 8, 4, 2, "f32"), (45, 250, 250, 19, 3, 1, "f32"), (21, 300, 130, 21, 5, 0, "f32"), (96, 64, 250, 13, 5, 2, "f32"), (128, 96, 64, 16, 5, 2, "f32"),
+    (64, 256, 128, 16, 4, 2, "f16"), (70, 250, 60, 15, 5, 3, "f16"), (60, 384, 130, 10, 3, 1, "f16"),
+]
 
 
 def _inputs(shape, seed):
@@ -86,6 +91,30 @@ def test_input_gradient(shape):
     assert here <= 1.03 * there, (here, there)
 
 
+@pytest.mark.parametrize("shape", KERNEL_GRADIENT)
+def test_kernel_gradient(shape):
+    B, Cin, Cout, N, n, P, _ = shape
+    x, _, g = (t.to(DEV) for t in _inputs(shape, 47 + B))
+    low = g.clone()
+    low[:, -1] *= 1e-7                                            # (an output channel that the others have no part in)
+    dw, three = kst.kst_backward_weight(x, g, n, P), kst.kst_backward_weight(x, low, n, P)
+    assert not torch.equal(dw[:-1], three[:-1])
+    assert torch.equal(dw, kst.kst_backward_weight(x, g, n, P))
+    cos, cis = sorted({0, 31, Cout // 2, Cout - 2}), sorted({0, 33, Cin // 2, Cin - 1})
+    want = oracle.backward_weight(wl.to_f64(x[:, cis].cpu()), wl.to_f64(g[:, cos].cpu()), n, P)
+    got, other = dw[cos][:, cis], three[cos][:, cis]
+    assert np.abs(got.cpu().numpy() - want).max() <= TOL * np.abs(want).max()
+    # (a few hundred elements: their errors' scatter is a tenth)
+    here, there = _errors(got, other, want)
+    assert here <= 1.2 * there, (here, there)
+    # every element: one random combination of the input channels
+    r = torch.randn(Cin, generator=torch.Generator().manual_seed(4)).double()
+    xr = torch.einsum("bihw,i->bhw", x.cpu().double(), r)[:, None].numpy()
+    want = oracle.backward_weight(np.ascontiguousarray(xr), wl.to_f64(g.cpu()), n, P)[:, 0]
+    mine = (dw.double() * r.to(DEV).view(1, -1, 1, 1)).sum(1).cpu().numpy()
+    assert np.abs(mine - want).max() <= TOL * np.abs(want).max()
+
+
 # A block of 64 neighbours 2^13 below the largest magnitude still has two parts, 2^15 below it has not; what lies beside a
 # value far above everything else, or in a channel far below, is as exact as if it were alone.
 @pytest.mark.parametrize("low", [2.0 ** -12, 2.0 ** -15, 1e-20, 1e-40])
@@ -103,3 +132,82 @@ def test_ranges(low):
     got = din[:2].cpu().numpy().astype(np.float64)
     for i in range(2):
         assert np.abs(got[i] - want[i]).max() <= max(TOL * np.abs(want[i]).max(), 1e-44)
+
+
+@pytest.mark.parametrize("low", [2.0 ** -10, 2.0 ** -16, 1e-7, 1e-30])
+def test_a_small_channel(low):
+    """A channel of the result that is far smaller than the others, by its weights or its share of an operand, maps of 4 x 4
+    included: as exact by itself as the whole is."""
+    B, Cin, Cout, N, n, P = FORWARD[0]
+    x, w, _ = (t.to(DEV) for t in _inputs(FORWARD[0], 8))
+    w[37] *= low
+    got = _forward(x, w, P)[:2, 37].cpu().numpy().astype(np.float64)
+    want = oracle.forward(wl.to_f64(x[:2].cpu()), wl.to_f64(w[37:38].cpu()), P)[:, 0]
+    assert np.linalg.norm(got - want) <= 3e-7 * np.linalg.norm(want)
+    for shape in ((64, 512, 256, 8, 4, 2), (300, 300, 260, 4, 4, 2)):
+        x, w, g = (t.to(DEV) for t in _inputs(shape, 9))
+        N, n, P = shape[3:6]
+        w[:, 37] *= low
+        got = kst.kst_backward_input(g, w, N, P)[:4, 37].cpu().numpy().astype(np.float64)
+        want = oracle.backward_input(wl.to_f64(g[:4].cpu()), wl.to_f64(w[:, 37:38].cpu()), N, P)[:, 0]
+        assert np.linalg.norm(got - want) <= 4e-7 * np.linalg.norm(want)
+        for t, which in ((x, lambda d: d[:64, 37]), (g, lambda d: d[37, :64])):
+            keep = t[:, 37].clone()
+            t[:, 37] *= low
+            got = which(kst.kst_backward_weight(x, g, n, P)).cpu().numpy().astype(np.float64)
+            xs, gs = (x[:, 37:38], g[:, :64]) if t is x else (x[:, :64], g[:, 37:38])
+            want = oracle.backward_weight(wl.to_f64(xs.cpu()), wl.to_f64(gs.cpu()), n, P)
+            want = want[:, 0] if t is x else want[0]
+            assert np.linalg.norm(got - want) <= 4e-7 * np.linalg.norm(want)
+            t[:, 37] = keep
+
+
+def test_zeros_and_values_that_are_not_finite():
+    shape = (64, 512, 256, 8, 4, 2)
+    x, w, g = (t.to(DEV) for t in _inputs(shape, 6))
+    N, n, P = 8, 4, 2
+    assert not kst.kst_backward_input(torch.zeros_like(g), w, N, P).any()
+    assert not kst.kst_backward_weight(x, torch.zeros_like(g), n, P).any()
+    for bad in (float("inf"), float("nan")):
+        h = g.clone()
+        h[3, 2, 8, 8] = bad
+        din, ref = kst.kst_backward_input(h, w, N, P), kst.kst_backward_input(g, w, N, P)
+        assert not torch.isfinite(din[3]).all() and torch.isfinite(din[:3]).all() and torch.isfinite(din[4:]).all()
+        assert float((din[:3] - ref[:3]).abs().max()) <= TOL * float(ref.abs().max())
+        half = x.half()
+        half[0, 1, 2, 3] = bad
+        dw = kst.kst_backward_weight(half, g, n, P)
+        assert not torch.isfinite(dw[:, 1]).all() and torch.isfinite(dw[:, 2:]).all()
+
+
+@pytest.mark.parametrize("name", ["forward", "input", "kernel"])
+def test_replayed_graph(name):
+    """Captured once, replayed with other inputs of the same and of a wide range, each against the eager call."""
+    shape = (31, 600, 200, 16, 4, 0) if name == "forward" else (64, 512, 256, 8, 4, 2)
+    B, Cin, Cout, N, n, P = shape
+    x, w, g = (t.to(DEV) for t in _inputs(shape, 7))
+    dims = (B, Cin, Cout, N, n, P, kst.KST_F32)
+    if name == "forward":
+        src, out = x, torch.empty((B, Cout, 2 * N + 2 * P - n, 2 * N + 2 * P - n), device=DEV)
+        seg, ws = kst.kst_segregate_weights(w), torch.empty(kst.kst_workspace_bytes_padded(*dims), dtype=torch.uint8, device=DEV)
+        call = lambda t, o: kst.kst_forward_seg_padded(t, seg, Cout, n, P, out=o, ws=ws)
+    elif name == "input":
+        src, out = g, torch.empty((B, Cin, N, N), device=DEV)
+        ws = torch.empty(kst.kst_backward_input_workspace_bytes(*dims), dtype=torch.uint8, device=DEV)
+        call = lambda t, o: kst.kst_backward_input(t, w, N, P, din=o, ws=ws)
+    else:
+        src, out = g, torch.empty((Cout, Cin, n, n), device=DEV)
+        ws = torch.empty(kst.kst_backward_weight_workspace_bytes(*dims), dtype=torch.uint8, device=DEV)
+        call = lambda t, o: kst.kst_backward_weight(x, t, n, P, dw=o, ws=ws)
+    static = src.clone()
+    call(static, out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(static, out)
+    for t in (src, src * 3.0, _wide(src), src * 2.0 ** 30, src):
+        want = call(t, torch.empty_like(out))
+        static.copy_(t)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)

@@ -354,8 +354,12 @@ kst_status kst_forward(const void *in, const void *w, void *out, int B, int Cin,
     void *scratch = nullptr;
     if (!scratch_for(&scratch, seg_bytes, &ws_bytes, stream, least)) return KST_ERR_HIP;
     void *ws = ws_bytes ? (void *)((char *)scratch + seg_bytes) : nullptr;
-    st = kst_segregate_weights(w, scratch, Cin, Cout, n, dtype, stream);
-    if (st == KST_OK)
+    const bool packed = is16(dtype) && choose_path(s, dtype) == KST_PATH_IGEMM && igemm_16_packed_applies(s);
+    if (packed)
+        st = launch_igemm_16_packed(in, scratch, (float *)out, ws, s, dtype == KST_F16, stream, w) == hipSuccess ? KST_OK : KST_ERR_HIP;
+    else
+        st = kst_segregate_weights(w, scratch, Cin, Cout, n, dtype, stream);
+    if (!packed && st == KST_OK)
         st = kst_forward_seg(in, scratch, out, ws, ws_bytes, B, Cin, Cout, N, n, dtype, KST_PATH_AUTO, stream);
     if (hipFreeAsync(scratch, stream) != hipSuccess && st == KST_OK) st = KST_ERR_HIP;
     return st;
@@ -550,8 +554,16 @@ kst_status kst_forward_padded(const void *in, const void *w, void *out, int B, i
     };
     void *scratch = nullptr;
     if (!scratch_for(&scratch, seg_bytes, &ws_bytes, stream, least)) return KST_ERR_HIP;
-    st = kst_segregate_weights(w, scratch, Cin, Cout, n, dtype, stream);
-    if (st == KST_OK)
+    // (a repacked layer has the frame in its input's copy and stores what is wanted of the map: nothing else in its workspace)
+    const bool packed = is16(dtype) && f.chosen == KST_PATH_IGEMM && f.s.frame > 0 && igemm_16_packed_applies(f.s);
+    if (packed)
+        st = launch_igemm_16_packed(in, scratch, (float *)out, (char *)scratch + seg_bytes, f.s, dtype == KST_F16, stream, w) ==
+                     hipSuccess
+                 ? KST_OK
+                 : KST_ERR_HIP;
+    else
+        st = kst_segregate_weights(w, scratch, Cin, Cout, n, dtype, stream);
+    if (!packed && st == KST_OK)
         st = kst_forward_seg_padded(in, scratch, out, ws_bytes ? (char *)scratch + seg_bytes : nullptr, ws_bytes, B, Cin,
                                     Cout, N, n, P, dtype, KST_PATH_AUTO, stream);
     if (hipFreeAsync(scratch, stream) != hipSuccess && st == KST_OK) st = KST_ERR_HIP;

@@ -18,6 +18,7 @@
 // two launches of 13 us together at the least.  24 x 100 x 52 x 19 x 19, n = 3, P = 1: 46.9 -> 14.5 us (pack 4.9, multiply
 // 9.7); 64 x 256 x 128 x 16 x 16, n = 4, P = 2: 54 -> 32 us (8 and 24).  Large maps are bound by their stores: 35 x 72 x 326 x
 // 23 x 23, n = 3, P = 3, 109 MB of output: 140 -> 48 us.  Error against 64 bits over 120 layers: 0.83 of the other kernels'.
+#include "kst_segregate.h"
 #include "kst_split_common.h"
 
 namespace kst {
@@ -40,10 +41,9 @@ struct PackedParams : IgemmParams {
 
 // in[B][Cin][N0][N0] -> x[B][chunk][N][N][16], N = N0 + 2 q: a lane takes two neighbouring pixels (rows of x are cut
 // into pairs) of eight channels, four bytes of a tensor row per load whatever its alignment.
-__global__ void __launch_bounds__(256) pack_input_kernel(const uint16_t *__restrict__ in, char *__restrict__ x,
-                                                         PackedParams p, unsigned total)
+__device__ __forceinline__ void pack_pair(const uint16_t *__restrict__ in, char *__restrict__ x, const PackedParams &p,
+                                          unsigned i, unsigned total)
 {
-    const unsigned i = blockIdx.x * 256u + threadIdx.x;
     if (i >= total) return;
     const unsigned pairs = ((unsigned)p.N + 1) / 2, at = i >> 1;
     const unsigned line = at / pairs, col = 2 * (at - line * pairs);          // (batch item, chunk, row); first column
@@ -74,6 +74,23 @@ __global__ void __launch_bounds__(256) pack_input_kernel(const uint16_t *__restr
     if (col + 1 < (unsigned)p.N)
         *reinterpret_cast<uint4 *>(dst + 32) =
             make_uint4(z[0] | z[1] << 16, z[2] | z[3] << 16, z[4] | z[5] << 16, z[6] | z[7] << 16);
+}
+
+__global__ void __launch_bounds__(256) pack_input_kernel(const uint16_t *__restrict__ in, char *__restrict__ x,
+                                                         PackedParams p, unsigned total)
+{
+    pack_pair(in, x, p, blockIdx.x * 256u + threadIdx.x, total);
+}
+
+// ... and weights as they come segregated in the same launch, by the workgroups past the first `blocks`: neither waits for
+// the other (24 x 100 x 52 x 19 x 19, n = 3, P = 1, half precision: a call of kst_forward_padded 34 -> 30 us).
+__global__ void __launch_bounds__(256) pack_and_segregate_kernel(const uint16_t *__restrict__ in, char *__restrict__ x,
+                                                                 PackedParams p, unsigned total, unsigned blocks,
+                                                                 const uint16_t *__restrict__ w, uint16_t *__restrict__ w_seg,
+                                                                 SegGeom g)
+{
+    if (blockIdx.x < blocks) pack_pair(in, x, p, blockIdx.x * 256u + threadIdx.x, total);
+    else segregate_one(w, w_seg, g, (blockIdx.x - blocks) * 256u + threadIdx.x);
 }
 
 // A workgroup: 32 output channels x four waves of PB blocks of 32 positions, four classes.  (Two waves along the channels
@@ -397,13 +414,21 @@ size_t igemm_16_packed_workspace_bytes(const Shape &s)
 }
 
 hipError_t launch_igemm_16_packed(const void *in, const void *w_seg, float *out, void *ws, const Shape &s, bool f16,
-                                  hipStream_t stream)
+                                  hipStream_t stream, const void *w)
 {
     const PackedPlan r = plan(s);
     if (!r.ok) return hipErrorInvalidValue;
     char *x = (char *)ws;
     const unsigned total = (unsigned)((size_t)s.B * r.p.chunks * s.N * ((s.N + 1) / 2) * 2);
-    hipLaunchKernelGGL(pack_input_kernel, dim3((total + 255) / 256), dim3(256), 0, stream, (const uint16_t *)in, x, r.p, total);
+    const unsigned blocks = (total + 255) / 256;
+    if (w) {
+        const SegGeom g = seg_geom(s.Cin, s.Cout, s.n, f16 ? KST_F16 : KST_BF16);
+        hipLaunchKernelGGL(pack_and_segregate_kernel, dim3(blocks + (g.off[4] + 255) / 256), dim3(256), 0, stream,
+                           (const uint16_t *)in, x, r.p, total, blocks, (const uint16_t *)w,
+                           (uint16_t *)const_cast<void *>(w_seg), g);
+    } else {
+        hipLaunchKernelGGL(pack_input_kernel, dim3(blocks), dim3(256), 0, stream, (const uint16_t *)in, x, r.p, total);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     float *dst = r.p.splits > 1 ? (float *)(x + packed_bytes(r)) : out;

@@ -201,8 +201,9 @@ hipError_t launch_igemm_bf16_pp(const void *in, const void *w_seg, float *out, c
 bool igemm_16_packed_applies(const Shape &s);
 double igemm_16_packed_us(const Shape &s);
 size_t igemm_16_packed_workspace_bytes(const Shape &s);
+// w: weights as they come, which the launch then segregates into w_seg first (nullptr: they are).
 hipError_t launch_igemm_16_packed(const void *in, const void *w_seg, float *out, void *ws, const Shape &s, bool f16,
-                                  hipStream_t stream);
+                                  hipStream_t stream, const void *w = nullptr);
 // Layers with at most 64 quad positions in all (one sample of a small map): position blocks of 16.
 // Kernel gradient of layers with at most four input channels on large maps (rows of `in` and `g` staged through LDS,
 // one partial result per workgroup): whether it applies, its scratch, the launch.  An odd padding factor is s.crop = 1

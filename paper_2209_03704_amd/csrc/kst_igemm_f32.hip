@@ -558,6 +558,22 @@ __global__ void __launch_bounds__(G_THREADS) igemm_f32_streamk_sum_kernel(const 
                       L.mb, L.mi, L.mj);
 }
 
+// a + p[0] + p[stride] + ... (count of them, in that order).  Eight loads are on their way together: one after the other, a
+// walk over the partial results of a small tensor is memory's latency times their number (1 x 128 x 3 x 32 x 32, n = 4,
+// P = 2: 6.2 -> 4.2 us for the sums).
+__device__ __forceinline__ float sum_along(const float *__restrict__ p, size_t stride, int count, float a)
+{
+    constexpr int AT_ONCE = 8;
+    for (int s = 0; s < count; s += AT_ONCE) {
+        float v[AT_ONCE];
+#pragma unroll
+        for (int i = 0; i < AT_ONCE; ++i) v[i] = p[(size_t)min(s + i, count - 1) * stride];
+#pragma unroll
+        for (int i = 0; i < AT_ONCE; ++i) a = s + i < count ? a + v[i] : a;
+    }
+    return a;
+}
+
 // Sum the per-split partial outputs (fixed order: deterministic).
 __global__ void __launch_bounds__(256) splitk_reduce_kernel(const float *__restrict__ ws, float *__restrict__ out,
                                                               size_t elems, int splits, Epilogue epi, size_t plane_elems,
@@ -565,8 +581,7 @@ __global__ void __launch_bounds__(256) splitk_reduce_kernel(const float *__restr
 {
     const size_t e = (size_t)blockIdx.x * 256u + threadIdx.x;
     if (e >= elems) return;
-    float a = ws[e];
-    for (int s = 1; s < splits; ++s) a += ws[(size_t)s * elems + e];
+    float a = sum_along(ws + elems + e, elems, splits - 1, ws[e]);
     if (epi_on(epi)) a = epi_apply(a, epi_bias(epi, (int)((e / plane_elems) % (size_t)Cout)), epi.act);
     out[e] = a;
 }
@@ -868,8 +883,7 @@ __global__ void __launch_bounds__(256) splitk_reduce_shares_kernel(const float *
     const int el = threadIdx.x % EL, share = threadIdx.x / EL;
     const size_t e = (size_t)blockIdx.x * EL + el;
     float a = 0.0f;
-    if (e < elems)
-        for (int s = share; s < splits; s += SH) a += ws[(size_t)s * elems + e];
+    if (e < elems) a = sum_along(ws + (size_t)share * elems + e, SH * elems, (splits - share + SH - 1) / SH, a);
     red[share][el] = a;
     __syncthreads();
     if (share == 0 && e < elems) {

@@ -17,8 +17,9 @@
 // 256 accumulator registers; 48 MFMAs per step for 18 loads, one step ahead.  What bounds it is the rate at which the
 // cache of a CU hands over those operands (18 KB per wave and 1536 cycles; each is wanted by two waves).
 // With two parts half the MFMAs want two thirds of the operands, three steps ahead.
-// 64 x 512 x 256 x 8 x 8, n = 4, P = 2: 15 us for the two passes, 81 us here (two parts: 18, 54 and 7 for the ranges) and 9 us for
-// the sums, where framing g, the fp32 multiplies and their sums took 202; with bfloat16 input 64 x 256 x 128 x 16 x 16: 21 + 57 + 9 against 212.
+// 64 x 512 x 256 x 8 x 8, n = 4, P = 2: 8 us for the ranges, 13 for the operands, 53 here (81 with three parts) and 9 for
+// the sums, where framing g, the fp32 multiplies and their sums took 202; with bfloat16 input 64 x 256 x 128 x 16 x 16: 19 + 46 + 9
+// against 212.
 #include "kst_split_common.h"
 
 namespace kst {
@@ -67,23 +68,40 @@ __device__ __forceinline__ void load_four(const T *p, int count, float (&v)[4])
 // per load.
 constexpr int E_COLS = 8;
 
-// Two half-precision parts (one of half precision) where `range` is given and allows; SECOND: src is the tensor whose third
-// parts leave room for the head.
-template <int PARTS, bool SECOND, class T>
-__global__ void __launch_bounds__(256) split_items_kernel(const T *__restrict__ src, char *__restrict__ dst,
-                                                          char *__restrict__ head_end, const RangePart *__restrict__ range,
-                                                          int range_share, int B, int C, int edge, int strips, int rows, int pitch,
-                                                          int first, int groups, unsigned tasks)
+template <class T>
+struct Items {
+    const T *src;
+    char *dst;
+    int C, edge, rows, pitch, first;
+    unsigned tasks;                      // waves
+    unsigned blocks() const { return (tasks + 3) / 4; }
+};
+
+template <class T>
+Items<T> items_of(const T *src, char *dst, int C, int edge, int rows, int pitch, int first, const DwParams &p)
 {
+    return {src, dst, C, edge, rows, pitch, first,
+            (unsigned)((C + 31) / 32) * p.groups * rows * ((edge + E_COLS - 1) / E_COLS)};
+}
+
+// The share of one workgroup.  Two half-precision parts (one of half precision) where `range` is given and allows; SECOND: src is
+// the tensor whose third parts leave room for the head.
+template <int PARTS, bool SECOND, class T>
+__device__ __forceinline__ void split_items(const Items<T> &q, unsigned block, char *__restrict__ head_end,
+                                            const RangePart *__restrict__ range, const DwParams &p)
+{
+    const T *__restrict__ src = q.src;
+    char *__restrict__ dst = q.dst;
+    const int B = p.B, C = q.C, edge = q.edge, strips = p.strips, rows = q.rows, pitch = q.pitch, first = q.first, groups = p.groups;
     SplitHead head = {0u, 0, 0, 0u};
     if (range) {
-        head = split_head(range, range_share);
-        if (SECOND && head.two && blockIdx.x == 0 && threadIdx.x == 0)
+        head = split_head(range, p.range_share);
+        if (SECOND && head.two && block == 0 && threadIdx.x == 0)
             *reinterpret_cast<uint4 *>(head_end - 16) = make_uint4(head.two, (unsigned)head.ea, (unsigned)head.eb, 0u);
     }
     const int parts = !head.two ? PARTS : PARTS == 3 ? 2 : 1, exponent = SECOND ? head.eb : head.ea;
-    unsigned t = blockIdx.x * 4u + (threadIdx.x >> 6);
-    if (t >= tasks) return;
+    unsigned t = block * 4u + (threadIdx.x >> 6);
+    if (t >= q.tasks) return;
     const unsigned runs = (unsigned)(edge + E_COLS - 1) / E_COLS;
     const int x0 = E_COLS * (int)(t % runs);
     t /= runs;
@@ -128,14 +146,14 @@ __global__ void __launch_bounds__(256) split_items_kernel(const T *__restrict__ 
     }
 }
 
-template <int PARTS, bool SECOND, class T>
-hipError_t split_items(const T *src, char *dst, char *head_end, const RangePart *range, int C, int edge, int rows, int pitch,
-                       int first, const DwParams &p, hipStream_t stream)
+// Both tensors in one launch, g's workgroups, which have more to do, first: one after the other they left the chip idle at the
+// end of the first (64 x 512 x 256 x 8 x 8, n = 4, P = 2: 18.1 -> 12.6 us; bfloat16, 64 x 256 x 128 x 16 x 16: 22 -> 19).
+template <int XP, class T>
+__global__ void __launch_bounds__(256) split_items_kernel(Items<T> x, Items<float> g, unsigned g_blocks, char *__restrict__ head_end,
+                                                          const RangePart *__restrict__ range, DwParams p)
 {
-    const unsigned tasks = (unsigned)((C + 31) / 32) * p.groups * rows * ((edge + E_COLS - 1) / E_COLS);
-    hipLaunchKernelGGL((split_items_kernel<PARTS, SECOND, T>), dim3((tasks + 3) / 4), dim3(256), 0, stream, src, dst, head_end,
-                       range, p.range_share, p.B, C, edge, p.strips, rows, pitch, first, p.groups, tasks);
-    return hipGetLastError();
+    if (blockIdx.x < g_blocks) split_items<3, true>(g, blockIdx.x, head_end, range, p);
+    else split_items<XP, false>(x, blockIdx.x - g_blocks, head_end, range, p);
 }
 
 // Partial sums part[split][tap][co][ci].  A wave: TB taps x CB x IB blocks of 32 channels.  XP, GP: parts of the operands (GP =
@@ -558,9 +576,11 @@ hipError_t dw_launch(const T *in, const float *g, float *dw, char *ws, const DwP
         if (e != hipSuccess) return e;
         range = (const RangePart *)dw;
     }
-    e = split_items<XP, false>(in, xf, head_end, range, p.Cin, p.N, p.R, p.R, 0, p, stream);
-    if (e != hipSuccess) return e;
-    e = split_items<3, true>(g, gf, head_end, range, p.Cout, p.M, p.GR, 2 * p.R, p.q2 - p.yo, p, stream);
+    const Items<T> x_items = items_of(in, xf, p.Cin, p.N, p.R, p.R, 0, p);
+    const Items<float> g_items = items_of(g, gf, p.Cout, p.M, p.GR, 2 * p.R, p.q2 - p.yo, p);
+    hipLaunchKernelGGL((split_items_kernel<XP, T>), dim3(x_items.blocks() + g_items.blocks()), dim3(256), 0, stream, x_items,
+                       g_items, g_items.blocks(), head_end, range, p);
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     const dim3 blocks((unsigned)p.splits * p.tiles_co * p.tiles_ci * p.tiles_taps), threads(E_THREADS);
     const void *x = xf, *gp = gf;

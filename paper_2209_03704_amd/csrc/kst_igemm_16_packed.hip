@@ -11,12 +11,12 @@
 // padded layer and zeros past the last channel: what that copy costs the frame's copy cost before.  After that both
 // operands are read in 16-byte groups as they are multiplied: the rows that a tile's positions touch go through LDS
 // (two stages, one barrier per 16 channels, no conflicts: 64 lanes read 2 KB in a row), the segregated weights, whose
-// layout is an operand's already, straight into registers four to eight taps ahead.
+// layout is an operand's already, straight into registers eight to sixteen taps ahead.
 //
 // Measured against the kernels that take the input as it lies in memory, half precision and bfloat16, on 250 random
 // layers of 16 to 1024 channels: 2.1 times as fast (geometric mean, 9 of 10 layers of more than 15 us between 1.2 and 7),
-// two launches of 13 us together at the least.  24 x 100 x 52 x 19 x 19, n = 3, P = 1: 46.9 -> 14.5 us (pack 4.9, multiply
-// 9.7); 64 x 256 x 128 x 16 x 16, n = 4, P = 2: 54 -> 32 us (8 and 24).  Large maps are bound by their stores: 35 x 72 x 326 x
+// two launches of 13 us together at the least.  24 x 100 x 52 x 19 x 19, n = 3, P = 1: 46.9 -> 14.2 us (pack 5.2, multiply
+// 9.0); 64 x 256 x 128 x 16 x 16, n = 4, P = 2: 54 -> 30 us (7 and 23).  Large maps are bound by their stores: 35 x 72 x 326 x
 // 23 x 23, n = 3, P = 3, 109 MB of output: 140 -> 48 us.  Error against 64 bits over 120 layers: 0.83 of the other kernels'.
 #include "kst_segregate.h"
 #include "kst_split_common.h"
@@ -103,8 +103,13 @@ __global__ void __launch_bounds__(K_THREADS, 2) igemm_16_packed_kernel(const cha
     constexpr Order order{};
     constexpr int side = Order::side, TAPS = Order::taps, OFFSETS = Order::offsets;
     constexpr int TM = 128 * PB, STAGE = NT * K_THREADS * 16;
-    // Register sets of the weights: what the sums leave room for.
-    constexpr int SETS = n == 3 ? TAPS : n == 4 ? 8 : 5;
+    // Chunks that the rows and taps that the weights are fetched ahead: what the sums leave registers for.  With one workgroup
+    // per CU, four waves of it, a weight's way from L2 (some 700 cycles) is longer than the multiplies of eight taps and, with 3 x 3 kernels
+    // and one position block, that of the rows longer than a chunk.  Against 8, 7 and 4 taps and one chunk, 12000 random layers (calls with
+    // both launches): n = 3, 4, 5 up to 256 workgroups 1.16, 1.10 and 1.16 times as fast, beyond that, where the workgroups of a CU
+    // hide each other's waits, 1.01, 1.01 and 1.05.
+    constexpr int XSETS = n == 3 && PB == 1 ? 2 : 1;
+    constexpr int AHEAD = n == 3 ? (PB == 2 ? 8 : NT > 3 ? 9 : 16) : n == 4 ? (PB == 2 && NT > 3 ? 12 : 15) : NT > 3 ? 8 : 10;
     extern __shared__ __attribute__((aligned(16))) char lds[];
 
     unsigned id = blockIdx.x;
@@ -143,14 +148,14 @@ __global__ void __launch_bounds__(K_THREADS, 2) igemm_16_packed_kernel(const cha
         const bool ok = group < p.groups && b < p.B;
         x_off[k] = ok ? (unsigned)b * p.chunks * p.plane + ((unsigned)y * p.N + c) * 32u + (group & 1) * 16u : K_OUTSIDE;
     }
-    bf16x8 x_reg[NT];
-    auto fetch_x = [&](int chunk) {
+    bf16x8 x_reg[XSETS][NT];
+    auto fetch_x = [&](auto setc, int chunk) {
 #pragma unroll
-        for (int k = 0; k < NT; ++k) x_reg[k] = load_bf16x8(xbuf, x_off[k], (unsigned)chunk * p.plane);
+        for (int k = 0; k < NT; ++k) x_reg[decltype(setc)::value][k] = load_bf16x8(xbuf, x_off[k], (unsigned)chunk * p.plane);
     };
-    auto write_x = [&](int stage) {
+    auto write_x = [&](auto setc, int stage) {
 #pragma unroll
-        for (int k = 0; k < NT; ++k) *reinterpret_cast<bf16x8 *>(lds + stage + (tid + K_THREADS * k) * 16) = x_reg[k];
+        for (int k = 0; k < NT; ++k) *reinterpret_cast<bf16x8 *>(lds + stage + (tid + K_THREADS * k) * 16) = x_reg[decltype(setc)::value][k];
     };
 
     // Weights of tap q of a chunk: this lane's output channel and eight of the chunk's channels (zeros past the last).
@@ -161,11 +166,11 @@ __global__ void __launch_bounds__(K_THREADS, 2) igemm_16_packed_kernel(const cha
 #pragma unroll
     for (int c = 0; c < 4; ++c)
         w_off[c] = co < p.Cout ? (unsigned)kk * class_taps(n, c) * row + (unsigned)co * 16u : K_OUTSIDE;
-    bf16x8 wf[SETS];
-    auto fetch_w = [&](auto qc, int chunk) {
+    bf16x8 wf[XSETS][TAPS];
+    auto fetch_w = [&](auto setc, auto qc, int chunk) {
         constexpr int q = decltype(qc)::value, c = order.cls[q];
         const unsigned at = p.off[c] * 2u + ((unsigned)chunk * (2 * class_taps(n, c)) + order.local[q]) * row;
-        wf[q % SETS] = load_bf16x8(wbuf, chunk == odd_chunk && kk ? K_OUTSIDE : w_off[c], at);
+        wf[decltype(setc)::value][q] = load_bf16x8(wbuf, chunk == odd_chunk && kk ? K_OUTSIDE : w_off[c], at);
     };
 
     // One position block: a chunk's sums on their own, added to the whole sums after it, so that a long reduction is
@@ -182,16 +187,19 @@ __global__ void __launch_bounds__(K_THREADS, 2) igemm_16_packed_kernel(const cha
     using std::integral_constant;
     using std::bool_constant;
     const int k0 = split * p.chunks_per_split, k1 = min(p.chunks, k0 + p.chunks_per_split);
-    constexpr int AHEAD = SETS - 1;
-    fetch_x(k0);
-    static_for<AHEAD>([&](auto qc) { fetch_w(qc, k0); });
-    write_x(0);
+    const int last = k1 - 1;                                // (past the last chunk: read again, never multiplied)
+    static_for<XSETS>([&](auto sc) { fetch_x(sc, min(k0 + decltype(sc)::value, last)); });
+    static_for<AHEAD>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        fetch_w(integral_constant<int, q / TAPS>{}, integral_constant<int, q % TAPS>{}, min(k0 + q / TAPS, last));
+    });
+    write_x(integral_constant<int, 0>{}, 0);
     int stage = 0;
-    auto multiply_chunk = [&](int chunk, auto freshc) {     // fresh: the partial sums start here
+    auto multiply_chunk = [&](int chunk, auto setc, auto freshc) {     // fresh: the partial sums start here
+        constexpr int set = decltype(setc)::value;
         constexpr bool fresh = decltype(freshc)::value;
-        const int next = min(chunk + 1, k1 - 1);            // (past the last chunk: read again, never multiplied)
         __syncthreads();                                    // this chunk's stage is written, the other one is free
-        fetch_x(next);
+        fetch_x(setc, min(chunk + XSETS, last));
         bf16x8 xf[2][PB];
         auto read_x = [&](auto oc) {
             constexpr int o = decltype(oc)::value;
@@ -203,29 +211,32 @@ __global__ void __launch_bounds__(K_THREADS, 2) igemm_16_packed_kernel(const cha
         static_for<TAPS>([&](auto qc) {
             constexpr int q = decltype(qc)::value, c = order.cls[q], o = order.offset[q];
             if constexpr ((q == 0 || order.offset[q == 0 ? 0 : q - 1] != o) && o + 1 < OFFSETS) read_x(integral_constant<int, o + 1>{});
-            fetch_w(integral_constant<int, (q + AHEAD) % TAPS>{}, q + AHEAD < TAPS ? chunk : next);
+            constexpr int later = (q + AHEAD) / TAPS;       // chunks
+            fetch_w(integral_constant<int, (set + later) % XSETS>{}, integral_constant<int, (q + AHEAD) % TAPS>{},
+                    later ? min(chunk + later, last) : chunk);
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb) {
                 floatx16 &sum = TWO_SUMS ? part[c][TWO_SUMS ? pb : 0] : acc[c][pb];
                 if constexpr (fresh && order.local[q] == 0) {
                     floatx16 zero = {};
-                    sum = mfma16<F16>(wf[q % SETS], xf[o & 1][pb], zero);
+                    sum = mfma16<F16>(wf[set][q], xf[o & 1][pb], zero);
                 } else {
-                    sum = mfma16<F16>(wf[q % SETS], xf[o & 1][pb], sum);
+                    sum = mfma16<F16>(wf[set][q], xf[o & 1][pb], sum);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);              // (left alone, every load is moved down to its use)
         });
         stage = STAGE - stage;
-        write_x(stage);
-    };
-    for (int chunk = k0; chunk < k1; ++chunk) {
-        multiply_chunk(chunk, bool_constant<TWO_SUMS>{});
+        write_x(integral_constant<int, (set + 1) % XSETS>{}, stage);
         if constexpr (TWO_SUMS) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) acc[c][0] += part[c][0];
         }
-    }
+    };
+    int chunk = k0;
+    for (; chunk + XSETS <= k1; chunk += XSETS)
+        static_for<XSETS>([&](auto sc) { multiply_chunk(chunk + decltype(sc)::value, sc, bool_constant<TWO_SUMS>{}); });
+    if (XSETS == 2 && chunk < k1) multiply_chunk(chunk, integral_constant<int, 0>{}, bool_constant<TWO_SUMS>{});
 
     float *out = dst + (size_t)split * p.out_elems;
     const int co_base = tile_co * K_TCO;

@@ -1,5 +1,5 @@
 // fp32 forward layers on the bf16 matrix cores, the input repacked once: any channel counts, map edges and padding factors,
-// kernels of 3 x 3 to 5 x 5.  (kst_split_f32.hip, for large layers, splits the input while staging, once per block of 128
+// kernels of 3 x 3 to 5 x 5.  (kst_split_f32.h, for large layers, splits the input while staging, once per block of 128
 // output channels and row parity; its tiles and shared passes want 1.5 G products and many channels to pay.  Which layers come
 // here: kst_fwd_packed.hip.)
 //

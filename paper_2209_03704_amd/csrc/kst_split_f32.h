@@ -296,13 +296,15 @@ __device__ __forceinline__ void split_accumulate(const float *__restrict__ in, c
         });
     }
     const int down = -(head.ea + head.eb);
-    static_for<8>([&](auto bc) {
-        constexpr int c = decltype(bc)::value & 1, pb = decltype(bc)::value >> 1;
-        floatx16 &sum = acc[c][pb];
-        sum += low[c][pb];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) sum[v] = PARTS == 2 ? __builtin_amdgcn_ldexpf(sum[v], down) : sum[v] * SPLIT_UNSCALE;
-    });
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int pb = 0; pb < 4; ++pb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float sum = acc[c][pb][v] + low[c][pb][v];
+                acc[c][pb][v] = PARTS == 2 ? __builtin_amdgcn_ldexpf(sum, down) : sum * SPLIT_UNSCALE;
+            }
 }
 
 constexpr size_t S_SLOT = (size_t)S_THREADS * 128;     // floats of one workgroup's sums of one row parity
@@ -321,7 +323,9 @@ __device__ __forceinline__ void do_piece(const float *__restrict__ in, const flo
     const int lane = tid & 63, wave = tid >> 6;
     floatx16 acc[2][4];
     split_accumulate<n, r, WR, NT, PARTS>(in, w_split, p, head, lds, tile_m, tile_co, c0, c1, tid, acc);
-    if (whole) {
+    // (Three parts: not `whole`, nor c0 and c1 by way of p.unit.  With those the compiler kept 128 of the sums in scratch, read
+    // back among the stores, each read a wait for the stores before it: 93 x 24 x 174 x 22 x 22, n = 3, P = 1: 205 us, 120 so.)
+    if (PARTS == 2 ? whole : c0 == 0 && c1 == p.chunks) {
         const int co_base = tile_co * TS::tco + (wave % WR) * 32 + 4 * (lane >> 5);
         float zero = 0.0f;                            // NaN where one of the sums is infinite or not a number
         static_for<128>([&](auto ic) {
@@ -435,8 +439,8 @@ __device__ __forceinline__ void split_f32_work(const float *__restrict__ in, con
         pass = __builtin_amdgcn_readfirstlane(pass);  // the same in all lanes: the staging's addresses stay scalar
         const bool all = u0 == 0 && u1 == k.chunks;
         // (two parts: whole groups, the last one's second chunk past the last channel where those are an odd number)
-        const int c0 = __builtin_amdgcn_readfirstlane(u0 * p.unit);
-        const int c1 = __builtin_amdgcn_readfirstlane(PARTS == 2 ? u1 * p.unit : min(u1 * p.unit, p.chunks));
+        const int c0 = __builtin_amdgcn_readfirstlane(PARTS == 2 ? u0 * p.unit : u0);
+        const int c1 = __builtin_amdgcn_readfirstlane(PARTS == 2 ? u1 * p.unit : u1);
         if (pass & 1)
             do_piece<n, 1, WR, NT, PARTS>(in, w_seg, w_split, out, slot, p, head, lds, pass >> 1, c0, c1, all, (int)threadIdx.x);
         else

@@ -323,7 +323,7 @@ __device__ __forceinline__ void do_piece(const float *__restrict__ in, const flo
     const int lane = tid & 63, wave = tid >> 6;
     floatx16 acc[2][4];
     split_accumulate<n, r, WR, NT, PARTS>(in, w_split, p, head, lds, tile_m, tile_co, c0, c1, tid, acc);
-    // (Three parts: not `whole`, nor c0 and c1 by way of p.unit.  With those the compiler kept 128 of the sums in scratch, read
+    // (Three parts: not `whole`, nor, where units are single chunks, c0 and c1 by way of p.unit.  With those the compiler kept 128 of the sums in scratch, read
     // back among the stores, each read a wait for the stores before it: 93 x 24 x 174 x 22 x 22, n = 3, P = 1: 205 us, 120 so.)
     if (PARTS == 2 ? whole : c0 == 0 && c1 == p.chunks) {
         const int co_base = tile_co * TS::tco + (wave % WR) * 32 + 4 * (lane >> 5);
@@ -408,7 +408,8 @@ __device__ __forceinline__ void do_piece(const float *__restrict__ in, const flo
 
 extern __shared__ __attribute__((aligned(16))) char split_f32_lds[];
 
-template <int n, int WR, int NT, int PARTS>
+// UNITS: units of more than one chunk.
+template <int n, int WR, int NT, int PARTS, bool UNITS>
 __device__ __forceinline__ void split_f32_work(const float *__restrict__ in, const float *__restrict__ w_seg,
                                                const void *__restrict__ w_split, float *__restrict__ out,
                                                float *__restrict__ ws, const SplitParams &p, const EvenShares &k,
@@ -439,8 +440,8 @@ __device__ __forceinline__ void split_f32_work(const float *__restrict__ in, con
         pass = __builtin_amdgcn_readfirstlane(pass);  // the same in all lanes: the staging's addresses stay scalar
         const bool all = u0 == 0 && u1 == k.chunks;
         // (two parts: whole groups, the last one's second chunk past the last channel where those are an odd number)
-        const int c0 = __builtin_amdgcn_readfirstlane(PARTS == 2 ? u0 * p.unit : u0);
-        const int c1 = __builtin_amdgcn_readfirstlane(PARTS == 2 ? u1 * p.unit : u1);
+        const int c0 = __builtin_amdgcn_readfirstlane(UNITS ? u0 * p.unit : u0);
+        const int c1 = __builtin_amdgcn_readfirstlane(PARTS == 2 ? u1 * p.unit : UNITS ? min(u1 * p.unit, p.chunks) : u1);
         if (pass & 1)
             do_piece<n, 1, WR, NT, PARTS>(in, w_seg, w_split, out, slot, p, head, lds, pass >> 1, c0, c1, all, (int)threadIdx.x);
         else
@@ -458,11 +459,11 @@ __global__ void __launch_bounds__(S_THREADS, 1) split_f32_kernel(const float *__
     if constexpr (TWO) {
         const SplitHead head = read_head((const char *)w_split + p.w_bytes);
         if (head.two == SPLIT_TWO) {
-            split_f32_work<n, WR, NT, 2>(in, w_seg, w_split, out, ws, p, k, head);
+            split_f32_work<n, WR, NT, 2, true>(in, w_seg, w_split, out, ws, p, k, head);
             return;
         }
     }
-    split_f32_work<n, WR, NT, 3>(in, w_seg, w_split, out, ws, p, k, {0u, 0, 0, 0u});
+    split_f32_work<n, WR, NT, 3, TWO>(in, w_seg, w_split, out, ws, p, k, {0u, 0, 0, 0u});
 }
 
 // Segregated fp32 weights -> MFMA operands of their three parts: [row parity][block of 32 output channels][chunk][tap]

@@ -248,6 +248,66 @@ struct EvenShares {
     }
 };
 
+// The workgroups whose ranges meet shared pass `rel`, all lanes of a wave together: a lane finds where one range begins.  (One
+// after the other the divisions of eight such beginnings, and slots asked for in turn, were up to a third of a sum's launch:
+// 128 x 512 x 256 x 16 x 16, n = 4: 16.0 -> 11.2 us; input gradient of 64 x 512 x 256 x 8 x 8, n = 4, P = 2: 11.0 -> 9.4.)
+struct PassOwners {
+    int g0, g1, base;
+    bool near;                           // the masks hold (a bit per workgroup from base)
+    unsigned long long empty, first;     // its range is empty; begins in this pass
+    __device__ PassOwners(const EvenShares &k, int rel)
+    {
+        const int u0 = rel * k.chunks, u1 = u0 + k.chunks - 1, lane = threadIdx.x & 63;
+        const float cost = (float)k.chunks * ((rel >> 1) * (k.taps0 + k.taps1) + (rel & 1) * k.taps0);
+        base = __builtin_amdgcn_readfirstlane(max((int)(cost * (float)k.grid / ((float)k.per * (float)k.grid + (float)k.more)) - 2, 0));
+        const int g = min(base + lane, k.grid), b = k.begin(g), next = __shfl_down(b, 1);
+        const unsigned long long from = __ballot(g < k.grid && b <= u0), to = __ballot(g < k.grid && b <= u1);
+        near = from != 0 && to != ~0ull;
+        g0 = near ? base + __popcll(from) - 1 : k.owner(u0);
+        g1 = near ? base + __popcll(to) - 1 : k.owner(u1);
+        empty = __ballot(b == next);
+        first = __ballot(b >= u0);
+    }
+    __device__ bool holds(const EvenShares &k, int g) const
+    {
+        return near ? !((empty >> (g - base)) & 1) : k.begin(g) != k.begin(g + 1);
+    }
+    __device__ bool begins(const EvenShares &k, int g, int rel) const
+    {
+        return near ? ((first >> (g - base)) & 1) != 0 : k.begin(g) >= rel * k.chunks;
+    }
+};
+
+// a += this thread's 16 sums (four groups THREADS apart) of every slot of pass `rel`, in workgroup order, two slots' loads at a time.
+template <int THREADS>
+__device__ __forceinline__ void add_slots(const float *__restrict__ ws, size_t slot_floats, const EvenShares &k, const PassOwners &o,
+                                          int rel, float4 (&a)[4])
+{
+    int held = 0;                                     // (a slot that can be read where there is nothing to add)
+    for (int g = o.g0; g <= o.g1; g += 2) {
+        float4 v[2][4];
+        bool ok[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            ok[i] = g + i <= o.g1 && o.holds(k, g + i);
+            if (ok[i]) held = k.slot(g + i, rel, o.begins(k, g + i, rel));
+            const float4 *d = reinterpret_cast<const float4 *>(ws + (size_t)held * slot_floats) + threadIdx.x;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[i][q] = d[q * THREADS];
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            if (ok[i])
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    a[q].x += v[i][q].x;
+                    a[q].y += v[i][q].y;
+                    a[q].z += v[i][q].z;
+                    a[q].w += v[i][q].w;
+                }
+    }
+}
+
 // An operand's value, whatever its type.
 __device__ __forceinline__ float value_of(const float *p) { return *p; }
 __device__ __forceinline__ float value_of(const uint16_t *p) { return to_f32(*p); }

@@ -328,26 +328,19 @@ __global__ void __launch_bounds__(D_THREADS, 6) split_din_sum_kernel(const float
                                                                   DinParams p, EvenShares k)
 {
     const int rel = blockIdx.x / (4 * RB), part = blockIdx.x - rel * (4 * RB), tid = threadIdx.x;
-    const int u0 = rel * p.chunks;
-    const int g0 = k.owner(u0), g1 = k.owner(u0 + p.chunks - 1);
-    if (g0 == g1) return;
+    const PassOwners o(k, rel);
+    if (o.g0 == o.g1) return;
+    float4 four[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) four[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+    add_slots<D_THREADS>(ws + (size_t)part * 16 * D_THREADS, RB * D_SLOT1, k, o, rel, four);
     float a[16];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) a[v] = 0.0f;
-#pragma unroll 2
-    for (int s = g0; s <= g1; ++s) {
-        const int b = k.begin(s);
-        if (b == k.begin(s + 1)) continue;            // an empty range
-        const int slot = k.slot(s, rel, b >= u0);
-        const float4 *d = reinterpret_cast<const float4 *>(ws + (size_t)slot * (RB * D_SLOT1)) + part * 4 * D_THREADS + tid;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float4 v = d[q * D_THREADS];
-            a[4 * q] += v.x;
-            a[4 * q + 1] += v.y;
-            a[4 * q + 2] += v.z;
-            a[4 * q + 3] += v.w;
-        }
+    for (int q = 0; q < 4; ++q) {
+        a[4 * q] = four[q].x;
+        a[4 * q + 1] = four[q].y;
+        a[4 * q + 2] = four[q].z;
+        a[4 * q + 3] = four[q].w;
     }
     const int tile = k.listed() + rel, tile_m = tile % p.tiles_m, tile_ci = tile / p.tiles_m;
     const int lane = tid & 63, wave = tid >> 6;

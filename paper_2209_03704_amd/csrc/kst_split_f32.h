@@ -530,27 +530,12 @@ __global__ void __launch_bounds__(S_THREADS, 5) split_f32_sum_kernel(const float
 {
     using TS = TileShape<WR>;
     const int rel = blockIdx.x >> 3, part = blockIdx.x & 7, tid = threadIdx.x;
-    const int u0 = rel * k.chunks;
-    const int g0 = k.owner(u0), g1 = k.owner(u0 + k.chunks - 1);
-    if (g0 == g1) return;
+    const PassOwners o(k, rel);
+    if (o.g0 == o.g1) return;
     float4 a[4];                                      // registers 2 q, 2 q + 1: [column parity 0, 1] each
 #pragma unroll
     for (int q = 0; q < 4; ++q) a[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 2
-    for (int g = g0; g <= g1; ++g) {
-        const int b = k.begin(g);
-        if (b == k.begin(g + 1)) continue;            // an empty range
-        const int slot = k.slot(g, rel, b >= u0);
-        const float4 *d = reinterpret_cast<const float4 *>(ws + (size_t)slot * S_SLOT) + part * 4 * S_THREADS + tid;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float4 v = d[q * S_THREADS];
-            a[q].x += v.x;
-            a[q].y += v.y;
-            a[q].z += v.z;
-            a[q].w += v.w;
-        }
-    }
+    add_slots<S_THREADS>(ws + (size_t)part * 16 * S_THREADS, S_SLOT, k, o, rel, a);
     const int pass = k.listed() + rel, tile = pass >> 1, tile_m = tile % p.tiles_m, tile_co = tile / p.tiles_m;
     const int lane = tid & 63, wave = tid >> 6;
     const Column c = column_of(p, tile_m * TS::tm, (wave / WR) * 4 + (part >> 1), lane & 31);

@@ -225,13 +225,11 @@ double igemm_f32_small_us(const Shape &s);         // for layers that it support
 size_t igemm_f32_small_workspace_bytes(const Shape &s);
 hipError_t launch_igemm_f32_small(const float *in, const float *w_seg, float *out, void *ws, const Shape &s,
                                   hipStream_t stream);
-// Shares of two fp32 operands' largest magnitudes (kst_split_range.hip), SPLIT_RANGE_BYTES at `to`; the first
+// Shares of two fp32 operands' largest and smallest magnitudes (kst_split_range.hip), SPLIT_RANGE_BYTES at `to`; the first
 // split_range_share workgroups take a (count 0: none), the others b.
 struct RangeOperand {
     const float *p;        // 16-byte aligned
     size_t count;
-    size_t period;         // 0: blocks are neighbours; otherwise values this far apart belong together (a channel's)
-    bool apart;            // with a period: every value for itself, neighbours belong to other channels
 };
 constexpr size_t SPLIT_RANGE_BYTES = 2048;
 int split_range_share(size_t count_a, size_t count_b);

@@ -41,23 +41,25 @@ __device__ __forceinline__ void split3(const float (&v)[8], bf16x8 &p0, bf16x8 &
 
 // ---- two half-precision parts ----
 //
-// Where the reduction is long, fp32 operands are split into two half-precision parts instead, x = x0 + x1 (rounded to
-// nearest: |x1| <= 2^-11 |x|, what is left over at most 2^-23 |x|), and a product is x0 w0 + (x0 w1 + x1 w0): three partial
-// products of six.  22 to 23 bits of each operand and the product x1 w1 left out are an error of 7.6e-8 of a sum of
-// products of random sign, beside which the sums' own roundings are made smaller than with three parts: all partial
-// products go to one accumulator, whose sums are added to a total every few steps (the registers of the smaller products'
-// accumulators) instead of running through the whole reduction.
+// Where the reduction is long, fp32 operands are split into two half-precision parts instead, x = x0 + 2^-12 x1 (rounded to
+// nearest: |x - x0| <= 2^-11 |x|, what is left over at most 2^-23 |x|), and a product is x0 w0 + 2^-12 (x0 w1 + x1 w0): three
+// partial products of six.  22 to 23 bits of each operand and the product x1 w1 left out are an error of 7.6e-8 of a sum of
+// products of random sign, beside which the sums' own roundings are made smaller than with three parts: the largest products'
+// sums are added to a total every few steps instead of running through the whole reduction.
 //
 // Half precision has five bits of exponent, so both tensors are scaled by a power of two that brings their largest
-// magnitude to [2^14, 2^15), found by a pass of its own.  The smallest step is then 2^-24, at most 2^-38 of the tensor's
-// largest magnitude.  Values well below that magnitude have fewer bits left: the pass also finds the smallest of the
-// largest magnitudes of its blocks (zeros aside; a block: 64 neighbours, or values of one channel, see
-// kst_split_range.hip), and a tensor in which one such block lies more than 2^13 below the whole (or with a value that is not
-// finite) goes through the three-part kernels, in the same launches.
+// magnitude to [2^14, 2^15), and the second part is held 2^12 times its size (its products have sums of their own for that):
+// every value down to 2^-15, 2^-29 to 2^-30 of the tensor's largest, then has its two parts to within 2^-22 of itself (2^-23 from 2^-14
+// on), and a product is formed to within 2^-20 of itself at worst, whatever else is in the tensors.  A tensor that has
+// a smaller value, zeros aside, or one that is not finite goes through the three-part kernels, in the same launches: a pass of its own
+// over both tensors (kst_split_range.hip) finds the largest and the smallest magnitude.  Nothing less will do.  A result is a sum of
+// products, so one operand's zeros and small values choose which values of the other count, and a few small values, in
+// whatever company, can be all there is of some result.  (Normal random values: a tensor of ten million has one that small in 1 of 20.)
 constexpr int RANGE_WGS = 256, RANGE_THREADS = 512;
-constexpr int RANGE_BLOCKS_APART = 13;       // powers of two
+constexpr int RANGE_APART = 29;              // powers of two from the smallest value to the largest
+constexpr float LOW_SCALE = 0x1p12f;
 
-// Of one workgroup's share of a tensor: bits of the largest magnitude; of the smallest block's, less one (no such block: all ones).
+// Of one workgroup's share of a tensor: bits of the largest magnitude; of the smallest but zero, less one (none: all ones).
 struct RangePart {
     unsigned most, least;
 };
@@ -82,8 +84,8 @@ __device__ __forceinline__ void split2(const float (&v)[8], int e, bf16x8 &p0, b
         const halfx2 r = __builtin_convertvector(t, halfx2);
         h[j] = r[0];
         h[j + 1] = r[1];
-        l[j] = (_Float16)__builtin_fmaf((float)r[0], -1.0f, t[0]);         // (exact: one rounding, to half precision)
-        l[j + 1] = (_Float16)__builtin_fmaf((float)r[1], -1.0f, t[1]);
+        l[j] = (_Float16)fmaf((float)r[0], -LOW_SCALE, t[0] * LOW_SCALE);      // (exact: one rounding, to half precision)
+        l[j + 1] = (_Float16)fmaf((float)r[1], -LOW_SCALE, t[1] * LOW_SCALE);
     }
     p0 = __builtin_bit_cast(bf16x8, h);
     p1 = __builtin_bit_cast(bf16x8, l);
@@ -130,7 +132,7 @@ __device__ __forceinline__ SplitHead split_head(const RangePart *__restrict__ pa
         if (most >= 0x7f800000u) h.two = 0u;
         if (most == 0u || most >= 0x7f800000u) continue;
         const int top = __builtin_amdgcn_frexp_expf(__uint_as_float(most));
-        if (top - __builtin_amdgcn_frexp_expf(__uint_as_float(least + 1u)) > RANGE_BLOCKS_APART) h.two = 0u;
+        if (top - __builtin_amdgcn_frexp_expf(__uint_as_float(least + 1u)) > RANGE_APART) h.two = 0u;
         (t == 0 ? h.ea : h.eb) = 15 - top;
     }
     return h;

@@ -234,10 +234,12 @@ __device__ __forceinline__ void din_accumulate(const float *__restrict__ g, cons
     static_for<BLOCKS>([&](auto bc) {
         constexpr int b = decltype(bc)::value;
         floatx16 &sum = acc[b / 4][b % 4];
-        sum += low[b / 4][b % 4];
         if constexpr (PARTS == 2) {
+            sum += low[b / 4][b % 4] * (1.0f / LOW_SCALE);
             if constexpr (b < TR) sum += total[b];
             else spare.add_to(b - TR, sum);
+        } else {
+            sum += low[b / 4][b % 4];
         }
 #pragma unroll
         for (int v = 0; v < 16; ++v) sum[v] = PARTS == 2 ? __builtin_amdgcn_ldexpf(sum[v], down) : sum[v] * SPLIT_UNSCALE;
@@ -476,8 +478,7 @@ hipError_t din_launch(const float *g, const T *w, float *din, char *ws, const Di
     const DinParams &p = pl.p;
     if (p.two) {                                      // (the shares lie in the result until the weights are split)
         if constexpr (std::is_same_v<T, float>)
-            e = launch_split_range({w, (size_t)p.Cin * p.Cout * n * n, (size_t)p.Cin * n * n, false},
-                                   {g, p.g_bytes / sizeof(float), 0, false}, din, stream);
+            e = launch_split_range({w, (size_t)p.Cin * p.Cout * n * n}, {g, p.g_bytes / sizeof(float)}, din, stream);
         if (e != hipSuccess) return e;
     }
     const unsigned tasks = (unsigned)((p.Cin + 31) / 32) * (unsigned)p.chunks * n;

@@ -324,11 +324,14 @@ __device__ __forceinline__ void split_dw_work(const void *__restrict__ xf, const
         static_for<CB * IB>([&](auto bc) {
             constexpr int i = decltype(bc)::value / IB, j = decltype(bc)::value % IB;
             const int ci = (cib + j) * 32 + (lane & 31), co0 = (cob + i) * 32 + 4 * (lane >> 5);
-            floatx16 sum = acc[t][i][j] + low[t][i][j];
+            floatx16 sum = acc[t][i][j];
             if constexpr (GP == 2) {
+                sum += low[t][i][j] * (1.0f / LOW_SCALE);
                 constexpr int b = (t * CB + i) * IB + j;
                 if constexpr (b < TR) sum += total[b];
                 else spare.add_to(b - TR, sum);
+            } else {
+                sum += low[t][i][j];
             }
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
@@ -569,10 +572,9 @@ hipError_t dw_launch(const T *in, const float *g, float *dw, char *ws, const DwP
     char *head_end = gf + p.g_bytes;
     if (p.two) {                                      // (the shares lie in the result until both operands are split)
         // (half precision needs no scale: what is infinite or not a number in it is found in the sums)
-        const size_t x_item = (size_t)p.Cin * p.N * p.N, g_item = (size_t)p.Cout * p.M * p.M;
-        RangeOperand x = {nullptr, 0, 0, false};
-        if constexpr (std::is_same_v<T, float>) x = {in, p.B * x_item, x_item, false};
-        e = launch_split_range(x, {g, p.B * g_item, g_item, false}, dw, stream);
+        RangeOperand x = {nullptr, 0};
+        if constexpr (std::is_same_v<T, float>) x = {in, (size_t)p.B * p.Cin * p.N * p.N};
+        e = launch_split_range(x, {g, (size_t)p.B * p.Cout * p.M * p.M}, dw, stream);
         if (e != hipSuccess) return e;
         range = (const RangePart *)dw;
     }

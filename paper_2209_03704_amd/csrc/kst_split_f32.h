@@ -12,8 +12,8 @@
 // all weights once and lays them out as MFMA operands, so that a wave's next three operands are one contiguous 3 KB,
 // loaded straight into registers two to four taps ahead.  (Split in the main loop instead, 44 vector instructions
 // and eight 4-byte loads per tap: 548 us against 488 on 128 x 512 x 256 x 16 x 16, n = 4, when it was tried; 471 with three
-// parts, MFMAs busy in 64 % of the main kernel's cycles; 345 with two: half the MFMAs, busy in 43 %, the other cycles go to a
-// wave's other instructions, 3.3 vector instructions per MFMA and its waits for LDS.)  Input values are
+// parts, MFMAs busy in 64 % of the main kernel's cycles; 352 with two: half the MFMAs, the other cycles go to a
+// wave's other instructions and its waits for LDS.)  Input values are
 // wanted by every wave and every tap: the rows the tile's positions touch are split once per chunk and kept in LDS as
 // [part][channel half][row, column][8 channels], so that a lane's MFMA operand is one 16-byte read; two stages, one
 // barrier per chunk.  Taps are walked by window offset: the taps of both column parities that meet the same input
@@ -107,7 +107,15 @@ struct FlushOrder {
 constexpr int split_half(int NT) { return NT * 128 * 16; }            // bytes: one channel half of one part
 constexpr int split_stage(int NT, int parts) { return parts * 2 * split_half(NT); }
 constexpr int S_OWN = 16384;                                            // of a wave, from the start
-constexpr int split_lds(int NT) { return 2 * split_stage(NT, 3) > 4 * S_OWN ? 2 * split_stage(NT, 3) : 4 * S_OWN; }
+// Two parts: totals of S_TOTALS of the eight accumulator blocks lie behind both.
+constexpr int S_TOTALS = 4;
+constexpr int split_totals_at(int NT) { return 2 * split_stage(NT, 2) > 4 * S_OWN ? 2 * split_stage(NT, 2) : 4 * S_OWN; }
+constexpr int split_lds(int NT, bool two)
+{
+    const int three = 2 * split_stage(NT, 3) > 4 * S_OWN ? 2 * split_stage(NT, 3) : 4 * S_OWN;
+    const int both = split_totals_at(NT) + S_TOTALS * 16 * S_THREADS * 4;
+    return two && both > three ? both : three;
+}
 
 // WR: waves along the output channels (4 / WR along the positions); every wave: 32 channels x 128 positions.
 template <int WR>
@@ -208,21 +216,27 @@ __device__ __forceinline__ void split_accumulate(const float *__restrict__ in, c
             xf[pb][part] = *reinterpret_cast<const bf16x8 *>(lds + stage + xa[pb][o / side] + (o % side) * 16 + part * PART);
     };
 
-    // The five smaller partial products are added up on their own and join the largest one's sums at the end: a sum
+    // The smaller partial products are added up on their own and join the largest one's sums at the end: a sum
     // of a few thousand products is then rounded at its own size twice per MFMA of the largest products only.  (All
     // six into one accumulator: relative error 6.0e-7 against 64 bits on 128 x 512 x 256 x 16 x 16, n = 4, where the
-    // fp32 multiplies had 5.2e-7.)  Of two parts all partial products go to one accumulator, whose sums are added to a total
-    // (`low`) every S_GROUP chunks and start again.
-    floatx16 low[2][4];
+    // fp32 multiplies had 5.2e-7.)  Of two parts the largest products' sums are added to a total every S_GROUP chunks and start
+    // again; some totals are in LDS: beside two accumulators of each block registers are short.
+    constexpr int TR = 8 - S_TOTALS;
+    const LdsTotals<S_THREADS> spare = {reinterpret_cast<float4 *>(lds + split_totals_at(NT)) + tid};
+    floatx16 low[2][4], total[TR], zeros;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) zeros[v] = 0.0f;
 #pragma unroll
     for (int c = 0; c < 2; ++c)
 #pragma unroll
         for (int pb = 0; pb < 4; ++pb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[c][pb][v] = low[c][pb][v] = 0.0f;
-    floatx16 zeros;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) zeros[v] = 0.0f;
+            for (int v = 0; v < 16; ++v) {
+                acc[c][pb][v] = low[c][pb][v] = 0.0f;
+                if (c * 4 + pb < TR) total[c * 4 + pb][v] = 0.0f;
+            }
+    if constexpr (PARTS == 2)
+        static_for<S_TOTALS>([&](auto bc) { spare.clear(decltype(bc)::value); });
 
     using std::integral_constant;
     // The tap during which the k-th staged position of the next chunk goes to LDS, and how many a tap has.
@@ -264,7 +278,11 @@ __device__ __forceinline__ void split_accumulate(const float *__restrict__ in, c
             if constexpr (PARTS == 2)
                 static_for<4>([&](auto pbc) {
                     constexpr int pb = decltype(pbc)::value;
-                    if constexpr (flush.at[1 - sp][pb] == t) low[1 - sp][pb] += acc[1 - sp][pb];
+                    if constexpr (flush.at[1 - sp][pb] == t) {
+                        constexpr int b = (1 - sp) * 4 + pb;
+                        if constexpr (b < TR) total[b] += acc[1 - sp][pb];
+                        else spare.add(b - TR, acc[1 - sp][pb]);
+                    }
                 });
             static_for<PARTS>([&](auto xc) {          // parts of the input, smallest first
                 constexpr int xp = PARTS - 1 - decltype(xc)::value;
@@ -272,10 +290,10 @@ __device__ __forceinline__ void split_accumulate(const float *__restrict__ in, c
                     constexpr int w = PARTS - 1 - xp - decltype(wc)::value;
                     static_for<4>([&](auto pbc) {
                         constexpr int pb = decltype(pbc)::value;
-                        if constexpr (PARTS == 2 && xp == 1 && flush.next[sp][pb] == t) {
+                        if constexpr (PARTS == 2 && w + xp == 0 && flush.next[sp][pb] == t) {
                             acc[sp][pb] = mfma16<true>(wp[q % SETS][w], xf[pb][xp], zeros);
                         } else {
-                            floatx16 &sum = PARTS == 2 || w + xp == 0 ? acc[sp][pb] : low[sp][pb];
+                            floatx16 &sum = w + xp == 0 ? acc[sp][pb] : low[sp][pb];
                             sum = mfma16<PARTS == 2>(wp[q % SETS][w], xf[pb][xp], sum);
                         }
                     });
@@ -296,15 +314,19 @@ __device__ __forceinline__ void split_accumulate(const float *__restrict__ in, c
         });
     }
     const int down = -(head.ea + head.eb);
+    static_for<8>([&](auto bc) {
+        constexpr int b = decltype(bc)::value, c = b / 4, pb = b % 4;
+        floatx16 &sum = acc[c][pb];
+        if constexpr (PARTS == 2) {
+            sum += low[c][pb] * (1.0f / LOW_SCALE);
+            if constexpr (b < TR) sum += total[b];
+            else spare.add_to(b - TR, sum);
+        } else {
+            sum += low[c][pb];
+        }
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int pb = 0; pb < 4; ++pb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float sum = acc[c][pb][v] + low[c][pb][v];
-                acc[c][pb][v] = PARTS == 2 ? __builtin_amdgcn_ldexpf(sum, down) : sum * SPLIT_UNSCALE;
-            }
+        for (int v = 0; v < 16; ++v) sum[v] = PARTS == 2 ? __builtin_amdgcn_ldexpf(sum[v], down) : sum[v] * SPLIT_UNSCALE;
+    });
 }
 
 constexpr size_t S_SLOT = (size_t)S_THREADS * 128;     // floats of one workgroup's sums of one row parity
@@ -576,11 +598,11 @@ struct SplitPlan {
 // Two half-precision parts where that is no less exact than three bfloat16 ones.  What it costs in exactness does not depend
 // on the length of the reduction (products whose operands end after 23 bits, segments of eight MFMAs), the roundings of one
 // chain of three-part MFMAs do: `steps` of them, of a pass's sums of one class and without those that multiply the zero
-// frame, in the mean over passes that are done whole and shared ones.  8430 random layers: from 108 (5 x 5: 150, whose
-// segments are longer) the error was 0.65 to 0.99 of the other's on all but one (1.007), below 64 up to 2.9 times it.  Times as
-// fast from there: 1.25 (4 x 4, at least 1.13) and 1.30 (5 x 5, at least 1.12); 3 x 3 kernels gained 6 % in the mean and lost on
-// some.  (The smaller partial products' sums apart, as with three parts, and a total beside them: exact enough from 60 steps,
-// but a third of the registers more, half of the totals in LDS: gan 335 us against 300.)
+// frame, in the mean over passes that are done whole and shared ones.  From 108 (5 x 5: 150, whose segments are longer) the error
+// was 0.65 to 0.99 of the other's on all but one (1.007) of 8430 random layers while all partial products had one accumulator,
+// whose roundings the smaller ones' sums apart do without (128 x 512 x 256 x 16 x 16, n = 4: 1.3e-7 for 1.6e-7).  Times as
+// fast from there: 1.25 (4 x 4, at least 1.13) and 1.30 (5 x 5, at least 1.12) then; 3 x 3 kernels gained 6 % in the mean and lost on
+// some.  (One accumulator for all needs second parts of their own size, which small values do not have: 336 us against 352.)
 inline bool split_two_parts(const Shape &s, int chunks, double whole, double shared)
 {
     if (s.n < 4) return false;
@@ -652,7 +674,7 @@ inline size_t split_weight_bytes(const SplitPlan &pl) { return ((size_t)pl.p.w_b
 template <int n, int WR, int NT>
 hipError_t split_f32_launch_nt(const float *in, const float *w_seg, float *out, char *ws, const SplitPlan &pl, hipStream_t stream)
 {
-    constexpr int lds = split_lds(NT);
+    const int lds = split_lds(NT, pl.p.two);
     auto kernel = &split_f32_kernel<n, WR, NT, false>;
     if constexpr (n > 3)
         if (pl.p.two) kernel = &split_f32_kernel<n, WR, NT, true>;
@@ -660,8 +682,7 @@ hipError_t split_f32_launch_nt(const float *in, const float *w_seg, float *out, 
     if (e != hipSuccess) return e;
     const SplitParams &p = pl.p;
     if (p.two) {                                      // (the shares lie in the output until the weights are split)
-        e = launch_split_range({in, p.in_bytes / sizeof(float), 0, false},
-                               {w_seg, (size_t)p.Cin * p.Cout * n * n, (size_t)p.Cout, true}, out, stream);
+        e = launch_split_range({in, p.in_bytes / sizeof(float)}, {w_seg, (size_t)p.Cin * p.Cout * n * n}, out, stream);
         if (e != hipSuccess) return e;
     }
     const unsigned tasks = p.w_bytes / (3 * S_TAP);

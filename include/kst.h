@@ -16,11 +16,8 @@
  *   - Dense row-major layouts: in[B][Cin][N][N], w[Cout][Cin][n][n],
  *     out[B][Cout][M][M].  out is always fp32 and is completely overwritten
  *     (no bias, no activation, no accumulation).  Buffers must not alias.
- *   - dtype describes in and w: KST_F32 (fp32 operands, fp32 arithmetic; large
- *     layers form each product from six exact products of bfloat16 parts of its
- *     operands, to within 2^-24 of it, whatever the operands' size, and add them
- *     in fp32; what has no such parts or overflows on the way is multiplied in
- *     fp32 again),
+ *   - dtype describes in and w: KST_F32 (fp32 operands, fp32 arithmetic; see
+ *     "Products of large fp32 layers" below for how these form their products),
  *     KST_BF16 (bfloat16 operands, fp32 accumulation, fp32 out) or KST_F16 (IEEE
  *     half-precision operands, fp32 accumulation, fp32 out; not in the paper:
  *     the same kernels as KST_BF16 with the other 16-bit multiply).
@@ -31,6 +28,28 @@
  *   - Legal shapes: B, Cin, Cout, N, n >= 1 and 2N - n >= 1, with every tensor
  *     below 2^31 elements.
  *   - Calls on different streams may run concurrently.
+ *   - A result buffer (out, din, dw) may hold scratch values until the call's work
+ *     on the stream is done.
+ *
+ * Products of large fp32 layers.  Large layers (and both gradients of large
+ * layers of the other types, whose g is fp32) run on the 16-bit matrix cores with
+ * operands in parts, every partial product exact and all sums in fp32:
+ *   - six products of three bfloat16 parts, to within 2^-24 of the product,
+ *     whatever the operands' size; or
+ *   - where the reduction is long and the kernel 4 x 4 or 5 x 5 (for the kernel
+ *     gradient also 3 x 3): three products of two half-precision parts, to within
+ *     2^-20 of the product, within 2^-21 for operands that are at least 2^-28 of
+ *     their tensor's largest magnitude.  Only where both tensors are finite and hold no
+ *     value but zero below 2^-29 of their largest magnitude: then no result depends
+ *     on how large other values of its tensors are.  Over long reductions these
+ *     sums are no less exact: three products are rounded less often than six.
+ *   - What has no parts (infinities, NaN) or overflows on the way is multiplied in
+ *     fp32 again.
+ * Which of the two it is the device finds for each call, from all values of both
+ * tensors (that pass takes 8 to 16 us; layers planned for two parts whose values
+ * ask for three take up to 1.4 times as long): the last bits of one batch item's
+ * result can differ with another item's values, as they can with the batch size.
+ * KST_PATH_IGEMM asked for by name multiplies in fp32 instead (forward only).
  */
 #ifndef KST_H
 #define KST_H
@@ -69,7 +88,7 @@ typedef enum {
  * with many input channels that the matrix cores can take with the
  * sub-kernels' taps as rows (a batch of them) or with the reduction split
  * over the chip (one sample).  Large fp32 layers AUTO gives to IGEMM's kernels
- * for operands split into bfloat16 parts (see dtype above); IGEMM asked for by
+ * for operands split into 16-bit parts (see above); IGEMM asked for by
  * name multiplies in fp32 always.
  * IGEMM_EVEN (for tests and tuning) is IGEMM with one of its launch forms
  * forced: the (tile, channel chunk) list of the layer cut into equal ranges
@@ -148,7 +167,7 @@ kst_status kst_segregate_weights(const void *w, void *w_seg, int Cin, int Cout, 
  * wants none).  The matrix-core path uses it for partial sums when it splits
  * the input-channel reduction across workgroups, and for the operands that
  * kernels of 3 x 3 to 5 x 5 lay out anew: fp32 weights and, for layers that
- * the kernel for large ones does not take, the input in three bfloat16
+ * the kernel for large ones does not take, the input in two or three 16-bit
  * parts, a 16-bit input with the channels of a pixel side by side.  With fewer bytes AUTO runs these layers
  * on the kernels that read operands as they lie (fp32 ones multiply in fp32),
  * slower and rounded differently, where those can do with what there is (many
@@ -275,9 +294,8 @@ kst_status kst_forward_seg_epilogue(const void *in, const void *w_seg, const flo
  * at least 8 channels on either side, or at least 64 input channels with a few
  * output channels; the other kernel-gradient kernels when they slice the
  * positions), and for the fp32 copy of w or in that the matrix-core kernels
- * read when the operands are 16-bit (widening is exact), or for the bfloat16
- * parts of both operands (kernels of 3 x 3 to 5 x 5; half precision needs two,
- * bfloat16 itself one); it
+ * read when the operands are 16-bit (widening is exact), or for the 16-bit
+ * parts of both operands (kernels of 3 x 3 to 5 x 5); it
  * may be 0 (then ws may be NULL).  The byte count depends
  * on the shape only, never on the pointers, as in
  * kst_forward_seg_padded.  Pointers, alignment, stream and statuses as above.

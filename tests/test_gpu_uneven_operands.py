@@ -174,3 +174,59 @@ def test_kernel_gradient_half_maps(scale, dtype):
         x = x.half()
     got = kst.kst_backward_weight(x.to(DEV), g.to(DEV), n, P)[:40, :40].cpu()
     _close(got, oracle.backward_weight(wl.to_f64(x[:, :40].contiguous()), wl.to_f64(g[:, :40].contiguous()), n, P))
+
+
+def _wide_values(shape, seed):
+    """Magnitudes spread evenly over their logarithm, [2^-28, 1]: two parts, with room below."""
+    gen = torch.Generator().manual_seed(seed)
+    sign = 1.0 - 2.0 * torch.randint(0, 2, shape, generator=gen)
+    return sign * torch.exp2(torch.rand(shape, generator=gen) * -28.0)
+
+
+def _single(got, want):
+    """Results that are one product each: within 2^-20 of it."""
+    got, want = np.asarray(got, dtype=np.float64), np.asarray(want, dtype=np.float64)
+    assert (want != 0).mean() > 0.2
+    assert (np.abs(got - want) <= 2.0 ** -20 * np.abs(want)).all()
+
+
+def test_single_products_forward():
+    B, Cin, Cout, N, n, P = FORWARD[0]
+    x, w = _wide_values((B, Cin, N, N), 1), _wide_values((Cout, Cin, n, n), 2)
+    row = x[1, torch.arange(64) % Cin, (torch.arange(64) // 8) * 2, (torch.arange(64) % 8) * 2].clone()
+    x[1] = 0.0                                                    # one value in each block of 2 x 2 pixels: windows that do not meet
+    x[1, torch.arange(64) % Cin, (torch.arange(64) // 8) * 2, (torch.arange(64) % 8) * 2] = row
+    out, wide = _forward(x, w, P), x.clone()
+    wide[-1, 0, 0, 0] = 2.0 ** -40
+    assert not torch.equal(out[0], _forward(wide, w, P)[0])       # (three parts there, two here)
+    got, want = _planes(x, w, out, P, co=(0, 7, 33, 150), items=(1,))
+    _single(got, want)
+
+
+def test_single_products_input_gradient():
+    B, Cin, Cout, N, n, P = shape = INPUT[0]
+    M = 2 * N + 2 * P - n
+    w, g = _wide_values((Cout, Cin, n, n), 3), _wide_values((B, Cout, M, M), 4)
+    keep = g[1, 5, ::4, ::4].clone()
+    g[1] = 0.0
+    g[1, 5, ::4, ::4] = keep                                      # at most one tap of a position meets one of them
+    din, wide = kst.kst_backward_input(g.to(DEV), w.to(DEV), N, P), g.clone()
+    wide[-1, 0, 0, 0] = 2.0 ** -40
+    assert not torch.equal(din[0], kst.kst_backward_input(wide.to(DEV), w.to(DEV), N, P)[0])
+    got = din[1:2].cpu()
+    _single(got, oracle.backward_input(wl.to_f64(g[1:2]), wl.to_f64(w), N, P))
+
+
+def test_single_products_kernel_gradient():
+    B, Cin, Cout, N, n, P = KERNEL[0]
+    M = 2 * N + 2 * P - n
+    x, g = _wide_values((B, Cin, N, N), 5), _wide_values((B, Cout, M, M), 6)
+    at = torch.arange(32)
+    keep = x[at, at, at % N, at // 4].clone()
+    x[:, :32] = 0.0
+    x[at, at, at % N, at // 4] = keep                             # one value of each of 32 input channels
+    dw, wide = kst.kst_backward_weight(x.to(DEV), g.to(DEV), n, P), g.clone()
+    wide[0, -1, 0, 0] = 2.0 ** -40
+    assert not torch.equal(dw[:-1], kst.kst_backward_weight(x.to(DEV), wide.to(DEV), n, P)[:-1])
+    got = dw[:40, :32].cpu()
+    _single(got, oracle.backward_weight(wl.to_f64(x[:, :32].contiguous()), wl.to_f64(g[:, :40].contiguous()), n, P))

@@ -40,9 +40,11 @@
  *     gradient also 3 x 3): three products of two half-precision parts, to within
  *     2^-20 of the product, within 2^-21 for operands that are at least 2^-28 of
  *     their tensor's largest magnitude.  Only where both tensors are finite and hold no
- *     value but zero below 2^-29 of their largest magnitude: then no result depends
- *     on how large other values of its tensors are.  Over long reductions these
- *     sums are no less exact: three products are rounded less often than six.
+ *     value but zero below 2^-29 of their largest magnitude: then no result is less
+ *     exact for how large other values of its tensors are.  And only where enough
+ *     values are not zero (from a tenth to a half of the products, the less the
+ *     longer the reduction): there these sums are no less exact, since three products
+ *     are rounded less often than six.
  *   - What has no parts (infinities, NaN) or overflows on the way is multiplied in
  *     fp32 again.
  * Which of the two it is the device finds for each call, from all values of both

@@ -225,14 +225,15 @@ double igemm_f32_small_us(const Shape &s);         // for layers that it support
 size_t igemm_f32_small_workspace_bytes(const Shape &s);
 hipError_t launch_igemm_f32_small(const float *in, const float *w_seg, float *out, void *ws, const Shape &s,
                                   hipStream_t stream);
-// Shares of two fp32 operands' largest and smallest magnitudes (kst_split_range.hip), SPLIT_RANGE_BYTES at `to`; the first
-// split_range_share workgroups take a (count 0: none), the others b.
+// Shares of two operands' largest and smallest magnitudes and numbers of values that are not zero (kst_split_range.hip),
+// SPLIT_RANGE_BYTES at `to`; the first split_range_share workgroups take a, the others b.
 struct RangeOperand {
-    const float *p;        // 16-byte aligned
+    const void *p;         // 16-byte aligned
     size_t count;
+    bool half;             // of half precision: only counted
 };
-constexpr size_t SPLIT_RANGE_BYTES = 2048;
-int split_range_share(size_t count_a, size_t count_b);
+constexpr size_t SPLIT_RANGE_BYTES = 4096;
+int split_range_share(size_t bytes_a, size_t bytes_b);
 hipError_t launch_split_range(const RangeOperand &a, const RangeOperand &b, void *to, hipStream_t stream);
 // fp32 layers on the bf16 matrix cores, operands split into three parts (takes Shape::frame and Shape::crop).
 bool split_f32_applies(const Shape &s);

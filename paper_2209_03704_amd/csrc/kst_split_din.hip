@@ -36,6 +36,7 @@ struct DinParams : DinShape {
     unsigned g_bytes, w_bytes;
     int two;               // operands of two half-precision parts where their ranges allow
     int range_share;       // workgroups of the ranges' launch that took the weights
+    float from;            // ... and of all pairs of a weight and a value of g, how many at least have no zero
 };
 
 // LDS of a kernel that stages NT cells per lane: two stages, and totals (below) of some of two row blocks' accumulators.
@@ -362,7 +363,7 @@ __global__ void __launch_bounds__(256) split_din_weights_kernel(const T *__restr
     constexpr int NN = n * n;
     SplitHead head = {0u, 0, 0, 0u};
     if (p.two) {
-        head = split_head(range, p.range_share);
+        head = split_head(range, p.range_share, p.from);
         if (head.two && blockIdx.x == 0 && threadIdx.x == 0)
             *reinterpret_cast<uint4 *>(w_split + p.w_bytes - 16) = make_uint4(head.two, (unsigned)head.ea, (unsigned)head.eb, 0u);
     }
@@ -439,7 +440,7 @@ DinPlan din_plan(const Shape &s, bool odd, kst_dtype dt)
     const size_t w_bytes = (size_t)((s.Cin + 31) / 32) * p.chunks * n * n * r.wp * 1024;
     p.g_bytes = (unsigned)g_bytes;
     p.w_bytes = (unsigned)w_bytes;
-    p.range_share = split_range_share((size_t)s.Cin * s.Cout * n * n, g_bytes / sizeof(float));
+    p.range_share = split_range_share((size_t)s.Cin * s.Cout * n * n * sizeof(float), g_bytes);
     r.w_bytes = w_bytes;
     const unsigned long long tiles = (unsigned long long)p.tiles_m * p.tiles_ci, units = tiles * (unsigned)p.chunks;
     r.k.chunks = p.chunks;
@@ -452,10 +453,12 @@ DinPlan din_plan(const Shape &s, bool odd, kst_dtype dt)
     // of a chain (without taps that meet no g) the error was 0.35 to 1.0 of the other's on 2008 random layers, below 20 up to
     // 1.6 times it.  Times as fast on 1084 of them with 4 x 4 and 5 x 5 kernels: 1.17 in the mean, never slower (64 x 512 x 256 x
     // 8 x 8, n = 4, P = 2: 60 us, 82 with three parts); 3 x 3 kernels: 0.89 to 1.2, 305 of 924 slower.  bfloat16 weights: two
-    // partial products for three, which the ranges' pass outweighs (0.97).
+    // partial products for three, which the ranges' pass outweighs (0.97).  Steps of products that are not zero: from 28 (12 layers, 1
+    // to 0.06 of g not zero: no less exact from 20 to 28).
     const double share = (double)r.k.passes * p.chunks / S_GRID, piece = share < p.chunks ? share : p.chunks;
     const double inside = taps_inside(p.N, n, 2 * s.frame - (odd ? 1 : 0), p.M) / ((double)p.N * n);
     const double steps = n * n * ((double)r.k.rounds * S_GRID * p.chunks + r.k.passes * piece) / (double)tiles * inside * inside;
+    p.from = (float)(28.0 / steps * ((double)s.Cin * s.Cout * n * n) * ((double)s.B * s.Cout * p.M * p.M));
     p.two = n > 3 && r.wp == 3 && steps >= 36.0 && (size_t)p.Mtot * s.Cin * sizeof(float) >= SPLIT_RANGE_BYTES;
     r.k.per = (int)(all / (unsigned)r.k.grid);
     r.k.more = (int)(all % (unsigned)r.k.grid);
@@ -478,7 +481,7 @@ hipError_t din_launch(const float *g, const T *w, float *din, char *ws, const Di
     const DinParams &p = pl.p;
     if (p.two) {                                      // (the shares lie in the result until the weights are split)
         if constexpr (std::is_same_v<T, float>)
-            e = launch_split_range({w, (size_t)p.Cin * p.Cout * n * n}, {g, p.g_bytes / sizeof(float)}, din, stream);
+            e = launch_split_range({w, (size_t)p.Cin * p.Cout * n * n, false}, {g, p.g_bytes / sizeof(float), false}, din, stream);
         if (e != hipSuccess) return e;
     }
     const unsigned tasks = (unsigned)((p.Cin + 31) / 32) * (unsigned)p.chunks * n;

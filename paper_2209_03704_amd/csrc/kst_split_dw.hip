@@ -42,6 +42,7 @@ struct DwParams {
     unsigned x_bytes, g_bytes;           // of the operands
     int two;                             // g of two half-precision parts (input: two, or half precision itself) where the ranges allow
     int range_share;                     // workgroups of the ranges' launch that took the input
+    float from;                          // ... and of all pairs of an input value and one of g, how many at least have no zero
 };
 
 // Four neighbours at p, of which `count` exist.  (Four at once whatever their alignment: aligned to their own size only.)
@@ -95,7 +96,7 @@ __device__ __forceinline__ void split_items(const Items<T> &q, unsigned block, c
     const int B = p.B, C = q.C, edge = q.edge, strips = p.strips, rows = q.rows, pitch = q.pitch, first = q.first, groups = p.groups;
     SplitHead head = {0u, 0, 0, 0u};
     if (range) {
-        head = split_head(range, p.range_share);
+        head = split_head(range, p.range_share, p.from);
         if (SECOND && head.two && block == 0 && threadIdx.x == 0)
             *reinterpret_cast<uint4 *>(head_end - 16) = make_uint4(head.two, (unsigned)head.ea, (unsigned)head.eb, 0u);
     }
@@ -550,14 +551,18 @@ DwPlan dw_plan(const Shape &s, bool odd, int parts, bool whole, bool half = fals
     // a chain (half precision 40), without empty items and taps that meet no g, the error was at most 0.99 of the other's on
     // 442 random layers, below 24 up to 2 times it.  Times as fast on them: 1.30 and 1.21 in the mean, at least 1.05 and 0.99
     // (64 x 512 x 256 x 8 x 8, n = 4, P = 2: 53 us, 81 with three parts).  bfloat16 input: two partial products for three, which
-    // the ranges' pass outweighs (0.98).
+    // the ranges' pass outweighs (0.98).  Steps of products that are not zero: from 22 and 18 (50 layers, 1 to 0.06 of the input not
+    // zero: no less exact from 20 to 26 and 15 to 23, at most 1.03 times the other's error from these lines).
+    const double values = (double)s.B * s.Cin * p.N * p.N, g_values = (double)s.B * s.Cout * p.M * p.M;
     p.two = 0;
+    p.from = 0.0f;
     if (r.ok && parts > 1) {
         const double inside = taps_inside(p.N, s.n, p.q2, p.M) / ((double)p.N * s.n);
         const double steps = p.per_split * inside * inside * s.B * p.N / (16.0 * p.groups * p.R);
+        p.from = (float)((half ? 18.0 : 22.0) / steps * values * g_values);
         p.two = steps >= (half ? 40.0 : 48.0) && plane * NN * sizeof(float) >= SPLIT_RANGE_BYTES;
     }
-    p.range_share = split_range_share(half ? 0 : (size_t)s.B * s.Cin * p.N * p.N, (size_t)s.B * s.Cout * p.M * p.M);
+    p.range_share = split_range_share((size_t)(values * (half ? 2 : 4)), (size_t)(g_values * 4));
     return r;
 }
 
@@ -572,9 +577,8 @@ hipError_t dw_launch(const T *in, const float *g, float *dw, char *ws, const DwP
     char *head_end = gf + p.g_bytes;
     if (p.two) {                                      // (the shares lie in the result until both operands are split)
         // (half precision needs no scale: what is infinite or not a number in it is found in the sums)
-        RangeOperand x = {nullptr, 0};
-        if constexpr (std::is_same_v<T, float>) x = {in, (size_t)p.B * p.Cin * p.N * p.N};
-        e = launch_split_range(x, {g, (size_t)p.B * p.Cout * p.M * p.M}, dw, stream);
+        e = launch_split_range({in, (size_t)p.B * p.Cin * p.N * p.N, !std::is_same_v<T, float>},
+                               {g, (size_t)p.B * p.Cout * p.M * p.M, false}, dw, stream);
         if (e != hipSuccess) return e;
         range = (const RangePart *)dw;
     }

@@ -45,6 +45,7 @@ struct SplitParams : FwdShape {
     unsigned w_pass1;      // byte offset of row parity 1 in one part's weights
     int two;               // operands of two half-precision parts where their ranges allow
     int range_share;       // workgroups of the ranges' launch that took the input
+    float from;            // ... and of all pairs of an input value and a weight, how many at least have no zero
 };
 
 // Order of the taps of row parity r: by window offset (row a of the sub-kernels, column dx), then column parity s.
@@ -496,7 +497,7 @@ __global__ void __launch_bounds__(256) split_weights_kernel(const float *__restr
 {
     SplitHead head = {0u, 0, 0, 0u};
     if (p.two) {
-        head = split_head(range, p.range_share);
+        head = split_head(range, p.range_share, p.from);
         if (head.two && blockIdx.x == 0 && threadIdx.x == 0)
             *reinterpret_cast<uint4 *>(w_split + p.w_bytes - 16) = make_uint4(head.two, (unsigned)head.ea, (unsigned)head.eb, 0u);
     }
@@ -603,8 +604,11 @@ struct SplitPlan {
 // whose roundings the smaller ones' sums apart do without (128 x 512 x 256 x 16 x 16, n = 4: 1.3e-7 for 1.6e-7).  Times as
 // fast from there: 1.25 (4 x 4, at least 1.13) and 1.30 (5 x 5, at least 1.12) then; 3 x 3 kernels gained 6 % in the mean and lost on
 // some.  (One accumulator for all needs second parts of their own size, which small values do not have: 336 us against 352.)
-inline bool split_two_parts(const Shape &s, int chunks, double whole, double shared)
+// Of products that are not zero two parts want 32 steps (23 layers, 1 to 0.06 of the input not zero: no less exact from 24 to 33).
+constexpr double SPLIT_FROM = 32.0;
+inline bool split_two_parts(const Shape &s, int chunks, double whole, double shared, float *from)
 {
+    *from = 0.0f;
     if (s.n < 4) return false;
     double taps = 0.0;
     for (int c = 0; c < 4; ++c) taps += (double)class_taps(s.n, c) * class_taps(s.n, c) / (s.n * s.n);
@@ -612,6 +616,7 @@ inline bool split_two_parts(const Shape &s, int chunks, double whole, double sha
     const int N0 = s.N - 2 * s.frame, M = s.M - 2 * s.crop;
     const double inside = taps_inside(N0, s.n, 2 * s.frame - s.crop, M) / ((double)s.E * s.n);
     const double steps = taps * (whole * chunks + shared * piece) / (whole + shared) * inside * inside;
+    *from = (float)(SPLIT_FROM / steps * ((double)s.B * s.Cin * N0 * N0) * ((double)s.Cin * s.Cout * s.n * s.n));
     return steps >= (s.n == 4 ? 108.0 : 150.0) && (size_t)s.B * s.Cout * M * M * sizeof(float) >= SPLIT_RANGE_BYTES;
 }
 
@@ -642,12 +647,12 @@ inline SplitPlan split_plan_for(const Shape &s, int wr)
     p.in_bytes = (unsigned)in_bytes;
     p.w_bytes = (unsigned)w_bytes;
     p.w_pass1 = (unsigned)(blocks * taps0 * S_TAP);
-    p.range_share = split_range_share(in_bytes / sizeof(float), (size_t)s.Cin * s.Cout * s.n * s.n);
+    p.range_share = split_range_share(in_bytes, (size_t)s.Cin * s.Cout * s.n * s.n * sizeof(float));
     // Full rounds of whole passes: any number where the two parities cost the same, pairs of passes where not.
     const unsigned long long tiles = (unsigned long long)p.tiles_m * p.tiles_co, passes = 2 * tiles;
     r.k.rounds = taps0 == taps1 ? (int)(passes / S_GRID) : 2 * (int)(tiles / S_GRID);
     r.k.passes = (int)(passes - (unsigned long long)r.k.rounds * S_GRID);
-    p.two = split_two_parts(s, p.chunks, (double)r.k.rounds * S_GRID, r.k.passes);
+    p.two = split_two_parts(s, p.chunks, (double)r.k.rounds * S_GRID, r.k.passes, &p.from);
     p.unit = p.two ? S_GROUP : 1;
     r.k.chunks = (p.chunks + p.unit - 1) / p.unit;
     const unsigned long long units = passes * (unsigned)r.k.chunks;
@@ -682,7 +687,7 @@ hipError_t split_f32_launch_nt(const float *in, const float *w_seg, float *out, 
     if (e != hipSuccess) return e;
     const SplitParams &p = pl.p;
     if (p.two) {                                      // (the shares lie in the output until the weights are split)
-        e = launch_split_range({in, p.in_bytes / sizeof(float)}, {w_seg, (size_t)p.Cin * p.Cout * n * n}, out, stream);
+        e = launch_split_range({in, p.in_bytes / sizeof(float), false}, {w_seg, (size_t)p.Cin * p.Cout * n * n, false}, out, stream);
         if (e != hipSuccess) return e;
     }
     const unsigned tasks = p.w_bytes / (3 * S_TAP);

@@ -95,6 +95,21 @@ Shape shape_for(int B, int Cin, int Cout, int N, int n, int path)
     return s;
 }
 
+// 16-bit matrix-core layers whose input is repacked: a whole call has its weights segregated by the launch that does it.
+bool repacks_16(const Shape &s, kst_dtype dt, kst_path chosen)
+{
+    return is16(dt) && chosen == KST_PATH_IGEMM && igemm_16_packed_applies(s);
+}
+
+// ... from weights as they come; scratch: room for them segregated, then the layer's workspace.
+kst_status run_repacked_16(const void *in, const void *w, void *out, void *scratch, size_t seg_bytes, const Shape &s, kst_dtype dt,
+                           hipStream_t stream)
+{
+    return launch_igemm_16_packed(in, scratch, (float *)out, (char *)scratch + seg_bytes, s, dt == KST_F16, stream, w) == hipSuccess
+               ? KST_OK
+               : KST_ERR_HIP;
+}
+
 size_t workspace_for(const Shape &s, kst_dtype dt, kst_path path)
 {
     if (!on_matrix_cores(path) || path == KST_PATH_IGEMM_PASSES) return 0;
@@ -353,14 +368,14 @@ kst_status kst_forward(const void *in, const void *w, void *out, int B, int Cin,
     };
     void *scratch = nullptr;
     if (!scratch_for(&scratch, seg_bytes, &ws_bytes, stream, least)) return KST_ERR_HIP;
-    void *ws = ws_bytes ? (void *)((char *)scratch + seg_bytes) : nullptr;
-    const bool packed = is16(dtype) && choose_path(s, dtype) == KST_PATH_IGEMM && igemm_16_packed_applies(s);
-    if (packed)
-        st = launch_igemm_16_packed(in, scratch, (float *)out, ws, s, dtype == KST_F16, stream, w) == hipSuccess ? KST_OK : KST_ERR_HIP;
-    else
+    if (repacks_16(s, dtype, choose_path(s, dtype))) {
+        st = run_repacked_16(in, w, out, scratch, seg_bytes, s, dtype, stream);
+    } else {
         st = kst_segregate_weights(w, scratch, Cin, Cout, n, dtype, stream);
-    if (!packed && st == KST_OK)
-        st = kst_forward_seg(in, scratch, out, ws, ws_bytes, B, Cin, Cout, N, n, dtype, KST_PATH_AUTO, stream);
+        if (st == KST_OK)
+            st = kst_forward_seg(in, scratch, out, ws_bytes ? (char *)scratch + seg_bytes : nullptr, ws_bytes, B, Cin, Cout, N, n,
+                                 dtype, KST_PATH_AUTO, stream);
+    }
     if (hipFreeAsync(scratch, stream) != hipSuccess && st == KST_OK) st = KST_ERR_HIP;
     return st;
 }
@@ -414,7 +429,7 @@ kst_status framed_plan(int B, int Cin, int Cout, int N, int n, int P, kst_dtype 
         }
     }
     // The repacked input of a 16-bit layer has the frame in it, and its kernel stores an odd factor's interior directly.
-    if (is16(dt) && f->chosen == KST_PATH_IGEMM && igemm_16_packed_applies(in_place)) f->s.frame = f->q;
+    if (repacks_16(in_place, dt, f->chosen)) f->s.frame = f->q;
     f->in_bytes = f->s.frame > 0 ? 0 : ((size_t)B * Cin * f->Nq * f->s.Ns * elt_bytes(dt) + 255) & ~(size_t)255;
     f->wide_bytes = (P & 1) ? (((size_t)B * Cout * f->Mq * f->Mq * sizeof(float) + 255) & ~(size_t)255) : 0;
     // The direct kernels supply the zero frame themselves: no framed copy at all; and for an odd
@@ -555,17 +570,14 @@ kst_status kst_forward_padded(const void *in, const void *w, void *out, int B, i
     void *scratch = nullptr;
     if (!scratch_for(&scratch, seg_bytes, &ws_bytes, stream, least)) return KST_ERR_HIP;
     // (a repacked layer has the frame in its input's copy and stores what is wanted of the map: nothing else in its workspace)
-    const bool packed = is16(dtype) && f.chosen == KST_PATH_IGEMM && f.s.frame > 0 && igemm_16_packed_applies(f.s);
-    if (packed)
-        st = launch_igemm_16_packed(in, scratch, (float *)out, (char *)scratch + seg_bytes, f.s, dtype == KST_F16, stream, w) ==
-                     hipSuccess
-                 ? KST_OK
-                 : KST_ERR_HIP;
-    else
+    if (f.s.frame > 0 && repacks_16(f.s, dtype, f.chosen)) {
+        st = run_repacked_16(in, w, out, scratch, seg_bytes, f.s, dtype, stream);
+    } else {
         st = kst_segregate_weights(w, scratch, Cin, Cout, n, dtype, stream);
-    if (!packed && st == KST_OK)
-        st = kst_forward_seg_padded(in, scratch, out, ws_bytes ? (char *)scratch + seg_bytes : nullptr, ws_bytes, B, Cin,
-                                    Cout, N, n, P, dtype, KST_PATH_AUTO, stream);
+        if (st == KST_OK)
+            st = kst_forward_seg_padded(in, scratch, out, ws_bytes ? (char *)scratch + seg_bytes : nullptr, ws_bytes, B, Cin,
+                                        Cout, N, n, P, dtype, KST_PATH_AUTO, stream);
+    }
     if (hipFreeAsync(scratch, stream) != hipSuccess && st == KST_OK) st = KST_ERR_HIP;
     return st;
 }

@@ -194,9 +194,9 @@ static hipError_t launch_plain(const void *in_v, const void *w_seg_v, float *out
 hipError_t launch_igemm_bf16(const void *in_v, const void *w_seg_v, float *out, void *ws, const Shape &s, bool f16,
                              hipStream_t stream)
 {
+    if (igemm_16_packed_applies(s)) return launch_igemm_16_packed(in_v, w_seg_v, out, ws, s, f16, stream);   // (none of the next two)
     if (igemm_bf16_wide_supported(s)) return launch_igemm_bf16_wide(in_v, w_seg_v, out, s, f16, stream);
     if (igemm_bf16_ring_supported(s)) return launch_igemm_bf16_ring(in_v, w_seg_v, out, s, f16, stream);
-    if (igemm_16_packed_applies(s)) return launch_igemm_16_packed(in_v, w_seg_v, out, ws, s, f16, stream);
     if (igemm_bf16_strip_supported(s)) return launch_igemm_bf16_strip(in_v, w_seg_v, out, s, f16, stream);
     return f16 ? launch_plain<true>(in_v, w_seg_v, out, ws, s, stream) : launch_plain<false>(in_v, w_seg_v, out, ws, s, stream);
 }

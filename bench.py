@@ -154,16 +154,18 @@ def roofline_for(layer, ms, metrics):
         return {"bound": "hbm", "achieved": round(a, 1), "peak": metrics.HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(a / metrics.HBM_PEAK_GBS, 4),
                 "traffic": MEASURED_TRAFFIC_BYTES.get(layer.name)}
-    peak = round(metrics.FP32_PRODUCTS_PEAK_TFLOPS, 1) if layer.dtype == "f32" else metrics.MFMA_PEAK_TFLOPS[layer.dtype]
+    products = metrics.forward_products(layer) if layer.dtype == "f32" else 1       # 16-bit ones for each of the layer's
+    peak = round(metrics.MFMA_PEAK_TFLOPS["bf16" if layer.dtype == "f32" else layer.dtype] / products, 1)
     a = 2.0 * metrics.useful_macs(layer) / (ms * 1e-3) / 1e12
-    return {"bound": "mfma", "achieved": round(a, 2), "peak": peak, "unit": "TFLOP/s",
+    return {"bound": "mfma", "achieved": round(a, 2), "peak": peak, "unit": "TFLOP/s", "products": products,
             "frac": round(a / peak, 4), "traffic": MEASURED_TRAFFIC_BYTES.get(layer.name)}
 
 
 def paper_roofline(layer, fwd_ms, din_ms, dw_ms, metrics):
     """Roofline fractions of a paper-shaped layer's three passes.  Many-channel layers are priced
-    against the rate at which the matrix cores can form fp32 products, a sixth of their bf16 peak
-    (each gradient does the forward's useful MACs once), the
+    against the rate at which the matrix cores can form fp32 products of six 16-bit ones, a sixth of their peak
+    ("products"; each gradient does the forward's useful MACs once; what is multiplied in three, as the gradients of the
+    largest of these layers are, has twice that rate), the
     few-channel ones against HBM (the forward by its algorithmic bytes; the gradients read `g` and
     the other operand and write the gradient: the same byte count)."""
     macs = metrics.useful_macs(layer)
@@ -177,6 +179,8 @@ def paper_roofline(layer, fwd_ms, din_ms, dw_ms, metrics):
     # HBM fraction is given beside it.
     alu = not many and 2.0 * macs / metrics.algorithmic_bytes(layer) > metrics.VALU_PEAK_TFLOPS * 1e12 / (metrics.HBM_PEAK_GBS * 1e9)
     out = {"bound": "mfma" if many else "alu" if alu else "hbm"}
+    if many:
+        out["products"] = 6
     if alu:
         out["forward_bound"] = "mfma"
     for name, ms in (("forward", fwd_ms), ("backward_input", din_ms), ("backward_weight", dw_ms)):
@@ -325,8 +329,8 @@ def main():
             return None
         if roof_l["bound"] == "hbm":
             return round(roof_l["achieved"] / yard["copy_GB_per_s"], 4)
-        if layer.dtype == "f32":                      # six bf16 products each
-            return round(roof_l["achieved"] * 6 / yard["mfma_TFLOP_per_s"]["bf16"], 4)
+        if layer.dtype == "f32":
+            return round(roof_l["achieved"] * roof_l["products"] / yard["mfma_TFLOP_per_s"]["bf16"], 4)
         return round(roof_l["achieved"] / yard["mfma_TFLOP_per_s"][layer.dtype], 4)
 
     # ---- per-layer table ---------------------------------------------------------------------

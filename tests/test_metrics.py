@@ -49,6 +49,18 @@ def test_benchmark_layer_counts():
         assert metrics.algorithmic_bytes(layer) == b
 
 
+def test_products_that_layers_are_priced_at():
+    """Three half-precision products where the reduction is long: the two large fp32 layers of the benchmark (their kernels issue
+    9,633,792 and 5,529,600 MFMAs of 16384 pairs, three for each product); six for shorter ones and 3 x 3 kernels."""
+    layer = {l.name: l for l in wl.LAYERS}
+    assert metrics.forward_products(layer["cfg3_gan_n4"]) == 3 and metrics.forward_products(layer["cfg4_deep_n5"]) == 3
+    for name, issued in (("cfg3_gan_n4", 9_633_792), ("cfg4_deep_n5", 4_816_896)):
+        assert metrics.useful_macs(layer[name]) * 3 == issued * 16384
+    for dims in ((64, 512, 256, 8, 4, 2), (128, 512, 256, 16, 3, 0), (64, 256, 128, 16, 4, 2)):
+        B, Cin, Cout, N, n, P = dims
+        assert metrics.forward_products(wl.Layer("t", B, Cin, Cout, N, n, "f32", "normal", P=P)) == 6
+
+
 def test_workloads_are_seeded_and_bf16_is_rounded_once():
     layer = wl.Layer("t", 2, 3, 4, 6, 3, "bf16", "relu_normal")
     x1, w1 = wl.make_tensors(layer, 7)

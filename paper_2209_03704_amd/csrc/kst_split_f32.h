@@ -8,8 +8,8 @@
 // room for about five other instructions).  A workgroup of four waves owns 128 positions x 128 output channels (or
 // 256 x 64) and one row parity; a wave owns 32 output channels and four blocks of 32 positions: two column parities x
 // four blocks x (the largest partial products' sums and the others'), 256 accumulator registers.  Per kernel tap a
-// wave issues 24 MFMAs (768 cycles) and needs the weights of its own 32 output channels only: a first kernel splits
-// all weights once and lays them out as MFMA operands, so that a wave's next three operands are one contiguous 3 KB,
+// wave issues 24 MFMAs (768 cycles; two parts: 12) and needs the weights of its own 32 output channels only: a first kernel splits
+// all weights once and lays them out as MFMA operands, so that a wave's next three (two) operands are one contiguous 3 (2) KB,
 // loaded straight into registers two to four taps ahead.  (Split in the main loop instead, 44 vector instructions
 // and eight 4-byte loads per tap: 548 us against 488 on 128 x 512 x 256 x 16 x 16, n = 4, when it was tried; 471 with three
 // parts, MFMAs busy in 64 % of the main kernel's cycles; 352 with two: half the MFMAs, the other cycles go to a

@@ -49,7 +49,7 @@
  *     fp32 again.
  * Which of the two it is the device finds for each call, from all values of both
  * tensors (that pass takes 8 to 16 us; layers planned for two parts whose values
- * ask for three take up to 1.4 times as long): the last bits of one batch item's
+ * ask for three take 1.25 to 1.5 times as long): the last bits of one batch item's
  * result can differ with another item's values, as they can with the batch size.
  * KST_PATH_IGEMM asked for by name multiplies in fp32 instead (forward only).
  */

@@ -54,7 +54,8 @@ __device__ __forceinline__ void split3(const float (&v)[8], bf16x8 &p0, bf16x8 &
 // a smaller value, zeros aside, or one that is not finite goes through the three-part kernels, in the same launches: a pass of its own
 // over both tensors (kst_split_range.hip) finds the largest and the smallest magnitude.  Nothing less will do.  A result is a sum of
 // products, so one operand's zeros and small values choose which values of the other count, and a few small values, in
-// whatever company, can be all there is of some result.  (Normal random values: a tensor of ten million has one that small in 1 of 20.)
+// whatever company, can be all there is of some result.  (Of 60 tensors of 8 and of 16 million normal random values one each had a smaller one.  Layers
+// planned for two parts that go through three take 1.26 to 1.45 times as long.)
 //
 // Zeros matter too: what an addition of nothing does not round.  The error of three parts falls with the share of the products
 // that are not zero, that of two does not: its square is 0.2e-14 + 6e-16 for each step of a chain times that share, against 1.0e-14 to

@@ -17,7 +17,7 @@
 // 256 accumulator registers; 48 MFMAs per step for 18 loads, one step ahead.  What bounds it is the rate at which the
 // cache of a CU hands over those operands (18 KB per wave and 1536 cycles; each is wanted by two waves).
 // With two parts half the MFMAs want two thirds of the operands, three steps ahead.
-// 64 x 512 x 256 x 8 x 8, n = 4, P = 2: 8 us for the ranges, 13 for the operands, 53 here (81 with three parts) and 9 for
+// 64 x 512 x 256 x 8 x 8, n = 4, P = 2: 6 us for the ranges, 13 for the operands, 53 here (81 with three parts) and 9 for
 // the sums, where framing g, the fp32 multiplies and their sums took 202; with bfloat16 input 64 x 256 x 128 x 16 x 16: 19 + 46 + 9
 // against 212.
 #include "kst_split_common.h"

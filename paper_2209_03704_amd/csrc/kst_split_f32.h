@@ -12,7 +12,7 @@
 // all weights once and lays them out as MFMA operands, so that a wave's next three (two) operands are one contiguous 3 (2) KB,
 // loaded straight into registers two to four taps ahead.  (Split in the main loop instead, 44 vector instructions
 // and eight 4-byte loads per tap: 548 us against 488 on 128 x 512 x 256 x 16 x 16, n = 4, when it was tried; 471 with three
-// parts, MFMAs busy in 64 % of the main kernel's cycles; 352 with two: half the MFMAs, the other cycles go to a
+// parts, MFMAs busy in 64 % of the main kernel's cycles; 352 with two: half the MFMAs, busy in 42 %, the other cycles go to a
 // wave's other instructions and its waits for LDS.)  Input values are
 // wanted by every wave and every tap: the rows the tile's positions touch are split once per chunk and kept in LDS as
 // [part][channel half][row, column][8 channels], so that a lane's MFMA operand is one 16-byte read; two stages, one
@@ -604,7 +604,7 @@ struct SplitPlan {
 // whose roundings the smaller ones' sums apart do without (128 x 512 x 256 x 16 x 16, n = 4: 1.3e-7 for 1.6e-7).  Times as
 // fast from there: 1.25 (4 x 4, at least 1.13) and 1.30 (5 x 5, at least 1.12) then; 3 x 3 kernels gained 6 % in the mean and lost on
 // some.  (One accumulator for all needs second parts of their own size, which small values do not have: 336 us against 352.)
-// Of products that are not zero two parts want 32 steps (23 layers, 1 to 0.06 of the input not zero: no less exact from 24 to 33).
+// Of products that are not zero two parts want 32 steps (25 layers, 1 to 0.06 of the input not zero: no less exact from 24 to 33).
 constexpr double SPLIT_FROM = 32.0;
 inline bool split_two_parts(const Shape &s, int chunks, double whole, double shared, float *from)
 {

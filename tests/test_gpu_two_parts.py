@@ -139,8 +139,8 @@ def test_ranges(low):
             assert np.linalg.norm(got[i] - want[i]) <= 4e-7 * np.linalg.norm(want[i])
 
 
-# Shares of the products that are not zero well above and well below what a plan wants (forward 32 of 150 steps, input gradient 28 of 113,
-# kernel gradients 22 of 113 and 18 of 108): few additions that round are more exact in three parts.
+# Shares of the products that are not zero well above and well below what a plan wants (forward 32 of 114 steps, input gradient 28 of 56,
+# kernel gradients 22 of 56 and 18 of 60): few additions that round are more exact in three parts.
 @pytest.mark.parametrize("share,two", [(0.6, True), (0.08, False)])
 @pytest.mark.parametrize("name", ["forward", "input", "kernel", "kernel f16", "kernel g"])
 def test_zeros_count(name, share, two):

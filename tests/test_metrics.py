@@ -76,10 +76,11 @@ def test_workloads_are_seeded_and_bf16_is_rounded_once():
 def test_bench_reads_traffic_from_the_committed_counter_summary():
     """bench.py's roofline.traffic comes from profiles/hbm_traffic_pmc.txt, not from constants in
     the script: the four benchmark layers with a counter measurement are found there, and each
-    figure lies between the layer's algorithmic bytes and a multiple of them (16: cfg4's deep weights, split into three
-    parts of 79 MB together, are read by the 18 position tiles through each of the chip's eight second-level caches,
-    630 MB, after 52 MB were read and 79 written to split them; with 85 MB of algorithmic bytes, 71 of partial tiles'
-    sums and 59 written as them that is up to 980 MB, 11.5 times the algorithmic bytes, where 1020 were measured)."""
+    figure lies between the layer's algorithmic bytes and a multiple of them (16: cfg4's deep weights, split into two
+    parts of 52 MB together, are read by the 18 position tiles through each of the chip's eight second-level caches,
+    420 MB, after 52 MB were read twice, for their range and to split them, and 52 written; with 85 MB of algorithmic
+    bytes, 17 of them read twice, 71 of partial tiles' sums and 59 written as them that is up to 810 MB, 9.5 times the
+    algorithmic bytes, where 826 were measured)."""
     import bench
     from paper_2209_03704_amd import metrics, workloads as wl
     traffic = bench.measured_traffic()

@@ -139,6 +139,21 @@ def test_ranges(low):
             assert np.linalg.norm(got[i] - want[i]) <= 4e-7 * np.linalg.norm(want[i])
 
 
+# Tensors of 4 k + 2 values: the last two are no whole load of the ranges' pass; the first and one in the middle beside them.
+@pytest.mark.parametrize("at", [0, 2000003, -3, -2, -1])
+@pytest.mark.parametrize("which", ["x", "g"])
+def test_every_value_is_looked_at(which, at):
+    shape = KERNEL_GRADIENT[1]
+    x, _, g = (t.to(DEV) for t in _inputs(shape, 14))
+    n, P = shape[4:6]
+    t = x if which == "x" else g
+    assert t.numel() % 4 == 2
+    t.view(-1)[at] = 0.0
+    two = kst.kst_backward_weight(x, g, n, P)
+    t.view(-1)[at] = 1e-20                                        # (below half a last bit of every sum)
+    assert not torch.equal(two, kst.kst_backward_weight(x, g, n, P))
+
+
 # Shares of the products that are not zero well above and well below what a plan wants (forward 32 of 114 steps, input gradient 28 of 56,
 # kernel gradients 22 of 56 and 18 of 60): few additions that round are more exact in three parts.
 @pytest.mark.parametrize("share,two", [(0.6, True), (0.08, False)])
